@@ -115,13 +115,15 @@ int axo_shard_dims(const axo_problem_t *p, int64_t *M, int64_t *Kl, int64_t *Nl,
  * Returns 0 for an invalid problem (the op call itself reports the error). */
 size_t axo_workspace_bytes(const axo_problem_t *p, int op);
 
-/* Which kernels a product takes, as axo_fc_route reports it. */
+/* Which kernels a product takes, as axo_fc_route reports it: how its shape fits the tuned kernel's 256-row
+ * tiles.  Within TILED, COVERED and INTERIOR_STRIPS a product that is too small to occupy the GPU with such
+ * tiles runs on 32 x 32 or 64 x 64 tiles instead, wherever those are estimated quicker from the shape alone. */
 typedef enum axo_route {
     AXO_ROUTE_NONE = 0,            /* an empty output: nothing is launched                                 */
     AXO_ROUTE_TILED = 1,           /* the tuned MFMA kernel, one launch                                    */
     AXO_ROUTE_COVERED = 2,         /* a ragged output covered with whole (overlapping) tuned tiles         */
-    AXO_ROUTE_INTERIOR_STRIPS = 3, /* the interior on the tuned kernel, leftover strips on the general one */
-    AXO_ROUTE_GENERAL = 4          /* the general (bounds-checked, untuned) kernel                         */
+    AXO_ROUTE_INTERIOR_STRIPS = 3, /* the interior on the tuned kernel, leftover strips on small tiles    */
+    AXO_ROUTE_GENERAL = 4          /* small tiles; past a span of 4 GiB the bounds-checked 64-bit kernel   */
 } axo_route_t;
 
 /* Host only.  Reports in *route (axo_route_t) which kernels the product `op` (axo_op_t) of this
@@ -145,7 +147,8 @@ int axo_fc_route(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int
  * Speed: the tuned kernel takes shards whose reduction length (Kl here, Nl for dgrad) is a multiple of 8 and
  * whose output has at least 256 rows and 128 columns, the column count a multiple of 8; leading dimensions
  * that are multiples of 64 elements keep every 128-byte row segment inside one cache line (worth 10-20 %).
- * Everything else is computed by a general kernel that is several times slower; axo_fc_route tells which. */
+ * Everything else runs on small tiles (at best about half the tuned kernel's rate), apart from operands whose
+ * span passes 4 GiB, for which a bounds-checked kernel is several times slower; axo_fc_route tells which. */
 int axo_fc_fwd(const axo_problem_t *p, const void *X, int64_t ldx, const void *W, int64_t ldw,
                const void *bias, int epilogue, void *Y, int64_t ldy,
                void *ws, size_t ws_bytes, void *hip_stream);

@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 #include <deque>
 #include <functional>
@@ -20,6 +21,7 @@
 #include "axo_common.hpp"
 #include "bias_grad.hpp"
 #include "gemm_generic.hpp"
+#include "gemm_slim.hpp"
 #include "gemm_tile.hpp"
 
 // Scratch memory of the allocation-free entry point (axo_bias_grad_static): arrival counters and
@@ -103,6 +105,13 @@ bool span_ok(int layout, int64_t ld, int64_t R) {
     return elems * 2 < (int64_t)0xFFFF0000;
 }
 
+// The span is that of the rows the kernels walk: the reduction rounded up to the unrolled loop's 128
+// (the surplus rows of wgrad read as zeros, but their offsets are still formed in 32 bits).
+bool spans_ok(const GemmArgs& g, int la, int lb) {
+    const int64_t walked = ((int64_t)g.R + 2 * axo::TILE_BK - 1) / (2 * axo::TILE_BK) * (2 * axo::TILE_BK);
+    return span_ok(la, g.lda, walked) && span_ok(lb, g.ldb, walked);
+}
+
 // Reductions: any length where both operands have the reduction index as their row index (wgrad:
 // rows beyond the end read as zeros through the buffer bound); any multiple of 8 otherwise (an
 // operand with the reduction inside its rows has its last fragments masked in registers, which
@@ -112,10 +121,7 @@ bool tileable(const GemmArgs& g, int la, int lb) {
     if (!(g.R > 0 && (any_reduction || g.R % 8 == 0) && g.Mo > 0 && g.No > 0 && g.Mo % 256 == 0 &&
           g.No % 128 == 0))
         return false;
-    // the span is that of the rows the kernel walks: the reduction rounded up to the unrolled loop's
-    // 128 (the surplus rows of wgrad read as zeros, but their offsets are still formed in 32 bits)
-    const int64_t walked = ((int64_t)g.R + 2 * axo::TILE_BK - 1) / (2 * axo::TILE_BK) * (2 * axo::TILE_BK);
-    return span_ok(la, g.lda, walked) && span_ok(lb, g.ldb, walked);
+    return spans_ok(g, la, lb);
 }
 
 // Time (in big-tile units) a greedy dispatch of n_big big tiles followed by n_small small tiles
@@ -174,12 +180,12 @@ axo::TileSched plan_tiles(int Mo, int No) {
 // The tuned kernels' dynamic LDS size is above the default limit, so the limit is raised once per
 // kernel and device (`raised` holds one bit per device ordinal; a process rarely sees more than
 // 8, and beyond 64 the attribute is simply set on every launch).
-bool raise_lds_limit(const void* kernel, std::atomic<uint64_t>* raised) {
+bool raise_lds_limit(const void* kernel, int bytes, std::atomic<uint64_t>* raised) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
     if (bit && (raised->load(std::memory_order_acquire) & bit)) return true;
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, axo::MIX_LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
         return false;
     raised->fetch_or(bit, std::memory_order_release);
     return true;
@@ -190,7 +196,7 @@ template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
     auto kern = axo::gemm_mixed_kernel<LA, LB>;
     static std::atomic<uint64_t> raised{0};
-    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), &raised)) return AXO_ERR_HIP;
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
     const axo::TileSched sc = plan_tiles(g.Mo, g.No);
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), axo::MIX_LDS_BYTES, st, g, sc);
@@ -203,6 +209,74 @@ int launch_tile_layout(const GemmArgs& g, int la, int lb, hipStream_t st) {
     return launch_tile<axo::MC, axo::MC>(g, st);
 }
 
+// ---- small-tile launch (gemm_slim.hpp) ---------------------------------------------------------
+// Estimated kernel time in microseconds of a product on small tiles and on the 256-row tiles, from
+// its sizes alone.  Fitted to 177 measured products (M 1..8000, K and N 94..13312, all three layout
+// pairs; 85-89 % of the small-tile estimates are within 20 %, and what the choice below picks took 2 % longer than
+// the best kernel on average).  A small tile costs a fixed part (start, first load,
+// addition of the partial tiles, store) plus its operand bytes at the rate a CU pulls them in; a
+// product with few tiles is bound by one workgroup's chain of chunks instead.
+struct SlimModel {
+    int rows;          // square tile
+    int slots;         // workgroups that fit one CU beside each other
+    double fixed;      // us per tile on a busy CU
+    double chunk_us;   // us per chunk of one wave when nothing else runs on the CU
+    double rate[3];    // KB per us of a busy CU, by layout pair
+};
+constexpr SlimModel SLIM_MODEL[2] = {{32, 5, 0.2, 0.24, {80.0, 106.0, 60.0}}, {64, 2, 1.5, 0.47, {112.0, 115.0, 95.0}}};
+double slim_time(const SlimModel& m, int Mo, int No, int R, int pair) {
+    const double tiles = (double)((Mo + m.rows - 1) / m.rows) * ((No + m.rows - 1) / m.rows);
+    const double chunks = (R + axo::TILE_BK - 1) / axo::TILE_BK, kb = chunks * (2.0 * m.rows * axo::TILE_BK * 2 / 1024.0);
+    const double busy = std::ceil(tiles / NUM_CU) * (kb / m.rate[pair] + m.fixed);
+    const double chain = std::ceil(tiles / (NUM_CU * m.slots)) * (0.7 + std::ceil(chunks / axo::SLIM_WAVES) * m.chunk_us);
+    return 2.5 + std::max(busy, chain);
+}
+// The 256-row tiles: rounds of 256 x 256 tiles or of half-width ones, 1.33 us per reduction step.
+double tile_time(int Mo, int No, int R) {
+    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
+    const double big = std::ceil(tm * ((No + 255) / 256) / NUM_CU), half = std::ceil(tm * ((No + 127) / 128) / NUM_CU) * SMALL_TILE_COST;
+    return 2.0 + std::min(big, half) * steps * 1.33;
+}
+
+int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
+
+// Rows of the small tile (32 or 64) that is quicker for this product.
+int slim_rows(const GemmArgs& g, int pair) {
+    return slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair) <= slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair) ? 32 : 64;
+}
+// Whether a product that the 256-row tiles could take runs on small tiles instead: where those are
+// estimated at least 10 % quicker.  A function of sizes and layouts only, because the waves of a small tile
+// split the reduction and so sum in another order: a product has the same bits on its own and in a chain.
+bool prefers_slim(const GemmArgs& g, int la, int lb) {
+    const int pair = layout_pair(la, lb);
+    const double slim = std::min(slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair), slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair));
+    return slim < 0.9 * tile_time(g.Mo, g.No, g.R);
+}
+
+template <int ROWS, int LA, int LB>
+int launch_slim_rows(const GemmArgs& g, hipStream_t st) {
+    using C = axo::SlimCfg<ROWS, ROWS, axo::SLIM_WAVES>;
+    auto kern = axo::gemm_slim_kernel<ROWS, ROWS, axo::SLIM_WAVES, LA, LB>;
+    static std::atomic<uint64_t> raised{0};
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, &raised)) return AXO_ERR_HIP;
+    axo::SlimSched sc{(g.Mo + ROWS - 1) / ROWS, (g.No + ROWS - 1) / ROWS, 0};
+    sc.group_m = std::min(sc.tiles_m, 8);  // 8 tile rows share the column panels in an XCD's L2
+    const int64_t blocks = (int64_t)sc.tiles_m * sc.tiles_n;
+    if (blocks > INT32_MAX / C::THREADS) return AXO_ERR_BAD_SIZE;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, g, sc);
+    return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+}
+template <int LA, int LB>
+int launch_slim_layout(const GemmArgs& g, int rows, hipStream_t st) {
+    return rows == 32 ? launch_slim_rows<32, LA, LB>(g, st) : launch_slim_rows<64, LA, LB>(g, st);
+}
+int launch_slim(const GemmArgs& g, int la, int lb, hipStream_t st) {
+    const int rows = slim_rows(g, layout_pair(la, lb));
+    if (la == axo::KC && lb == axo::MC) return launch_slim_layout<axo::KC, axo::MC>(g, rows, st);
+    if (la == axo::KC && lb == axo::KC) return launch_slim_layout<axo::KC, axo::KC>(g, rows, st);
+    return launch_slim_layout<axo::MC, axo::MC>(g, rows, st);
+}
+
 // ---- grouped launch ------------------------------------------------------------------------
 // Cost of one tile in reduction steps of a big tile: the steps themselves plus a fixed share for
 // the tile's first loads and its epilogue (measured: a two-step tile takes about as long as six
@@ -211,8 +285,6 @@ constexpr double TILE_OVERHEAD_STEPS = 4.0;
 double tile_cost(int R, bool small) {
     return (R / (double)axo::TILE_BK + TILE_OVERHEAD_STEPS) * (small ? SMALL_TILE_COST : 1.0);
 }
-
-int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
 
 struct GroupItem {
     int Mo, No, R, pair;
@@ -323,7 +395,7 @@ struct Plan {
 // GROUP_MAX_PRODUCTS of them).
 int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     static std::atomic<uint64_t> raised{0};
-    if (!raise_lds_limit(reinterpret_cast<const void*>(axo::gemm_group_kernel), &raised)) return AXO_ERR_HIP;
+    if (!raise_lds_limit(reinterpret_cast<const void*>(axo::gemm_group_kernel), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
     std::vector<GroupItem> items(n);
     for (int i = 0; i < n; ++i)
         items[i] = plans[i]->bias_grad ? GroupItem{plans[i]->bg.M, plans[i]->bg.Nl, 0, PAIR_BIAS_GRAD}
@@ -418,9 +490,9 @@ bool cover_with_tiles(const Plan& pl, std::vector<Plan>* out) {
 }
 
 // One product: the tuned kernel when it takes the shape; a cover of whole tiles in one grouped
-// launch when only the output's granularity is in the way (measured on 4096 x 2048 x 6152, eight
-// columns over: 198 TFLOP/s through the general kernel alone); failing that, the interior on the
-// tuned kernel and the leftover strips on the general one; the general kernel for the rest.
+// launch when only the output's granularity is in the way; failing that, the interior on the
+// tuned kernel and the leftover strips on small tiles; small tiles for the rest, and the
+// general kernel (64-bit addressing, an order of magnitude slower) where a span passes 4 GiB.
 int route_of(const GemmArgs& g, int la, int lb, std::vector<Plan>* pieces) {
     if (g.Mo == 0 || g.No == 0) return AXO_ROUTE_NONE;
     if (tileable(g, la, lb)) return AXO_ROUTE_TILED;
@@ -436,9 +508,11 @@ int route_of(const GemmArgs& g, int la, int lb, std::vector<Plan>* pieces) {
 }
 
 int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
+    if (g.Mo == 0 || g.No == 0) return AXO_OK;
+    if (!spans_ok(g, la, lb)) return launch_generic(g, la, lb, st);
+    if (prefers_slim(g, la, lb)) return launch_slim(g, la, lb, st);
     std::vector<Plan> pieces;
     switch (route_of(g, la, lb, &pieces)) {
-        case AXO_ROUTE_NONE: return AXO_OK;
         case AXO_ROUTE_TILED: return launch_tile_layout(g, la, lb, st);
         case AXO_ROUTE_COVERED: {
             const Plan* ptr[4];
@@ -448,11 +522,11 @@ int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
         case AXO_ROUTE_INTERIOR_STRIPS: {
             const int Mi = g.Mo / 256 * 256, Ni = g.No / 128 * 128;
             int rc = launch_tile_layout(sub_product(g, la, lb, 0, Mi, 0, Ni), la, lb, st);
-            if (rc == AXO_OK && g.No > Ni) rc = launch_generic(sub_product(g, la, lb, 0, g.Mo, Ni, g.No - Ni), la, lb, st);
-            if (rc == AXO_OK && g.Mo > Mi) rc = launch_generic(sub_product(g, la, lb, Mi, g.Mo - Mi, 0, Ni), la, lb, st);
+            if (rc == AXO_OK && g.No > Ni) rc = launch_slim(sub_product(g, la, lb, 0, g.Mo, Ni, g.No - Ni), la, lb, st);
+            if (rc == AXO_OK && g.Mo > Mi) rc = launch_slim(sub_product(g, la, lb, Mi, g.Mo - Mi, 0, Ni), la, lb, st);
             return rc;
         }
-        default: return launch_generic(g, la, lb, st);
+        default: return launch_slim(g, la, lb, st);
     }
 }
 
@@ -879,9 +953,9 @@ int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& lev
                 else rc = launch_bias_grad(pl.bg, st);
                 continue;
             }
-            if (!tileable(pl.g, pl.la, pl.lb)) {
+            if (!tileable(pl.g, pl.la, pl.lb) || prefers_slim(pl.g, pl.la, pl.lb)) {
                 std::vector<Plan> pieces;
-                if (!cover_with_tiles(pl, &pieces)) {
+                if (prefers_slim(pl.g, pl.la, pl.lb) || !cover_with_tiles(pl, &pieces)) {
                     rc = launch(pl.g, pl.la, pl.lb, st);
                     continue;
                 }

@@ -1,0 +1,311 @@
+// Small-tile bf16 MFMA GEMM for gfx950: any Mo, No, R, every edge handled in the kernel.
+//   C[Mo x No] = sum_r A(i, r) * B(j, r)
+//
+// For products whose output is too small for the 256-row tiles of gemm_tile.hpp to occupy the chip.
+// Such a product is bound by latency and by how fast one CU pulls operands in (a 1 KB wave-load per
+// about 20 cycles), so the waves of a workgroup split the REDUCTION of one BM x BN tile between them:
+// wave w takes the 64-wide reduction chunks w, w + NW, w + 2 NW, ...  A wave copies its chunks into LDS
+// that nobody else touches, so the main loop has no workgroup barrier: it waits for its own loads
+// only, and the waves of a CU drift apart and cover each other's latency.  Splitting the reduction also
+// means that every LDS byte is read once (a tile shared by a 2 x 2 arrangement of waves reads each
+// operand twice).  The partial tiles are added through LDS in ascending wave order: no atomics, the
+// result is a fixed function of the input.
+//
+// One LDS stage per wave: its fragments go to registers before the next chunk is requested into the
+// same bytes, and what hides the latency is the other waves.  A second stage per wave was measured
+// slower almost everywhere (64 x 64 tiles, 2048^3: 38 us with two stages and one workgroup per CU, 28 us
+// with one stage and two; 4096 x 1536 x 1536: 48 and 32), as it halves the workgroups that fit beside
+// each other and with them what overlaps a workgroup's start and end.
+//
+// Edges cost nothing in the loop.  Loads go through a buffer descriptor whose bound is the last
+// valid element of the operand's tile (rounded up to the dword the range check works in), so rows beyond
+// the matrix read as zeros; columns beyond it read whatever the row pitch holds and only reach outputs
+// that are not stored.  The one thing a linear bound cannot mask, the end of a reduction that runs inside
+// the rows (KC), is masked in registers in the last chunk, on both operands (a zero times a stray infinity
+// would be a NaN).
+//
+// Measured, kernel time of forward / dgrad / wgrad: 96 x 2048 x 6144 10.5 / 13.2 / - us (the general kernel
+// took 130 / 238), 1001 x 1027 x 515 9.8 / 7.7 / 8.4 (85 / 39 / 178), 77 x 1000 x 48 4.1 / 3.1 / 2.9
+// (56 / 15 / 19), 256^3 3.3 / 3.2 / 3.1 (256 x 128 tiles: 5.3 each).
+#pragma once
+#include "gemm_tile.hpp"
+
+namespace axo {
+
+// 16-byte chunks of an LDS tile are permuted so that fragment reads spread over the banks.  KC (128-byte
+// rows): swz_kc.  MC: a transposing read of half a wave touches the 8 rows given by k % 4 and
+// (k / 8) % 2, two chunks each; with rows of 64 or 128 bytes, 4 or 2 rows share a 256-byte bank sweep
+// and the remaining bits of that choice pick the chunk.
+template <int ROWS>
+__device__ __forceinline__ int swz_mc_narrow(int k) {
+    static_assert(ROWS == 32 || ROWS == 64, "row pitch 64 or 128 bytes");
+    return ROWS == 32 ? ((k >> 3) & 1) << 1 : (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+}
+
+// The first `n` (none if n <= 0, all if n >= 8) of the 8 bf16 elements of a 16-byte chunk, the others zero.
+__device__ __forceinline__ u32x4 first_elements(u32x4 w, int n) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] &= n >= 2 * d + 2 ? 0xFFFFFFFFu : (n == 2 * d + 1 ? 0xFFFFu : 0u);
+    return w;
+}
+__device__ __forceinline__ bf16x8 first_elements(bf16x8 f, int n) {
+    union { bf16x8 v; u32x4 u; } x;
+    x.v = f;
+    x.u = first_elements(x.u, n);
+    return x.v;
+}
+
+// Bound of the buffer descriptor of an operand tile: bytes from the tile's origin to the end of the last
+// valid element of its `rows` valid rows (KC) or columns (MC) of a reduction of R.
+template <int LAYOUT>
+__device__ __forceinline__ uint32_t operand_bound(int64_t ld, int rows, int R) {
+    const int64_t elems = LAYOUT == KC ? (int64_t)(rows - 1) * ld + R : ((int64_t)R - 1) * ld + rows;
+    return R > 0 ? (uint32_t)((elems * 2 + 3) & ~(int64_t)3) : 0u;
+}
+
+// Raw buffer descriptor: base, stride 0, dword format, bound in bytes.
+__device__ __forceinline__ u32x4_t tile_rsrc(const bf16_t* p, uint32_t bound) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    u32x4_t r;
+    r[0] = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32) & 0xFFFFu);
+    r[2] = __builtin_amdgcn_readfirstlane(bound);
+    r[3] = 0x00020000u;
+    return r;
+}
+
+// Four consecutive outputs of one row, `valid` (1..4) of them inside the matrix: epilogue and store.
+__device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, const int row, const int col, const int valid) {
+    if (g.epilogue == EPI_ACC_F32) {
+        float* out = reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col;
+        if (valid == 4) *reinterpret_cast<f32x4*>(out) = *reinterpret_cast<const f32x4*>(out) + v;
+        else
+            for (int e = 0; e < valid; ++e) out[e] += v[e];
+        return;
+    }
+    if (g.epilogue != EPI_NONE) {
+        const bool fwd = g.epilogue <= EPI_BIAS_GELU_ERF;
+        float x[4] = {0.f, 0.f, 0.f, 0.f};  // bias, or the pre-activations
+        if (!fwd || g.add_bias) {
+            const bf16_t* src = fwd ? g.bias + col : g.aux + (int64_t)row * g.ldaux + col;
+            if (valid == 4) {
+                const uint2 raw = *reinterpret_cast<const uint2*>(src);
+                x[0] = __uint_as_float(raw.x << 16);
+                x[1] = __uint_as_float(raw.x & 0xFFFF0000u);
+                x[2] = __uint_as_float(raw.y << 16);
+                x[3] = __uint_as_float(raw.y & 0xFFFF0000u);
+            } else
+                for (int e = 0; e < valid; ++e) x[e] = bf16_bits_to_f32(src[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fwd ? apply_epilogue(v[e], x[e], g.epilogue) : apply_dact(v[e], x[e], g.epilogue);
+    }
+    bf16_t* out = g.C + (int64_t)row * g.ldc + col;
+    uint2 packed;
+    packed.x = pack_bf16x2(v[0], v[1]);
+    packed.y = pack_bf16x2(v[2], v[3]);
+    if (valid == 4) *reinterpret_cast<uint2*>(out) = packed;
+    else {
+        out[0] = (bf16_t)packed.x;
+        if (valid > 1) out[1] = (bf16_t)(packed.x >> 16);
+        if (valid > 2) out[2] = (bf16_t)packed.y;
+    }
+}
+
+// One operand of a tile as one wave sees it: ROWS output rows (or columns) by 64 reduction elements.
+template <int ROWS, int LAYOUT>
+struct SlimOperand {
+    static constexpr int BYTES = ROWS * TILE_BK * 2;
+    static constexpr int LOADS = BYTES / 1024;  // wave-loads of 16 bytes per lane
+    static constexpr int NT = ROWS / 16;        // MFMA tiles
+    static constexpr int NA = LAYOUT == KC ? 2 : NT;
+    uint32_t off[LOADS];  // per-lane byte offset of the chunk fetched by load j, from the tile origin
+    uint32_t addr[NA];    // per-lane LDS byte offset of a fragment, from the operand's stage
+
+    __device__ __forceinline__ void init(int lane, int64_t ld) {
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j) {
+            const int q = j * 64 + lane;
+            if (LAYOUT == KC) {
+                const int r = q >> 3, cs = q & 7;
+                off[j] = (uint32_t)(((int64_t)r * ld + ((cs ^ swz_kc(r)) << 3)) * 2);
+            } else {
+                constexpr int CPR = ROWS / 8;
+                const int k = q / CPR, cs = q % CPR;
+                off[j] = (uint32_t)(((int64_t)k * ld + ((cs ^ swz_mc_narrow<ROWS>(k)) << 3)) * 2);
+            }
+        }
+        if (LAYOUT == KC) {
+            const int r = lane & 15;
+#pragma unroll
+            for (int kq = 0; kq < 2; ++kq) addr[kq] = r * (TILE_BK * 2) + (((kq * 4 + (lane >> 4)) ^ swz_kc(r)) << 4);
+        } else {
+            const int i = lane & 15, krow = ((lane >> 4) << 3) + (i >> 2);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int n = t * 16 + ((i & 3) << 2);
+                addr[t % NA] = krow * (ROWS * 2) + (((n >> 3) ^ swz_mc_narrow<ROWS>(krow)) << 4) + (((n >> 2) & 1) << 3);
+            }
+        }
+    }
+    // fragment of MFMA tile t, 32-wide sub-step kq, of the stage at `stage`
+    __device__ __forceinline__ bf16x8 read(const char* stage, int t, int kq) const {
+        if (LAYOUT == KC) {
+            return *reinterpret_cast<const bf16x8*>(stage + addr[kq] + t * (16 * TILE_BK * 2));
+        } else {
+            typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+            const char* p = stage + addr[t % NA] + kq * (32 * ROWS * 2);
+            union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+            u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+            u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * (ROWS * 2)));
+            return u.v;
+        }
+    }
+    static __device__ __forceinline__ const bf16_t* origin(const bf16_t* p, int64_t ld, int i0) {
+        return LAYOUT == KC ? p + (int64_t)i0 * ld : p + i0;
+    }
+    static __device__ __forceinline__ uint32_t chunk_step(int64_t ld) {
+        return (uint32_t)(LAYOUT == KC ? TILE_BK * 2 : (int64_t)TILE_BK * ld * 2);
+    }
+};
+
+constexpr int SLIM_WAVES = 4;
+
+template <int BM, int BN, int NW>
+struct SlimCfg {
+    static constexpr int THREADS = NW * 64;
+    static constexpr int STAGE_BYTES = (BM + BN) * TILE_BK * 2;
+    static constexpr int PART_STRIDE = BN + 4;  // floats per row of a partial tile (padded)
+    static constexpr int PART_BYTES = BM * PART_STRIDE * 4;
+    static constexpr int WAVE_BYTES = STAGE_BYTES > PART_BYTES ? STAGE_BYTES : PART_BYTES;
+    static constexpr int LDS_BYTES = NW * WAVE_BYTES;
+    static_assert(BM % 32 == 0 && BN % 32 == 0 && LDS_BYTES <= 160 * 1024, "LDS of one CU");
+};
+
+template <int BM, int BN, int NW, int LA, int LB>
+__device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
+    using C = SlimCfg<BM, BN, NW>;
+    using OA = SlimOperand<BM, LA>;
+    using OB = SlimOperand<BN, LB>;
+    constexpr int TM = BM / 16, TN = BN / 16;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int KT = (g.R + TILE_BK - 1) / TILE_BK;
+
+    OA oa;
+    OB ob;
+    oa.init(lane, g.lda);
+    ob.init(lane, g.ldb);
+    const u32x4_t a_rsrc = tile_rsrc(OA::origin(g.A, g.lda, i0), operand_bound<LA>(g.lda, min(BM, g.Mo - i0), g.R));
+    const u32x4_t b_rsrc = tile_rsrc(OB::origin(g.B, g.ldb, j0), operand_bound<LB>(g.ldb, min(BN, g.No - j0), g.R));
+    const uint32_t a_step = OA::chunk_step(g.lda), b_step = OB::chunk_step(g.ldb);
+    char* const mine = smem + wave * C::WAVE_BYTES;
+    const uint32_t mine_lds = (uint32_t)(uintptr_t)(lds_void_ptr)smem + wave * C::WAVE_BYTES;
+
+    // one direct-to-LDS load: 16 bytes per lane to LDS address M0 + 16 * lane (see gemm_tile_body)
+    auto load_lds = [](uint32_t lds_dst, uint32_t off, u32x4_t rsrc, uint32_t soff) __attribute__((always_inline)) {
+        asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :
+                     : "v"(off), "s"(rsrc), "s"(soff), "{m0}"(lds_dst)
+                     : "memory");
+    };
+    auto issue = [&](const int chunk) __attribute__((always_inline)) {
+        const uint32_t a_soff = (uint32_t)chunk * a_step, b_soff = (uint32_t)chunk * b_step;
+#pragma unroll
+        for (int j = 0; j < OA::LOADS; ++j) load_lds(mine_lds + j * 1024, oa.off[j], a_rsrc, a_soff);
+#pragma unroll
+        for (int j = 0; j < OB::LOADS; ++j) load_lds(mine_lds + OA::BYTES + j * 1024, ob.off[j], b_rsrc, b_soff);
+    };
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
+
+    if (wave < KT) issue(wave);
+    for (int chunk = wave; chunk < KT; chunk += NW) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bf16x8 fa[2][TM], fb[2][TN];
+#pragma unroll
+        for (int kq = 0; kq < 2; ++kq) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) fa[kq][a] = oa.read(mine, a, kq);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) fb[kq][b] = ob.read(mine + OA::BYTES, b, kq);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage is in registers: refill it
+        if (chunk + NW < KT) issue(chunk + NW);
+        if ((LA == KC || LB == KC) && (g.R % TILE_BK) != 0 && chunk == KT - 1) {
+            const int left = g.R - chunk * TILE_BK - 8 * (lane >> 4);  // from this lane's 8 elements of sub-step 0
+#pragma unroll
+            for (int kq = 0; kq < 2; ++kq) {
+                if (LA == KC) {
+#pragma unroll
+                    for (int a = 0; a < TM; ++a) fa[kq][a] = first_elements(fa[kq][a], left - kq * 32);
+                }
+                if (LB == KC) {
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) fb[kq][b] = first_elements(fb[kq][b], left - kq * 32);
+                }
+            }
+        }
+#pragma unroll
+        for (int kq = 0; kq < 2; ++kq)
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kq][b], fa[kq][a], acc[a][b], 0, 0, 0);
+    }
+
+    // Partial tiles to LDS (each wave inside its own region, whose loads have all landed and been read),
+    // then every thread adds the partials of its outputs, four consecutive columns at a time.
+    // acc[a][b][e] is element (a * 16 + lane % 16, b * 16 + 4 * (lane / 16) + e) of the tile.
+    const int n_part = min(NW, KT);
+    if (wave < n_part) {
+        float* part = reinterpret_cast<float*>(mine);
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+                *reinterpret_cast<f32x4*>(part + (a * 16 + (lane & 15)) * C::PART_STRIDE + b * 16 + 4 * (lane >> 4)) = acc[a][b];
+    }
+    __syncthreads();
+    constexpr int QPR = BN / 4, QUADS = BM * QPR;  // quads of columns per row, per tile
+    static_assert(QUADS % C::THREADS == 0, "whole rounds of quads");
+#pragma unroll
+    for (int q0 = 0; q0 < QUADS; q0 += C::THREADS) {
+        const int q = q0 + (int)threadIdx.x;
+        const int lr = q / QPR, lc = (q % QPR) * 4;
+        const int row = i0 + lr, col = j0 + lc;
+        if (row >= g.Mo || col >= g.No) continue;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < n_part; ++w)
+            v += *reinterpret_cast<const f32x4*>(smem + w * C::WAVE_BYTES + (lr * C::PART_STRIDE + lc) * 4);
+        store_quad(g, v, row, col, min(4, g.No - col));
+    }
+}
+
+// How a product is cut: tiles_m x tiles_n workgroups, tiles ordered in bands of group_m tile rows.
+struct SlimSched {
+    int tiles_m, tiles_n, group_m;
+};
+
+// Workgroups go round-robin to the XCDs; this gives each XCD one contiguous run of tiles, whatever the count.
+__device__ __forceinline__ int xcd_run(int bid, int nblk) {
+    const int x = bid % NUM_XCD, q = nblk / NUM_XCD, r = nblk % NUM_XCD;
+    return x * q + min(x, r) + bid / NUM_XCD;
+}
+
+template <int BM, int BN, int NW, int LA, int LB>
+__global__ void __launch_bounds__(NW * 64) gemm_slim_kernel(GemmArgs g, SlimSched sc) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int tm, tn;
+    tile_of_index(xcd_run(blockIdx.x, gridDim.x), sc.tiles_m, sc.tiles_n, sc.group_m, tm, tn);
+    slim_tile_body<BM, BN, NW, LA, LB>(g, tm * BM, tn * BN, smem);
+}
+
+}  // namespace axo
