@@ -115,15 +115,16 @@ int axo_shard_dims(const axo_problem_t *p, int64_t *M, int64_t *Kl, int64_t *Nl,
  * Returns 0 for an invalid problem (the op call itself reports the error). */
 size_t axo_workspace_bytes(const axo_problem_t *p, int op);
 
-/* Which kernels a product takes, as axo_fc_route reports it: how its shape fits the tuned kernel's 256-row
- * tiles.  Within TILED, COVERED and INTERIOR_STRIPS a product that is too small to occupy the GPU with such
- * tiles runs on 32 x 32 or 64 x 64 tiles instead, wherever those are estimated quicker from the shape alone. */
+/* How a product's shape fits the tuned kernel's tiles (256 rows, 128 or 256 columns), as axo_fc_route
+ * reports it.  Under TILED and COVERED a product that is too small to occupy the GPU with such tiles runs on
+ * 32 x 32 or 64 x 64 tiles instead, wherever those are estimated quicker from the shape alone. */
 typedef enum axo_route {
     AXO_ROUTE_NONE = 0,            /* an empty output: nothing is launched                                 */
-    AXO_ROUTE_TILED = 1,           /* the tuned MFMA kernel, one launch                                    */
-    AXO_ROUTE_COVERED = 2,         /* a ragged output covered with whole (overlapping) tuned tiles         */
-    AXO_ROUTE_INTERIOR_STRIPS = 3, /* the interior on the tuned kernel, leftover strips on small tiles    */
-    AXO_ROUTE_GENERAL = 4          /* small tiles; past a span of 4 GiB the bounds-checked 64-bit kernel   */
+    AXO_ROUTE_TILED = 1,           /* whole tiles, one launch                                              */
+    AXO_ROUTE_COVERED = 2,         /* a ragged output: tiles that reach over its edge, one launch          */
+    AXO_ROUTE_INTERIOR_STRIPS = 3, /* no longer used                                                       */
+    AXO_ROUTE_GENERAL = 4          /* below one tile: small tiles; a span past 4 GiB: a bounds-checked     */
+                                   /* kernel with 64-bit addressing, several times slower                  */
 } axo_route_t;
 
 /* Host only.  Reports in *route (axo_route_t) which kernels the product `op` (axo_op_t) of this
@@ -144,11 +145,10 @@ int axo_fc_route(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int
  * Errors: those of axo_shard_dims; BAD_EPILOGUE (unknown epilogue, or one with bias == NULL);
  * NULL_PTR, BAD_LD, MISALIGNED for X, W, Y, bias; BAD_ARG (Y shares bytes with X, W or bias); WORKSPACE;
  * HIP; NO_MEMORY.
- * Speed: the tuned kernel takes shards whose reduction length (Kl here, Nl for dgrad) is a multiple of 8 and
- * whose output has at least 256 rows and 128 columns, the column count a multiple of 8; leading dimensions
- * that are multiples of 64 elements keep every 128-byte row segment inside one cache line (worth 10-20 %).
- * Everything else runs on small tiles (at best about half the tuned kernel's rate), apart from operands whose
- * span passes 4 GiB, for which a bounds-checked kernel is several times slower; axo_fc_route tells which. */
+ * Speed: any shard runs on MFMA tiles; leading dimensions that are multiples of 64 elements keep every 128-byte
+ * row segment inside one cache line (worth 10-20 %).  Operands whose span (256 rows, or the whole reduction
+ * where that is the row index) passes 4 GiB are computed by a bounds-checked kernel several times slower;
+ * axo_fc_route tells. */
 int axo_fc_fwd(const axo_problem_t *p, const void *X, int64_t ldx, const void *W, int64_t ldw,
                const void *bias, int epilogue, void *Y, int64_t ldy,
                void *ws, size_t ws_bytes, void *hip_stream);

@@ -9,7 +9,6 @@
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
-#include <deque>
 #include <functional>
 #include <map>
 #include <mutex>
@@ -112,18 +111,6 @@ bool spans_ok(const GemmArgs& g, int la, int lb) {
     return span_ok(la, g.lda, walked) && span_ok(lb, g.ldb, walked);
 }
 
-// Reductions: any length where both operands have the reduction index as their row index (wgrad:
-// rows beyond the end read as zeros through the buffer bound); any multiple of 8 otherwise (an
-// operand with the reduction inside its rows has its last fragments masked in registers, which
-// needs whole 16-byte fragments).  The kernel walks the length rounded up to 128.
-bool tileable(const GemmArgs& g, int la, int lb) {
-    const bool any_reduction = la == axo::MC && lb == axo::MC;
-    if (!(g.R > 0 && (any_reduction || g.R % 8 == 0) && g.Mo > 0 && g.No > 0 && g.Mo % 256 == 0 &&
-          g.No % 128 == 0))
-        return false;
-    return spans_ok(g, la, lb);
-}
-
 // Time (in big-tile units) a greedy dispatch of n_big big tiles followed by n_small small tiles
 // takes on NUM_CU CUs: workgroups are handed out in order to whichever CU is free first.
 double makespan(int n_big, int n_small) {
@@ -147,6 +134,9 @@ double makespan(int n_big, int n_small) {
 // apart, once the launch has a workgroup for every CU (a smaller one has no chip-wide burst).
 int stagger_units(int blocks) { return blocks >= NUM_CU ? 3 : 0; }
 
+// 128-wide tile columns that cover what `big_cols` 256-wide ones leave of No.
+int half_cols(int No, int big_cols) { return No > big_cols * 256 ? (No - big_cols * 256 + 127) / 128 : 0; }
+
 // Choose how many 256-wide tile columns to use; the remaining columns become 128-wide tiles.
 // Plans are cached per output shape (the search simulates the dispatch).
 axo::TileSched plan_tiles(int Mo, int No) {
@@ -156,12 +146,12 @@ axo::TileSched plan_tiles(int Mo, int No) {
     auto it = cache.find({Mo, No});
     if (it != cache.end()) return it->second;
     axo::TileSched sc{};
-    sc.tiles_m = Mo / 256;
-    const int max_big_cols = No / 256;
+    sc.tiles_m = (Mo + 255) / 256;
+    const int max_big_cols = (No + 255) / 256;  // the last one may reach over the edge
     int best_cols = max_big_cols;
     double best = 1e30;
     for (int cb = max_big_cols; cb >= 0; --cb) {
-        const int small_cols = (No - cb * 256) / 128;
+        const int small_cols = half_cols(No, cb);
         const double t = makespan(sc.tiles_m * cb, sc.tiles_m * small_cols);
         if (t < best - 1e-9) {
             best = t;
@@ -169,7 +159,7 @@ axo::TileSched plan_tiles(int Mo, int No) {
         }
     }
     sc.big_cols = best_cols;
-    sc.small_cols = (No - best_cols * 256) / 128;
+    sc.small_cols = half_cols(No, best_cols);
     sc.n_big = sc.tiles_m * sc.big_cols;
     sc.group_m = sc.tiles_m < 4 ? sc.tiles_m : 4;
     sc.stagger = stagger_units(sc.n_big + sc.tiles_m * sc.small_cols);
@@ -245,12 +235,12 @@ int slim_rows(const GemmArgs& g, int pair) {
     return slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair) <= slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair) ? 32 : 64;
 }
 // Whether a product that the 256-row tiles could take runs on small tiles instead: where those are
-// estimated at least 10 % quicker.  A function of sizes and layouts only, because the waves of a small tile
+// estimated at least 35 % quicker (in a chain the larger tiles share a launch with other products' tiles).  A function of sizes and layouts only, because the waves of a small tile
 // split the reduction and so sum in another order: a product has the same bits on its own and in a chain.
 bool prefers_slim(const GemmArgs& g, int la, int lb) {
     const int pair = layout_pair(la, lb);
     const double slim = std::min(slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair), slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair));
-    return slim < 0.9 * tile_time(g.Mo, g.No, g.R);
+    return slim < 0.65 * tile_time(g.Mo, g.No, g.R);
 }
 
 template <int ROWS, int LA, int LB>
@@ -320,7 +310,7 @@ std::vector<SegCost> group_segments(const std::vector<GroupItem>& items, const s
             segs.push_back({bias_strip_cost(items[i].Mo), bias_strips(items[i].No), (int)i, 0});
             continue;
         }
-        const int tiles_m = items[i].Mo / 256, cb = big_cols[i], cs = (items[i].No - cb * 256) / 128;
+        const int tiles_m = (items[i].Mo + 255) / 256, cb = big_cols[i], cs = half_cols(items[i].No, cb);
         if (cb > 0) segs.push_back({tile_cost(items[i].R, false), tiles_m * cb, (int)i, 0});
         if (cs > 0) segs.push_back({tile_cost(items[i].R, true), tiles_m * cs, (int)i, 1});
     }
@@ -351,12 +341,12 @@ std::vector<int> plan_group(const std::vector<GroupItem>& items) {
     auto it = cache.find(items);
     if (it != cache.end()) return it->second;
     std::vector<int> cols(items.size());
-    for (size_t i = 0; i < items.size(); ++i) cols[i] = items[i].pair == PAIR_BIAS_GRAD ? 0 : items[i].No / 256;
+    for (size_t i = 0; i < items.size(); ++i) cols[i] = items[i].pair == PAIR_BIAS_GRAD ? 0 : (items[i].No + 255) / 256;
     double best = group_makespan(group_segments(items, cols));
     for (int sweep = 0; sweep < 2; ++sweep)
         for (size_t i = 0; i < items.size(); ++i) {
             if (items[i].pair == PAIR_BIAS_GRAD) continue;
-            const int max_cols = items[i].No / 256;
+            const int max_cols = (items[i].No + 255) / 256;
             const int stride = max_cols > 16 ? (max_cols + 15) / 16 : 1;
             int best_c = cols[i];
             for (int c = max_cols; c >= 0; c -= stride) {
@@ -391,7 +381,7 @@ struct Plan {
     bool nothing_to_do() const { return bias_grad ? bg.Nl == 0 : (g.Mo == 0 || g.No == 0); }
 };
 
-// One launch over the tiles of all given products (each tileable and non-empty, at most
+// One launch over the tiles of all given products (each Kernel::tiles, at most
 // GROUP_MAX_PRODUCTS of them).
 int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     static std::atomic<uint64_t> raised{0};
@@ -420,7 +410,7 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
             sg.group_m = 1;
         } else {
             sg.kind = 2 * items[sc.item].pair + sc.small;
-            sg.tiles_m = items[sc.item].Mo / 256;
+            sg.tiles_m = (items[sc.item].Mo + 255) / 256;
             sg.cols = sc.count / sg.tiles_m;
             sg.col0 = sc.small ? cols[sc.item] * 256 : 0;
             sg.group_m = sg.tiles_m < 4 ? sg.tiles_m : 4;
@@ -445,89 +435,28 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 
-// The product restricted to output rows [r0, r0 + rows) and columns [c0, c0 + cols): the same
-// operands and output addressed through offset pointers, same leading dimensions.
-GemmArgs sub_product(const GemmArgs& g, int la, int lb, int r0, int rows, int c0, int cols) {
-    GemmArgs s = g;
-    s.A = la == axo::KC ? g.A + (int64_t)r0 * g.lda : g.A + r0;   // KC: row i of A; MC: column i of A
-    s.B = lb == axo::KC ? g.B + (int64_t)c0 * g.ldb : g.B + c0;
-    if (g.epilogue == axo::EPI_ACC_F32)                           // C counts fp32 elements
-        s.C = reinterpret_cast<axo::bf16_t*>(reinterpret_cast<float*>(g.C) + (int64_t)r0 * g.ldc + c0);
-    else
-        s.C = g.C + (int64_t)r0 * g.ldc + c0;
-    if (g.bias) s.bias = g.bias + c0;
-    if (g.aux) s.aux = g.aux + (int64_t)r0 * g.ldaux + c0;
-    s.Mo = rows;
-    s.No = cols;
-    return s;
-}
-
-// A product whose reduction fits the tuned kernel but whose output misses its granularity (256
-// rows, 128 columns) can still be covered with whole tiles: the interior, plus a band of the last
-// 256 rows and a band of the last 128 columns that reach back over the interior.  Where bands and
-// interior overlap an element is computed twice, by the same instructions in the same order (its
-// value does not depend on the tile it falls in), so the second store rewrites the same bits.
-// Conditions: the shifted origins must keep the 16-byte alignment of the loads and stores, i.e.
-// No % 8 == 0 and, where the output row index is the contiguous one of operand A (wgrad),
-// Mo % 8 == 0; and the epilogue must be a pure function of the sum (not the fp32 accumulation,
-// which would add twice).  On success `out` receives 2 to 4 tileable pieces.
-bool cover_with_tiles(const Plan& pl, std::vector<Plan>* out) {
-    const GemmArgs& g = pl.g;
-    if (g.epilogue == axo::EPI_ACC_F32 || g.Mo < 256 || g.No < 128 || g.No % 8 != 0) return false;
-    if (pl.la == axo::MC && g.Mo % 8 != 0) return false;
-    const int Mi = g.Mo / 256 * 256, Ni = g.No / 128 * 128;
-    int rows[2][2] = {{0, Mi}, {g.Mo - 256, 256}}, cols[2][2] = {{0, Ni}, {g.No - 128, 128}};
-    const int nr = g.Mo > Mi ? 2 : 1, nc = g.No > Ni ? 2 : 1;
-    out->clear();
-    for (int a = 0; a < nr; ++a)
-        for (int b = 0; b < nc; ++b) {
-            Plan piece = pl;
-            piece.g = sub_product(g, pl.la, pl.lb, rows[a][0], rows[a][1], cols[b][0], cols[b][1]);
-            if (!tileable(piece.g, pl.la, pl.lb)) return false;
-            out->push_back(piece);
-        }
-    return out->size() > 1;
-}
-
-// One product: the tuned kernel when it takes the shape; a cover of whole tiles in one grouped
-// launch when only the output's granularity is in the way; failing that, the interior on the
-// tuned kernel and the leftover strips on small tiles; small tiles for the rest, and the
-// general kernel (64-bit addressing, an order of magnitude slower) where a span passes 4 GiB.
-int route_of(const GemmArgs& g, int la, int lb, std::vector<Plan>* pieces) {
-    if (g.Mo == 0 || g.No == 0) return AXO_ROUTE_NONE;
-    if (tileable(g, la, lb)) return AXO_ROUTE_TILED;
-    Plan whole;
-    whole.g = g;
-    whole.la = la;
-    whole.lb = lb;
-    if (cover_with_tiles(whole, pieces)) return AXO_ROUTE_COVERED;
-    const int Mi = g.Mo / 256 * 256, Ni = g.No / 128 * 128;
-    // block offsets that are multiples of 256 rows and 128 columns keep every alignment
-    if (Mi > 0 && Ni > 0 && tileable(sub_product(g, la, lb, 0, Mi, 0, Ni), la, lb)) return AXO_ROUTE_INTERIOR_STRIPS;
-    return AXO_ROUTE_GENERAL;
+// Which kernel a product takes; a function of its sizes, layouts and leading dimensions.
+enum class Kernel { none, tiles, small_tiles, general };
+Kernel kernel_of(const GemmArgs& g, int la, int lb) {
+    if (g.Mo == 0 || g.No == 0) return Kernel::none;
+    if (!spans_ok(g, la, lb)) return Kernel::general;  // 64-bit addressing, an order of magnitude slower
+    return g.R == 0 || prefers_slim(g, la, lb) ? Kernel::small_tiles : Kernel::tiles;
 }
 
 int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
-    if (g.Mo == 0 || g.No == 0) return AXO_OK;
-    if (!spans_ok(g, la, lb)) return launch_generic(g, la, lb, st);
-    if (prefers_slim(g, la, lb)) return launch_slim(g, la, lb, st);
-    std::vector<Plan> pieces;
-    switch (route_of(g, la, lb, &pieces)) {
-        case AXO_ROUTE_TILED: return launch_tile_layout(g, la, lb, st);
-        case AXO_ROUTE_COVERED: {
-            const Plan* ptr[4];
-            for (size_t i = 0; i < pieces.size(); ++i) ptr[i] = &pieces[i];
-            return launch_group(ptr, (int)pieces.size(), st);
-        }
-        case AXO_ROUTE_INTERIOR_STRIPS: {
-            const int Mi = g.Mo / 256 * 256, Ni = g.No / 128 * 128;
-            int rc = launch_tile_layout(sub_product(g, la, lb, 0, Mi, 0, Ni), la, lb, st);
-            if (rc == AXO_OK && g.No > Ni) rc = launch_slim(sub_product(g, la, lb, 0, g.Mo, Ni, g.No - Ni), la, lb, st);
-            if (rc == AXO_OK && g.Mo > Mi) rc = launch_slim(sub_product(g, la, lb, Mi, g.Mo - Mi, 0, Ni), la, lb, st);
-            return rc;
-        }
-        default: return launch_slim(g, la, lb, st);
+    switch (kernel_of(g, la, lb)) {
+        case Kernel::none: return AXO_OK;
+        case Kernel::tiles: return launch_tile_layout(g, la, lb, st);
+        case Kernel::small_tiles: return launch_slim(g, la, lb, st);
+        default: return launch_generic(g, la, lb, st);
     }
+}
+
+// How the shape fits the 256 x 128 granularity of the tiles, for axo_fc_route.
+int route_of(const GemmArgs& g, int la, int lb) {
+    if (g.Mo == 0 || g.No == 0) return AXO_ROUTE_NONE;
+    if (!spans_ok(g, la, lb) || g.R == 0 || g.Mo < 256 || g.No < 128) return AXO_ROUTE_GENERAL;
+    return g.Mo % 256 == 0 && g.No % 128 == 0 ? AXO_ROUTE_TILED : AXO_ROUTE_COVERED;
 }
 
 int check_no_alias(const Plan& pl);  // defined with the byte-range code below
@@ -889,7 +818,7 @@ Footprint footprint(const Plan& pl) {
 }
 // The rule of the header, checked: an output that shares bytes with an input of its own product is
 // refused.  The kernels write an output tile while other workgroups still read the operands, and
-// a ragged output is covered with overlapping tiles that are computed twice, so an in-place call
+// the tiles along a ragged output's edge overlap and compute what they share twice, so an in-place call
 // (say dX written over the pre-activation it is multiplied with) would silently go wrong.
 int check_no_alias(const Plan& pl) { return footprint(pl).output_aliases_input() ? AXO_ERR_BAD_ARG : AXO_OK; }
 // Dependence level of every product of a chain given in program order: 0 when it conflicts with
@@ -925,7 +854,6 @@ int dependence_levels(const std::vector<Plan>& plans, std::vector<int>* level) {
 // grouped launches (GROUP_MAX_PRODUCTS per launch), the others get a launch of their own.
 int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& level, int levels, hipStream_t st) {
     int rc = AXO_OK;
-    std::deque<Plan> covers;          // pieces of covered products (a deque keeps their addresses)
     std::vector<const Plan*> group;   // products of the level the tiled kernel takes
     std::vector<const Plan*> riders;  // bias gradients of the level that may share their launch
     auto flush = [&]() {
@@ -953,18 +881,8 @@ int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& lev
                 else rc = launch_bias_grad(pl.bg, st);
                 continue;
             }
-            if (!tileable(pl.g, pl.la, pl.lb) || prefers_slim(pl.g, pl.la, pl.lb)) {
-                std::vector<Plan> pieces;
-                if (prefers_slim(pl.g, pl.la, pl.lb) || !cover_with_tiles(pl, &pieces)) {
-                    rc = launch(pl.g, pl.la, pl.lb, st);
-                    continue;
-                }
-                if (group.size() + pieces.size() > (size_t)axo::GROUP_MAX_PRODUCTS) flush();
-                for (const Plan& piece : pieces) {  // the pieces of a cover share the level's grouped launch
-                    covers.push_back(piece);
-                    group.push_back(&covers.back());
-                }
-                if ((int)group.size() >= axo::GROUP_MAX_PRODUCTS) flush();
+            if (kernel_of(pl.g, pl.la, pl.lb) != Kernel::tiles) {
+                rc = launch(pl.g, pl.la, pl.lb, st);
                 continue;
             }
             group.push_back(&pl);
@@ -1060,8 +978,7 @@ int axo_fc_route(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int
                        : op == AXO_OP_DGRAD ? plan_dgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, &pl)
                                             : plan_wgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, &pl);
         if (rc) return rc;
-        std::vector<Plan> pieces;
-        *route = route_of(pl.g, pl.la, pl.lb, &pieces);
+        *route = route_of(pl.g, pl.la, pl.lb);
         return AXO_OK;
     });
 }

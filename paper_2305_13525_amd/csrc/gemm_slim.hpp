@@ -42,76 +42,6 @@ __device__ __forceinline__ int swz_mc_narrow(int k) {
     return ROWS == 32 ? ((k >> 3) & 1) << 1 : (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
 }
 
-// The first `n` (none if n <= 0, all if n >= 8) of the 8 bf16 elements of a 16-byte chunk, the others zero.
-__device__ __forceinline__ u32x4 first_elements(u32x4 w, int n) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) w[d] &= n >= 2 * d + 2 ? 0xFFFFFFFFu : (n == 2 * d + 1 ? 0xFFFFu : 0u);
-    return w;
-}
-__device__ __forceinline__ bf16x8 first_elements(bf16x8 f, int n) {
-    union { bf16x8 v; u32x4 u; } x;
-    x.v = f;
-    x.u = first_elements(x.u, n);
-    return x.v;
-}
-
-// Bound of the buffer descriptor of an operand tile: bytes from the tile's origin to the end of the last
-// valid element of its `rows` valid rows (KC) or columns (MC) of a reduction of R.
-template <int LAYOUT>
-__device__ __forceinline__ uint32_t operand_bound(int64_t ld, int rows, int R) {
-    const int64_t elems = LAYOUT == KC ? (int64_t)(rows - 1) * ld + R : ((int64_t)R - 1) * ld + rows;
-    return R > 0 ? (uint32_t)((elems * 2 + 3) & ~(int64_t)3) : 0u;
-}
-
-// Raw buffer descriptor: base, stride 0, dword format, bound in bytes.
-__device__ __forceinline__ u32x4_t tile_rsrc(const bf16_t* p, uint32_t bound) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    u32x4_t r;
-    r[0] = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32) & 0xFFFFu);
-    r[2] = __builtin_amdgcn_readfirstlane(bound);
-    r[3] = 0x00020000u;
-    return r;
-}
-
-// Four consecutive outputs of one row, `valid` (1..4) of them inside the matrix: epilogue and store.
-__device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, const int row, const int col, const int valid) {
-    if (g.epilogue == EPI_ACC_F32) {
-        float* out = reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col;
-        if (valid == 4) *reinterpret_cast<f32x4*>(out) = *reinterpret_cast<const f32x4*>(out) + v;
-        else
-            for (int e = 0; e < valid; ++e) out[e] += v[e];
-        return;
-    }
-    if (g.epilogue != EPI_NONE) {
-        const bool fwd = g.epilogue <= EPI_BIAS_GELU_ERF;
-        float x[4] = {0.f, 0.f, 0.f, 0.f};  // bias, or the pre-activations
-        if (!fwd || g.add_bias) {
-            const bf16_t* src = fwd ? g.bias + col : g.aux + (int64_t)row * g.ldaux + col;
-            if (valid == 4) {
-                const uint2 raw = *reinterpret_cast<const uint2*>(src);
-                x[0] = __uint_as_float(raw.x << 16);
-                x[1] = __uint_as_float(raw.x & 0xFFFF0000u);
-                x[2] = __uint_as_float(raw.y << 16);
-                x[3] = __uint_as_float(raw.y & 0xFFFF0000u);
-            } else
-                for (int e = 0; e < valid; ++e) x[e] = bf16_bits_to_f32(src[e]);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = fwd ? apply_epilogue(v[e], x[e], g.epilogue) : apply_dact(v[e], x[e], g.epilogue);
-    }
-    bf16_t* out = g.C + (int64_t)row * g.ldc + col;
-    uint2 packed;
-    packed.x = pack_bf16x2(v[0], v[1]);
-    packed.y = pack_bf16x2(v[2], v[3]);
-    if (valid == 4) *reinterpret_cast<uint2*>(out) = packed;
-    else {
-        out[0] = (bf16_t)packed.x;
-        if (valid > 1) out[1] = (bf16_t)(packed.x >> 16);
-        if (valid > 2) out[2] = (bf16_t)packed.y;
-    }
-}
-
 // One operand of a tile as one wave sees it: ROWS output rows (or columns) by 64 reduction elements.
 template <int ROWS, int LAYOUT>
 struct SlimOperand {
@@ -282,10 +212,13 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
         const int lr = q / QPR, lc = (q % QPR) * 4;
         const int row = i0 + lr, col = j0 + lc;
         if (row >= g.Mo || col >= g.No) continue;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        const int valid = min(4, g.No - col);
+        f32x4 x = {0.f, 0.f, 0.f, 0.f}, v = x;
+        if (g.epilogue >= EPI_MUL_DGELU_TANH) x = load_quad_extra(g, row, col, valid);
+        else if (g.epilogue != EPI_NONE && g.add_bias) x = load_bf16x4(g.bias + col, valid);
         for (int w = 0; w < n_part; ++w)
             v += *reinterpret_cast<const f32x4*>(smem + w * C::WAVE_BYTES + (lr * C::PART_STRIDE + lc) * 4);
-        store_quad(g, v, row, col, min(4, g.No - col));
+        store_quad(g, v, x, row, col, valid);
     }
 }
 
@@ -293,12 +226,6 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
 struct SlimSched {
     int tiles_m, tiles_n, group_m;
 };
-
-// Workgroups go round-robin to the XCDs; this gives each XCD one contiguous run of tiles, whatever the count.
-__device__ __forceinline__ int xcd_run(int bid, int nblk) {
-    const int x = bid % NUM_XCD, q = nblk / NUM_XCD, r = nblk % NUM_XCD;
-    return x * q + min(x, r) + bid / NUM_XCD;
-}
 
 template <int BM, int BN, int NW, int LA, int LB>
 __global__ void __launch_bounds__(NW * 64) gemm_slim_kernel(GemmArgs g, SlimSched sc) {

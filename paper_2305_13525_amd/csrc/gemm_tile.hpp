@@ -1,8 +1,11 @@
-// Tuned bf16 MFMA GEMM for gfx950 (MI355X) for outputs that are whole multiples of the tile:
-//   C[Mo x No] = sum_r A(i, r) * B(j, r),  Mo % 256 == 0, No % 128 == 0; the reduction length R is
-//   any multiple of 8 (any length at all when both operands have it as their row index).
+// Tuned bf16 MFMA GEMM for gfx950 (MI355X):
+//   C[Mo x No] = sum_r A(i, r) * B(j, r),  any Mo, No and R > 0 (operand spans below 4 GiB).
 // Tile counts that do not fill the last round of CUs are balanced by covering part of the output
-// with half-width tiles (TileSched).
+// with half-width tiles (TileSched).  A tile that would reach over the output's edge is moved back inside
+// where the sizes allow (inside_row, inside_col); otherwise it is clipped: rows beyond an operand read as
+// zeros through the buffer bound, columns beyond it are not stored, and the tile takes an epilogue of its
+// own (tile_epilogue_clipped).  Clipping a tile that could have been moved costs it 3-4 us (measured on
+// 4000 x 2000 x 6000 with bias and GELU: 138 us forward clipped, 132 moved).
 //
 // One 512-thread workgroup (8 waves, two per SIMD) owns a BM x BN output tile and walks the
 // reduction in steps of 64 through two LDS stages.  Operand tiles are copied global -> LDS by
@@ -103,11 +106,10 @@ __device__ __forceinline__ void start_stagger(int bid, int units) {
 // Workgroup -> output tile.  Consecutive workgroup ids go round-robin to the 8 XCDs, each with
 // its own L2, so the ids that land on one XCD are given one contiguous run of tiles, and tiles
 // are ordered in bands of group_m tile-rows so that the tiles in flight on an XCD share operand
-// panels.
-__device__ __forceinline__ int xcd_contiguous(int bid, int nblk) {
-    if (nblk % NUM_XCD != 0) return bid;
-    const int per = nblk / NUM_XCD;
-    return (bid % NUM_XCD) * per + bid / NUM_XCD;
+// panels.  Any count: the first nblk % 8 XCDs get one tile more.
+__device__ __forceinline__ int xcd_run(int bid, int nblk) {
+    const int x = bid % NUM_XCD, q = nblk / NUM_XCD, r = nblk % NUM_XCD;
+    return x * q + min(x, r) + bid / NUM_XCD;
 }
 
 __device__ __forceinline__ void tile_of_index(int t, int tiles_m, int tiles_n, int group_m, int& tm, int& tn) {
@@ -127,25 +129,25 @@ struct TileCfg {
     static constexpr int AH = TM / 2;                     // A tiles per MFMA group (half the wave tile's rows)
     static constexpr int A_BYTES = BM * TILE_BK * 2, B_BYTES = BN * TILE_BK * 2;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    static constexpr int A_ROUNDS = BM * (TILE_BK / 8) / TILE_THREADS, B_ROUNDS = BN * (TILE_BK / 8) / TILE_THREADS;
+    static constexpr int WAVES = WGM * WGN, THREADS = WAVES * 64;
+    static constexpr int A_ROUNDS = BM * (TILE_BK / 8) / THREADS, B_ROUNDS = BN * (TILE_BK / 8) / THREADS;
     static constexpr int LOADS_PER_STAGE = A_ROUNDS + B_ROUNDS;
     static constexpr int EPI_STRIDE = WTN * 2 + 16;  // bytes per staged row (padded)
-    static constexpr int EPI_BYTES = 8 * WTM * EPI_STRIDE;
+    static constexpr int EPI_BYTES = WAVES * WTM * EPI_STRIDE;
     static constexpr int RING_BYTES = 2 * STAGE_BYTES;
     static constexpr int LDS_BYTES = (RING_BYTES > EPI_BYTES) ? RING_BYTES : EPI_BYTES;
-    static_assert(WGM * WGN == 8, "8 waves");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of pairs of 16x16 MFMA tiles");
-    static_assert((BM * (TILE_BK / 8)) % TILE_THREADS == 0 && (BN * (TILE_BK / 8)) % TILE_THREADS == 0, "whole load rounds");
+    static_assert((BM * (TILE_BK / 8)) % THREADS == 0 && (BN * (TILE_BK / 8)) % THREADS == 0, "whole load rounds");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
 // Per-lane byte offset (from the operand tile's origin at reduction step 0) of the 16-byte chunk
 // this lane fetches in each load round.  Must stay below 2^32 (checked on the host).
-template <int ROWS, int LAYOUT, int ROUNDS>
+template <int ROWS, int LAYOUT, int ROUNDS, int THREADS>
 __device__ __forceinline__ void load_offsets(int tid, int64_t ld, uint32_t* off) {
 #pragma unroll
     for (int j = 0; j < ROUNDS; ++j) {
-        const int q = j * TILE_THREADS + tid;
+        const int q = j * THREADS + tid;
         if (LAYOUT == KC) {
             constexpr int CPR = TILE_BK / 8;  // chunks per row
             const int r = q / CPR, cs = q % CPR;
@@ -210,6 +212,92 @@ struct FragAddr {
 };
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;  // a buffer resource descriptor in four SGPRs
+
+// The first `n` (none if n <= 0, all if n >= 8) of the 8 bf16 elements of a 16-byte chunk, the others zero.
+__device__ __forceinline__ u32x4 first_elements(u32x4 w, int n) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] &= n >= 2 * d + 2 ? 0xFFFFFFFFu : (n == 2 * d + 1 ? 0xFFFFu : 0u);
+    return w;
+}
+__device__ __forceinline__ bf16x8 first_elements(bf16x8 f, int n) {
+    union { bf16x8 v; u32x4 u; } x;
+    x.v = f;
+    x.u = first_elements(x.u, n);
+    return x.v;
+}
+
+// Bound of the buffer descriptor of an operand tile: bytes from the tile's origin to the end of the last
+// valid element of its `rows` valid rows (KC) or columns (MC) of a reduction of R.
+template <int LAYOUT>
+__device__ __forceinline__ uint32_t operand_bound(int64_t ld, int rows, int R) {
+    const int64_t elems = LAYOUT == KC ? (int64_t)(rows - 1) * ld + R : ((int64_t)R - 1) * ld + rows;
+    return R > 0 ? (uint32_t)((elems * 2 + 3) & ~(int64_t)3) : 0u;
+}
+
+// Raw buffer descriptor: base, stride 0, dword format, bound in bytes.
+__device__ __forceinline__ u32x4_t tile_rsrc(const bf16_t* p, uint32_t bound) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    u32x4_t r;
+    r[0] = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32) & 0xFFFFu);
+    r[2] = __builtin_amdgcn_readfirstlane(bound);
+    r[3] = 0x00020000u;
+    return r;
+}
+
+// Four consecutive bf16 values of memory (8-byte aligned), the first `valid` of them inside the matrix.
+__device__ __forceinline__ f32x4 load_bf16x4(const bf16_t* p, int valid) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (valid >= 4) {
+        const uint2 raw = *reinterpret_cast<const uint2*>(p);
+        x[0] = __uint_as_float(raw.x << 16);
+        x[1] = __uint_as_float(raw.x & 0xFFFF0000u);
+        x[2] = __uint_as_float(raw.y << 16);
+        x[3] = __uint_as_float(raw.y & 0xFFFF0000u);
+    } else
+        for (int e = 0; e < valid; ++e) x[e] = bf16_bits_to_f32(p[e]);
+    return x;
+}
+__device__ __forceinline__ f32x4 load_f32x4(const float* p, int valid) {
+    if (valid >= 4) return *reinterpret_cast<const f32x4*>(p);
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < valid; ++e) x[e] = p[e];
+    return x;
+}
+
+// Stores four consecutive outputs of one row, `valid` (1..4) of them inside the matrix, after the epilogue.
+// `x` is what the epilogue adds or multiplies with: bias, pre-activations, or the fp32 values accumulated into.
+__device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, f32x4 x, const int row, const int col, const int valid) {
+    if (g.epilogue == EPI_ACC_F32) {
+        float* out = reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col;
+        v = x + v;
+        if (valid >= 4) *reinterpret_cast<f32x4*>(out) = v;
+        else
+            for (int e = 0; e < valid; ++e) out[e] = v[e];
+        return;
+    }
+    if (g.epilogue != EPI_NONE) {
+        const bool fwd = g.epilogue <= EPI_BIAS_GELU_ERF;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fwd ? apply_epilogue(v[e], x[e], g.epilogue) : apply_dact(v[e], x[e], g.epilogue);
+    }
+    bf16_t* out = g.C + (int64_t)row * g.ldc + col;
+    uint2 packed;
+    packed.x = pack_bf16x2(v[0], v[1]);
+    packed.y = pack_bf16x2(v[2], v[3]);
+    if (valid >= 4) *reinterpret_cast<uint2*>(out) = packed;
+    else {
+        out[0] = (bf16_t)packed.x;
+        if (valid > 1) out[1] = (bf16_t)(packed.x >> 16);
+        if (valid > 2) out[2] = (bf16_t)packed.y;
+    }
+}
+// The `x` of store_quad for these outputs, apart from the bias, which depends on the column only.
+__device__ __forceinline__ f32x4 load_quad_extra(const GemmArgs& g, const int row, const int col, const int valid) {
+    if (g.epilogue == EPI_ACC_F32) return load_f32x4(reinterpret_cast<const float*>(g.C) + (int64_t)row * g.ldc + col, valid);
+    return load_bf16x4(g.aux + (int64_t)row * g.ldaux + col, valid);
+}
+
 template <int V>
 using IC = std::integral_constant<int, V>;
 
@@ -234,234 +322,10 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// One BM x BN output tile with its top-left corner at (i0, j0), whole reduction.
-template <int BM, int BN, int WGM, int WGN, int LA, int LB>
-__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
-    using C = TileCfg<BM, BN, WGM, WGN>;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
-    // The loop is unrolled over the two LDS stages, so it walks the reduction rounded up to the
-    // next multiple of 128; what lies beyond the true length must contribute nothing, whatever
-    // the memory there holds (zeros would do for finite data, but a stray infinity times a zero
-    // of the other operand would put a NaN into a row that has none: BOTH operands are made zero).
-    //  * MC operand (reduction index = row index): rows at or beyond R lie behind the buffer
-    //    descriptor's bound, the byte count from the tile origin to the end of the tile's columns
-    //    in row R - 1, and read as zeros.
-    //  * KC operand (reduction inside the rows): the overrun of a row lands in the next row,
-    //    which no linear bound can mask; the surplus 16-byte chunks of the last two steps are
-    //    overwritten with zeros in LDS instead (R is a multiple of 8 here, so a chunk is wholly
-    //    inside or wholly outside).  The bound (end of the tile's last row) only keeps the last
-    //    row's overrun from touching memory behind the matrix.
-    // On this chip the range check covers the sum of the per-lane offset and the scalar offset
-    // that carries the reduction step (measured: lowering the bound by the scalar offset at every
-    // step zeroed the second half of the reduction), so one constant bound serves the whole walk.
-    const int KT = (g.R + 2 * TILE_BK - 1) / (2 * TILE_BK) * 2;
-    const bool tail = (g.R % (2 * TILE_BK)) != 0;
-
-    // global side: descriptor at the tile origin, per-lane offsets, scalar step
-    const bf16_t* Ab = (LA == KC) ? g.A + (int64_t)i0 * g.lda : g.A + i0;
-    const bf16_t* Bb = (LB == KC) ? g.B + (int64_t)j0 * g.ldb : g.B + j0;
-    // raw buffer descriptor: base, stride 0, dword format, bound in bytes
-    auto make_rsrc = [](const bf16_t* p, uint32_t bound) __attribute__((always_inline)) {
-        const uint64_t v = reinterpret_cast<uint64_t>(p);
-        u32x4_t r;
-        r[0] = __builtin_amdgcn_readfirstlane((uint32_t)v);
-        r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32) & 0xFFFFu);
-        r[2] = __builtin_amdgcn_readfirstlane(bound);
-        r[3] = 0x00020000u;
-        return r;
-    };
-    const uint32_t a_valid = (LA == KC) ? (uint32_t)(((int64_t)(BM - 1) * g.lda + g.R) * 2)
-                                        : (uint32_t)((((int64_t)g.R - 1) * g.lda + BM) * 2);
-    const uint32_t b_valid = (LB == KC) ? (uint32_t)(((int64_t)(BN - 1) * g.ldb + g.R) * 2)
-                                        : (uint32_t)((((int64_t)g.R - 1) * g.ldb + BN) * 2);
-    const u32x4_t a_rsrc = make_rsrc(Ab, a_valid);
-    const u32x4_t b_rsrc = make_rsrc(Bb, b_valid);
-    const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
-    const uint32_t a_step = (uint32_t)((LA == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.lda * 2);
-    const uint32_t b_step = (uint32_t)((LB == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.ldb * 2);
-    uint32_t a_off[C::A_ROUNDS], b_off[C::B_ROUNDS];
-    load_offsets<BM, LA, C::A_ROUNDS>(tid, g.lda, a_off);
-    load_offsets<BN, LB, C::B_ROUNDS>(tid, g.ldb, b_off);
-
-    // LDS side: [A stage 0][A stage 1][B stage 0][B stage 1]; fragment addresses of stage 0
-    FragAddr<BM, LA, C::TM> fra;
-    FragAddr<BN, LB, C::TN> frb;
-    fra.init(wm * C::WTM, lane, 0);
-    frb.init(wn * C::WTN, lane, 2 * C::A_BYTES);
-
-    f32x4 acc[C::TM][C::TN];
-#pragma unroll
-    for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-        for (int b = 0; b < C::TN; ++b)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
-
-    // A reduction step of 64 is four MFMA groups: (sub-step kq, row half ah) for kq, ah in {0, 1};
-    // a group multiplies AH A fragments with all TN B fragments of its sub-step.  A fragments are
-    // double buffered per group, B fragments per sub-step.
-    bf16x8 fa[2][C::AH], fb[2][C::TN];
-    auto read_a = [&](int set, int s, int kq, int ah) __attribute__((always_inline)) {
-#pragma unroll
-        for (int a = 0; a < C::AH; ++a) fa[set][a] = fra.read(smem, s, ah * C::AH + a, kq);
-    };
-    auto read_b = [&](int set, int s, int kq) __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < C::TN; ++b) fb[set][b] = frb.read(smem, s, b, kq);
-    };
-    auto mfma_group = [&](int aset, int bset, int ah) __attribute__((always_inline)) {
-#pragma unroll
-        for (int a = 0; a < C::AH; ++a)
-#pragma unroll
-            for (int b = 0; b < C::TN; ++b)
-                acc[ah * C::AH + a][b] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[bset][b], fa[aset][a], acc[ah * C::AH + a][b], 0, 0, 0);
-    };
-    constexpr int N_MFMA = C::AH * C::TN;
-    constexpr int RD_A = (LA == KC ? 1 : 2) * C::AH, RD_B = (LB == KC ? 1 : 2) * C::TN;
-    uint32_t a_soff = 0, b_soff = 0;  // scalar byte offsets of the reduction step being loaded
-    constexpr int NL = C::LOADS_PER_STAGE;
-    // One direct-to-LDS load: 16 bytes per lane from descriptor base + off + soff to LDS address
-    // M0 + 16 * lane.  Issued through inline assembly on purpose: for a load the compiler knows
-    // to write LDS it puts a full vmcnt(0) wait in front of every later transposing LDS read,
-    // which stalls the wave for a whole memory latency in every step.  The kernel keeps the
-    // ordering itself: the vmcnt(0) wait and the barrier before the last MFMA group of each step.
-    // M0 (the LDS destination of the load) is an input operand bound to the physical register, so
-    // the compiler writes it itself and knows what the statement reads.
-    auto load_lds = [](uint32_t lds_dst, uint32_t off, u32x4_t rsrc, uint32_t soff) __attribute__((always_inline)) {
-        asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds"
-                     :
-                     : "v"(off), "s"(rsrc), "s"(soff), "{m0}"(lds_dst)
-                     : "memory");
-    };
-    // Loads LO..HI-1 of the NL loads that fill stage s with the step at (a_soff, b_soff): the A
-    // rounds first, then the B rounds; round j of wave w lands at tile + (j * 512 + w * 64 + lane) * 16.
-    auto issue_range = [&](auto lo_tag, auto hi_tag, int s) __attribute__((always_inline)) {
-        constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
-#pragma unroll
-        for (int j = LO; j < HI; ++j) {
-            if (j < C::A_ROUNDS) {
-                load_lds(smem_base + s * C::A_BYTES + (j * TILE_THREADS + wave * 64) * 16, a_off[j], a_rsrc, a_soff);
-            } else {
-                const int jb = j - C::A_ROUNDS;
-                load_lds(smem_base + 2 * C::A_BYTES + s * C::B_BYTES + (jb * TILE_THREADS + wave * 64) * 16,
-                         b_off[jb], b_rsrc, b_soff);
-            }
-        }
-    };
-    auto advance = [&]() __attribute__((always_inline)) {
-        a_soff += a_step;
-        b_soff += b_step;
-    };
-    // A stage's loads are dealt out over three MFMA groups instead of one burst: half right after
-    // the barrier that frees the stage, a quarter in each of the first two groups of the next
-    // step.  The texture addresser takes one 1 KB wave-load per ~20 cycles, so eight waves that
-    // all issue their loads after the barrier block each other (and their MFMAs) for most of a
-    // group; the third group of the next step stays free of loads to cover their latency.
-    constexpr int E4 = (NL + 1) / 2, E1 = E4 + (NL - E4 + 1) / 2, E2 = NL;
-
-    // One reduction step held in stage s (compile-time).  On entry the fragments of sub-step 0
-    // are in register set 0.  The workgroup barrier sits before the last MFMA group: at that
-    // point this wave has read all its fragments of stage s and has seen its own copies of stage
-    // s^1 land, so after the barrier stage s can be refilled (step j+2) and stage s^1 read.
-    // `head`: the previous step began a refill of stage s^1 that this step has to finish;
-    // `load`: begin the refill of stage s; `next`: read the first fragments of the next step.
-    // Wave priorities fall through the step and are highest right after the barrier: of the two
-    // waves of a SIMD the one that lags is then preferred by the MFMA arbiter, which keeps them
-    // from serialising (measured: without this one wave of each SIMD waits at the barrier for
-    // about 40 % of the step while the other one is starved of MFMA issue slots).
-    // A reduction that ends inside the last two steps: the 16-byte chunks of a KC operand that lie
-    // beyond its end are overwritten with zeros in LDS once the stage has landed, by the lane
-    // that fetched them (round j of thread tid filled slot q = j * 512 + tid of the tile: row
-    // q / 8, LDS chunk q % 8, which holds global chunk (q % 8) ^ swz_kc(row), i.e. reduction
-    // elements 8 * that onwards).  `rem` = reduction elements of the stage that are real.
-    auto zero_tail = [&](auto s_tag, const int rem) __attribute__((always_inline)) {
-        constexpr int s = decltype(s_tag)::value;
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        if (LA == KC) {
-#pragma unroll
-            for (int j = 0; j < C::A_ROUNDS; ++j) {
-                const int q = j * TILE_THREADS + tid, r = q >> 3, cs = q & 7;
-                if (((cs ^ swz_kc(r)) << 3) >= rem) *reinterpret_cast<u32x4*>(smem + s * C::A_BYTES + q * 16) = zero;
-            }
-        }
-        if (LB == KC) {
-#pragma unroll
-            for (int j = 0; j < C::B_ROUNDS; ++j) {
-                const int q = j * TILE_THREADS + tid, r = q >> 3, cs = q & 7;
-                if (((cs ^ swz_kc(r)) << 3) >= rem)
-                    *reinterpret_cast<u32x4*>(smem + 2 * C::A_BYTES + s * C::B_BYTES + q * 16) = zero;
-            }
-        }
-    };
-    // `fix` (first of the two tail steps only): stage s^1 holds the last step, which has just
-    // landed; its chunks beyond the end of the reduction are zeroed before the barrier publishes it.
-    auto step = [&](auto s_tag, const bool head, const bool load, const bool next, const bool fix) __attribute__((always_inline)) {
-        constexpr int s = decltype(s_tag)::value;
-        AXO_SETPRIO(2);
-        if (head) issue_range(IC<E4>{}, IC<E1>{}, s ^ 1);
-        read_a(1, s, 0, 1);
-        mfma_group(0, 0, 0);  // (kq 0, ah 0)
-        Interleave<N_MFMA, 0, RD_A, 0>::run();
-        AXO_SETPRIO(1);
-        if (head) {
-            issue_range(IC<E1>{}, IC<E2>{}, s ^ 1);
-            advance();
-        }
-        read_a(0, s, 1, 0);
-        read_b(1, s, 1);
-        mfma_group(1, 0, 1);  // (kq 0, ah 1)
-        Interleave<N_MFMA, 0, RD_A + RD_B, 0>::run();
-        AXO_SETPRIO(0);
-        read_a(1, s, 1, 1);
-        mfma_group(0, 1, 0);  // (kq 1, ah 0)
-        Interleave<N_MFMA, 0, RD_A, 0>::run();
-        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-        if (fix) zero_tail(IC<s ^ 1>{}, g.R - (KT - 1) * TILE_BK);
-        __syncthreads();
-        AXO_SETPRIO(3);
-        if (load) issue_range(IC<0>{}, IC<E4>{}, s);
-        if (next) {
-            read_a(0, s ^ 1, 0, 0);
-            read_b(0, s ^ 1, 0);
-        }
-        mfma_group(1, 1, 1);  // (kq 1, ah 1)
-        Interleave<N_MFMA, 0, RD_A + RD_B, 0>::run();
-    };
-    using T0 = std::integral_constant<int, 0>;
-    using T1 = std::integral_constant<int, 1>;
-
-    // KT is even and at least 2
-    issue_range(IC<0>{}, IC<NL>{}, 0);
-    advance();
-    issue_range(IC<0>{}, IC<E4>{}, 1);  // step 0 issues the rest of stage 1
-    AXO_WAIT_VMCNT(E4);                 // stage 0 has landed
-    __syncthreads();
-    read_a(0, 0, 0, 0);
-    read_b(0, 0, 0);
-    for (int j = 0; j + 2 < KT; j += 2) {  // steady state, branch free: steps j, j+1; refills j+2, j+3
-        step(T0{}, true, true, true, false);
-        step(T1{}, true, true, true, false);
-    }
-    // The last two steps: nothing left to load.  Step KT-2 sits in stage 0, landed and published
-    // (by the barrier of the step before, or the one above); where the reduction ends inside it
-    // its surplus chunks are zeroed now, behind a barrier of their own, and the fragments that
-    // were read ahead are read again.
-    const bool fix = (LA == KC || LB == KC) && tail;
-    if (fix) {
-        zero_tail(T0{}, g.R - (KT - 2) * TILE_BK);
-        __syncthreads();
-        read_a(0, 0, 0, 0);
-        read_b(0, 0, 0);
-    }
-    step(T0{}, true, false, true, fix);
-    step(T1{}, false, false, false, false);
-    AXO_SETPRIO(0);
-
-    // ---- epilogue: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e]
+// Epilogue of a workgroup tile: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
+template <typename C, int LA, int LB>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
+                                              const int wave, const int wm, const int wn, const int lane, char* smem) {
     __syncthreads();  // all waves are done reading the operand buffers
     char* stage = smem + wave * (C::WTM * C::EPI_STRIDE);
     // The epilogue kind is decided once, outside the element loops: the plain path is then
@@ -604,9 +468,284 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     }
 }
 
+// The epilogue of a tile that reaches over the output's edge, any kind, one compact path: the wave stages its
+// sums in fp32, half its rows at a time, and stores the quads of columns that lie inside.  (wrow0, wcol0): the
+// wave tile's origin.  Same operations per element as the whole-tile epilogue, so an element's bits do not
+// depend on the tile that it falls in.
+template <typename C>
+__device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int wrow0,
+                                                      const int wcol0, const int wave, const int lane, char* smem) {
+    __syncthreads();  // all waves are done reading the operand buffers
+    char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
+    constexpr int F_STRIDE = C::WTN * 4 + 16, RP = C::WTM / 2, QPR = C::WTN / 4;
+    static_assert(RP * F_STRIDE <= C::WTM * C::EPI_STRIDE, "fits the wave's staging region");
+    // a lane keeps its four columns; what its outputs need from memory is requested BATCH rows ahead
+    constexpr int RPI = 64 / QPR, ITERS = RP / RPI, BATCH = ITERS < 4 ? ITERS : 4;
+    const int lc = (lane % QPR) * 4, col = wcol0 + lc, valid = min(4, g.No - col);
+    const bool per_row = g.epilogue >= EPI_MUL_DGELU_TANH;
+    f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+    if (g.epilogue != EPI_NONE && !per_row && g.add_bias && valid > 0) bias = load_bf16x4(g.bias + col, valid);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int a = 0; a < C::TM / 2; ++a)
+#pragma unroll
+            for (int b = 0; b < C::TN; ++b)
+                *reinterpret_cast<f32x4*>(stage + (a * 16 + (lane & 15)) * F_STRIDE + (b * 16 + 4 * (lane >> 4)) * 4) =
+                    acc[h * (C::TM / 2) + a][b];
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the region is private to the wave
+        __builtin_amdgcn_wave_barrier();
+#pragma nounroll
+        for (int i0 = 0; i0 < ITERS; i0 += BATCH) {
+            f32x4 x[BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int row = wrow0 + h * RP + (i0 + i) * RPI + lane / QPR;
+                x[i] = bias;
+                if (per_row && row < g.Mo && valid > 0) x[i] = load_quad_extra(g, row, col, valid);
+            }
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int lr = (i0 + i) * RPI + lane / QPR, row = wrow0 + h * RP + lr;
+                if (row < g.Mo && valid > 0)
+                    store_quad(g, *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), x[i], row, col, valid);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
+    }
+}
+
+// One BM x BN output tile with its top-left corner at (i0, j0), whole reduction.
+template <int BM, int BN, int WGM, int WGN, int LA, int LB>
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
+    using C = TileCfg<BM, BN, WGM, WGN>;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    // The loop is unrolled over the two LDS stages, so it walks the reduction rounded up to the
+    // next multiple of 128; what lies beyond the true length must contribute nothing, whatever
+    // the memory there holds (zeros would do for finite data, but a stray infinity times a zero
+    // of the other operand would put a NaN into a row that has none: BOTH operands are made zero).
+    //  * MC operand (reduction index = row index): rows at or beyond R lie behind the buffer
+    //    descriptor's bound, the byte count from the tile origin to the end of the tile's columns
+    //    in row R - 1, and read as zeros.
+    //  * KC operand (reduction inside the rows): the overrun of a row lands in the next row,
+    //    which no linear bound can mask; the surplus 16-byte chunks of the last two steps are
+    //    overwritten with zeros in LDS instead, and a chunk that is part inside is masked.  The bound
+    //    (end of the tile's last valid row) keeps the last row's overrun from touching memory behind
+    //    the matrix and makes rows beyond the matrix read as zeros.
+    // On this chip the range check covers the sum of the per-lane offset and the scalar offset
+    // that carries the reduction step (measured: lowering the bound by the scalar offset at every
+    // step zeroed the second half of the reduction), so one constant bound serves the whole walk.
+    const int KT = (g.R + 2 * TILE_BK - 1) / (2 * TILE_BK) * 2;
+    const bool tail = (g.R % (2 * TILE_BK)) != 0;
+
+    // global side: descriptor at the tile origin, per-lane offsets, scalar step
+    const bf16_t* Ab = (LA == KC) ? g.A + (int64_t)i0 * g.lda : g.A + i0;
+    const bf16_t* Bb = (LB == KC) ? g.B + (int64_t)j0 * g.ldb : g.B + j0;
+    const uint32_t a_valid = operand_bound<LA>(g.lda, min(BM, g.Mo - i0), g.R);
+    const uint32_t b_valid = operand_bound<LB>(g.ldb, min(BN, g.No - j0), g.R);
+    const u32x4_t a_rsrc = tile_rsrc(Ab, a_valid);
+    const u32x4_t b_rsrc = tile_rsrc(Bb, b_valid);
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
+    const uint32_t a_step = (uint32_t)((LA == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.lda * 2);
+    const uint32_t b_step = (uint32_t)((LB == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.ldb * 2);
+    uint32_t a_off[C::A_ROUNDS], b_off[C::B_ROUNDS];
+    load_offsets<BM, LA, C::A_ROUNDS, C::THREADS>(tid, g.lda, a_off);
+    load_offsets<BN, LB, C::B_ROUNDS, C::THREADS>(tid, g.ldb, b_off);
+
+    // LDS side: [A stage 0][A stage 1][B stage 0][B stage 1]; fragment addresses of stage 0
+    FragAddr<BM, LA, C::TM> fra;
+    FragAddr<BN, LB, C::TN> frb;
+    fra.init(wm * C::WTM, lane, 0);
+    frb.init(wn * C::WTN, lane, 2 * C::A_BYTES);
+
+    f32x4 acc[C::TM][C::TN];
+#pragma unroll
+    for (int a = 0; a < C::TM; ++a)
+#pragma unroll
+        for (int b = 0; b < C::TN; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
+
+    // A reduction step of 64 is four MFMA groups: (sub-step kq, row half ah) for kq, ah in {0, 1};
+    // a group multiplies AH A fragments with all TN B fragments of its sub-step.  A fragments are
+    // double buffered per group, B fragments per sub-step.
+    bf16x8 fa[2][C::AH], fb[2][C::TN];
+    auto read_a = [&](int set, int s, int kq, int ah) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < C::AH; ++a) fa[set][a] = fra.read(smem, s, ah * C::AH + a, kq);
+    };
+    auto read_b = [&](int set, int s, int kq) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < C::TN; ++b) fb[set][b] = frb.read(smem, s, b, kq);
+    };
+    auto mfma_group = [&](int aset, int bset, int ah) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < C::AH; ++a)
+#pragma unroll
+            for (int b = 0; b < C::TN; ++b)
+                acc[ah * C::AH + a][b] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[bset][b], fa[aset][a], acc[ah * C::AH + a][b], 0, 0, 0);
+    };
+    constexpr int N_MFMA = C::AH * C::TN;
+    constexpr int RD_A = (LA == KC ? 1 : 2) * C::AH, RD_B = (LB == KC ? 1 : 2) * C::TN;
+    uint32_t a_soff = 0, b_soff = 0;  // scalar byte offsets of the reduction step being loaded
+    constexpr int NL = C::LOADS_PER_STAGE;
+    // One direct-to-LDS load: 16 bytes per lane from descriptor base + off + soff to LDS address
+    // M0 + 16 * lane.  Issued through inline assembly on purpose: for a load the compiler knows
+    // to write LDS it puts a full vmcnt(0) wait in front of every later transposing LDS read,
+    // which stalls the wave for a whole memory latency in every step.  The kernel keeps the
+    // ordering itself: the vmcnt(0) wait and the barrier before the last MFMA group of each step.
+    // M0 (the LDS destination of the load) is an input operand bound to the physical register, so
+    // the compiler writes it itself and knows what the statement reads.
+    auto load_lds = [](uint32_t lds_dst, uint32_t off, u32x4_t rsrc, uint32_t soff) __attribute__((always_inline)) {
+        asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :
+                     : "v"(off), "s"(rsrc), "s"(soff), "{m0}"(lds_dst)
+                     : "memory");
+    };
+    // Loads LO..HI-1 of the NL loads that fill stage s with the step at (a_soff, b_soff): the A
+    // rounds first, then the B rounds; round j of wave w lands at tile + (j * 512 + w * 64 + lane) * 16.
+    auto issue_range = [&](auto lo_tag, auto hi_tag, int s) __attribute__((always_inline)) {
+        constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
+#pragma unroll
+        for (int j = LO; j < HI; ++j) {
+            if (j < C::A_ROUNDS) {
+                load_lds(smem_base + s * C::A_BYTES + (j * C::THREADS + wave * 64) * 16, a_off[j], a_rsrc, a_soff);
+            } else {
+                const int jb = j - C::A_ROUNDS;
+                load_lds(smem_base + 2 * C::A_BYTES + s * C::B_BYTES + (jb * C::THREADS + wave * 64) * 16,
+                         b_off[jb], b_rsrc, b_soff);
+            }
+        }
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+        a_soff += a_step;
+        b_soff += b_step;
+    };
+    // A stage's loads are dealt out over three MFMA groups instead of one burst: half right after
+    // the barrier that frees the stage, a quarter in each of the first two groups of the next
+    // step.  The texture addresser takes one 1 KB wave-load per ~20 cycles, so eight waves that
+    // all issue their loads after the barrier block each other (and their MFMAs) for most of a
+    // group; the third group of the next step stays free of loads to cover their latency.
+    constexpr int E4 = (NL + 1) / 2, E1 = E4 + (NL - E4 + 1) / 2, E2 = NL;
+
+    // One reduction step held in stage s (compile-time).  On entry the fragments of sub-step 0
+    // are in register set 0.  The workgroup barrier sits before the last MFMA group: at that
+    // point this wave has read all its fragments of stage s and has seen its own copies of stage
+    // s^1 land, so after the barrier stage s can be refilled (step j+2) and stage s^1 read.
+    // `head`: the previous step began a refill of stage s^1 that this step has to finish;
+    // `load`: begin the refill of stage s; `next`: read the first fragments of the next step.
+    // Wave priorities fall through the step and are highest right after the barrier: of the two
+    // waves of a SIMD the one that lags is then preferred by the MFMA arbiter, which keeps them
+    // from serialising (measured: without this one wave of each SIMD waits at the barrier for
+    // about 40 % of the step while the other one is starved of MFMA issue slots).
+    // A reduction that ends inside the last two steps: what a KC operand's 16-byte chunks hold beyond
+    // its end is overwritten with zeros in LDS once the stage has landed, by the lane
+    // that fetched them (round j of thread tid filled slot q = j * THREADS + tid of the tile: row
+    // q / 8, LDS chunk q % 8, which holds global chunk (q % 8) ^ swz_kc(row), i.e. reduction
+    // elements 8 * that onwards).  `rem` = reduction elements of the stage that are real.
+    auto zero_tail = [&](auto s_tag, const int rem) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_tag)::value;
+        auto clear = [&](char* base, const int rounds) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < rounds; ++j) {
+                const int q = j * C::THREADS + tid, r = q >> 3, cs = q & 7;
+                const int left = rem - ((cs ^ swz_kc(r)) << 3);
+                u32x4* const p = reinterpret_cast<u32x4*>(base + q * 16);
+                if (left < 8) *p = first_elements(left > 0 ? *p : u32x4{0u, 0u, 0u, 0u}, left);
+            }
+        };
+        if (LA == KC) clear(smem + s * C::A_BYTES, C::A_ROUNDS);
+        if (LB == KC) clear(smem + 2 * C::A_BYTES + s * C::B_BYTES, C::B_ROUNDS);
+    };
+    // `fix` (first of the two tail steps only): stage s^1 holds the last step, which has just
+    // landed; its chunks beyond the end of the reduction are zeroed before the barrier publishes it.
+    auto step = [&](auto s_tag, const bool head, const bool load, const bool next, const bool fix) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_tag)::value;
+        AXO_SETPRIO(2);
+        if (head) issue_range(IC<E4>{}, IC<E1>{}, s ^ 1);
+        read_a(1, s, 0, 1);
+        mfma_group(0, 0, 0);  // (kq 0, ah 0)
+        Interleave<N_MFMA, 0, RD_A, 0>::run();
+        AXO_SETPRIO(1);
+        if (head) {
+            issue_range(IC<E1>{}, IC<E2>{}, s ^ 1);
+            advance();
+        }
+        read_a(0, s, 1, 0);
+        read_b(1, s, 1);
+        mfma_group(1, 0, 1);  // (kq 0, ah 1)
+        Interleave<N_MFMA, 0, RD_A + RD_B, 0>::run();
+        AXO_SETPRIO(0);
+        read_a(1, s, 1, 1);
+        mfma_group(0, 1, 0);  // (kq 1, ah 0)
+        Interleave<N_MFMA, 0, RD_A, 0>::run();
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+        if (fix) zero_tail(IC<s ^ 1>{}, g.R - (KT - 1) * TILE_BK);
+        __syncthreads();
+        AXO_SETPRIO(3);
+        if (load) issue_range(IC<0>{}, IC<E4>{}, s);
+        if (next) {
+            read_a(0, s ^ 1, 0, 0);
+            read_b(0, s ^ 1, 0);
+        }
+        mfma_group(1, 1, 1);  // (kq 1, ah 1)
+        Interleave<N_MFMA, 0, RD_A + RD_B, 0>::run();
+    };
+    using T0 = std::integral_constant<int, 0>;
+    using T1 = std::integral_constant<int, 1>;
+
+    // KT is even and at least 2
+    issue_range(IC<0>{}, IC<NL>{}, 0);
+    advance();
+    issue_range(IC<0>{}, IC<E4>{}, 1);  // step 0 issues the rest of stage 1
+    AXO_WAIT_VMCNT(E4);                 // stage 0 has landed
+    __syncthreads();
+    read_a(0, 0, 0, 0);
+    read_b(0, 0, 0);
+    for (int j = 0; j + 2 < KT; j += 2) {  // steady state, branch free: steps j, j+1; refills j+2, j+3
+        step(T0{}, true, true, true, false);
+        step(T1{}, true, true, true, false);
+    }
+    // The last two steps: nothing left to load.  Step KT-2 sits in stage 0, landed and published
+    // (by the barrier of the step before, or the one above); where the reduction ends inside it
+    // its surplus chunks are zeroed now, behind a barrier of their own, and the fragments that
+    // were read ahead are read again.
+    const bool fix = (LA == KC || LB == KC) && tail;
+    if (fix) {
+        zero_tail(T0{}, g.R - (KT - 2) * TILE_BK);
+        __syncthreads();
+        read_a(0, 0, 0, 0);
+        read_b(0, 0, 0);
+    }
+    step(T0{}, true, false, true, fix);
+    step(T1{}, false, false, false, false);
+    AXO_SETPRIO(0);
+
+    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+}
+
 using MixBigCfg = TileCfg<256, 256, 2, 4>;
 using MixSmallCfg = TileCfg<256, 128, 4, 2>;
 constexpr int MIX_LDS_BYTES = MixBigCfg::LDS_BYTES > MixSmallCfg::LDS_BYTES ? MixBigCfg::LDS_BYTES : MixSmallCfg::LDS_BYTES;
+
+// Origin of a tile that would reach over the output's edge, moved back inside where that is possible, so that it
+// is a whole tile: the elements it then shares with its neighbour are computed twice, by the same instructions
+// in the same order, and stored twice with the same bits.  Not for sums that are added to memory, and not where
+// the moved origin would break the 16-byte alignment of loads and stores.
+template <int BM, int LAYOUT>
+__device__ __forceinline__ int inside_row(const GemmArgs& g, const int i0) {
+    const bool ok = g.Mo >= BM && g.epilogue != EPI_ACC_F32 && (LAYOUT == KC || g.Mo % 8 == 0);
+    return ok ? min(i0, g.Mo - BM) : i0;
+}
+template <int BN>
+__device__ __forceinline__ int inside_col(const GemmArgs& g, const int j0) {
+    return g.No >= BN && g.epilogue != EPI_ACC_F32 && g.No % 8 == 0 ? min(j0, g.No - BN) : j0;
+}
 
 // One launch over both regions of a TileSched.
 template <int LA, int LB>
@@ -616,12 +755,12 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     start_stagger(bid, sc.stagger);
     int tm, tn;
     if (bid < sc.n_big) {
-        tile_of_index(xcd_contiguous(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
-        gemm_tile_body<256, 256, 2, 4, LA, LB>(g, tm * 256, tn * 256, smem);
+        tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
+        gemm_tile_body<256, 256, 2, 4, LA, LB>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
-        tile_of_index(xcd_contiguous(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_tile_body<256, 128, 4, 2, LA, LB>(g, tm * 256, sc.big_cols * 256 + tn * 128, smem);
+        tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
+        gemm_tile_body<256, 128, 4, 2, LA, LB>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
     }
 }
 
@@ -681,14 +820,14 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
     }
     int tm, tn;
     // workgroup ids with equal id % 8 share an XCD whatever the segment's first id is
-    tile_of_index(xcd_contiguous(bid - sg.first_block, sg.n_blocks), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
+    tile_of_index(xcd_run(bid - sg.first_block, sg.n_blocks), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
     switch (sg.kind) {
-        case 0: gemm_tile_body<256, 256, 2, 4, KC, MC>(g, tm * 256, sg.col0 + tn * 256, smem); break;
-        case 1: gemm_tile_body<256, 128, 4, 2, KC, MC>(g, tm * 256, sg.col0 + tn * 128, smem); break;
-        case 2: gemm_tile_body<256, 256, 2, 4, KC, KC>(g, tm * 256, sg.col0 + tn * 256, smem); break;
-        case 3: gemm_tile_body<256, 128, 4, 2, KC, KC>(g, tm * 256, sg.col0 + tn * 128, smem); break;
-        case 4: gemm_tile_body<256, 256, 2, 4, MC, MC>(g, tm * 256, sg.col0 + tn * 256, smem); break;
-        default: gemm_tile_body<256, 128, 4, 2, MC, MC>(g, tm * 256, sg.col0 + tn * 128, smem); break;
+        case 0: gemm_tile_body<256, 256, 2, 4, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
+        case 1: gemm_tile_body<256, 128, 4, 2, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
+        case 2: gemm_tile_body<256, 256, 2, 4, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
+        case 3: gemm_tile_body<256, 128, 4, 2, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
+        case 4: gemm_tile_body<256, 256, 2, 4, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
+        default: gemm_tile_body<256, 128, 4, 2, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
     }
 }
 

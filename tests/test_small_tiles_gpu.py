@@ -93,3 +93,28 @@ def test_special_values_at_the_end_of_the_reduction():
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     plain = [r for r in range(M) if r not in (7, 44)]
     gu.assert_close(oracle, gu.to_host(Y)[plain, :Nl], ref[plain], "rows without special values")
+
+
+@pytest.mark.parametrize("M,Kl,Nl", [(2304, 2051, 2049), (2305, 2048, 2304), (2500, 2309, 2100)])
+def test_large_tiles_at_odd_edges(M, Kl, Nl):
+    """The 256-row tiles on outputs and reductions that are no multiple of 8: clipped tiles, part-chunk reduction
+    ends, and an fp32-accumulating weight gradient (whose tiles must not overlap) at a ragged size."""
+    Xb, Wb, dYb = (syn.normal_bf16(80 + M, s, sh, 1.0) for s, sh in ((0, (M, Kl)), (1, (Kl, Nl)), (2, (M, Nl))))
+    X, W, dY, p = padded(Xb), padded(Wb), padded(dYb), P(M, Kl, Nl)
+    Y, dX, dW = out(M, Nl), out(M, Kl), out(Kl, Nl)
+    lead = (Nl + 3) // 4 * 4 + 4
+    dW32 = torch.full((Kl, lead), -7.0, device="cuda:0")
+    dW32[:, :Nl] = 0.0
+    gu.run_fwd(p, X, W, Y)
+    gu.run_dgrad(p, dY, W, dX)
+    gu.run_wgrad(p, X, dY, dW)
+    axo.axo_fc_wgrad_acc(p, X.data_ptr(), gu.ld(X), dY.data_ptr(), gu.ld(dY), dW32.data_ptr(), lead, None, 0, gu.stream())
+    torch.cuda.synchronize()
+    wg = oracle.fc_wgrad(Xb, dYb)
+    for got, ref, what in ((Y, oracle.fc_fwd(Xb, Wb), "fwd"), (dX, oracle.fc_dgrad(dYb, Wb), "dgrad"), (dW, wg, "wgrad")):
+        h = gu.to_host(got)
+        gu.assert_close(oracle, h[:, :ref.shape[1]], ref, f"{what} {M}x{Kl}x{Nl}")
+        assert (h[:, ref.shape[1]:] == NAN).all(), f"{what}: wrote beyond the row"
+    got = dW32.cpu().numpy()
+    # fp32 sums of M products of unit Gaussians: the same sums that the bf16 output rounds
+    assert np.abs(got[:, :Nl] - wg).max() <= 1e-4 * np.abs(wg).max() and (got[:, Nl:] == -7.0).all()
