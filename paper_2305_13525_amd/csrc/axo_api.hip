@@ -130,10 +130,6 @@ double makespan(int n_big, int n_small) {
     return end;
 }
 
-// Start-up phase shift of a single-product launch (see start_stagger): 8 phases 1920 cycles
-// apart, once the launch has a workgroup for every CU (a smaller one has no chip-wide burst).
-int stagger_units(int blocks) { return blocks >= NUM_CU ? 3 : 0; }
-
 // 128-wide tile columns that cover what `big_cols` 256-wide ones leave of No.
 int half_cols(int No, int big_cols) { return No > big_cols * 256 ? (No - big_cols * 256 + 127) / 128 : 0; }
 
@@ -162,7 +158,6 @@ axo::TileSched plan_tiles(int Mo, int No) {
     sc.small_cols = half_cols(No, best_cols);
     sc.n_big = sc.tiles_m * sc.big_cols;
     sc.group_m = sc.tiles_m < 4 ? sc.tiles_m : 4;
-    sc.stagger = stagger_units(sc.n_big + sc.tiles_m * sc.small_cols);
     if (cache.size() < 4096) cache[{Mo, No}] = sc;
     return sc;
 }

@@ -83,25 +83,7 @@ struct TileSched {
     int small_cols;  // tile columns of the 128-wide region
     int n_big;       // = tiles_m * big_cols
     int group_m;     // band height of the tile order
-    int stagger;     // start_stagger() units, 0 = none
 };
-
-// Start-up phase shift.  Tiles of equal length that start together end together, and then all
-// 256 CUs write their outputs in one burst (33 MB for 256x256 tiles), which the memory side takes
-// 5-6 us to absorb while nothing computes; spread out, a CU's epilogue takes half as long.  The
-// first workgroup on every CU (ids below 256) therefore sleeps phase * units * 640 cycles before
-// it starts, phase = 0..7 dealt round-robin over the CUs of each XCD; later workgroups start
-// whenever their CU falls free, so the shift persists through the launch.  Measured on launches
-// of one product: +2 to +5 % (dgrad 4096x2048x16384 1296 -> 1344 TFLOP/s, a one-round launch of
-// 256 half-width tiles 1243 -> 1301).  The grouped launch does without: its tiles differ in
-// length, which spreads the bursts already, and the idle start then only costs (-1 %).
-constexpr int STAGGER_PHASES = 8;
-__device__ __forceinline__ void start_stagger(int bid, int units) {
-    if (units > 0 && bid < 256) {
-        const int n = ((bid >> 3) % STAGGER_PHASES) * units;
-        for (int i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(10);
-    }
-}
 
 // Workgroup -> output tile.  Consecutive workgroup ids go round-robin to the 8 XCDs, each with
 // its own L2, so the ids that land on one XCD are given one contiguous run of tiles, and tiles
@@ -891,7 +873,6 @@ template <int LA, int LB>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g, TileSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
-    start_stagger(bid, sc.stagger);
     int tm, tn;
     if (bid < sc.n_big) {
         tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
