@@ -176,9 +176,31 @@ bool raise_lds_limit(const void* kernel, int bytes, std::atomic<uint64_t>* raise
     return true;
 }
 
-// Launch of one tuned-kernel instantiation.
+// Estimated kernel time in microseconds of a product on its own, from its sizes alone.  256-row tiles: rounds of
+// 256 x 256 tiles or of half-width ones, 1.33 us per reduction step.  128 x 128 tiles: 0.42 us per step.
+double tile_time(int Mo, int No, int R) {
+    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
+    const double big = std::ceil(tm * ((No + 255) / 256) / NUM_CU), half = std::ceil(tm * ((No + 127) / 128) / NUM_CU) * SMALL_TILE_COST;
+    return 2.0 + std::min(big, half) * steps * 1.33;
+}
+double mid_time(int Mo, int No, int R) {
+    if ((double)((Mo + 127) / 128) * ((No + 127) / 128) > NUM_CU) return 1e30;  // more than one tile per CU: see below
+    return 4.5 + (R + axo::TILE_BK - 1) / axo::TILE_BK * 0.42;
+}
+
+// Launch of one product on 128 x 128 tiles or on the 256-row ones, whichever is estimated quicker (both give
+// the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by LDS
+// traffic (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
+    if (mid_time(g.Mo, g.No, g.R) < tile_time(g.Mo, g.No, g.R)) {
+        auto mid = axo::gemm_mid_kernel<LA, LB>;
+        static std::atomic<uint64_t> mid_raised{0};
+        if (!raise_lds_limit(reinterpret_cast<const void*>(mid), axo::MidCfg::LDS_BYTES, &mid_raised)) return AXO_ERR_HIP;
+        const int tm = (g.Mo + 127) / 128, tn = (g.No + 127) / 128;
+        hipLaunchKernelGGL(mid, dim3(tm * tn), dim3(axo::TILE_THREADS), axo::MidCfg::LDS_BYTES, st, g, tm, tn, std::min(tm, 8));
+        return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+    }
     auto kern = axo::gemm_mixed_kernel<LA, LB>;
     static std::atomic<uint64_t> raised{0};
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
@@ -195,8 +217,7 @@ int launch_tile_layout(const GemmArgs& g, int la, int lb, hipStream_t st) {
 }
 
 // ---- small-tile launch (gemm_slim.hpp) ---------------------------------------------------------
-// Estimated kernel time in microseconds of a product on small tiles and on the 256-row tiles, from
-// its sizes alone.  Fitted to 177 measured products (M 1..8000, K and N 94..13312, all three layout
+// Estimated kernel time in microseconds of a product on small tiles, from its sizes alone.  Fitted to 177 measured products (M 1..8000, K and N 94..13312, all three layout
 // pairs; 85-89 % of the small-tile estimates are within 20 %, and what the choice below picks took 2 % longer than
 // the best kernel on average).  A small tile costs a fixed part (start, first load,
 // addition of the partial tiles, store) plus its operand bytes at the rate a CU pulls them in; a
@@ -216,26 +237,21 @@ double slim_time(const SlimModel& m, int Mo, int No, int R, int pair) {
     const double chain = std::ceil(tiles / (NUM_CU * m.slots)) * (0.7 + std::ceil(chunks / axo::SLIM_WAVES) * m.chunk_us);
     return 2.5 + std::max(busy, chain);
 }
-// The 256-row tiles: rounds of 256 x 256 tiles or of half-width ones, 1.33 us per reduction step.
-double tile_time(int Mo, int No, int R) {
-    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
-    const double big = std::ceil(tm * ((No + 255) / 256) / NUM_CU), half = std::ceil(tm * ((No + 127) / 128) / NUM_CU) * SMALL_TILE_COST;
-    return 2.0 + std::min(big, half) * steps * 1.33;
-}
-
 int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
 
 // Rows of the small tile (32 or 64) that is quicker for this product.
 int slim_rows(const GemmArgs& g, int pair) {
     return slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair) <= slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair) ? 32 : 64;
 }
-// Whether a product that the 256-row tiles could take runs on small tiles instead: where those are
-// estimated at least 35 % quicker (in a chain the larger tiles share a launch with other products' tiles).  A function of sizes and layouts only, because the waves of a small tile
-// split the reduction and so sum in another order: a product has the same bits on its own and in a chain.
+// Whether a product runs on small tiles: where those are estimated at least 10 % quicker than the larger ones.
+// A function of sizes and layouts only, because the waves of a small tile split the reduction and so sum in
+// another order: a product has the same bits on its own and in a chain.  (The margin also keeps products out of it
+// that a chain's grouped launch takes along: a 1536 x 1536 weight gradient of 4096 tokens on small tiles cost a
+// block of four layers 3.5 %.)
 bool prefers_slim(const GemmArgs& g, int la, int lb) {
     const int pair = layout_pair(la, lb);
     const double slim = std::min(slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair), slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair));
-    return slim < 0.65 * tile_time(g.Mo, g.No, g.R);
+    return slim < 0.9 * std::min(tile_time(g.Mo, g.No, g.R), mid_time(g.Mo, g.No, g.R));
 }
 
 template <int ROWS, int LA, int LB>

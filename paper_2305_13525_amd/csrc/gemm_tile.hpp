@@ -884,6 +884,22 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     }
 }
 
+// One product on 128 x 128 tiles, eight waves of 32 x 64 each on a four-stage ring, for outputs of at most one
+// such tile per CU (4096 x 1024, 2048 x 2048): 256-row tiles leave most CUs without work there.  A step is bound by
+// LDS traffic (128 KB per 515 cycles of MFMA), so this is no tile for larger outputs.  Eight waves rather than
+// four of 64 x 64 (a quarter less LDS traffic, but one wave per SIMD: 2048^3 21 us), four stages rather than two
+// and two workgroups per CU (24 us).  Measured against the 256-row tiles, forward / dgrad / wgrad: 2048^3
+// 25.6 / 24.9 / 24.2 -> 19.5 / 19.0 / 18.4 us, 1536^3 19.6 / 19.0 / 18.4 -> 14.4 / 13.8 / 13.2, wgrad 1536 x 1536 of 4096
+// tokens 44 -> 30.  Sums run in the same order as on the other tiles: same bits.
+using MidCfg = RingCfg<128, 128, 4, 2, 4>;
+template <int LA, int LB>
+__global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int tm, tn;
+    tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
+    gemm_ring_body<128, 128, 4, 2, 4, LA, LB>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
+}
+
 // ---- grouped launch: the tiles of several independent products in one grid ----------------
 // A product on its own often cannot fill the 256 CUs (a 1536x1536 output is 36 big tiles), and a
 // chain of such launches pays a ramp-up and a tail each.  A group launch strings the tile lists of

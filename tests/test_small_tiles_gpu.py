@@ -1,4 +1,4 @@
-"""The small-tile kernel (32 x 32 and 64 x 64 tiles whose four waves split the reduction in 64-wide chunks) at the
+"""The tile kernels at odd sizes.  Above all the small-tile kernel (32 x 32 and 64 x 64 tiles whose four waves split the reduction in 64-wide chunks) at the
 sizes where it can go wrong: output edges one short of, at and one past a tile; reductions that end in any
 position of a chunk, give some of the four waves nothing, or wrap around them; every epilogue.  Against the
 fp64 oracle under the usual gates (tests/gpu_util.py)."""
@@ -95,9 +95,10 @@ def test_special_values_at_the_end_of_the_reduction():
     gu.assert_close(oracle, gu.to_host(Y)[plain, :Nl], ref[plain], "rows without special values")
 
 
-@pytest.mark.parametrize("M,Kl,Nl", [(2304, 2051, 2049), (2305, 2048, 2304), (2500, 2309, 2100)])
+@pytest.mark.parametrize("M,Kl,Nl", [(2304, 2051, 2049), (2305, 2048, 2304), (2500, 2309, 2100),
+                                     (1540, 1500, 1411), (1535, 1544, 1537), (1502, 901, 702)])  # these: 128 x 128 tiles
 def test_large_tiles_at_odd_edges(M, Kl, Nl):
-    """The 256-row tiles on outputs and reductions that are no multiple of 8: clipped tiles, part-chunk reduction
+    """The 256-row and 128 x 128 tiles on outputs and reductions that are no multiple of 8: clipped tiles, part-chunk reduction
     ends, and an fp32-accumulating weight gradient (whose tiles must not overlap) at a ragged size."""
     Xb, Wb, dYb = (syn.normal_bf16(80 + M, s, sh, 1.0) for s, sh in ((0, (M, Kl)), (1, (Kl, Nl)), (2, (M, Nl))))
     X, W, dY, p = padded(Xb), padded(Wb), padded(dYb), P(M, Kl, Nl)
