@@ -254,10 +254,10 @@ bool prefers_slim(const GemmArgs& g, int la, int lb) {
     return slim < 0.9 * std::min(tile_time(g.Mo, g.No, g.R), mid_time(g.Mo, g.No, g.R));
 }
 
-template <int ROWS, int LA, int LB>
+template <int ROWS, int ST, int LA, int LB>
 int launch_slim_rows(const GemmArgs& g, hipStream_t st) {
-    using C = axo::SlimCfg<ROWS, ROWS, axo::SLIM_WAVES>;
-    auto kern = axo::gemm_slim_kernel<ROWS, ROWS, axo::SLIM_WAVES, LA, LB>;
+    using C = axo::SlimCfg<ROWS, ROWS, axo::SLIM_WAVES, ST>;
+    auto kern = axo::gemm_slim_kernel<ROWS, ROWS, axo::SLIM_WAVES, ST, LA, LB>;
     static std::atomic<uint64_t> raised{0};
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, &raised)) return AXO_ERR_HIP;
     axo::SlimSched sc{(g.Mo + ROWS - 1) / ROWS, (g.No + ROWS - 1) / ROWS, 0};
@@ -269,7 +269,11 @@ int launch_slim_rows(const GemmArgs& g, hipStream_t st) {
 }
 template <int LA, int LB>
 int launch_slim_layout(const GemmArgs& g, int rows, hipStream_t st) {
-    return rows == 32 ? launch_slim_rows<32, LA, LB>(g, st) : launch_slim_rows<64, LA, LB>(g, st);
+    if (rows == 64) return launch_slim_rows<64, 1, LA, LB>(g, st);
+    // two stages leave room for two workgroups on a CU, one stage for five; below 16 chunks per wave the second
+    // stage's longer start costs what it gains (200 x 2000 x 512 forward 5.5 us with one, 5.8 with two)
+    const int64_t tiles = ((int64_t)g.Mo + 31) / 32 * (((int64_t)g.No + 31) / 32);
+    return tiles <= 2 * NUM_CU && g.R >= 16 * axo::SLIM_WAVES * axo::TILE_BK ? launch_slim_rows<32, 2, LA, LB>(g, st) : launch_slim_rows<32, 1, LA, LB>(g, st);
 }
 int launch_slim(const GemmArgs& g, int la, int lb, hipStream_t st) {
     const int rows = slim_rows(g, layout_pair(la, lb));

@@ -11,11 +11,12 @@
 // operand twice).  The partial tiles are added through LDS in ascending wave order: no atomics, the
 // result is a fixed function of the input.
 //
-// One LDS stage per wave: its fragments go to registers before the next chunk is requested into the
-// same bytes, and what hides the latency is the other waves.  A second stage per wave was measured
-// slower almost everywhere (64 x 64 tiles, 2048^3: 38 us with two stages and one workgroup per CU, 28 us
-// with one stage and two; 4096 x 1536 x 1536: 48 and 32), as it halves the workgroups that fit beside
-// each other and with them what overlaps a workgroup's start and end.
+// A chunk's fragments go to registers before the next one is requested into the same bytes.  On a busy CU one
+// LDS stage per wave is best: what hides the latency is the other waves, and a second stage halves the
+// workgroups that fit beside each other and with them what overlaps a workgroup's start and end (64 x 64 tiles,
+// 2048^3: 38 us with two stages and one workgroup per CU, 28 with one stage and two; 4096 x 1536 x 1536: 48 and
+// 32).  A long reduction on at most two 32 x 32 tiles per CU has nothing beside it and takes two stages (dgrad of
+// 16 x 2048 x 6144: 13.3 us with one, 9.8 with two; forward of 128 x 9088 x 640: 22.7 and 19.7).
 //
 // Edges cost nothing in the loop.  Loads go through a buffer descriptor whose bound is the last
 // valid element of the operand's tile (rounded up to the dword the range check works in), so rows beyond
@@ -101,20 +102,20 @@ struct SlimOperand {
 
 constexpr int SLIM_WAVES = 4;
 
-template <int BM, int BN, int NW>
+template <int BM, int BN, int NW, int ST>
 struct SlimCfg {
     static constexpr int THREADS = NW * 64;
     static constexpr int STAGE_BYTES = (BM + BN) * TILE_BK * 2;
     static constexpr int PART_STRIDE = BN + 4;  // floats per row of a partial tile (padded)
     static constexpr int PART_BYTES = BM * PART_STRIDE * 4;
-    static constexpr int WAVE_BYTES = STAGE_BYTES > PART_BYTES ? STAGE_BYTES : PART_BYTES;
+    static constexpr int WAVE_BYTES = ST * STAGE_BYTES > PART_BYTES ? ST * STAGE_BYTES : PART_BYTES;
     static constexpr int LDS_BYTES = NW * WAVE_BYTES;
     static_assert(BM % 32 == 0 && BN % 32 == 0 && LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
-template <int BM, int BN, int NW, int LA, int LB>
+template <int BM, int BN, int NW, int ST, int LA, int LB>
 __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
-    using C = SlimCfg<BM, BN, NW>;
+    using C = SlimCfg<BM, BN, NW, ST>;
     using OA = SlimOperand<BM, LA>;
     using OB = SlimOperand<BN, LB>;
     constexpr int TM = BM / 16, TN = BN / 16;
@@ -139,12 +140,13 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
                      : "v"(off), "s"(rsrc), "s"(soff), "{m0}"(lds_dst)
                      : "memory");
     };
-    auto issue = [&](const int chunk) __attribute__((always_inline)) {
+    auto issue = [&](const int s, const int chunk) __attribute__((always_inline)) {
         const uint32_t a_soff = (uint32_t)chunk * a_step, b_soff = (uint32_t)chunk * b_step;
+        const uint32_t dst = mine_lds + s * C::STAGE_BYTES;
 #pragma unroll
-        for (int j = 0; j < OA::LOADS; ++j) load_lds(mine_lds + j * 1024, oa.off[j], a_rsrc, a_soff);
+        for (int j = 0; j < OA::LOADS; ++j) load_lds(dst + j * 1024, oa.off[j], a_rsrc, a_soff);
 #pragma unroll
-        for (int j = 0; j < OB::LOADS; ++j) load_lds(mine_lds + OA::BYTES + j * 1024, ob.off[j], b_rsrc, b_soff);
+        for (int j = 0; j < OB::LOADS; ++j) load_lds(dst + OA::BYTES + j * 1024, ob.off[j], b_rsrc, b_soff);
     };
 
     f32x4 acc[TM][TN];
@@ -155,19 +157,22 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
 
-    if (wave < KT) issue(wave);
-    for (int chunk = wave; chunk < KT; chunk += NW) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // One chunk, held in stage s (compile-time); the stages of a wave are filled in turn.
+    auto chunk_step = [&](auto s_tag, const int chunk) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_tag)::value;
+        if (ST == 2 && chunk + NW < KT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OA::LOADS + OB::LOADS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const char* const stage = mine + s * C::STAGE_BYTES;
         bf16x8 fa[2][TM], fb[2][TN];
 #pragma unroll
         for (int kq = 0; kq < 2; ++kq) {
 #pragma unroll
-            for (int a = 0; a < TM; ++a) fa[kq][a] = oa.read(mine, a, kq);
+            for (int a = 0; a < TM; ++a) fa[kq][a] = oa.read(stage, a, kq);
 #pragma unroll
-            for (int b = 0; b < TN; ++b) fb[kq][b] = ob.read(mine + OA::BYTES, b, kq);
+            for (int b = 0; b < TN; ++b) fb[kq][b] = ob.read(stage + OA::BYTES, b, kq);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage is in registers: refill it
-        if (chunk + NW < KT) issue(chunk + NW);
+        if (chunk + ST * NW < KT) issue(s, chunk + ST * NW);
         if ((LA == KC || LB == KC) && (g.R % TILE_BK) != 0 && chunk == KT - 1) {
             const int left = g.R - chunk * TILE_BK - 8 * (lane >> 4);  // from this lane's 8 elements of sub-step 0
 #pragma unroll
@@ -189,6 +194,12 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kq][b], fa[kq][a], acc[a][b], 0, 0, 0);
+    };
+    if (wave < KT) issue(0, wave);
+    if (ST == 2 && wave + NW < KT) issue(1, wave + NW);
+    for (int chunk = wave; chunk < KT; chunk += ST * NW) {
+        chunk_step(IC<0>{}, chunk);
+        if (ST == 2 && chunk + NW < KT) chunk_step(IC<ST - 1>{}, chunk + NW);
     }
 
     // Partial tiles to LDS (each wave inside its own region, whose loads have all landed and been read),
@@ -227,12 +238,12 @@ struct SlimSched {
     int tiles_m, tiles_n, group_m;
 };
 
-template <int BM, int BN, int NW, int LA, int LB>
+template <int BM, int BN, int NW, int ST, int LA, int LB>
 __global__ void __launch_bounds__(NW * 64) gemm_slim_kernel(GemmArgs g, SlimSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), sc.tiles_m, sc.tiles_n, sc.group_m, tm, tn);
-    slim_tile_body<BM, BN, NW, LA, LB>(g, tm * BM, tn * BN, smem);
+    slim_tile_body<BM, BN, NW, ST, LA, LB>(g, tm * BM, tn * BN, smem);
 }
 
 }  // namespace axo
