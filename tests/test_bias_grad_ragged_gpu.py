@@ -1,0 +1,43 @@
+"""The bias gradient at column counts that end inside a 16-byte chunk, and at the row counts where the number of row
+slices changes.  Rows are padded with NaNs: the kernels read into the row pitch and must not count it."""
+import numpy as np
+import pytest
+import torch
+
+import axo_synth as syn
+import oracle
+import paper_2305_13525_amd as axo
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [1, 64, 65, 1535, 1537, 2049, 5000])
+@pytest.mark.parametrize("N", [1, 7, 63, 515, 4100])
+def test_ragged_columns(M, N):
+    bits = syn.normal_bf16(90 + N, 2, (M, N), 1.0)
+    full = np.full((M, (N + 7) // 8 * 8), 0x7FC0, dtype=np.uint16)
+    full[:, :N] = bits
+    dY, p = gu.to_dev(full), axo.Problem.make((1, 1, 1), (0, 0, 0), M, 8, N)
+    nws = axo.axo_bias_grad_workspace_bytes(p)
+    ws = torch.zeros(max(16, nws), dtype=torch.uint8, device="cuda:0")
+    old = np.random.default_rng(M).standard_normal(N).astype(np.float32)
+    ref = oracle.bias_grad(bits)
+    # fp32: at most M + 1 additions of magnitudes that add up to the sum of absolute values
+    bound = (M + 1) * 2.0 ** -24 * (np.abs(syn.bf16_bits_to_f64(bits)).sum(0) + np.abs(old))
+    got = {}
+    for form in ("plain", "ws", "static"):
+        for acc in (0, 1):
+            db = torch.from_numpy(old.copy()).to("cuda:0")
+            args = (p, dY.data_ptr(), dY.stride(0), db.data_ptr(), acc)
+            if form == "plain":
+                axo.axo_bias_grad(*args, gu.stream())
+            elif form == "ws":
+                axo.axo_bias_grad_ws(*args, ws.data_ptr(), nws, gu.stream())
+            else:
+                axo.axo_bias_grad_static(*args, gu.stream())
+            got[form, acc] = db.cpu().numpy()
+            assert (np.abs(got[form, acc] - (ref + acc * old)) <= bound).all(), (form, acc)
+    for acc in (0, 1):
+        assert np.array_equal(got["ws", acc], got["static", acc])
+    assert nws == 0 or not ws[:(N + 63) // 64 * 4].any()  # the arrival counters are back at zero
