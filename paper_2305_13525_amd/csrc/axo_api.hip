@@ -597,6 +597,7 @@ BiasSplit plan_bias_split(int64_t M, int64_t Nl) {
     if (b.strips > 0 && M > 0) {
         int64_t want = (BIAS_SPLIT_WORKGROUPS + b.strips / 2) / b.strips;
         want = std::min<int64_t>(std::min<int64_t>(want, axo::BGS_MAX_SPLIT), M / 128);
+        if (b.strips * (int64_t)sizeof(uint32_t) > axo::BGS_MAX_COUNTER_BYTES) want = 1;  // (it already is there)
         if (want > 1) {
             const int64_t rows = ((M + want - 1) / want + axo::BGS_ROW_LANES - 1) / axo::BGS_ROW_LANES * axo::BGS_ROW_LANES;
             b.rows_per_slice = (int)rows;

@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(BG_THREADS) bias_grad_kernel(BiasGradArgs g) {
 //
 // Scratch: `counters` (one uint32 per strip) must be zero when the kernel starts; the last
 // workgroup of every strip sets its counter back to zero, so the kernel leaves them as it found
-// them.  `partial` needs no initialisation.  Launches that share scratch memory must not overlap.
+// them, and the same holds for all bytes where another shape's counters may lie.  `partial` needs no initialisation.  Launches that share scratch memory must not overlap.
 //
 // A 512-thread workgroup is 8 column lanes (16 bytes = 8 columns each: one 128-byte line per row)
 // by 64 row lanes; a thread's rows are 64 apart, their loads are issued eight at a time, summed in
@@ -121,6 +121,7 @@ constexpr int BGS_THREADS = 512;
 constexpr int BGS_COLS = 64;
 constexpr int BGS_ROW_LANES = BGS_THREADS / (BGS_COLS / 8);  // 64
 constexpr int BGS_MAX_SPLIT = 32;
+constexpr int BGS_MAX_COUNTER_BYTES = 1024;  // no shape of more than 256 strips is split (checked on the host)
 
 struct BiasGradSplitArgs {
     const bf16_t* dY; int64_t lddy;
@@ -214,6 +215,13 @@ __global__ void __launch_bounds__(BGS_THREADS) bias_grad_split_kernel(BiasGradSp
                 p[k] = k0 + k < g.S ? __hip_atomic_load(g.partial + (int64_t)(k0 + k) * g.Nl + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k) sum += p[k];
+        }
+        // This shape's slice sums may lie where a shape with more strips keeps its arrival counters: those bytes
+        // go back to zero, now that nobody else reads them, so that calls of any shapes may follow each other.
+        for (int k = 0; k < g.S; ++k) {
+            float* const p = g.partial + (int64_t)k * g.Nl + c;
+            if (reinterpret_cast<char*>(p) - reinterpret_cast<char*>(g.counters) >= BGS_MAX_COUNTER_BYTES) break;
+            __hip_atomic_store(p, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         g.db[c] = g.accumulate ? g.db[c] + sum : sum;
     }

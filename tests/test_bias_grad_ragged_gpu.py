@@ -41,3 +41,20 @@ def test_ragged_columns(M, N):
     for acc in (0, 1):
         assert np.array_equal(got["ws", acc], got["static", acc])
     assert nws == 0 or not ws[:(N + 63) // 64 * 4].any()  # the arrival counters are back at zero
+
+
+@pytest.mark.parametrize("form", ["ws", "static"])
+def test_shapes_that_share_scratch_in_any_order(form):
+    """A few-column shape keeps slice sums where a wide one keeps arrival counters: each call has to leave those
+    bytes at zero, or the next wide call's strips never see their last slice (or see it too early)."""
+    shapes = [(5000, 63), (5000, 8200), (4000, 515), (3000, 16300), (9000, 24), (5000, 8200), (2100, 200), (3000, 16300)]
+    P = lambda M, N: axo.Problem.make((1, 1, 1), (0, 0, 0), M, 8, N)
+    nws = max(axo.axo_bias_grad_workspace_bytes(P(*s)) for s in shapes)
+    ws = torch.zeros(nws, dtype=torch.uint8, device="cuda:0")
+    for k, (M, N) in enumerate(shapes):
+        dY = torch.randint(-8, 9, (M, (N + 7) // 8 * 8), device="cuda:0").to(torch.bfloat16)  # sums exact in fp32
+        db = torch.full((N,), -1.0, device="cuda:0")
+        args = (P(M, N), dY.data_ptr(), dY.stride(0), db.data_ptr(), 0)
+        axo.axo_bias_grad_ws(*args, ws.data_ptr(), nws, gu.stream()) if form == "ws" else axo.axo_bias_grad_static(*args, gu.stream())
+        assert torch.equal(db, dY[:, :N].float().sum(0)), (k, M, N)
+    assert not ws[:1024].any()
