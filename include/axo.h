@@ -264,7 +264,7 @@ size_t axo_layer_step_workspace_bytes(const axo_layer_t *layers, int n_layers);
  * dereferenced), gives every product a dependence level (0: conflicts with no earlier product;
  * otherwise one more than the highest level among the earlier products whose output it reads or
  * overwrites, or whose input it overwrites), and enqueues level by level.  The products of one
- * level are independent, and those the tiled kernel takes share grouped launches: the output
+ * level are independent and share grouped launches: the output
  * tiles of up to 12 products in one grid, most expensive tiles first, so that products too small
  * to fill the GPU on their own (a 1536 x 1536 shard is 36 tiles for 256 compute units) run side by
  * side and the level pays one ramp-up and one tail instead of one per product.  A chain whose

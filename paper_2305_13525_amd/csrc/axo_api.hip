@@ -20,6 +20,7 @@
 #include "axo_common.hpp"
 #include "bias_grad.hpp"
 #include "gemm_generic.hpp"
+#include "gemm_group.hpp"
 #include "gemm_slim.hpp"
 #include "gemm_tile.hpp"
 
@@ -230,12 +231,18 @@ struct SlimModel {
     double rate[3];    // KB per us of a busy CU, by layout pair
 };
 constexpr SlimModel SLIM_MODEL[2] = {{32, 5, 0.2, 0.24, {80.0, 106.0, 60.0}}, {64, 2, 1.5, 0.47, {112.0, 115.0, 95.0}}};
+double slim_tiles(const SlimModel& m, int Mo, int No) { return (double)((Mo + m.rows - 1) / m.rows) * ((No + m.rows - 1) / m.rows); }
+double slim_tile_us(const SlimModel& m, int R, int pair) {  // one tile on a busy CU
+    const double chunks = (R + axo::TILE_BK - 1) / axo::TILE_BK;
+    return chunks * (2.0 * m.rows * axo::TILE_BK * 2 / 1024.0) / m.rate[pair] + m.fixed;
+}
+double slim_chain_us(const SlimModel& m, int R) {  // one tile on a CU of its own
+    return 0.7 + std::ceil(std::ceil((double)R / axo::TILE_BK) / axo::SLIM_WAVES) * m.chunk_us;
+}
 double slim_time(const SlimModel& m, int Mo, int No, int R, int pair) {
-    const double tiles = (double)((Mo + m.rows - 1) / m.rows) * ((No + m.rows - 1) / m.rows);
-    const double chunks = (R + axo::TILE_BK - 1) / axo::TILE_BK, kb = chunks * (2.0 * m.rows * axo::TILE_BK * 2 / 1024.0);
-    const double busy = std::ceil(tiles / NUM_CU) * (kb / m.rate[pair] + m.fixed);
-    const double chain = std::ceil(tiles / (NUM_CU * m.slots)) * (0.7 + std::ceil(chunks / axo::SLIM_WAVES) * m.chunk_us);
-    return 2.5 + std::max(busy, chain);
+    const double tiles = slim_tiles(m, Mo, No);
+    return 2.5 + std::max(std::ceil(tiles / NUM_CU) * slim_tile_us(m, R, pair),
+                          std::ceil(tiles / (NUM_CU * m.slots)) * slim_chain_us(m, R));
 }
 int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
 
@@ -311,6 +318,11 @@ struct SegCost {
 // is bound by memory latency, not bandwidth: measured 19 us for 4096 rows, which is what 15
 // reduction steps of a big tile take.
 constexpr int PAIR_BIAS_GRAD = 3;
+// A product on small tiles inside a grouped launch (GroupItem::pair == PAIR_SLIM + its layout pair): a workgroup
+// takes two 64 x 64 tiles; their cost in reduction steps of a big tile (1.33 us).
+constexpr int PAIR_SLIM = 4;
+double slim_pair_cost(int R, int pair) { return 2.0 * slim_tile_us(SLIM_MODEL[1], R, pair) / 1.33; }
+int slim_pair_blocks(int Mo, int No) { return ((Mo + 63) / 64 * ((No + 63) / 64) + 1) / 2; }
 double bias_strip_cost(int rows) { return 1.0 + 15.0 * rows / 4096.0; }
 int bias_strips(int cols) { return (cols + axo::GROUP_BIAS_COLS - 1) / axo::GROUP_BIAS_COLS; }
 // The standalone launch picks its strip width by shape; only shapes for which it picks the
@@ -323,6 +335,10 @@ std::vector<SegCost> group_segments(const std::vector<GroupItem>& items, const s
     for (size_t i = 0; i < items.size(); ++i) {
         if (items[i].pair == PAIR_BIAS_GRAD) {
             segs.push_back({bias_strip_cost(items[i].Mo), bias_strips(items[i].No), (int)i, 0});
+            continue;
+        }
+        if (items[i].pair >= PAIR_SLIM) {
+            segs.push_back({slim_pair_cost(items[i].R, items[i].pair - PAIR_SLIM), slim_pair_blocks(items[i].Mo, items[i].No), (int)i, 0});
             continue;
         }
         const int tiles_m = (items[i].Mo + 255) / 256, cb = big_cols[i], cs = half_cols(items[i].No, cb);
@@ -356,11 +372,11 @@ std::vector<int> plan_group(const std::vector<GroupItem>& items) {
     auto it = cache.find(items);
     if (it != cache.end()) return it->second;
     std::vector<int> cols(items.size());
-    for (size_t i = 0; i < items.size(); ++i) cols[i] = items[i].pair == PAIR_BIAS_GRAD ? 0 : (items[i].No + 255) / 256;
+    for (size_t i = 0; i < items.size(); ++i) cols[i] = items[i].pair >= PAIR_BIAS_GRAD ? 0 : (items[i].No + 255) / 256;
     double best = group_makespan(group_segments(items, cols));
     for (int sweep = 0; sweep < 2; ++sweep)
         for (size_t i = 0; i < items.size(); ++i) {
-            if (items[i].pair == PAIR_BIAS_GRAD) continue;
+            if (items[i].pair >= PAIR_BIAS_GRAD) continue;
             const int max_cols = (items[i].No + 255) / 256;
             const int stride = max_cols > 16 ? (max_cols + 15) / 16 : 1;
             int best_c = cols[i];
@@ -391,6 +407,7 @@ int check_workspace(const axo_problem_t* p, int op, const void* ws, size_t ws_by
 struct Plan {
     GemmArgs g{};
     int la = 0, lb = 0;
+    bool small = false;       // the product runs on small tiles (filled in when it is enqueued with others)
     bool bias_grad = false;   // bg is valid instead of g
     axo::BiasGradArgs bg{};
     bool nothing_to_do() const { return bias_grad ? bg.Nl == 0 : (g.Mo == 0 || g.No == 0); }
@@ -405,7 +422,7 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     for (int i = 0; i < n; ++i)
         items[i] = plans[i]->bias_grad ? GroupItem{plans[i]->bg.M, plans[i]->bg.Nl, 0, PAIR_BIAS_GRAD}
                                        : GroupItem{plans[i]->g.Mo, plans[i]->g.No, plans[i]->g.R,
-                                                   layout_pair(plans[i]->la, plans[i]->lb)};
+                                                   layout_pair(plans[i]->la, plans[i]->lb) + (plans[i]->small ? PAIR_SLIM : 0)};
     const std::vector<int> cols = plan_group(items);
     const std::vector<SegCost> segs = group_segments(items, cols);
     axo::GroupArgs ga{};
@@ -423,6 +440,12 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
             sg.cols = sc.count;
             sg.col0 = 0;
             sg.group_m = 1;
+        } else if (items[sc.item].pair >= PAIR_SLIM) {
+            sg.kind = axo::GROUP_KIND_SLIM + items[sc.item].pair - PAIR_SLIM;
+            sg.tiles_m = (items[sc.item].Mo + 63) / 64;
+            sg.cols = (items[sc.item].No + 63) / 64;
+            sg.col0 = 0;
+            sg.group_m = std::min(sg.tiles_m, 8);
         } else {
             sg.kind = 2 * items[sc.item].pair + sc.small;
             sg.tiles_m = (items[sc.item].Mo + 255) / 256;
@@ -879,11 +902,56 @@ int dependence_levels(const std::vector<Plan>& plans, std::vector<int>* level) {
     return levels;
 }
 
+// One launch over the small tiles of several products (Kernel::small_tiles with R > 0 each, at most
+// SLIM_GROUP_MAX).  Both tile sizes sum in the same order, so the size is the group's to choose.
+template <int ROWS>
+int launch_slim_group_rows(const std::vector<const Plan*>& plans, hipStream_t st) {
+    using C = axo::SlimCfg<ROWS, ROWS, axo::SLIM_WAVES, 1>;
+    auto kern = axo::gemm_slim_group_kernel<ROWS>;
+    static std::atomic<uint64_t> raised{0};
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, &raised)) return AXO_ERR_HIP;
+    axo::SlimGroupArgs ga{};
+    ga.n = (int)plans.size();
+    int64_t blocks = 0;
+    for (int i = 0; i < ga.n; ++i) {
+        const GemmArgs& g = plans[i]->g;
+        ga.first_block[i] = (int)blocks;
+        ga.pair[i] = layout_pair(plans[i]->la, plans[i]->lb);
+        ga.sched[i] = {(g.Mo + ROWS - 1) / ROWS, (g.No + ROWS - 1) / ROWS, 0};
+        ga.sched[i].group_m = std::min(ga.sched[i].tiles_m, 8);
+        ga.g[i] = g;
+        blocks += (int64_t)ga.sched[i].tiles_m * ga.sched[i].tiles_n;
+    }
+    if (blocks > INT32_MAX / C::THREADS) return AXO_ERR_BAD_SIZE;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, ga);
+    return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+}
+int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
+    if (plans.size() == 1) return launch_slim(plans[0]->g, plans[0]->la, plans[0]->lb, st);
+    std::stable_sort(plans.begin(), plans.end(), [](const Plan* a, const Plan* b) { return a->g.R > b->g.R; });
+    double us[2];
+    for (int m = 0; m < 2; ++m) {
+        double busy = 0.0, chain = 0.0;
+        for (const Plan* pl : plans) {
+            const double tile = slim_tile_us(SLIM_MODEL[m], pl->g.R, layout_pair(pl->la, pl->lb));
+            busy += slim_tiles(SLIM_MODEL[m], pl->g.Mo, pl->g.No) / NUM_CU * tile;
+            chain = std::max(chain, slim_chain_us(SLIM_MODEL[m], pl->g.R));
+        }
+        us[m] = std::max(busy, chain);
+    }
+    return us[0] <= us[1] ? launch_slim_group_rows<32>(plans, st) : launch_slim_group_rows<64>(plans, st);
+}
+
 // Enqueues the products level by level: those of a level that the tiled kernel takes share
-// grouped launches (GROUP_MAX_PRODUCTS per launch), the others get a launch of their own.
-int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& level, int levels, hipStream_t st) {
+// grouped launches (GROUP_MAX_PRODUCTS per launch), those on small tiles likewise, the others get a launch of their own.
+int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, int levels, hipStream_t st) {
     int rc = AXO_OK;
     std::vector<const Plan*> group;   // products of the level the tiled kernel takes
+    std::vector<const Plan*> small;   // products of the level that run on small tiles
+    auto flush_small = [&]() {
+        if (!small.empty() && rc == AXO_OK) rc = launch_slim_group(small, st);
+        small.clear();
+    };
     std::vector<const Plan*> riders;  // bias gradients of the level that may share their launch
     auto flush = [&]() {
         if (group.empty() || rc != AXO_OK) return;
@@ -891,26 +959,38 @@ int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& lev
                                : launch_group(group.data(), (int)group.size(), st);
         group.clear();
     };
-    // the last launch of a level takes the level's bias gradients along, as many as fit
+    // the last launch of a level takes the level's small products and bias gradients along, as many as fit
     auto flush_level = [&]() {
+        while (!small.empty() && !group.empty() && (int)group.size() < axo::GROUP_MAX_PRODUCTS) {
+            group.push_back(small.back());
+            small.pop_back();
+        }
         while (!riders.empty() && !group.empty() && (int)group.size() < axo::GROUP_MAX_PRODUCTS) {
             group.push_back(riders.back());
             riders.pop_back();
         }
         flush();
+        flush_small();
         for (size_t k = 0; k < riders.size() && rc == AXO_OK; ++k) rc = launch_bias_grad(riders[k]->bg, st);
         riders.clear();
     };
     for (int lv = 0; lv < levels && rc == AXO_OK; ++lv) {
         for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) {
-            const Plan& pl = plans[i];
+            Plan& pl = plans[i];
             if (level[i] != lv || pl.nothing_to_do()) continue;
             if (pl.bias_grad) {
                 if (bias_grad_groupable(pl.bg)) riders.push_back(&pl);
                 else rc = launch_bias_grad(pl.bg, st);
                 continue;
             }
-            if (kernel_of(pl.g, pl.la, pl.lb) != Kernel::tiles) {
+            const Kernel kernel = kernel_of(pl.g, pl.la, pl.lb);
+            if (kernel == Kernel::small_tiles) {
+                pl.small = true;
+                small.push_back(&pl);
+                if ((int)small.size() == axo::SLIM_GROUP_MAX) flush_small();
+                continue;
+            }
+            if (kernel != Kernel::tiles) {
                 rc = launch(pl.g, pl.la, pl.lb, st);
                 continue;
             }
@@ -923,7 +1003,7 @@ int enqueue_by_level(const std::vector<Plan>& plans, const std::vector<int>& lev
 }
 
 // A validated chain, scheduled by dependence level.
-int enqueue_scheduled(const std::vector<Plan>& plans, hipStream_t st) {
+int enqueue_scheduled(std::vector<Plan>& plans, hipStream_t st) {
     if (plans.size() > MAX_ANALYSED) {  // not analysed: program order, one unit per launch
         int rc = AXO_OK;
         for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = launch_plan(plans[i], st);

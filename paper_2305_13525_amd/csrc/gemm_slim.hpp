@@ -113,14 +113,15 @@ struct SlimCfg {
     static_assert(BM % 32 == 0 && BN % 32 == 0 && LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
+// One tile; tid: 0 .. NW * 64 - 1 among the threads that work on it.  Holds exactly one workgroup barrier.
 template <int BM, int BN, int NW, int ST, int LA, int LB>
-__device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
+__device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, const int j0, const int tid, char* smem) {
     using C = SlimCfg<BM, BN, NW, ST>;
     using OA = SlimOperand<BM, LA>;
     using OB = SlimOperand<BN, LB>;
     constexpr int TM = BM / 16, TN = BN / 16;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KT = (g.R + TILE_BK - 1) / TILE_BK;
 
     OA oa;
@@ -219,7 +220,7 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
     static_assert(QUADS % C::THREADS == 0, "whole rounds of quads");
 #pragma unroll
     for (int q0 = 0; q0 < QUADS; q0 += C::THREADS) {
-        const int q = q0 + (int)threadIdx.x;
+        const int q = q0 + tid;
         const int lr = q / QPR, lc = (q % QPR) * 4;
         const int row = i0 + lr, col = j0 + lc;
         if (row >= g.Mo || col >= g.No) continue;
@@ -243,7 +244,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_slim_kernel(GemmArgs g, SlimSche
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), sc.tiles_m, sc.tiles_n, sc.group_m, tm, tn);
-    slim_tile_body<BM, BN, NW, ST, LA, LB>(g, tm * BM, tn * BN, smem);
+    slim_tile_body<BM, BN, NW, ST, LA, LB>(g, tm * BM, tn * BN, threadIdx.x, smem);
 }
 
 }  // namespace axo

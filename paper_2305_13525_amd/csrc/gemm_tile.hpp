@@ -35,13 +35,12 @@
 // lower clock, for the same time.  What is worth changing here is therefore what saves energy per
 // flop (operand traffic) or removes idle time of whole CUs, not what hides stalls.
 //
-// Two kernels share the tile body: gemm_mixed_kernel (one product per launch) and
-// gemm_group_kernel (the tiles of up to twelve independent products in one grid).
+// The tile bodies serve gemm_mixed_kernel and gemm_mid_kernel (one product per launch) and gemm_group_kernel
+// (gemm_group.hpp: the tiles of up to twelve independent products in one grid).
 #pragma once
 #include <type_traits>
 
 #include "axo_common.hpp"
-#include "bias_grad.hpp"
 
 namespace axo {
 
@@ -898,73 +897,6 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
     gemm_ring_body<128, 128, 4, 2, 4, LA, LB>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
-}
-
-// ---- grouped launch: the tiles of several independent products in one grid ----------------
-// A product on its own often cannot fill the 256 CUs (a 1536x1536 output is 36 big tiles), and a
-// chain of such launches pays a ramp-up and a tail each.  A group launch strings the tile lists of
-// up to GROUP_MAX_PRODUCTS products together: the grid is cut into segments, a segment is all the
-// tiles of one size of one product, and segments are ordered by decreasing tile cost so that the
-// in-order workgroup dispatch approximates longest-processing-time-first scheduling.  One of the
-// slots may instead hold a bias gradient, whose 64-column strips form one more (cheap, hence
-// late) segment of memory-bound workgroups.
-constexpr int GROUP_MAX_PRODUCTS = 12;
-constexpr int GROUP_MAX_SEGMENTS = 2 * GROUP_MAX_PRODUCTS;
-
-struct GroupSeg {
-    int first_block;  // first workgroup id of the segment
-    int n_blocks;
-    int product;      // index into GroupArgs::g
-    int kind;         // 2 * layout pair (0: KC/MC, 1: KC/KC, 2: MC/MC) + (1 if 256x128 tiles);
-                      // GROUP_KIND_BIAS_GRAD: 64-column strips of a bias gradient
-    int tiles_m;      // tile rows
-    int cols;         // tile columns of this segment
-    int col0;         // first output column of this segment
-    int group_m;      // band height of the tile order
-};
-
-constexpr int GROUP_KIND_BIAS_GRAD = 6;
-constexpr int GROUP_BIAS_COLS = 64;
-
-struct GroupArgs {
-    int n_seg;
-    GroupSeg seg[GROUP_MAX_SEGMENTS];
-    GemmArgs g[GROUP_MAX_PRODUCTS];
-};
-
-__global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs ga) {
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
-    const int bid = blockIdx.x;
-    int si = 0;
-    for (int i = 1; i < ga.n_seg; ++i)
-        if (bid >= ga.seg[i].first_block) si = i;
-    const GroupSeg sg = ga.seg[si];
-    const GemmArgs g = ga.g[sg.product];
-    if (sg.kind == GROUP_KIND_BIAS_GRAD) {
-        // A bias gradient rides along: memory-bound strips that fill CUs the products leave idle
-        // towards the end of the launch.  Its arguments travel in a GemmArgs: A = dY, C = db (fp32),
-        // Mo = rows, No = columns, epilogue = accumulate flag.
-        BiasGradArgs bg;
-        bg.dY = g.A;
-        bg.lddy = g.lda;
-        bg.db = reinterpret_cast<float*>(g.C);
-        bg.M = g.Mo;
-        bg.Nl = g.No;
-        bg.accumulate = g.epilogue;
-        bias_grad_strip<GROUP_BIAS_COLS, TILE_THREADS>(bg, bid - sg.first_block, reinterpret_cast<float*>(smem));
-        return;
-    }
-    int tm, tn;
-    // workgroup ids with equal id % 8 share an XCD whatever the segment's first id is
-    tile_of_index(xcd_run(bid - sg.first_block, sg.n_blocks), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
-    switch (sg.kind) {
-        case 0: gemm_tile_body<256, 256, 2, 4, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        case 1: gemm_ring_body<256, 128, 4, 2, 3, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
-        case 2: gemm_tile_body<256, 256, 2, 4, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
-        case 4: gemm_tile_body<256, 256, 2, 4, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        default: gemm_ring_body<256, 128, 4, 2, 3, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
-    }
 }
 
 }  // namespace axo

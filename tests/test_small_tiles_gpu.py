@@ -119,3 +119,31 @@ def test_large_tiles_at_odd_edges(M, Kl, Nl):
     got = dW32.cpu().numpy()
     # fp32 sums of M products of unit Gaussians: the same sums that the bf16 output rounds
     assert np.abs(got[:, :Nl] - wg).max() <= 1e-4 * np.abs(wg).max() and (got[:, Nl:] == -7.0).all()
+
+
+def test_chain_that_mixes_all_tile_kinds_equals_single_calls():
+    """Layers whose products run on small tiles, on 128 x 128 tiles when called alone, and on 256-row tiles, all
+    independent and so in one level: small products ride along in the larger ones' grouped launch (an odd number
+    of 64 x 64 tiles among them), or share one of their own.  Every buffer as the single calls leave it, bit for bit."""
+    for shapes in ([(2304, 1024, 2048), (520, 300, 136), (1536, 1408, 1536), (33, 65, 100), (2000, 64, 200)],
+                   [(520, 300, 136), (33, 65, 100), (300, 1000, 40), (7, 9, 3)]):
+        layers, results = [], []
+        for step in (axo.axo_layer_step, axo.axo_layer_step_ordered):
+            bufs, layers = [], []
+            for i, (M, Kl, Nl) in enumerate(shapes):
+                X, W, dY = (padded(syn.normal_bf16(110 + i, s, sh, 1.0)) for s, sh in ((0, (M, Kl)), (1, (Kl, Nl)), (2, (M, Nl))))
+                Y, dX, dW = out(M, Nl), out(M, Kl), out(Kl, Nl)
+                bufs.append((X, W, dY, Y, dX, dW))
+                layers.append(axo.Layer(P(M, Kl, Nl), 0, 0, X.data_ptr(), gu.ld(X), W.data_ptr(), gu.ld(W), None, Y.data_ptr(),
+                                        gu.ld(Y), dY.data_ptr(), gu.ld(dY), dX.data_ptr(), gu.ld(dX), dW.data_ptr(), gu.ld(dW)))
+            assert axo.axo_layer_step_levels(layers)[1] == 1
+            step(layers, None, 0, gu.stream())
+            torch.cuda.synchronize()
+            results.append([t.clone() for b in bufs for t in b[3:]])
+        for k, (a, b) in enumerate(zip(*results)):
+            assert torch.equal(a, b), (k // 3, k % 3)
+        for i, (M, Kl, Nl) in enumerate(shapes):  # and against the oracle
+            Xb, Wb, dYb = (syn.normal_bf16(110 + i, s, sh, 1.0) for s, sh in ((0, (M, Kl)), (1, (Kl, Nl)), (2, (M, Nl))))
+            if M * Kl * Nl < 10 ** 8:
+                for got, ref in zip(results[0][3 * i:], (oracle.fc_fwd(Xb, Wb), oracle.fc_dgrad(dYb, Wb), oracle.fc_wgrad(Xb, dYb))):
+                    gu.assert_close(oracle, gu.to_host(got)[:, :ref.shape[1]], ref, f"chain {M}x{Kl}x{Nl}")
