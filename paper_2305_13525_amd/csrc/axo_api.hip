@@ -189,18 +189,36 @@ double mid_time(int Mo, int No, int R) {
     return 4.5 + (R + axo::TILE_BK - 1) / axo::TILE_BK * 0.42;
 }
 
-// Launch of one product on 128 x 128 tiles or on the 256-row ones, whichever is estimated quicker (both give
+// 64 x 64 tiles of a ring: a step takes 0.235 us with a CU to itself, and 0.15 us on a busy one, where two run beside
+// each other.  (Estimates of the three within 20 % for nearly all of 60 products of 256 to 8192 tokens.)
+double small_time(int Mo, int No, int R) {
+    const double steps = (R + axo::TILE_BK - 1) / axo::TILE_BK;
+    const double n = std::ceil((double)((Mo + 63) / 64) * ((No + 63) / 64) / NUM_CU);
+    return n <= 1.0 ? 3.2 + steps * 0.235 : 3.0 + n * (0.85 + steps * 0.15);
+}
+
+// Launch of one product on square tiles of `ROWS` rows.
+template <typename C, int ROWS>
+int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* raised, const GemmArgs& g, hipStream_t st) {
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, raised)) return AXO_ERR_HIP;
+    const int tm = (g.Mo + ROWS - 1) / ROWS, tn = (g.No + ROWS - 1) / ROWS;
+    hipLaunchKernelGGL(kern, dim3((unsigned)tm * (unsigned)tn), dim3(C::THREADS), C::LDS_BYTES, st, g, tm, tn, std::min(tm, 8));
+    return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+}
+
+// Launch of one product on 64 x 64, 128 x 128 or 256-row tiles, whichever are estimated quickest (all give
 // the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by LDS
 // traffic (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
-    if (mid_time(g.Mo, g.No, g.R) < tile_time(g.Mo, g.No, g.R)) {
-        auto mid = axo::gemm_mid_kernel<LA, LB>;
-        static std::atomic<uint64_t> mid_raised{0};
-        if (!raise_lds_limit(reinterpret_cast<const void*>(mid), axo::MidCfg::LDS_BYTES, &mid_raised)) return AXO_ERR_HIP;
-        const int tm = (g.Mo + 127) / 128, tn = (g.No + 127) / 128;
-        hipLaunchKernelGGL(mid, dim3(tm * tn), dim3(axo::TILE_THREADS), axo::MidCfg::LDS_BYTES, st, g, tm, tn, std::min(tm, 8));
-        return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+    const double small_us = small_time(g.Mo, g.No, g.R), mid_us = mid_time(g.Mo, g.No, g.R), big_us = tile_time(g.Mo, g.No, g.R);
+    if (small_us < mid_us && small_us < big_us) {
+        static std::atomic<uint64_t> raised{0};
+        return launch_square<axo::SmallCfg, 64>(axo::gemm_small_kernel<LA, LB>, &raised, g, st);
+    }
+    if (mid_us < big_us) {
+        static std::atomic<uint64_t> raised{0};
+        return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB>, &raised, g, st);
     }
     auto kern = axo::gemm_mixed_kernel<LA, LB>;
     static std::atomic<uint64_t> raised{0};
@@ -250,15 +268,25 @@ int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : 
 int slim_rows(const GemmArgs& g, int pair) {
     return slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair) <= slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair) ? 32 : 64;
 }
-// Whether a product runs on small tiles: where those are estimated at least 10 % quicker than the larger ones.
-// A function of sizes and layouts only, because the waves of a small tile split the reduction and so sum in
-// another order: a product has the same bits on its own and in a chain.  (The margin also keeps products out of it
-// that a chain's grouped launch takes along: a 1536 x 1536 weight gradient of 4096 tokens on small tiles cost a
-// block of four layers 3.5 %.)
+// Share of the chip's time that a product's 256-row tiles take in a launch that fills it.
+double tile_share(int Mo, int No, int R) {
+    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
+    return tm * std::min((No + 255) / 256 * 1.0, (No + 127) / 128 * SMALL_TILE_COST) * steps * 1.33 / NUM_CU;
+}
+// Whether a product runs on tiles whose waves split the reduction: where those are estimated at least 15 % quicker than
+// the others, and where a chain's grouped launch, in which the larger tiles of other products keep the chip
+// full, loses no more than about a microsecond by it.  A function of sizes and layouts only, because these tiles sum
+// in another order: a product has the same bits on its own and in a chain.  (Without the second condition a block of
+// four layers, 2048 tokens of width 1024, took 181 us instead of 127.)
 bool prefers_slim(const GemmArgs& g, int la, int lb) {
     const int pair = layout_pair(la, lb);
-    const double slim = std::min(slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair), slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair));
-    return slim < 0.9 * std::min(tile_time(g.Mo, g.No, g.R), mid_time(g.Mo, g.No, g.R));
+    double us = 1e30, share = 1e30;
+    for (const SlimModel& m : SLIM_MODEL) {
+        us = std::min(us, slim_time(m, g.Mo, g.No, g.R, pair));
+        share = std::min(share, slim_tiles(m, g.Mo, g.No) / NUM_CU * slim_tile_us(m, g.R, pair));
+    }
+    return us < 0.85 * std::min({tile_time(g.Mo, g.No, g.R), mid_time(g.Mo, g.No, g.R), small_time(g.Mo, g.No, g.R)}) &&
+           share < 1.3 * tile_share(g.Mo, g.No, g.R) + 1.0;
 }
 
 template <int ROWS, int ST, int LA, int LB>

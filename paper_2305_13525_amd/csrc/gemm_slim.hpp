@@ -33,16 +33,6 @@
 
 namespace axo {
 
-// 16-byte chunks of an LDS tile are permuted so that fragment reads spread over the banks.  KC (128-byte
-// rows): swz_kc.  MC: a transposing read of half a wave touches the 8 rows given by k % 4 and
-// (k / 8) % 2, two chunks each; with rows of 64 or 128 bytes, 4 or 2 rows share a 256-byte bank sweep
-// and the remaining bits of that choice pick the chunk.
-template <int ROWS>
-__device__ __forceinline__ int swz_mc_narrow(int k) {
-    static_assert(ROWS == 32 || ROWS == 64, "row pitch 64 or 128 bytes");
-    return ROWS == 32 ? ((k >> 3) & 1) << 1 : (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
-}
-
 // One operand of a tile as one wave sees it: ROWS output rows (or columns) by 64 reduction elements.
 template <int ROWS, int LAYOUT>
 struct SlimOperand {
@@ -63,7 +53,7 @@ struct SlimOperand {
             } else {
                 constexpr int CPR = ROWS / 8;
                 const int k = q / CPR, cs = q % CPR;
-                off[j] = (uint32_t)(((int64_t)k * ld + ((cs ^ swz_mc_narrow<ROWS>(k)) << 3)) * 2);
+                off[j] = (uint32_t)(((int64_t)k * ld + ((cs ^ swz_mc<ROWS>(k)) << 3)) * 2);
             }
         }
         if (LAYOUT == KC) {
@@ -75,7 +65,7 @@ struct SlimOperand {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int n = t * 16 + ((i & 3) << 2);
-                addr[t % NA] = krow * (ROWS * 2) + (((n >> 3) ^ swz_mc_narrow<ROWS>(krow)) << 4) + (((n >> 2) & 1) << 3);
+                addr[t % NA] = krow * (ROWS * 2) + (((n >> 3) ^ swz_mc<ROWS>(krow)) << 4) + (((n >> 2) & 1) << 3);
             }
         }
     }

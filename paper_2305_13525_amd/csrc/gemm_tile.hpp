@@ -69,7 +69,15 @@ __device__ __forceinline__ int swz_kc(int r) { return (r >> 1) & 7; }
 // f(k) = 4*(k % 4) + 2*((k / 8) % 2): half a wave's transposing read touches 8 reduction rows
 // (k % 4 and (k / 8) % 2 vary) times two 16-byte chunks, which then land in 16 different bank
 // groups (without the second term the 16-lane groups collide: measured 50 % conflict cycles).
-__device__ __forceinline__ int swz_mc(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
+// Rows of 64 or 128 bytes (32 or 64 output indices): 4 or 2 of them share a 256-byte sweep of the banks, and the
+// remaining bits of that choice pick the chunk.
+template <int ROWS>
+__device__ __forceinline__ int swz_mc(int k) {
+    static_assert(ROWS == 32 || ROWS == 64 || ROWS == 128 || ROWS == 256, "row pitch");
+    return ROWS == 32   ? ((k >> 3) & 1) << 1
+           : ROWS == 64 ? (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2)
+                        : ((k & 3) << 2) | (((k >> 3) & 1) << 1);
+}
 
 // How one launch is cut into workgroups.  The output is covered by two column regions: columns
 // [0, big_cols * 256) with 256x256 tiles and the rest with 256x128 tiles.  Workgroups
@@ -143,7 +151,7 @@ __device__ __forceinline__ void load_offsets(int tid, int64_t ld, uint32_t* off)
         } else {
             constexpr int CPR = ROWS / 8;  // chunks per reduction row
             const int k = q / CPR, cs = q % CPR;
-            off[j] = (uint32_t)(((int64_t)k * ld + ((cs ^ swz_mc(k)) << 3)) * 2);
+            off[j] = (uint32_t)(((int64_t)k * ld + ((cs ^ swz_mc<ROWS>(k)) << 3)) * 2);
         }
     }
 }
@@ -171,7 +179,7 @@ struct FragAddr {
         } else {
             const int i = lane & 15;
             const int krow = ((lane >> 4) << 3) + (i >> 2);
-            const int sw = swz_mc(krow);  // unchanged by the +4 and +32 row offsets added in read()
+            const int sw = swz_mc<ROWS>(krow);  // unchanged by the +4 and +32 row offsets added in read()
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int n = row0 + t * 16 + ((i & 3) << 2);
@@ -413,7 +421,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
             default: finish(IC<EPI_MUL_DGELU_ERF>{}); return;
         }
     } else {  // wgrad
-        if (g.epilogue == EPI_ACC_F32) {
+        if constexpr (C::WTN == 64) if (g.epilogue == EPI_ACC_F32) {
             // fp32 accumulation dW32 += acc, no rounding.  The wave's 64 fp32 columns are 256 bytes
             // per row: the sums are staged through the wave's LDS region (half the wave tile's rows
             // at a time, rows padded to 272 bytes) so that 16 lanes read, add and write back one
@@ -845,7 +853,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
         if constexpr (D > 2) if (j + 2 < KT) step(IC<2 % D>{}, j + 2);
         if constexpr (D > 3) if (j + 3 < KT) step(IC<3 % D>{}, j + 3);
     }
-    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No && (C::WTN == 64 || g.epilogue != EPI_ACC_F32);
+    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
@@ -897,6 +906,19 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
     gemm_ring_body<128, 128, 4, 2, 4, LA, LB>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
+}
+
+// The same for smaller outputs: 64 x 64, four waves of 32 x 32 on a four-stage ring, two workgroups per CU.  Measured
+// against the small tiles whose waves split the reduction (gemm_slim.hpp), forward / dgrad / wgrad: 2048 x 1024 x 1024
+// 11.9 / 12.1 / 11.5 -> 9.4 / 8.5 / 10.2 us, 1000^3 10.0 / 9.6 / 10.2 -> 8.8 / 8.6 / 8.2, wgrad 1024 x 1024 of 8192 tokens 30
+// both (128 x 128 tiles: 51).  Those stay quicker below some 100 tiles (300^3 3.7 against 5.4).
+using SmallCfg = RingCfg<64, 64, 2, 2, 4>;
+template <int LA, int LB>
+__global__ void __launch_bounds__(SmallCfg::THREADS, 2) gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    int tm, tn;
+    tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
+    gemm_ring_body<64, 64, 2, 2, 4, LA, LB>(g, inside_row<64, LA>(g, tm * 64), inside_col<64>(g, tn * 64), smem);
 }
 
 }  // namespace axo
