@@ -1,6 +1,6 @@
 // General-shape bf16 MFMA GEMM for gfx950: any Mo, No, R (including ragged tails), both operand
-// layouts.  This is the correctness-first kernel: it serves shapes the tuned kernel does not
-// take.  128x128 output tile per 256-thread workgroup (4 waves in a 2x2 arrangement, 64x64 per
+// layouts.  This is the correctness-first kernel: it serves operands whose span passes 4 GiB, which the
+// other kernels' 32-bit byte offsets do not reach.  128x128 output tile per 256-thread workgroup (4 waves in a 2x2 arrangement, 64x64 per
 // wave = 2x2 MFMA 32x32x16 tiles), reduction step 32, one LDS buffer, operands staged
 // global -> registers -> LDS with the reduction index contiguous in LDS for both operands.
 #pragma once

@@ -1,8 +1,8 @@
 // Small-tile bf16 MFMA GEMM for gfx950: any Mo, No, R, every edge handled in the kernel.
 //   C[Mo x No] = sum_r A(i, r) * B(j, r)
 //
-// For products whose output is too small for the 256-row tiles of gemm_tile.hpp to occupy the chip.
-// Such a product is bound by latency and by how fast one CU pulls operands in (a 1 KB wave-load per
+// For products whose output is so small, or whose batch is so short, that the tiles of gemm_tile.hpp come to a
+// few workgroups with a long serial reduction each.  Such a product is bound by latency and by how fast one CU pulls operands in (a 1 KB wave-load per
 // about 20 cycles), so the waves of a workgroup split the REDUCTION of one BM x BN tile between them:
 // wave w takes the 64-wide reduction chunks w, w + NW, w + 2 NW, ...  A wave copies its chunks into LDS
 // that nobody else touches, so the main loop has no workgroup barrier: it waits for its own loads
@@ -25,9 +25,8 @@
 // the rows (KC), is masked in registers in the last chunk, on both operands (a zero times a stray infinity
 // would be a NaN).
 //
-// Measured, kernel time of forward / dgrad / wgrad: 96 x 2048 x 6144 10.5 / 13.2 / - us (the general kernel
-// took 130 / 238), 1001 x 1027 x 515 9.8 / 7.7 / 8.4 (85 / 39 / 178), 77 x 1000 x 48 4.1 / 3.1 / 2.9
-// (56 / 15 / 19), 256^3 3.3 / 3.2 / 3.1 (256 x 128 tiles: 5.3 each).
+// Measured, kernel time of forward / dgrad / wgrad: 96 x 2048 x 6144 11.7 / 11.6 / - us (the general kernel
+// took 130 / 238), 77 x 1000 x 48 4.2 / 3.1 / 3.0 (56 / 15 / 19), 256^3 3.3 / 3.3 / 3.2 (256 x 128 tiles: 5.3 each).
 #pragma once
 #include "gemm_tile.hpp"
 
