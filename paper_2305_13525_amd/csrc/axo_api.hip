@@ -505,8 +505,9 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
 enum class Kernel { none, tiles, small_tiles, general };
 Kernel kernel_of(const GemmArgs& g, int la, int lb) {
     if (g.Mo == 0 || g.No == 0) return Kernel::none;
-    if (!spans_ok(g, la, lb)) return Kernel::general;  // 64-bit addressing, an order of magnitude slower
-    return g.R == 0 || prefers_slim(g, la, lb) ? Kernel::small_tiles : Kernel::tiles;
+    // 64-bit addressing, an order of magnitude slower; and what an empty reduction leaves: epilogue(0)
+    if (!spans_ok(g, la, lb) || g.R == 0) return Kernel::general;
+    return prefers_slim(g, la, lb) ? Kernel::small_tiles : Kernel::tiles;
 }
 
 int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
@@ -930,7 +931,7 @@ int dependence_levels(const std::vector<Plan>& plans, std::vector<int>* level) {
     return levels;
 }
 
-// One launch over the small tiles of several products (Kernel::small_tiles with R > 0 each, at most
+// One launch over the small tiles of several products (Kernel::small_tiles each, at most
 // SLIM_GROUP_MAX).  Both tile sizes sum in the same order, so the size is the group's to choose.
 template <int ROWS>
 int launch_slim_group_rows(const std::vector<const Plan*>& plans, hipStream_t st) {
