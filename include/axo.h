@@ -115,25 +115,46 @@ int axo_shard_dims(const axo_problem_t *p, int64_t *M, int64_t *Kl, int64_t *Nl,
  * Returns 0 for an invalid problem (the op call itself reports the error). */
 size_t axo_workspace_bytes(const axo_problem_t *p, int op);
 
-/* How a product's shape fits the tuned kernel's tiles (256 rows, 128 or 256 columns), as axo_fc_route
- * reports it.  Under TILED and COVERED a product that is too small to occupy the GPU with such tiles runs on
- * 32 x 32 or 64 x 64 tiles instead, wherever those are estimated quicker from the shape alone. */
+/* How a product's shape fits the granularity of the largest tiles (256 rows, 128 columns), as axo_fc_route
+ * reports it.  This is a property of the shape and of the operand spans; which kernel runs, and so how fast the
+ * product is, axo_fc_kernel tells. */
 typedef enum axo_route {
     AXO_ROUTE_NONE = 0,            /* an empty output: nothing is launched                                 */
-    AXO_ROUTE_TILED = 1,           /* whole tiles, one launch                                              */
-    AXO_ROUTE_COVERED = 2,         /* a ragged output: tiles that reach over its edge, one launch          */
-    AXO_ROUTE_INTERIOR_STRIPS = 3, /* no longer used                                                       */
-    AXO_ROUTE_GENERAL = 4          /* below one tile: small tiles; a span past 4 GiB: a bounds-checked     */
-                                   /* kernel with 64-bit addressing, several times slower                  */
+    AXO_ROUTE_TILED = 1,           /* a whole number of 256 x 128 blocks                                   */
+    AXO_ROUTE_COVERED = 2,         /* at least one such block, and a ragged edge                           */
+    AXO_ROUTE_INTERIOR_STRIPS = 3, /* no longer returned                                                   */
+    AXO_ROUTE_GENERAL = 4          /* fewer than 256 rows or 128 columns, an empty reduction, or a span    */
+                                   /* past 4 GiB                                                           */
 } axo_route_t;
 
-/* Host only.  Reports in *route (axo_route_t) which kernels the product `op` (axo_op_t) of this
- * problem takes when its two inputs have leading dimensions ld_a, ld_b (in the argument order of the
- * product's entry point: X, W for forward; dY, W for dgrad; X, dY for wgrad) and its output ld_out.
- * The choice depends on the shard shape and on the leading dimensions only (the tuned kernel forms
- * 32-bit byte offsets inside an operand tile), never on data.  For capacity planning and tests.
+/* Host only.  Reports in *route (axo_route_t) how the product `op` (axo_op_t) of this problem fits, when its
+ * two inputs have leading dimensions ld_a, ld_b (in the argument order of the product's entry point: X, W for
+ * forward; dY, W for dgrad; X, dY for wgrad) and its output ld_out.  A function of the shard shape and of
+ * the leading dimensions only (the tile kernels form 32-bit byte offsets inside an operand tile), never of data.
  * Errors: those of the product's argument checks; NULL_PTR (route); BAD_ARG (unknown op). */
 int axo_fc_route(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int *route);
+
+/* The kernel that a product runs on, as axo_fc_kernel reports it. */
+typedef enum axo_kernel {
+    AXO_KERNEL_NONE = 0,                /* an empty output: nothing is launched                            */
+    AXO_KERNEL_GENERAL = 1,             /* bounds-checked, 64-bit addressing, an order of magnitude slower:  */
+                                        /* operand spans past 4 GiB, empty reductions                      */
+    AXO_KERNEL_SPLIT_32 = 2,            /* 32 x 32 tiles whose four waves split the reduction              */
+    AXO_KERNEL_SPLIT_32_TWO_STAGES = 3, /* the same with two LDS stages per wave                           */
+    AXO_KERNEL_SPLIT_64 = 4,            /* 64 x 64 tiles whose four waves split the reduction              */
+    AXO_KERNEL_TILES_64 = 5,            /* 64 x 64 tiles, reduction in order                               */
+    AXO_KERNEL_TILES_128 = 6,           /* 128 x 128 tiles, reduction in order                             */
+    AXO_KERNEL_TILES_256 = 7,           /* 256 x 256 tiles, reduction in order                             */
+    AXO_KERNEL_TILES_256_HALF = 8,      /* 256 x 128 tiles, reduction in order                             */
+    AXO_KERNEL_TILES_256_MIXED = 9      /* both of these in one launch                                     */
+} axo_kernel_t;
+
+/* Host only.  Reports in *kernel (axo_kernel_t) the kernel on which the product runs when it is called on its
+ * own; arguments and errors as axo_fc_route.  A function of the shard shape and the leading dimensions only.
+ * The kernels are chosen by estimated time, so the answer for a shape may change from one version to the next.  In
+ * a chain's grouped launch the products of classes 5 to 9 run on 256-row tiles and those of classes 2 to 4 on
+ * either size of split tile; all kernels of one of these two classes give the same bits. */
+int axo_fc_kernel(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int *kernel);
 
 /* Forward local product  Y[M x Nl] = epilogue( X[M x Kl] . W[Kl x Nl] ).
  * X, W, Y: device pointers, bf16, row-major, 16-byte aligned; ldx >= Kl, ldw >= Nl, ldy >= Nl,
@@ -147,8 +168,8 @@ int axo_fc_route(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int
  * HIP; NO_MEMORY.
  * Speed: any shard runs on MFMA tiles; leading dimensions that are multiples of 64 elements keep every 128-byte
  * row segment inside one cache line (worth 10-20 %).  Operands whose span (256 rows, or the whole reduction
- * where that is the row index) passes 4 GiB are computed by a bounds-checked kernel several times slower;
- * axo_fc_route tells. */
+ * where that is the row index) passes 4 GiB are computed by a bounds-checked kernel an order of magnitude slower;
+ * axo_fc_kernel tells. */
 int axo_fc_fwd(const axo_problem_t *p, const void *X, int64_t ldx, const void *W, int64_t ldw,
                const void *bias, int epilogue, void *Y, int64_t ldy,
                void *ws, size_t ws_bytes, void *hip_stream);

@@ -206,17 +206,25 @@ int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* 
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 
-// Launch of one product on 64 x 64, 128 x 128 or 256-row tiles, whichever are estimated quickest (all give
+// The tiles of a product on its own, 64 x 64, 128 x 128 or 256-row ones, whichever are estimated quickest (all give
 // the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by LDS
 // traffic (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
+enum class Tiles { small, mid, big };
+Tiles tiles_of(int Mo, int No, int R) {
+    const double small_us = small_time(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
+    if (small_us < mid_us && small_us < big_us) return Tiles::small;
+    return mid_us < big_us ? Tiles::mid : Tiles::big;
+}
+
+// Launch of one product on those tiles.
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
-    const double small_us = small_time(g.Mo, g.No, g.R), mid_us = mid_time(g.Mo, g.No, g.R), big_us = tile_time(g.Mo, g.No, g.R);
-    if (small_us < mid_us && small_us < big_us) {
+    const Tiles tiles = tiles_of(g.Mo, g.No, g.R);
+    if (tiles == Tiles::small) {
         static std::atomic<uint64_t> raised{0};
         return launch_square<axo::SmallCfg, 64>(axo::gemm_small_kernel<LA, LB>, &raised, g, st);
     }
-    if (mid_us < big_us) {
+    if (tiles == Tiles::mid) {
         static std::atomic<uint64_t> raised{0};
         return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB>, &raised, g, st);
     }
@@ -302,13 +310,17 @@ int launch_slim_rows(const GemmArgs& g, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
+// Whether a product on 32 x 32 tiles keeps two LDS stages per wave.  Two stages leave room for two workgroups on a
+// CU, one stage for five; below 16 chunks per wave the second stage's longer start costs what it gains (200 x 2000 x 512
+// forward 5.5 us with one, 5.8 with two).
+bool slim_two_stages(const GemmArgs& g) {
+    const int64_t tiles = ((int64_t)g.Mo + 31) / 32 * (((int64_t)g.No + 31) / 32);
+    return tiles <= 2 * NUM_CU && g.R >= 16 * axo::SLIM_WAVES * axo::TILE_BK;
+}
 template <int LA, int LB>
 int launch_slim_layout(const GemmArgs& g, int rows, hipStream_t st) {
     if (rows == 64) return launch_slim_rows<64, 1, LA, LB>(g, st);
-    // two stages leave room for two workgroups on a CU, one stage for five; below 16 chunks per wave the second
-    // stage's longer start costs what it gains (200 x 2000 x 512 forward 5.5 us with one, 5.8 with two)
-    const int64_t tiles = ((int64_t)g.Mo + 31) / 32 * (((int64_t)g.No + 31) / 32);
-    return tiles <= 2 * NUM_CU && g.R >= 16 * axo::SLIM_WAVES * axo::TILE_BK ? launch_slim_rows<32, 2, LA, LB>(g, st) : launch_slim_rows<32, 1, LA, LB>(g, st);
+    return slim_two_stages(g) ? launch_slim_rows<32, 2, LA, LB>(g, st) : launch_slim_rows<32, 1, LA, LB>(g, st);
 }
 int launch_slim(const GemmArgs& g, int la, int lb, hipStream_t st) {
     const int rows = slim_rows(g, layout_pair(la, lb));
@@ -517,6 +529,25 @@ int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
         case Kernel::small_tiles: return launch_slim(g, la, lb, st);
         default: return launch_generic(g, la, lb, st);
     }
+}
+
+// The same choice as axo_fc_kernel reports it, down to the tile sizes of a call on its own.
+int kernel_id(const GemmArgs& g, int la, int lb) {
+    switch (kernel_of(g, la, lb)) {
+        case Kernel::none: return AXO_KERNEL_NONE;
+        case Kernel::general: return AXO_KERNEL_GENERAL;
+        case Kernel::small_tiles:
+            if (slim_rows(g, layout_pair(la, lb)) == 64) return AXO_KERNEL_SPLIT_64;
+            return slim_two_stages(g) ? AXO_KERNEL_SPLIT_32_TWO_STAGES : AXO_KERNEL_SPLIT_32;
+        default: break;
+    }
+    switch (tiles_of(g.Mo, g.No, g.R)) {
+        case Tiles::small: return AXO_KERNEL_TILES_64;
+        case Tiles::mid: return AXO_KERNEL_TILES_128;
+        default: break;
+    }
+    const axo::TileSched sc = plan_tiles(g.Mo, g.No);
+    return sc.small_cols == 0 ? AXO_KERNEL_TILES_256 : sc.big_cols == 0 ? AXO_KERNEL_TILES_256_HALF : AXO_KERNEL_TILES_256_MIXED;
 }
 
 // How the shape fits the 256 x 128 granularity of the tiles, for axo_fc_route.
@@ -1043,6 +1074,18 @@ int enqueue_scheduled(std::vector<Plan>& plans, hipStream_t st) {
     return enqueue_by_level(plans, level, levels, st);
 }
 
+// The product that a query (axo_fc_route, axo_fc_kernel) asks about, at made-up, well-separated and aligned
+// addresses: the planners compare pointers, never follow them.
+int plan_query(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, Plan* pl) {
+    if (op < AXO_OP_FWD || op > AXO_OP_WGRAD) return AXO_ERR_BAD_ARG;
+    const void* a = reinterpret_cast<const void*>((uintptr_t)1 << 40);
+    const void* b = reinterpret_cast<const void*>((uintptr_t)2 << 40);
+    void* c = reinterpret_cast<void*>((uintptr_t)3 << 40);
+    if (op == AXO_OP_FWD) return plan_fwd(p, a, ld_a, b, ld_b, nullptr, AXO_EPI_NONE, c, ld_out, nullptr, 0, pl);
+    if (op == AXO_OP_DGRAD) return plan_dgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, pl);
+    return plan_wgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, pl);
+}
+
 // No exception leaves the library: the planners keep their lists and caches in standard
 // containers, whose allocations can fail.
 template <typename F>
@@ -1106,17 +1149,21 @@ size_t axo_workspace_bytes(const axo_problem_t* p, int op) {
 int axo_fc_route(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int* route) {
     return guarded([&]() -> int {
         if (!route) return AXO_ERR_NULL_PTR;
-        if (op < AXO_OP_FWD || op > AXO_OP_WGRAD) return AXO_ERR_BAD_ARG;
-        // made-up, well-separated and aligned addresses: the planners compare pointers, never follow them
-        const void* a = reinterpret_cast<const void*>((uintptr_t)1 << 40);
-        const void* b = reinterpret_cast<const void*>((uintptr_t)2 << 40);
-        void* c = reinterpret_cast<void*>((uintptr_t)3 << 40);
         Plan pl;
-        const int rc = op == AXO_OP_FWD     ? plan_fwd(p, a, ld_a, b, ld_b, nullptr, AXO_EPI_NONE, c, ld_out, nullptr, 0, &pl)
-                       : op == AXO_OP_DGRAD ? plan_dgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, &pl)
-                                            : plan_wgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, &pl);
+        const int rc = plan_query(p, op, ld_a, ld_b, ld_out, &pl);
         if (rc) return rc;
         *route = route_of(pl.g, pl.la, pl.lb);
+        return AXO_OK;
+    });
+}
+
+int axo_fc_kernel(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int* kernel) {
+    return guarded([&]() -> int {
+        if (!kernel) return AXO_ERR_NULL_PTR;
+        Plan pl;
+        const int rc = plan_query(p, op, ld_a, ld_b, ld_out, &pl);
+        if (rc) return rc;
+        *kernel = kernel_id(pl.g, pl.la, pl.lb);
         return AXO_OK;
     });
 }
