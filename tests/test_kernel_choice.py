@@ -31,3 +31,14 @@ def test_errors_are_those_of_the_product():
     assert axo.axo_fc_kernel(mk(64, 32, 48), 5, 32, 48, 48, check=False)[0] == -11            # BAD_ARG
     assert axo.axo_fc_kernel(mk(64, 32, 48), FWD, 32, 44, 48, check=False)[0] in (-5, -6)     # MISALIGNED or BAD_LD
     assert axo.library().axo_fc_kernel(None, 0, 8, 8, 8, None) == -4                          # NULL_PTR
+
+
+def test_a_new_batch_length_costs_no_new_plan():
+    """The split of an output into 256- and 128-wide tile columns depends on the counts of tiles, so the token counts
+    of one 256-row band share a plan, and a new plan is a short search.  400 token counts of an output of 50257 columns:
+    14 s when each of them simulated its dispatch, tile by tile and split by split; milliseconds now."""
+    import time
+    t = time.perf_counter()
+    kinds = {kernel(16384 + i, 256, 50257, FWD) for i in range(400)}
+    assert time.perf_counter() - t < 2.0
+    assert kinds <= {axo.AXO_KERNEL_TILES_256, axo.AXO_KERNEL_TILES_256_HALF, axo.AXO_KERNEL_TILES_256_MIXED}
