@@ -76,6 +76,11 @@ int check_matrix(const void* ptr, int64_t ld, int64_t rows, int64_t row_len) {
     return AXO_OK;
 }
 
+// A launch's threads per grid dimension have to stay below 2^32.  Thin outputs of hundreds of millions of rows or
+// columns pass that with the smaller tiles; the choices below then fall through to a kernel that takes them.
+bool grid_fits(int64_t blocks, int threads) { return blocks <= (int64_t)UINT32_MAX / threads; }
+int64_t tiles_in(int n, int size) { return ((int64_t)n + size - 1) / size; }
+
 int launch_generic(const GemmArgs& g, int la, int lb, hipStream_t st) {
     dim3 grid((g.No + axo::GEN_BN - 1) / axo::GEN_BN, (g.Mo + axo::GEN_BM - 1) / axo::GEN_BM, 1);
     dim3 block(256, 1, 1);
@@ -221,7 +226,7 @@ int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* 
 enum class Tiles { small, mid, big };
 Tiles tiles_of(int Mo, int No, int R) {
     const double small_us = small_time(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
-    if (small_us < mid_us && small_us < big_us) return Tiles::small;
+    if (small_us < mid_us && small_us < big_us && grid_fits(tiles_in(Mo, 64) * tiles_in(No, 64), axo::SmallCfg::THREADS)) return Tiles::small;
     return mid_us < big_us ? Tiles::mid : Tiles::big;
 }
 
@@ -281,8 +286,13 @@ double slim_time(const SlimModel& m, int Mo, int No, int R, int pair) {
 }
 int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
 
+// Whether all tiles of one size go into one launch: square split-reduction tiles, 256-row tiles (none wider than half).
+bool slim_fits(const GemmArgs& g, int rows) { return grid_fits(tiles_in(g.Mo, rows) * tiles_in(g.No, rows), axo::SLIM_WAVES * 64); }
+int64_t most_tile_blocks(const GemmArgs& g) { return tiles_in(g.Mo, 256) * tiles_in(g.No, 128); }
+
 // Rows of the small tile (32 or 64) that is quicker for this product.
 int slim_rows(const GemmArgs& g, int pair) {
+    if (!slim_fits(g, 32)) return 64;
     return slim_time(SLIM_MODEL[0], g.Mo, g.No, g.R, pair) <= slim_time(SLIM_MODEL[1], g.Mo, g.No, g.R, pair) ? 32 : 64;
 }
 // Share of the chip's time that a product's 256-row tiles take in a launch that fills it.
@@ -314,9 +324,7 @@ int launch_slim_rows(const GemmArgs& g, hipStream_t st) {
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, &raised)) return AXO_ERR_HIP;
     axo::SlimSched sc{(g.Mo + ROWS - 1) / ROWS, (g.No + ROWS - 1) / ROWS, 0};
     sc.group_m = std::min(sc.tiles_m, 8);  // 8 tile rows share the column panels in an XCD's L2
-    const int64_t blocks = (int64_t)sc.tiles_m * sc.tiles_n;
-    if (blocks > INT32_MAX / C::THREADS) return AXO_ERR_BAD_SIZE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, g, sc);
+    hipLaunchKernelGGL(kern, dim3((unsigned)sc.tiles_m * (unsigned)sc.tiles_n), dim3(C::THREADS), C::LDS_BYTES, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 // Whether a product on 32 x 32 tiles keeps two LDS stages per wave.  Two stages leave room for two workgroups on a
@@ -371,7 +379,7 @@ constexpr int PAIR_BIAS_GRAD = 3;
 // takes two 64 x 64 tiles; their cost in reduction steps of a big tile (1.33 us).
 constexpr int PAIR_SLIM = 4;
 double slim_pair_cost(int R, int pair) { return 2.0 * slim_tile_us(SLIM_MODEL[1], R, pair) / 1.33; }
-int slim_pair_blocks(int Mo, int No) { return ((Mo + 63) / 64 * ((No + 63) / 64) + 1) / 2; }
+int slim_pair_blocks(int Mo, int No) { return (int)((tiles_in(Mo, 64) * tiles_in(No, 64) + 1) / 2); }
 double bias_strip_cost(int rows) { return 1.0 + 15.0 * rows / 4096.0; }
 int bias_strips(int cols) { return (cols + axo::GROUP_BIAS_COLS - 1) / axo::GROUP_BIAS_COLS; }
 // The standalone launch picks its strip width by shape; only shapes for which it picks the
@@ -462,8 +470,9 @@ struct Plan {
     bool nothing_to_do() const { return bias_grad ? bg.Nl == 0 : (g.Mo == 0 || g.No == 0); }
 };
 
-// One launch over the tiles of all given products (each Kernel::tiles, at most
-// GROUP_MAX_PRODUCTS of them).
+// One launch over the tiles of all given units of work: products on 256-row tiles (Kernel::tiles), products on
+// small tiles that ride along (Plan::small), bias gradients; at most GROUP_MAX_PRODUCTS of them, together no more
+// workgroups than a grid holds.
 int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     static std::atomic<uint64_t> raised{0};
     if (!raise_lds_limit(reinterpret_cast<const void*>(axo::gemm_group_kernel), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
@@ -528,7 +537,8 @@ Kernel kernel_of(const GemmArgs& g, int la, int lb) {
     if (g.Mo == 0 || g.No == 0) return Kernel::none;
     // 64-bit addressing, an order of magnitude slower; and what an empty reduction leaves: epilogue(0)
     if (!spans_ok(g, la, lb) || g.R == 0) return Kernel::general;
-    return prefers_slim(g, la, lb) ? Kernel::small_tiles : Kernel::tiles;
+    if (prefers_slim(g, la, lb) && slim_fits(g, 64)) return Kernel::small_tiles;
+    return grid_fits(most_tile_blocks(g), axo::TILE_THREADS) ? Kernel::tiles : Kernel::general;
 }
 
 int launch(const GemmArgs& g, int la, int lb, hipStream_t st) {
@@ -972,7 +982,7 @@ int dependence_levels(const std::vector<Plan>& plans, std::vector<int>* level) {
 }
 
 // One launch over the small tiles of several products (Kernel::small_tiles each, at most
-// SLIM_GROUP_MAX).  Both tile sizes sum in the same order, so the size is the group's to choose.
+// SLIM_GROUP_MAX, together no more tiles than a grid holds).  Both tile sizes sum in the same order, so the size is the group's to choose.
 template <int ROWS>
 int launch_slim_group_rows(const std::vector<const Plan*>& plans, hipStream_t st) {
     using C = axo::SlimCfg<ROWS, ROWS, axo::SLIM_WAVES, 1>;
@@ -991,12 +1001,18 @@ int launch_slim_group_rows(const std::vector<const Plan*>& plans, hipStream_t st
         ga.g[i] = g;
         blocks += (int64_t)ga.sched[i].tiles_m * ga.sched[i].tiles_n;
     }
-    if (blocks > INT32_MAX / C::THREADS) return AXO_ERR_BAD_SIZE;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, ga);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
-    if (plans.size() == 1) return launch_slim(plans[0]->g, plans[0]->la, plans[0]->lb, st);
+    int64_t blocks[2] = {0, 0};
+    for (const Plan* pl : plans)
+        for (int m = 0; m < 2; ++m) blocks[m] += tiles_in(pl->g.Mo, SLIM_MODEL[m].rows) * tiles_in(pl->g.No, SLIM_MODEL[m].rows);
+    if (plans.size() == 1 || !grid_fits(blocks[1], axo::SLIM_WAVES * 64)) {  // one by one, each of which fits
+        int rc = AXO_OK;
+        for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = launch_slim(plans[i]->g, plans[i]->la, plans[i]->lb, st);
+        return rc;
+    }
     std::stable_sort(plans.begin(), plans.end(), [](const Plan* a, const Plan* b) { return a->g.R > b->g.R; });
     double us[2];
     for (int m = 0; m < 2; ++m) {
@@ -1008,7 +1024,7 @@ int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
         }
         us[m] = std::max(busy, chain);
     }
-    return us[0] <= us[1] ? launch_slim_group_rows<32>(plans, st) : launch_slim_group_rows<64>(plans, st);
+    return us[0] <= us[1] && grid_fits(blocks[0], axo::SLIM_WAVES * 64) ? launch_slim_group_rows<32>(plans, st) : launch_slim_group_rows<64>(plans, st);
 }
 
 // Enqueues the products level by level: those of a level that the tiled kernel takes share
@@ -1022,7 +1038,17 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
         small.clear();
     };
     std::vector<const Plan*> riders;  // bias gradients of the level that may share their launch
+    int64_t group_blocks = 0;         // at most so many workgroups in the group so far
+    auto blocks_of = [](const Plan& pl) -> int64_t {
+        return pl.bias_grad ? bias_strips(pl.bg.Nl) : pl.small ? slim_pair_blocks(pl.g.Mo, pl.g.No) : most_tile_blocks(pl.g);
+    };
+    auto joins = [&](const Plan& pl) { return grid_fits(group_blocks + blocks_of(pl), axo::TILE_THREADS); };
+    auto join = [&](const Plan* pl) {
+        group_blocks += blocks_of(*pl);
+        group.push_back(pl);
+    };
     auto flush = [&]() {
+        group_blocks = 0;
         if (group.empty() || rc != AXO_OK) return;
         rc = group.size() == 1 ? launch_tile_layout(group[0]->g, group[0]->la, group[0]->lb, st)
                                : launch_group(group.data(), (int)group.size(), st);
@@ -1030,14 +1056,11 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
     };
     // the last launch of a level takes the level's small products and bias gradients along, as many as fit
     auto flush_level = [&]() {
-        while (!small.empty() && !group.empty() && (int)group.size() < axo::GROUP_MAX_PRODUCTS) {
-            group.push_back(small.back());
-            small.pop_back();
-        }
-        while (!riders.empty() && !group.empty() && (int)group.size() < axo::GROUP_MAX_PRODUCTS) {
-            group.push_back(riders.back());
-            riders.pop_back();
-        }
+        for (std::vector<const Plan*>* list : {&small, &riders})
+            while (!list->empty() && !group.empty() && (int)group.size() < axo::GROUP_MAX_PRODUCTS && joins(*list->back())) {
+                join(list->back());
+                list->pop_back();
+            }
         flush();
         flush_small();
         for (size_t k = 0; k < riders.size() && rc == AXO_OK; ++k) rc = launch_bias_grad(riders[k]->bg, st);
@@ -1063,7 +1086,8 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
                 rc = launch(pl.g, pl.la, pl.lb, st);
                 continue;
             }
-            group.push_back(&pl);
+            if (!group.empty() && !joins(pl)) flush();
+            join(&pl);
             if ((int)group.size() == axo::GROUP_MAX_PRODUCTS) flush();
         }
         flush_level();
