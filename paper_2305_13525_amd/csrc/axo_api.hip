@@ -716,9 +716,9 @@ BiasSplit plan_bias_split(int64_t M, int64_t Nl) {
 // of one workgroup 0.5 us.  Measured with the plan's own count / with this one: 7296 x 512 8.6 us (29 slices) / 6.0,
 // 4096 x 1536 8.1 (16) / 5.2, 16384 x 256 7.5 (32) / 6.1, 1000 x 1000 5.3 (7) / 4.2, 300 x 300 4.6 (2) / 3.5.
 BiasSplit launch_slices(BiasSplit b, int M) {
-    const int want = M <= 1536 ? 1 : (M + 1023) / 1024;
+    const int64_t want = M <= 1536 ? 1 : ((int64_t)M + 1023) / 1024;
     if (want >= b.S) return b;
-    b.rows_per_slice = (int)((((int64_t)M + want - 1) / want + axo::BGS_ROW_LANES - 1) / axo::BGS_ROW_LANES * axo::BGS_ROW_LANES);
+    b.rows_per_slice = (int)(((M + want - 1) / want + axo::BGS_ROW_LANES - 1) / axo::BGS_ROW_LANES * axo::BGS_ROW_LANES);
     b.S = M > 0 ? (int)(((int64_t)M + b.rows_per_slice - 1) / b.rows_per_slice) : 1;
     return b;
 }

@@ -60,9 +60,12 @@ __device__ __forceinline__ void bias_grad_strip(const BiasGradArgs& g, int strip
         if (valid > 0) {
             // a part-filled last chunk reads on into the row pitch, in every row but the matrix's last
             const int row_end = valid >= 8 ? g.M : g.M - 1;
+            // rows are counted, not compared with the end: a row index plus LANES may pass 2^31
+            const int rows = r0 < row_end ? (int)(((uint32_t)(row_end - r0) + LANES - 1) / LANES) : 0;
 #pragma unroll 4
-            for (int t = r0; t < row_end; t += LANES) {
-                const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(g.dY + (int64_t)t * g.lddy + col));
+            for (int k = 0; k < rows; ++k) {
+                const int64_t t = r0 + (int64_t)k * LANES;
+                const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(g.dY + t * g.lddy + col));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     s[f][2 * i] += __uint_as_float(w[i] << 16);
@@ -141,15 +144,16 @@ __global__ void __launch_bounds__(BGS_THREADS) bias_grad_split_kernel(BiasGradSp
     const int cx = lane & 7, ry = wave * 8 + (lane >> 3);
     const int col = strip * BGS_COLS + cx * 8;
     const int valid = g.Nl - col;  // columns of this thread's chunk inside the matrix (may be <= 0 or >= 8)
-    const int row_end = min(g.M, (slice + 1) * g.rows_per_slice);
+    // unsigned: the rounded-up end of the last slice, and a row index plus a batch, may pass 2^31
+    const uint32_t row_end = min((uint32_t)g.M, (slice + 1u) * (uint32_t)g.rows_per_slice);
     float s[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] = 0.f;
     if (valid > 0) {
         // a part-filled last chunk reads on into the row pitch, in every row but the matrix's last
-        const int end = valid >= 8 ? row_end : min(row_end, g.M - 1);
+        const uint32_t end = valid >= 8 ? row_end : min(row_end, (uint32_t)max(g.M - 1, 0));
         const bf16_t* base = g.dY + col;
-        int t = slice * g.rows_per_slice + ry;
+        uint32_t t = (uint32_t)slice * (uint32_t)g.rows_per_slice + ry;
         for (; t + 7 * BGS_ROW_LANES < end; t += 8 * BGS_ROW_LANES) {  // eight loads in flight
             u32x4 w[8];
 #pragma unroll

@@ -58,3 +58,24 @@ def test_shapes_that_share_scratch_in_any_order(form):
         axo.axo_bias_grad_ws(*args, ws.data_ptr(), nws, gu.stream()) if form == "ws" else axo.axo_bias_grad_static(*args, gu.stream())
         assert torch.equal(db, dY[:, :N].float().sum(0)), (k, M, N)
     assert not ws[:1024].any()
+
+
+@pytest.mark.parametrize("N", [5, 8])
+def test_as_many_rows_as_a_shard_may_have(N):
+    """2^31 - 1 rows: the end of the last slice, rounded up, and a row index plus the rows of a batch pass 2^31.  Nonzero
+    rows at both ends of the matrix and of the last slices; all sums are exact."""
+    M = 2 ** 31 - 1
+    dY = torch.zeros((M, 8), dtype=torch.bfloat16, device="cuda:0")
+    marked = {0: 1, 2 ** 30: 2, M - 2 ** 26: 4, M - 1025: 8, M - 64: 16, M - 2: 32, M - 1: 64}
+    for row, v in marked.items():
+        dY[row] = torch.arange(1, 9, device="cuda:0") * v
+    want = torch.arange(1, N + 1, device="cuda:0").float() * sum(marked.values())
+    p = axo.Problem.make((1, 1, 1), (0, 0, 0), M, 8, N)
+    nws = axo.axo_bias_grad_workspace_bytes(p)
+    ws = torch.zeros(nws, dtype=torch.uint8, device="cuda:0")
+    db = torch.zeros((3, N), device="cuda:0")
+    axo.axo_bias_grad(p, dY.data_ptr(), 8, db[0].data_ptr(), 0, gu.stream())
+    axo.axo_bias_grad_ws(p, dY.data_ptr(), 8, db[1].data_ptr(), 0, ws.data_ptr(), nws, gu.stream())
+    axo.axo_bias_grad_static(p, dY.data_ptr(), 8, db[2].data_ptr(), 0, gu.stream())
+    torch.cuda.synchronize()
+    assert torch.equal(db, want.expand(3, N)), db
