@@ -47,5 +47,5 @@ def test_a_new_batch_length_costs_no_new_plan():
 def test_a_half_filled_last_column_takes_half_width_tiles():
     """Where 256 x 256 tiles over the edge and 256 x 128 tiles inside it end together, the plan with less work."""
     assert kernel(2176, 5504, 16384, DG) == axo.AXO_KERNEL_TILES_256_MIXED     # 9 x 21.5 tiles: 385 us over the edge, 323 inside
-    assert kernel(7552, 1152, 9984, FWD) == axo.AXO_KERNEL_TILES_256_MIXED     # 29.5 x 4.5: 213 and 182
+    assert kernel(7552, 9984, 1152, FWD) == axo.AXO_KERNEL_TILES_256_MIXED     # 29.5 x 4.5: 213 and 182
     assert kernel(2176, 5632, 16384, DG) == axo.AXO_KERNEL_TILES_256           # 9 x 22: nothing to halve
