@@ -234,6 +234,17 @@ Tiles tiles_of(int Mo, int No, int R) {
     return mid_us < big_us ? Tiles::mid : Tiles::big;
 }
 
+// Units of the start-up phase shift of a launch on 256-row tiles (see start_shift): short reductions over more
+// than one round of tiles.  Without / with 3 units: 4864 x 12288, reduction 128, 36.8 / 29.7 us; 8192 x 12416 x 256 77.8 / 66.2;
+// 4352 x 8704 x 128 24.0 / 21.1; medians of 1200 sizes at two rounds or more 1.12 times quicker up to 4 steps, 1.06 up to 12, 1.03 up
+// to 24, none beyond.  Between one round and two 2 units are the better choice (1.02 up to 16 steps).  Launches of at most one round
+// lose by it (0.7 up to 6 steps, 0.86 at 24).
+int shift_units(int Mo, int No, int R) {
+    const int64_t tiles = tiles_in(Mo, 256) * tiles_in(No, 256), steps = tiles_in(R, axo::TILE_BK);
+    if (tiles > 2 * NUM_CU) return steps <= 24 ? 3 : 0;
+    return tiles > NUM_CU && steps <= 16 ? 2 : 0;
+}
+
 // Launch of one product on those tiles.
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
@@ -249,7 +260,8 @@ int launch_tile(const GemmArgs& g, hipStream_t st) {
     auto kern = axo::gemm_mixed_kernel<LA, LB>;
     static std::atomic<uint64_t> raised{0};
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
-    const axo::TileSched sc = plan_tiles(g.Mo, g.No);
+    axo::TileSched sc = plan_tiles(g.Mo, g.No);
+    sc.shift = shift_units(g.Mo, g.No, g.R);
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), axo::MIX_LDS_BYTES, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;

@@ -90,7 +90,22 @@ struct TileSched {
     int small_cols;  // tile columns of the 128-wide region
     int n_big;       // = tiles_m * big_cols
     int group_m;     // band height of the tile order
+    int shift;       // start_shift() units, 0 = none
 };
+
+// Start-up phase shift.  Tiles of equal length that start together end together, and then all CUs write their
+// outputs in one burst, which the memory side takes microseconds to absorb while nothing computes.  The first workgroup on
+// every CU (ids below 256) therefore sleeps phase * units * 640 cycles before it starts, phase = 0..7 dealt round-robin over
+// the CUs of each XCD; later workgroups start whenever their CU falls free, so the shift persists through the launch.
+// What it costs is a late start of up to 7 units, so it pays only where a tile is short and the launch has several
+// rounds of them; the host decides (shift_units).
+constexpr int SHIFT_PHASES = 8;
+__device__ __forceinline__ void start_shift(int bid, int units) {
+    if (units > 0 && bid < 256) {
+        const int n = ((bid >> 3) % SHIFT_PHASES) * units;
+        for (int i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(10);
+    }
+}
 
 // Workgroup -> output tile.  Consecutive workgroup ids go round-robin to the 8 XCDs, each with
 // its own L2, so the ids that land on one XCD are given one contiguous run of tiles, and tiles
@@ -881,6 +896,7 @@ template <int LA, int LB>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g, TileSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
+    start_shift(bid, sc.shift);
     int tm, tn;
     if (bid < sc.n_big) {
         tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
