@@ -49,3 +49,10 @@ def test_a_half_filled_last_column_takes_half_width_tiles():
     assert kernel(2176, 5504, 16384, DG) == axo.AXO_KERNEL_TILES_256_MIXED     # 9 x 21.5 tiles: 385 us over the edge, 323 inside
     assert kernel(7552, 9984, 1152, FWD) == axo.AXO_KERNEL_TILES_256_MIXED     # 29.5 x 4.5: 213 and 182
     assert kernel(2176, 5632, 16384, DG) == axo.AXO_KERNEL_TILES_256           # 9 x 22: nothing to halve
+
+
+def test_short_data_gradients_into_straddled_rows_take_half_width_tiles():
+    """More tiles than CUs, a reduction of at most four steps, rows that do not end on cache lines."""
+    assert kernel(10600, 7736, 48, DG) == axo.AXO_KERNEL_TILES_256_HALF     # 101 us on 256 x 256 tiles, 74 on these
+    assert kernel(7128, 10360, 152, DG) == axo.AXO_KERNEL_TILES_256_HALF    # 99 and 77
+    assert kernel(10624, 7744, 512, DG) == axo.AXO_KERNEL_TILES_256         # whole lines, eight steps
