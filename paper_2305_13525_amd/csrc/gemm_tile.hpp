@@ -660,17 +660,26 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     // elements 8 * that onwards).  `rem` = reduction elements of the stage that are real.
     auto zero_tail = [&](auto s_tag, const int rem) __attribute__((always_inline)) {
         constexpr int s = decltype(s_tag)::value;
-        auto clear = [&](char* base, const int rounds) __attribute__((always_inline)) {
+        auto clear = [&](auto part_tag, char* base, const int rounds) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < rounds; ++j) {
                 const int q = j * C::THREADS + tid, r = q >> 3, cs = q & 7;
                 const int left = rem - ((cs ^ swz_kc(r)) << 3);
                 u32x4* const p = reinterpret_cast<u32x4*>(base + q * 16);
-                if (left < 8) *p = first_elements(left > 0 ? *p : u32x4{0u, 0u, 0u, 0u}, left);
+                if (!decltype(part_tag)::value) {
+                    if (left <= 0) *p = u32x4{0u, 0u, 0u, 0u};
+                } else if (left < 8) *p = first_elements(left > 0 ? *p : u32x4{0u, 0u, 0u, 0u}, left);
             }
         };
-        if (LA == KC) clear(smem + s * C::A_BYTES, C::A_ROUNDS);
-        if (LB == KC) clear(smem + 2 * C::A_BYTES + s * C::B_BYTES, C::B_ROUNDS);
+        auto clear_both = [&](auto part_tag) __attribute__((always_inline)) {
+            if (LA == KC) clear(part_tag, smem + s * C::A_BYTES, C::A_ROUNDS);
+            if (LB == KC) clear(part_tag, smem + 2 * C::A_BYTES + s * C::B_BYTES, C::B_ROUNDS);
+        };
+        // Only a length that is no multiple of 8 ends inside a chunk.  The others do without the code that may read
+        // one back: dgrad 8272 x 6328, reduction 712, 125 us with it, 119 without; 9864 x 2568 x 336 45.7 and 42.8; forward
+        // 4000 x 6000, reduction 2000, 93.7 and 90.6.
+        if (g.R % 8 == 0) clear_both(IC<0>{});
+        else clear_both(IC<1>{});
     };
     // `fix` (first of the two tail steps only): stage s^1 holds the last step, which has just
     // landed; its chunks beyond the end of the reduction are zeroed before the barrier publishes it.
