@@ -7,7 +7,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 #include <cstdlib>
 #include <functional>
 #include <map>
@@ -195,24 +194,39 @@ bool raise_lds_limit(const void* kernel, int bytes, std::atomic<uint64_t>* raise
     return true;
 }
 
-// Estimated kernel time in microseconds of a product on its own, from its sizes alone.  256-row tiles: rounds of
-// 256 x 256 tiles or of half-width ones, 1.33 us per reduction step.  128 x 128 tiles: 0.42 us per step.
+int64_t steps_in(int R) { return tiles_in(R, axo::TILE_BK); }
+int64_t rounds_of(int64_t tiles) { return (tiles + NUM_CU - 1) / NUM_CU; }
+
+// Estimated kernel time in microseconds of a product on its own, from its sizes alone.
+// 256-row tiles: half-width tiles where they have a CU each, else large ones, else rounds of either.  A reduction step of a
+// large tile takes 1.0 us on a chip that is nearly idle and 1.27 on a full one, which runs at its power limit.  Fitted to 3400
+// measured products; half of the estimates are within 11 %, nine of ten within 25 %.  (With 1.33 us at any load, few tiles with
+// long reductions were taken for slower than they are, and 64 x 64 tiles chosen instead: wgrad 1616 x 2960 of 8136
+// tokens 181 us, 87 on these; 1536 x 3072 of 6016 98 and 61; dgrad 2408 x 3264 with reduction 9288 357 and 266.)
 double tile_time(int Mo, int No, int R) {
-    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
-    const double big = std::ceil(tm * ((No + 255) / 256) / NUM_CU), half = std::ceil(tm * ((No + 127) / 128) / NUM_CU) * SMALL_TILE_COST;
-    return 2.0 + std::min(big, half) * steps * 1.33;
+    const int64_t tm = tiles_in(Mo, 256), big = tm * tiles_in(No, 256), half = tm * tiles_in(No, 128);
+    const double rounds = half <= NUM_CU ? SMALL_TILE_COST : std::min((double)rounds_of(big), SMALL_TILE_COST * rounds_of(half));
+    const double busy = std::min<int64_t>(half <= NUM_CU ? half : big, NUM_CU) / (double)NUM_CU;
+    return 3.4 + rounds * (steps_in(R) + 4.4) * (1.0 + 0.27 * busy * busy);
 }
+// 128 x 128 tiles, 0.42 us per step.
 double mid_time(int Mo, int No, int R) {
-    if ((double)((Mo + 127) / 128) * ((No + 127) / 128) > NUM_CU) return 1e30;  // more than one tile per CU: see below
-    return 4.5 + (R + axo::TILE_BK - 1) / axo::TILE_BK * 0.42;
+    if (tiles_in(Mo, 128) * tiles_in(No, 128) > NUM_CU) return 1e30;  // more than one tile per CU: see below
+    return 4.5 + steps_in(R) * 0.42;
 }
 
 // 64 x 64 tiles of a ring: a step takes 0.235 us with a CU to itself, and 0.15 us on a busy one, where two run beside
 // each other (2048 x 1024 x 1024 forward: 9.4 us measured, 9.5 estimated; wgrad 1024 x 1024 of 8192 tokens: 30 and 33).
 double small_time(int Mo, int No, int R) {
-    const double steps = (R + axo::TILE_BK - 1) / axo::TILE_BK;
-    const double n = std::ceil((double)((Mo + 63) / 64) * ((No + 63) / 64) / NUM_CU);
-    return n <= 1.0 ? 3.2 + steps * 0.235 : 3.0 + n * (0.85 + steps * 0.15);
+    const int64_t n = rounds_of(tiles_in(Mo, 64) * tiles_in(No, 64));
+    return n <= 1 ? 3.2 + steps_in(R) * 0.235 : 3.0 + n * (0.85 + steps_in(R) * 0.15);
+}
+// What several rounds of them lose beyond 32 steps, where the operands leave the L2 (1408 x 11008 x 7296 dgrad: 427 us measured,
+// 272 without this part).  Counts against the larger tiles only, not where split reductions are weighed against these
+// tiles: there the two kinds slow down alike.
+double small_time_long(int Mo, int No, int R) {
+    const int64_t n = rounds_of(tiles_in(Mo, 64) * tiles_in(No, 64)), late = steps_in(R) - 32;
+    return n <= 1 || late <= 0 ? 0.0 : n * late * 0.05;
 }
 
 // Launch of one product on square tiles of `ROWS` rows.
@@ -229,7 +243,7 @@ int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* 
 // traffic (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
 enum class Tiles { small, mid, big };
 Tiles tiles_of(int Mo, int No, int R) {
-    const double small_us = small_time(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
+    const double small_us = small_time(Mo, No, R) + small_time_long(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
     if (small_us < mid_us && small_us < big_us && grid_fits(tiles_in(Mo, 64) * tiles_in(No, 64), axo::SmallCfg::THREADS)) return Tiles::small;
     return mid_us < big_us ? Tiles::mid : Tiles::big;
 }
@@ -308,18 +322,16 @@ struct SlimModel {
     double rate[3];    // KB per us of a busy CU, by layout pair
 };
 constexpr SlimModel SLIM_MODEL[2] = {{32, 5, 0.2, 0.24, {80.0, 106.0, 60.0}}, {64, 2, 1.5, 0.47, {112.0, 115.0, 95.0}}};
-double slim_tiles(const SlimModel& m, int Mo, int No) { return (double)((Mo + m.rows - 1) / m.rows) * ((No + m.rows - 1) / m.rows); }
+int64_t slim_tiles(const SlimModel& m, int Mo, int No) { return m.rows == 32 ? tiles_in(Mo, 32) * tiles_in(No, 32) : tiles_in(Mo, 64) * tiles_in(No, 64); }
 double slim_tile_us(const SlimModel& m, int R, int pair) {  // one tile on a busy CU
-    const double chunks = (R + axo::TILE_BK - 1) / axo::TILE_BK;
-    return chunks * (2.0 * m.rows * axo::TILE_BK * 2 / 1024.0) / m.rate[pair] + m.fixed;
+    return steps_in(R) * (2.0 * m.rows * axo::TILE_BK * 2 / 1024.0) / m.rate[pair] + m.fixed;
 }
 double slim_chain_us(const SlimModel& m, int R) {  // one tile on a CU of its own
-    return 0.7 + std::ceil(std::ceil((double)R / axo::TILE_BK) / axo::SLIM_WAVES) * m.chunk_us;
+    return 0.7 + tiles_in(R, axo::SLIM_WAVES * axo::TILE_BK) * m.chunk_us;
 }
 double slim_time(const SlimModel& m, int Mo, int No, int R, int pair) {
-    const double tiles = slim_tiles(m, Mo, No);
-    return 2.5 + std::max(std::ceil(tiles / NUM_CU) * slim_tile_us(m, R, pair),
-                          std::ceil(tiles / (NUM_CU * m.slots)) * slim_chain_us(m, R));
+    const int64_t rounds = rounds_of(slim_tiles(m, Mo, No));
+    return 2.5 + std::max(rounds * slim_tile_us(m, R, pair), (rounds + m.slots - 1) / m.slots * slim_chain_us(m, R));
 }
 int layout_pair(int la, int lb) { return (la == axo::KC && lb == axo::MC) ? 0 : (la == axo::KC ? 1 : 2); }
 
@@ -334,8 +346,7 @@ int slim_rows(const GemmArgs& g, int pair) {
 }
 // Share of the chip's time that a product's 256-row tiles take in a launch that fills it.
 double tile_share(int Mo, int No, int R) {
-    const double tm = (Mo + 255) / 256, steps = (R + axo::TILE_BK - 1) / axo::TILE_BK + 4.0;
-    return tm * std::min((No + 255) / 256 * 1.0, (No + 127) / 128 * SMALL_TILE_COST) * steps * 1.33 / NUM_CU;
+    return tiles_in(Mo, 256) * std::min(tiles_in(No, 256) * 1.0, tiles_in(No, 128) * SMALL_TILE_COST) * (steps_in(R) + 4.0) * 1.33 / NUM_CU;
 }
 // Whether a product runs on tiles whose waves split the reduction: where those are estimated at least 15 % quicker than
 // the others, and where a chain's grouped launch, in which the larger tiles of other products keep the chip
@@ -347,7 +358,7 @@ bool prefers_slim(const GemmArgs& g, int la, int lb) {
     double us = 1e30, share = 1e30;
     for (const SlimModel& m : SLIM_MODEL) {
         us = std::min(us, slim_time(m, g.Mo, g.No, g.R, pair));
-        share = std::min(share, slim_tiles(m, g.Mo, g.No) / NUM_CU * slim_tile_us(m, g.R, pair));
+        share = std::min(share, slim_tiles(m, g.Mo, g.No) * slim_tile_us(m, g.R, pair) / NUM_CU);
     }
     return us < 0.85 * std::min({tile_time(g.Mo, g.No, g.R), mid_time(g.Mo, g.No, g.R), small_time(g.Mo, g.No, g.R)}) &&
            share < 1.3 * tile_share(g.Mo, g.No, g.R) + 1.0;
@@ -1056,7 +1067,7 @@ int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
         double busy = 0.0, chain = 0.0;
         for (const Plan* pl : plans) {
             const double tile = slim_tile_us(SLIM_MODEL[m], pl->g.R, layout_pair(pl->la, pl->lb));
-            busy += slim_tiles(SLIM_MODEL[m], pl->g.Mo, pl->g.No) / NUM_CU * tile;
+            busy += slim_tiles(SLIM_MODEL[m], pl->g.Mo, pl->g.No) * tile / NUM_CU;
             chain = std::max(chain, slim_chain_us(SLIM_MODEL[m], pl->g.R));
         }
         us[m] = std::max(busy, chain);

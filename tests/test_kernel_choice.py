@@ -56,3 +56,15 @@ def test_short_data_gradients_into_straddled_rows_take_half_width_tiles():
     assert kernel(10600, 7736, 48, DG) == axo.AXO_KERNEL_TILES_256_HALF     # 101 us on 256 x 256 tiles, 74 on these
     assert kernel(7128, 10360, 152, DG) == axo.AXO_KERNEL_TILES_256_HALF    # 99 and 77
     assert kernel(10624, 7744, 48, DG) != axo.AXO_KERNEL_TILES_256_HALF     # whole lines
+
+
+def test_long_reductions_on_few_large_tiles_stay_on_them():
+    """Outputs of some hundred half-width tiles with long reductions, measured on 64 x 64 tiles and on 256-row ones."""
+    big = (axo.AXO_KERNEL_TILES_256, axo.AXO_KERNEL_TILES_256_HALF, axo.AXO_KERNEL_TILES_256_MIXED)
+    assert kernel(8136, 1616, 2960, WG) in big       # 181 and 87 us
+    assert kernel(6016, 1536, 3072, WG) in big       # 98 and 61
+    assert kernel(2376, 5032, 1976, FWD) in big      # 109 and 67
+    assert kernel(2408, 3264, 9288, DG) in big       # 357 and 266
+    assert kernel(1176, 6592, 3872, DG) in big       # 111 and 79
+    assert kernel(1408, 11008, 7296, DG) in big      # 427 and 259
+    assert kernel(6320, 5648, 104, WG) == axo.AXO_KERNEL_TILES_64       # 89 x 2 of those tiles: 32 and 81
