@@ -865,7 +865,11 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
 #pragma unroll
         for (int s = 0; s < D; ++s)
             if (s < n0) issue(IC<0>{}, IC<NL>{}, s);
+        // The first step waits for its own stage only, also where the whole reduction is requested at once (waiting for
+        // all of it made two-step products of up to 256 half-width tiles 2 % slower).
         if (KT >= D) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * NL) : "memory");
+        else if (D > 3 && KT == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        else if (D > 2 && KT == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
