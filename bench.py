@@ -41,14 +41,14 @@ PEAK_HBM_GBPS = 8000.0
 # per WRITE_SIZE count.  Keyed by (workload, product); "group" is the single launch of the grouped step.
 FETCH_KIB_PER_COUNT, WRITE_KIB_PER_COUNT = 2.0, 1.0
 MEASURED_TRAFFIC_COUNTS = {
-    ("cfg2", "group"): (304881.7, 90117.6), ("cfg2", "fwd"): (82089.3, 49152.0),
-    ("cfg2", "dgrad"): (98376.9, 16385.4), ("cfg2", "wgrad"): (82012.0, 24585.7),
-    ("cfg3", "group"): (782891.4, 213002.6), ("cfg3", "fwd"): (196822.5, 131105.4),
-    ("cfg3", "dgrad"): (269250.1, 16394.7), ("cfg3", "wgrad"): (196700.0, 65536.4),
-    ("cfg4", "group"): (782160.2, 213008.2), ("cfg4", "fwd"): (272950.8, 16386.0),
-    ("cfg4", "dgrad"): (196708.5, 131092.2), ("cfg4", "wgrad"): (196700.0, 65536.2),
-    ("cfg5", "group"): (1087142.1, 251960.1), ("cfg5", "fwd"): (61667.2, 49152.0),
-    ("cfg5", "dgrad"): (86080.5, 12288.0), ("cfg5", "wgrad"): (83036.0, 18440.0),
+    ("cfg2", "group"): (305072.1, 90116.5), ("cfg2", "fwd"): (82102.0, 49167.7),
+    ("cfg2", "dgrad"): (98399.5, 16384.8), ("cfg2", "wgrad"): (82024.5, 24583.5),
+    ("cfg3", "group"): (783234.2, 212998.4), ("cfg3", "fwd"): (196831.2, 131213.9),
+    ("cfg3", "dgrad"): (266811.4, 16384.2), ("cfg3", "wgrad"): (196712.5, 65689.1),
+    ("cfg4", "group"): (783295.0, 213002.3), ("cfg4", "fwd"): (262393.2, 16384.0),
+    ("cfg4", "dgrad"): (196714.0, 131260.6), ("cfg4", "wgrad"): (196712.5, 65582.2),
+    ("cfg5", "group"): (1055678.8, 251929.4), ("cfg5", "fwd"): (61679.4, 49162.2),
+    ("cfg5", "dgrad"): (86111.5, 12288.7), ("cfg5", "wgrad"): (83048.5, 18441.4),
 }
 MEASURED_TRAFFIC_BYTES = {k: int((f * FETCH_KIB_PER_COUNT + w * WRITE_KIB_PER_COUNT) * 1024)
                           for k, (f, w) in MEASURED_TRAFFIC_COUNTS.items()}
