@@ -251,11 +251,11 @@ Tiles tiles_of(int Mo, int No, int R) {
 // Units of the start-up phase shift of a launch on 256-row tiles (see start_shift): short reductions over more
 // than one round of tiles.  Without / with 3 units: 4864 x 12288, reduction 128, 36.8 / 29.7 us; 8192 x 12416 x 256 77.8 / 66.2;
 // 4352 x 8704 x 128 24.0 / 21.1; medians of 1200 sizes at two rounds or more 1.12 times quicker up to 4 steps, 1.06 up to 12, 1.03 up
-// to 24, none beyond.  Between one round and two 2 units are the better choice (1.02 up to 16 steps).  Launches of at most one round
+// to 24, 1.02 up to 32 (4096 x 16384 x 2048 200 / 195.5), none beyond.  Between one round and two 2 units are the better choice (1.02 up to 16 steps).  Launches of at most one round
 // lose by it (0.7 up to 6 steps, 0.86 at 24).
 int shift_units(int Mo, int No, int R) {
     const int64_t tiles = tiles_in(Mo, 256) * tiles_in(No, 256), steps = tiles_in(R, axo::TILE_BK);
-    if (tiles > 2 * NUM_CU) return steps <= 24 ? 3 : 0;
+    if (tiles > 2 * NUM_CU) return steps <= 32 ? 3 : 0;
     return tiles > NUM_CU && steps <= 16 ? 2 : 0;
 }
 
@@ -729,10 +729,10 @@ int launch_bias_grad(const axo::BiasGradArgs& g, hipStream_t st) {
 }
 
 // ---- bias gradient with the rows split over workgroups (needs scratch memory) ----------------
-// How a shape is cut: 64-column strips, each cut into S row slices of a multiple of 64 rows so that
-// about BIAS_SPLIT_WORKGROUPS workgroups are in flight, no slice below 128 rows.  A function of the
-// shape alone, so the summation order (and with it every bit of the result) is too.  Measured on
-// 4096 rows (time per call in a loop, launch included; 6144 / 16384 / 1536 columns): 128
+// How a shape is cut at most, and what its workspace is sized for: 64-column strips, each cut into S row slices
+// of a multiple of 64 rows so that about BIAS_SPLIT_WORKGROUPS workgroups are in flight, no slice below 128 rows.  A
+// launch uses launch_slices() of them, up to eight times fewer.  Both are functions of the shape alone, so the
+// summation order (and with it every bit of the result) is too.  Measured on 4096 rows (time per call in a loop, launch included; 6144 / 16384 / 1536 columns): 128
 // workgroups 14.6 / 25.0 / 9.0 us, 256: 12.6 / 22.0 / 8.4, 384: 11.6 / 22.4 / 10.5, 512: 11.6 / 22.2 /
 // 10.6, 1024: 15.2 / 27.4 / 17.1 (every slice costs a publication and a share of the final
 // addition); the strips of axo_bias_grad: 15.6 / 24.6 / 14.7.
