@@ -222,7 +222,8 @@ size_t axo_bias_grad_workspace_bytes(const axo_problem_t *p);
 
 /* The bias gradient of axo_bias_grad, with the rows of dY split over several workgroups per
  * 64-column strip: a 6144-column shard gives axo_bias_grad 96 workgroups for 256 compute units, which
- * leaves it bound by memory latency; this form keeps about four workgroups per unit in flight.  Every
+ * leaves it bound by memory latency; this form cuts each strip's rows into at most one slice per 1024 rows
+ * (a single one up to 1536 rows).  The workspace is sized for more slices than that.  Every
  * workgroup writes the fp32 sums of its row slice to the workspace, and the one that finishes last
  * adds the slices of its strip in ascending order: no floating-point atomics, so the result is a fixed
  * function of the input (equal from run to run; it differs from axo_bias_grad's in the last bits,
@@ -291,8 +292,9 @@ size_t axo_layer_step_workspace_bytes(const axo_layer_t *layers, int n_layers);
  * side and the level pays one ramp-up and one tail instead of one per product.  A chain whose
  * layers have buffers of their own is a single level; a layer whose X is the previous layer's Y,
  * or whose dX is the previous layer's dY, lands on the next level; dgrad and wgrad of a layer
- * always share a level.  Results are the same, bit for bit, whatever the grouping (every output
- * element is accumulated in the same order in every tile shape).  Two column blocks interleaved
+ * always share a level.  Results are the same, bit for bit, whatever the grouping: which products split
+ * their reduction over waves is a function of their shape, and within either class every output element is
+ * accumulated in the same order in every tile shape.  Two column blocks interleaved
  * in one buffer count as overlapping, which only costs concurrency.  Chains of more than 256
  * layers are not analysed and keep the program order, one product per launch.
  * All layers are validated before the first launch; on a validation error nothing is enqueued. */

@@ -104,8 +104,8 @@ __global__ void __launch_bounds__(BG_THREADS) bias_grad_kernel(BiasGradArgs g) {
 // ---- bias gradient with the rows split over workgroups ------------------------------------------
 // The strip kernel above gives a 6144-column shard 96 workgroups for 256 CUs and is bound by memory
 // latency (a third of the HBM rate).  Here a strip's rows are cut into S slices, one workgroup each
-// (S chosen by the host from the shape alone, for a few hundred workgroups in all; plain loads:
-// non-temporal ones were measured 5-10 % slower here);
+// (S chosen by the host from the shape alone, one per 1024 rows at most; plain loads: non-temporal ones were
+// measured 5-10 % slower here);
 // a workgroup writes the fp32 sums of its slice to scratch memory [S x Nl], counts itself in on
 // its strip's arrival counter, and the workgroup that arrives last adds the S slices of the strip
 // in ascending slice order and writes db.  Which workgroup does that addition depends on timing,
@@ -114,7 +114,8 @@ __global__ void __launch_bounds__(BG_THREADS) bias_grad_kernel(BiasGradArgs g) {
 //
 // Scratch: `counters` (one uint32 per strip) must be zero when the kernel starts; the last
 // workgroup of every strip sets its counter back to zero, so the kernel leaves them as it found
-// them, and the same holds for all bytes where another shape's counters may lie.  `partial` needs no initialisation.  Launches that share scratch memory must not overlap.
+// them, and the same holds for all bytes where another shape's counters may lie.  `partial` needs no
+// initialisation.  Launches that share scratch memory must not overlap.
 //
 // A 512-thread workgroup is 8 column lanes (16 bytes = 8 columns each: one 128-byte line per row)
 // by 64 row lanes; a thread's rows are 64 apart, their loads are issued eight at a time, summed in

@@ -347,7 +347,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     // registers, so no branch has a version of its own to merge afterwards.  (An earlier form
     // computed the origin behind a three-way switch; the generated code of one dgrad branch then
     // lacked the upper half of the 64-bit column offset and the stores went astray.  Positional,
-    // bit-exact tests of every epilogue kind on both tile sizes guard this.)
+    // bit-exact tests of the dgrad epilogues on every tile kernel, which they ask for by name, guard this.)
     int wrow0 = i0 + wm * C::WTM, wcol0 = j0 + wn * C::WTN;
     asm volatile("" : "+s"(wrow0), "+s"(wcol0));
     bf16_t* const Cw = g.C + (int64_t)wrow0 * g.ldc + wcol0;

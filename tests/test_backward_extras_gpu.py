@@ -1,6 +1,8 @@
 """GPU parity of the backward-side extras against the fp64 oracle: dgrad with the GELU derivative
 fused in, wgrad accumulated into an fp32 matrix, and the bias gradient.  Same tolerances as the
-products for the bf16 output; the fp32 outputs are held to fp32 summation error."""
+products for the bf16 output; the fp32 outputs are held to fp32 summation error.  Called alone, these sizes run
+on small tiles whatever the remarks beside them say of tiles; the same operations on each tile kernel, asked for by
+name, are in test_kernel_variants_gpu.py."""
 import numpy as np
 import pytest
 

@@ -1,7 +1,12 @@
 """GPU parity: the HIP path, called through the C ABI, against the fp64 CPU oracle on the same
 seeded bf16 inputs.  Tolerances: relative Frobenius error <= 2e-3 and every element within
 1e-2 of its oracle row's infinity norm (gpu_util.REL_FRO_TOL / PER_ELEM_TOL).  Structured
-inputs whose products are exactly representable must match bit for bit."""
+inputs whose products are exactly representable must match bit for bit.
+
+Most sizes here are small, and called alone the library runs them on small tiles, also where a docstring below speaks
+of the tuned kernel, of whole tiles or of covered outputs (in a chain they do run on 256-row tiles).  What these tests
+ask of the results holds on any kernel; the same properties on each kernel, asked for by name (special values at the
+end of a reduction, tails, offsets above 2^31, epilogues, positions), are in test_kernel_variants_gpu.py."""
 import numpy as np
 import pytest
 
@@ -79,15 +84,15 @@ def test_cfg1_grid222_all_shards_and_decomposition_identity():
 
 RAGGED = [(1, 8, 8), (1000, 520, 264), (130, 40, 72), (257, 264, 136), (77, 1000, 48), (45, 100, 52),
           (129, 33, 127), (5, 7, 3), (256, 64, 256), (300, 1, 9), (128, 128, 128), (384, 96, 640),
-          # outputs that miss the tuned kernel's granularity while the reduction fits it: the library
-          # cuts these into a tuned interior and general-kernel strips (fwd; dgrad; wgrad; one strip only)
+          # outputs that miss the granularity of the 256-row tiles (at these sizes small tiles run them; those on
+          # larger tiles: test_kernel_variants_gpu.py)
           (300, 128, 136), (520, 384, 264), (520, 264, 384), (384, 264, 136), (256, 128, 200), (260, 128, 128),
           (1030, 512, 1160),
           # token counts (the reduction of wgrad) of any length, odd ones included: the wgrad kernel
           # rounds the reduction up itself and reads the surplus rows as zeros
           (1000, 256, 384), (77, 256, 128), (1, 256, 128), (129, 512, 256), (4101, 256, 640), (300, 264, 136),
           # reductions of forward (Kl) and dgrad (Nl) that are multiples of 8 but not of 128, on tile-multiple
-          # outputs and on ragged ones: the tuned kernel walks them rounded up and zeroes the surplus in LDS
+          # outputs and on ragged ones (small tiles mask the end in registers, 256-row ones in LDS: as above)
           (256, 200, 128), (256, 128, 200), (512, 328, 392), (256, 8, 136), (256, 136, 8), (512, 1928, 256),
           (256, 256, 1928), (768, 2000, 520), (1000, 72, 1016), (256, 64, 120), (256, 192, 448)]
 

@@ -10,7 +10,7 @@ import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("Mo,No,R", [(4352, 8704, 128), (3840, 4864, 40), (5640, 6152, 72), (6144, 5888, 1536),
+@pytest.mark.parametrize("Mo,No,R", [(4352, 8704, 128), (3840, 4864, 40), (5640, 6152, 72), (6144, 5888, 1536), (5888, 6144, 2048),
                                      (5888, 6016, 250), (4999, 7001, 130), (4104, 8008, 200),
                                      (4500, 4616, 256), (4500, 4616, 264)])
 @pytest.mark.parametrize("op", [axo.AXO_OP_FWD, axo.AXO_OP_DGRAD, axo.AXO_OP_WGRAD])

@@ -1,7 +1,7 @@
-"""The tile kernels at odd sizes.  Above all the small-tile kernel (32 x 32 and 64 x 64 tiles whose four waves split the reduction in 64-wide chunks) at the
-sizes where it can go wrong: output edges one short of, at and one past a tile; reductions that end in any
-position of a chunk, give some of the four waves nothing, or wrap around them; every epilogue.  Against the
-fp64 oracle under the usual gates (tests/gpu_util.py)."""
+"""The tile kernels at odd sizes: output edges one short of, at and one past a small tile; reductions that end in any
+position of a chunk, give some of the four waves of a split reduction nothing, or wrap around them; every epilogue.  Which
+of the small-tile kernels a size runs on is the library's choice; the sizes that pin each kernel down are in
+test_kernel_variants_gpu.py.  Against the fp64 oracle under the usual gates (tests/gpu_util.py)."""
 import numpy as np
 import pytest
 import torch
@@ -96,7 +96,7 @@ def test_special_values_at_the_end_of_the_reduction():
 
 
 @pytest.mark.parametrize("M,Kl,Nl", [(2304, 2051, 2049), (2305, 2048, 2304), (2500, 2309, 2100),
-                                     (1540, 1500, 1411), (1535, 1544, 1537), (1502, 901, 702)])  # these: 128 x 128 tiles
+                                     (1540, 1500, 1411), (1535, 1544, 1537), (1502, 901, 702)])  # 128 x 128 and 64 x 64
 def test_large_tiles_at_odd_edges(M, Kl, Nl):
     """The 256-row and 128 x 128 tiles on outputs and reductions that are no multiple of 8: clipped tiles, part-chunk reduction
     ends, and an fp32-accumulating weight gradient (whose tiles must not overlap) at a ragged size."""
