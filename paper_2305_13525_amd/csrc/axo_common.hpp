@@ -75,9 +75,36 @@ __device__ __forceinline__ float gelu_tanh(float v) {
     return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
-// GELU, erf form: 0.5 v (1 + erf(v / sqrt 2)) = 0.5 v erfc(-v / sqrt 2)  (no cancellation).
+// The upper tail Q(a) = erfc(a / sqrt 2) / 2 of the normal distribution at a = |v|, as ratio * gauss with gauss = exp(-v^2 / 2):
+// the ratio is smooth and tends to 1 / (a sqrt(2 pi)), here a polynomial of degree 10 in w = a / (1 + 0.35 a), 6e-9 off at
+// most up to a = 14, where the tail is below the normal range of floats.  (A minimax fit made for this file: weighted least
+// squares with reweighting by the error.)  Straight-line code of one reciprocal and one exp2, because an epilogue
+// runs it on every output: with erfcf, which branches over ranges and a wave takes all of them, forward, dgrad and wgrad of
+// 4000 x 2000 x 6000 took 326 us (the forward without an epilogue 34 less), now 310; 1001 x 1027 x 515 with it in the data gradient 32.4, now 29.3.  Errors against 64 bits, over |v| < 13, are at or below those of the erfcf form in every
+// range: 3e-8 to 7e-8 rms for v > -1, 1.4e-7 on [-3, -1], 2.3e-6 on [-13, -9], where that form had 4.1e-6.
+__device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss) {
+    const float a = fminf(__builtin_fabsf(v), 14.0f);  // an infinite v has gauss = 0 and wants a finite ratio
+    const float w = a * __builtin_amdgcn_rcpf(__builtin_fmaf(0.35f, a, 1.0f));
+    float r = 3.2823087e-07f;
+    r = __builtin_fmaf(r, w, -1.9183292e-06f);
+    r = __builtin_fmaf(r, w, -3.4882826e-06f);
+    r = __builtin_fmaf(r, w, 2.7562604e-05f);
+    r = __builtin_fmaf(r, w, 4.4766144e-05f);
+    r = __builtin_fmaf(r, w, 9.6836789e-05f);
+    r = __builtin_fmaf(r, w, -2.3905453e-03f);
+    r = __builtin_fmaf(r, w, -6.8393452e-03f);
+    r = __builtin_fmaf(r, w, 1.1036798e-01f);
+    r = __builtin_fmaf(r, w, -3.9894214e-01f);
+    ratio = __builtin_fmaf(r, w, 0.5f);
+    gauss = __builtin_amdgcn_exp2f(v * v * -0.72134752f);  // log2(e) / 2
+}
+
+// GELU, erf form: v Phi(v), Phi(v) = Q(|v|) below zero and 1 - Q(v) above (no cancellation).
 __device__ __forceinline__ float gelu_erf(float v) {
-    return 0.5f * v * erfcf(-v * 0.7071067811865475f);
+    float ratio, gauss;
+    normal_tail(v, ratio, gauss);
+    const float q = ratio * gauss;
+    return v * (v < 0.0f ? q : 1.0f - q);
 }
 
 // d/dv of the tanh-form GELU.  With s = sigmoid(2 z): 0.5 (1 + tanh z) = s and 1 - tanh^2 z = 4 s (1 - s),
@@ -91,10 +118,12 @@ __device__ __forceinline__ float dgelu_tanh(float v) {
     return s * __builtin_fmaf(2.0f * v * (1.0f - s), dz, 1.0f);
 }
 
-// d/dv of the exact GELU: Phi(v) + v phi(v).
+// d/dv of the exact GELU: Phi(v) + v phi(v), phi(v) = gauss / sqrt(2 pi).
 __device__ __forceinline__ float dgelu_erf(float v) {
-    const float phi = 0.3989422804014327f * __expf(-0.5f * v * v);
-    return 0.5f * erfcf(-v * 0.7071067811865475f) + v * phi;
+    float ratio, gauss;
+    normal_tail(v, ratio, gauss);
+    const float below = __builtin_fmaf(__builtin_fabsf(v), -0.3989422804014327f, ratio) * gauss;
+    return v < 0.0f ? below : 1.0f - below;
 }
 
 __device__ __forceinline__ float apply_epilogue(float acc, float b, int epi) {

@@ -1,0 +1,59 @@
+"""The GELU epilogues value by value: every bf16 number from 2^-20 to 13 in magnitude through a reduction of one term, whose
+sum is the number itself.  The epilogues compute in fp32 with relative errors below 1e-5 (3e-4 next to the derivative's zero, where no bf16
+number comes closer than 1e-3), far inside half a bf16 step (2e-3), so every result is the oracle's rounded once, or its neighbour."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2305_13525_amd as axo
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def bf16_values(cols):
+    bits = np.concatenate([np.arange(0x3580, 0x4151), np.arange(0xB580, 0xC151), [0x0000, 0x8000]]).astype(np.uint16)
+    rows = -(-len(bits) // cols)
+    return np.resize(bits, (rows, cols))
+
+
+@pytest.mark.parametrize("kind", [axo.AXO_EPI_BIAS_GELU_TANH, axo.AXO_EPI_BIAS_GELU_ERF])
+def test_every_value(kind):
+    pre = bf16_values(8)
+    rows = pre.shape[0]
+    ones = lambda r, c: np.full((r, c), 0x3F80, dtype=np.uint16)  # noqa: E731
+    # forward: Y[t, n] = g(v[t] * 1 + 0)
+    X, W, bias = pre.reshape(-1, 1), ones(1, 8), np.zeros(8, dtype=np.uint16)
+    padded = np.zeros((X.shape[0], 8), dtype=np.uint16)
+    padded[:, :1] = X
+    Xd, Y = gu.to_dev(padded), gu.empty_dev(X.shape[0], 8)
+    gu.run_fwd(axo.Problem.make((1, 1, 1), (0, 0, 0), X.shape[0], 1, 8), Xd, gu.to_dev(W), Y, gu.to_dev(bias), kind)
+    # data gradient: dX[t, k] = 1 * g'(pre[t, k])
+    dY, Wt = np.zeros((rows, 8), dtype=np.uint16), np.zeros((8, 8), dtype=np.uint16)
+    dY[:, :1], Wt[:, :1] = ones(rows, 1), ones(8, 1)
+    dX, p, d = gu.empty_dev(rows, 8), axo.Problem.make((1, 1, 1), (0, 0, 0), rows, 8, 1), [gu.to_dev(a) for a in (dY, Wt, pre)]
+    axo.axo_fc_dgrad_act(p, d[0].data_ptr(), 8, d[1].data_ptr(), 8, d[2].data_ptr(), 8, kind, dX.data_ptr(), 8, None, 0, gu.stream())
+    torch.cuda.synchronize()
+    for got, ref in ((Y, oracle.fc_fwd(X, W, bias, kind)), (dX, oracle.fc_dgrad_act(ones(rows, 1), ones(8, 1), pre, kind))):
+        # Far down the negative tail another bound holds than the bf16 step: the oracle's forms cancel there, 1 + tanh(z) and
+        # 1 + erf(z) in doubles, and are off by up to 13 * 2^-52 = 3e-15.
+        small, lost = 1e-10, 3e-15
+        out = gu.to_host(got)
+        value = (out.astype(np.uint32) << np.uint32(16)).view(np.float32).astype(np.float64)
+        steps = np.where(np.abs(ref) < small, 2 * (np.abs(value - ref) > lost + np.abs(ref) * 2.0 ** -8), oracle.ulp_distance_bf16(out, ref))
+        assert steps.max() <= 1, (kind, steps.max(), np.argwhere(steps > 1)[:4])
+
+
+def test_infinities_and_nans():
+    """g(+inf) = inf; -inf times zero and NaN are NaN, in both forms, as the formulas give it."""
+    x = np.array([[0x7F80], [0xFF80], [0x7FC0]], dtype=np.uint16)
+    Xd = gu.to_dev(np.pad(x, ((0, 0), (0, 7))))
+    for kind in (axo.AXO_EPI_BIAS_GELU_TANH, axo.AXO_EPI_BIAS_GELU_ERF):
+        Y = gu.empty_dev(3, 8, fill=0)
+        gu.run_fwd(axo.Problem.make((1, 1, 1), (0, 0, 0), 3, 1, 8), Xd, gu.to_dev(np.full((1, 8), 0x3F80, dtype=np.uint16)), Y,
+                   gu.to_dev(np.zeros(8, dtype=np.uint16)), kind)
+        torch.cuda.synchronize()
+        h = gu.to_host(Y)
+        assert (h[0] == 0x7F80).all()
+        assert ((h[1:] & 0x7FFF) > 0x7F80).all()
