@@ -256,7 +256,9 @@ __device__ __forceinline__ u32x4_t tile_rsrc(const bf16_t* p, uint32_t bound) {
     return r;
 }
 
-// Four consecutive bf16 values of memory (8-byte aligned), the first `valid` of them inside the matrix.
+// Four consecutive bf16 values of memory (8-byte aligned), the first `valid` of them inside the matrix, the others zero.
+// The loads of a part are independent of each other (indices clamped, not a loop of `valid` rounds, each of which waits for
+// its load).
 __device__ __forceinline__ f32x4 load_bf16x4(const bf16_t* p, int valid) {
     f32x4 x = {0.f, 0.f, 0.f, 0.f};
     if (valid >= 4) {
@@ -265,14 +267,23 @@ __device__ __forceinline__ f32x4 load_bf16x4(const bf16_t* p, int valid) {
         x[1] = __uint_as_float(raw.x & 0xFFFF0000u);
         x[2] = __uint_as_float(raw.y << 16);
         x[3] = __uint_as_float(raw.y & 0xFFFF0000u);
-    } else
-        for (int e = 0; e < valid; ++e) x[e] = bf16_bits_to_f32(p[e]);
+    } else if (valid > 0) {
+        const bf16_t v0 = p[0], v1 = p[min(1, valid - 1)], v2 = p[min(2, valid - 1)];
+        x[0] = bf16_bits_to_f32(v0);
+        x[1] = valid > 1 ? bf16_bits_to_f32(v1) : 0.f;
+        x[2] = valid > 2 ? bf16_bits_to_f32(v2) : 0.f;
+    }
     return x;
 }
 __device__ __forceinline__ f32x4 load_f32x4(const float* p, int valid) {
     if (valid >= 4) return *reinterpret_cast<const f32x4*>(p);
     f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    for (int e = 0; e < valid; ++e) x[e] = p[e];
+    if (valid > 0) {
+        const float v0 = p[0], v1 = p[min(1, valid - 1)], v2 = p[min(2, valid - 1)];
+        x[0] = v0;
+        x[1] = valid > 1 ? v1 : 0.f;
+        x[2] = valid > 2 ? v2 : 0.f;
+    }
     return x;
 }
 
