@@ -242,7 +242,7 @@ int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* 
 enum class Tiles { small, mid, big };
 Tiles tiles_of(int Mo, int No, int R) {
     const double small_us = small_time(Mo, No, R) + small_time_long(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
-    if (small_us < mid_us && small_us < big_us && grid_fits(tiles_in(Mo, 64) * tiles_in(No, 64), axo::SmallCfg::THREADS)) return Tiles::small;
+    if (small_us < mid_us && small_us < big_us && grid_fits(tiles_in(Mo, 64) * tiles_in(No, 64), axo::SmallCfg<false>::THREADS)) return Tiles::small;
     return mid_us < big_us ? Tiles::mid : Tiles::big;
 }
 
@@ -279,25 +279,41 @@ axo::TileSched plan_product(const GemmArgs& g, int la, int lb) {
     return sc;
 }
 
+// Whether a product on these tiles fetches its operands whose reduction runs inside the rows by whole cache lines
+// (line_phase): where such rows start elsewhere than on lines and the reduction is long enough to pay for the later start and the
+// one stage more.  Without / with it, rows 16 bytes off: 64 x 64 tiles, dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83
+// and 12.0 / 9.3 us, 1001 x 1027 (272 tiles) with 9 steps 6.25 / 6.62, 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35, dgrad
+// 2000 x 1000 x 3000 27.7 / 20.2; 128 x 128
+// tiles, dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3 and 23.1 / 20.1; half-width tiles, dgrad
+// 4096 x 2048 with 8 / 16 / 96 steps 16.1 / 16.1, 23.4 / 22.4 and 97 / 87; in forward, where only the first operand is of that
+// kind, 4096 x 1536 x 1536 24.6 / 24.9.
+bool takes_lines(const GemmArgs& g, int la, int lb, Tiles tiles) {
+    auto leaves = [](const axo::bf16_t* p, int64_t ld) { return ld % 64 != 0 || reinterpret_cast<uintptr_t>(p) % 128 != 0; };
+    if (!(la == axo::KC && leaves(g.A, g.lda)) && !(lb == axo::KC && leaves(g.B, g.ldb))) return false;
+    if (tiles == Tiles::big && lb != axo::KC) return false;
+    if (tiles == Tiles::mid) return steps_in(g.R) >= 8;
+    if (tiles == Tiles::big) return steps_in(g.R) >= 16;
+    return steps_in(g.R) >= (2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) <= 3 * NUM_CU ? 12 : 8);
+}
+
 // Launch of one product on those tiles.
-template <int LA, int LB>
-int launch_tile(const GemmArgs& g, hipStream_t st) {
-    const Tiles tiles = tiles_of(g.Mo, g.No, g.R);
-    if (tiles == Tiles::small) {
-        static std::atomic<uint64_t> raised{0};
-        return launch_square<axo::SmallCfg, 64>(axo::gemm_small_kernel<LA, LB>, &raised, g, st);
-    }
-    if (tiles == Tiles::mid) {
-        static std::atomic<uint64_t> raised{0};
-        return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB>, &raised, g, st);
-    }
-    auto kern = axo::gemm_mixed_kernel<LA, LB>;
-    static std::atomic<uint64_t> raised{0};
-    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
+template <int LA, int LB, bool LINES>
+int launch_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
+    static std::atomic<uint64_t> raised[3]{{0}, {0}, {0}};
+    if (tiles == Tiles::small) return launch_square<axo::SmallCfg<LINES>, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
+    if (tiles == Tiles::mid) return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[1], g, st);
+    auto kern = axo::gemm_mixed_kernel<LA, LB, LINES && LB == axo::KC>;
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised[2])) return AXO_ERR_HIP;
     const axo::TileSched sc = plan_product(g, LA, LB);
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), axo::MIX_LDS_BYTES, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
+}
+template <int LA, int LB>
+int launch_tile(const GemmArgs& g, hipStream_t st) {
+    const Tiles tiles = tiles_of(g.Mo, g.No, g.R);
+    if constexpr (LA == axo::KC) if (takes_lines(g, LA, LB, tiles)) return launch_tiles<LA, LB, true>(g, tiles, st);
+    return launch_tiles<LA, LB, false>(g, tiles, st);
 }
 
 int launch_tile_layout(const GemmArgs& g, int la, int lb, hipStream_t st) {

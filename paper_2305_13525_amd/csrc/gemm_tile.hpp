@@ -222,6 +222,47 @@ struct FragAddr {
     }
 };
 
+// Whole cache lines of a KC operand whose rows do not start on them.  A 128-byte segment of such a row lies in two lines, and
+// the loads of a step, which the texture path takes a line at a time, then touch each line twice, once for either step.
+// Here stage j receives the row's lines instead: its chunks 8 j - phase .. 8 j + 7 - phase, where `phase` is the position
+// of the row's start in its line.  Reduction chunk c of step j is then chunk (c + phase) % 8 of stage j, or of stage j + 1
+// where c + phase passes 7: a step needs two stages, and a product one more stage than steps.
+__device__ __forceinline__ int line_phase(const bf16_t* origin, int64_t ld, int r) {
+    return (int)((uint32_t)(reinterpret_cast<uint64_t>(origin) >> 4) + (uint32_t)r * (uint32_t)(ld >> 3)) & 7;
+}
+// load_offsets for that: `first` for stage 0, where chunks in front of the row are replaced by its first one; `later`
+// counts from the line behind stage 0's, so that it is never negative.
+template <int ROUNDS, int THREADS>
+__device__ __forceinline__ void line_load_offsets(int tid, const bf16_t* origin, int64_t ld, uint32_t* first, uint32_t* later) {
+#pragma unroll
+    for (int j = 0; j < ROUNDS; ++j) {
+        const int q = j * THREADS + tid, r = q >> 3, cs = q & 7;
+        const int chunk = (cs ^ swz_kc(r)) - line_phase(origin, ld, r);
+        const uint32_t row = (uint32_t)r * (uint32_t)(ld * 2);  // the caller sees to it that offsets stay below 2^32
+        first[j] = row + (uint32_t)(max(chunk, 0) * 16);
+        later[j] = row + (uint32_t)((chunk + 8) * 16);
+    }
+}
+// FragAddr for that, on a ring of D stages.  The rows of an operand's MFMA tiles lie 16 rows apart, which is a whole number
+// of lines, so a lane has the same phase in all of them.
+template <int ROWS, int D>
+struct LineFragAddr {
+    static constexpr int STAGE_STRIDE = ROWS * TILE_BK * 2;
+    uint32_t a[2], wrapped[2];  // per sub-step; `wrapped`: from the last stage, whose next one is stage 0
+    __device__ __forceinline__ void init(int row0, int lane, uint32_t tile_base, const bf16_t* origin, int64_t ld) {
+        const int r = row0 + (lane & 15), phase = line_phase(origin, ld, r);
+#pragma unroll
+        for (int kq = 0; kq < 2; ++kq) {
+            const int c = kq * 4 + (lane >> 4) + phase;
+            a[kq] = tile_base + r * (TILE_BK * 2) + (((c & 7) ^ swz_kc(r)) << 4) + (c >> 3) * STAGE_STRIDE;
+            wrapped[kq] = a[kq] - (c >> 3) * (D * STAGE_STRIDE);
+        }
+    }
+    __device__ __forceinline__ bf16x8 read(const char* lds0, int s, int t, int kq) const {
+        return *reinterpret_cast<const bf16x8*>(lds0 + (s == D - 1 ? wrapped[kq] : a[kq]) + s * STAGE_STRIDE + t * (16 * TILE_BK * 2));
+    }
+};
+
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;  // a buffer resource descriptor in four SGPRs
 
 // The first `n` (none if n <= 0, all if n >= 8) of the 8 bf16 elements of a 16-byte chunk, the others zero.
@@ -774,7 +815,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 // the compiler waits for all LDS reads in flight, those of the other sub-step too.  Peeled: forward 1024 x 1024 with
 // reduction 4096 on 64 x 64 tiles 18.7 -> 14.6 us, dgrad 2048^3 on 128 x 128 ones 18.6 -> 16.5, dgrad 4096 x 2048 with
 // reduction 6144 on half-width ones 80.3 -> 76.2, 10600 x 7736 with reduction 48 73.4 -> 66.4.
-template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB>
+template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB, bool LINES = false>
 __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
     using C = RingCfg<BM, BN, WGM, WGN, D>;
     const int tid = threadIdx.x;
@@ -783,18 +824,29 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     const int wm = wave / WGN, wn = wave % WGN;
     const int KT = (g.R + TILE_BK - 1) / TILE_BK;
 
-    const u32x4_t a_rsrc = tile_rsrc((LA == KC) ? g.A + (int64_t)i0 * g.lda : g.A + i0, operand_bound<LA>(g.lda, min(BM, g.Mo - i0), g.R));
-    const u32x4_t b_rsrc = tile_rsrc((LB == KC) ? g.B + (int64_t)j0 * g.ldb : g.B + j0, operand_bound<LB>(g.ldb, min(BN, g.No - j0), g.R));
+    constexpr bool A_LINES = LINES && LA == KC, B_LINES = LINES && LB == KC;
+    constexpr int AHEAD = LINES ? 1 : 0;  // stages that a step needs beyond its own
+    const int stages = KT + AHEAD;
+
+    const bf16_t* const Ab = (LA == KC) ? g.A + (int64_t)i0 * g.lda : g.A + i0;
+    const bf16_t* const Bb = (LB == KC) ? g.B + (int64_t)j0 * g.ldb : g.B + j0;
+    const u32x4_t a_rsrc = tile_rsrc(Ab, operand_bound<LA>(g.lda, min(BM, g.Mo - i0), g.R));
+    const u32x4_t b_rsrc = tile_rsrc(Bb, operand_bound<LB>(g.ldb, min(BN, g.No - j0), g.R));
     const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
     const uint32_t a_step = (uint32_t)((LA == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.lda * 2);
     const uint32_t b_step = (uint32_t)((LB == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.ldb * 2);
     uint32_t a_off[C::A_ROUNDS], b_off[C::B_ROUNDS];
-    load_offsets<BM, LA, C::A_ROUNDS, C::THREADS>(tid, g.lda, a_off);
-    load_offsets<BN, LB, C::B_ROUNDS, C::THREADS>(tid, g.ldb, b_off);
-    FragAddr<BM, LA, C::TM> fra;
-    FragAddr<BN, LB, C::TN> frb;
-    fra.init(wm * C::WTM, lane, 0);
-    frb.init(wn * C::WTN, lane, D * C::A_BYTES);
+    uint32_t a_later[C::A_ROUNDS], b_later[C::B_ROUNDS];
+    if constexpr (A_LINES) line_load_offsets<C::A_ROUNDS, C::THREADS>(tid, Ab, g.lda, a_off, a_later);
+    else load_offsets<BM, LA, C::A_ROUNDS, C::THREADS>(tid, g.lda, a_off);
+    if constexpr (B_LINES) line_load_offsets<C::B_ROUNDS, C::THREADS>(tid, Bb, g.ldb, b_off, b_later);
+    else load_offsets<BN, LB, C::B_ROUNDS, C::THREADS>(tid, g.ldb, b_off);
+    std::conditional_t<A_LINES, LineFragAddr<BM, D>, FragAddr<BM, LA, C::TM>> fra;
+    std::conditional_t<B_LINES, LineFragAddr<BN, D>, FragAddr<BN, LB, C::TN>> frb;
+    if constexpr (A_LINES) fra.init(wm * C::WTM, lane, 0, Ab, g.lda);
+    else fra.init(wm * C::WTM, lane, 0);
+    if constexpr (B_LINES) frb.init(wn * C::WTN, lane, D * C::A_BYTES, Bb, g.ldb);
+    else frb.init(wn * C::WTN, lane, D * C::A_BYTES);
 
     f32x4 acc[C::TM][C::TN];
 #pragma unroll
@@ -856,7 +908,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     auto step = [&](auto s_tag, auto left_tag) __attribute__((always_inline)) {
         constexpr int s = decltype(s_tag)::value, left = decltype(left_tag)::value;
         AXO_SETPRIO(2);
-        if (left >= D) issue(IC<NH>{}, IC<NL>{}, (s + D - 1) % D);
+        if (left >= D - AHEAD) issue(IC<NH>{}, IC<NL>{}, (s + D - 1) % D);
         read(s, 1);
         if (left == 1 && (LA == KC || LB == KC) && g.R % TILE_BK != 0) {
             mask(0, g.R % TILE_BK);
@@ -865,13 +917,14 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
         mfma(0);
         Interleave<N_MFMA, 0, RD, 0>::run();
         AXO_SETPRIO(0);
-        if (left > 1) {  // stage s + 1 has landed, stage s is in registers
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((left > D ? D - 2 : left > 2 ? left - 2 : 0) * NL) : "memory");
+        if (left > 1) {  // what the next step needs has landed, stage s is in registers
+            constexpr int in_flight = left >= D - AHEAD ? D - 2 - AHEAD : left > 2 ? left - 2 : 0;
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(in_flight * NL) : "memory");
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             AXO_SETPRIO(3);
-            if (left > D) issue(IC<0>{}, IC<NH>{}, s);
+            if (left > D - AHEAD) issue(IC<0>{}, IC<NH>{}, s);
             read((s + 1) % D, 0);
         }
         mfma(1);
@@ -879,19 +932,31 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     };
     // The walk ends in stage D - 1 and starts in whichever stage that takes, so that the last steps, which differ from the
     // others, exist once, behind a loop without branches.
-    static_assert(D == 3 || D == 4, "stages of the ring");
+    static_assert(D >= 3 && D <= 5, "stages of the ring");
     const int lead = KT % D, first = lead > 0 ? D - lead : 0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
         const int s = first + i < D ? first + i : first + i - D;
         if (i < D - 1) {
-            if (i < KT) issue(IC<0>{}, IC<NL>{}, s);
-        } else if (KT >= D) issue(IC<0>{}, IC<NH>{}, s);  // its first step issues the rest
+            if (i < stages) issue(IC<0>{}, IC<NL>{}, s);
+        } else if (stages >= D) issue(IC<0>{}, IC<NH>{}, s);  // its first step issues the rest
+        if (i > 0) continue;
+        if constexpr (A_LINES) {
+            a_soff = 0;
+#pragma unroll
+            for (int j = 0; j < C::A_ROUNDS; ++j) a_off[j] = a_later[j];
+        }
+        if constexpr (B_LINES) {
+            b_soff = 0;
+#pragma unroll
+            for (int j = 0; j < C::B_ROUNDS; ++j) b_off[j] = b_later[j];
+        }
     }
-    // The first step waits for its own stage only, also where the whole reduction is requested at once (waiting for
+    // The first step waits for what it needs only, also where the whole reduction is requested at once (waiting for
     // all of it made two-step products of up to 256 half-width tiles 2 % slower).
-    if (KT >= D) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * NL + NH) : "memory");
-    else if (D > 3 && KT == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+    if (stages >= D) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2 - AHEAD) * NL + NH) : "memory");
+    else if (KT == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+    else if (KT == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
     else if (KT == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -899,7 +964,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     read(first, 0);
     using More = IC<D + 1>;
     if (KT > D) {
-        if constexpr (D == 4) if (lead == 3) step(IC<1>{}, More{});
+        if constexpr (D > 4) if (lead >= 4) step(IC<D - 4>{}, More{});
+        if constexpr (D > 3) if (lead >= 3) step(IC<D - 3>{}, More{});
         if (lead >= 2) step(IC<D - 2>{}, More{});
         if (lead >= 1) step(IC<D - 1>{}, More{});
     }
@@ -907,9 +973,11 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
         step(IC<0>{}, More{});
         step(IC<1>{}, More{});
         step(IC<2>{}, More{});
-        if constexpr (D == 4) step(IC<3>{}, More{});
+        if constexpr (D > 3) step(IC<3>{}, More{});
+        if constexpr (D > 4) step(IC<4>{}, More{});
     }
-    if constexpr (D == 4) if (KT >= 4) step(IC<0>{}, IC<4>{});
+    if constexpr (D > 4) if (KT >= 5) step(IC<D - 5>{}, IC<5>{});
+    if constexpr (D > 3) if (KT >= 4) step(IC<D - 4>{}, IC<4>{});
     if (KT >= 3) step(IC<D - 3>{}, IC<3>{});
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
@@ -937,7 +1005,7 @@ __device__ __forceinline__ int inside_col(const GemmArgs& g, const int j0) {
 }
 
 // One launch over both regions of a TileSched.
-template <int LA, int LB>
+template <int LA, int LB, bool LINES>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g, TileSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
@@ -949,7 +1017,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
         tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_ring_body<256, 128, 4, 2, 3, LA, LB>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
+        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
     }
 }
 
@@ -961,25 +1029,28 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
 // 25.6 / 24.9 / 24.2 -> 19.5 / 19.0 / 18.4 us, 1536^3 19.6 / 19.0 / 18.4 -> 14.4 / 13.8 / 13.2, wgrad 1536 x 1536 of 4096
 // tokens 44 -> 30.  Sums run in the same order as on the other tiles: same bits.
 using MidCfg = RingCfg<128, 128, 4, 2, 4>;
-template <int LA, int LB>
+template <int LA, int LB, bool LINES>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
-    gemm_ring_body<128, 128, 4, 2, 4, LA, LB>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
+    gemm_ring_body<128, 128, 4, 2, 4, LA, LB, LINES>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
 }
 
-// The same for smaller outputs: 64 x 64, four waves of 32 x 32 on a four-stage ring, two workgroups per CU.  Measured
+// The same for smaller outputs: 64 x 64, four waves of 32 x 32 on a four-stage ring, two workgroups per CU.  (Five stages are
+// what two workgroups leave room for; they pay where a step needs two of them: 12.0 -> 9.3 us instead of 10.8 for dgrad 1024 x 1024
+// with 32 steps and rows 16 bytes off.)  Measured
 // against the small tiles whose waves split the reduction (gemm_slim.hpp), forward / dgrad / wgrad: 2048 x 1024 x 1024
 // 11.9 / 12.1 / 11.5 -> 9.4 / 8.5 / 10.2 us, 1000^3 10.0 / 9.6 / 10.2 -> 8.8 / 8.6 / 8.2, wgrad 1024 x 1024 of 8192 tokens 30
 // both (128 x 128 tiles: 51).  Those stay quicker below some 100 tiles (300^3 3.7 against 5.4).
-using SmallCfg = RingCfg<64, 64, 2, 2, 4>;
-template <int LA, int LB>
-__global__ void __launch_bounds__(SmallCfg::THREADS, 2) gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
+template <bool LINES>
+using SmallCfg = RingCfg<64, 64, 2, 2, LINES ? 5 : 4>;
+template <int LA, int LB, bool LINES>
+__global__ void __launch_bounds__(256, 2) gemm_small_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
-    gemm_ring_body<64, 64, 2, 2, 4, LA, LB>(g, inside_row<64, LA>(g, tm * 64), inside_col<64>(g, tn * 64), smem);
+    gemm_ring_body<64, 64, 2, 2, LINES ? 5 : 4, LA, LB, LINES>(g, inside_row<64, LA>(g, tm * 64), inside_col<64>(g, tn * 64), smem);
 }
 
 }  // namespace axo

@@ -1,0 +1,53 @@
+"""Operands whose rows start anywhere in a cache line.  Products on 64 x 64, 128 x 128 and half-width tiles fetch such rows by
+whole lines; where the rows lie must not show in the result, which is compared bit for bit with that of the same values in
+rows that start on lines.  Everything around the operands is NaN."""
+import pytest
+import torch
+
+import paper_2305_13525_amd as axo
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+SMALL, MID, HALF = axo.AXO_KERNEL_TILES_64, axo.AXO_KERNEL_TILES_128, axo.AXO_KERNEL_TILES_256_HALF
+
+
+def placed(values, extra, shift):
+    """A copy of the values in rows `extra` chunks of 8 longer than whole lines, `shift` chunks behind a line, amid NaNs."""
+    rows, cols = values.shape
+    lead = (cols + 63) // 64 * 64 + 8 * extra
+    flat = torch.full((rows * lead + 128,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    assert flat.data_ptr() % 128 == 0
+    view = torch.as_strided(flat, (rows, cols), (lead, 1), 8 * shift)
+    view.copy_(values)
+    return view
+
+
+# output rows, output columns, reduction: step counts of every remainder of the rings, ends inside a step, a chunk and on them
+@pytest.mark.parametrize("Mo,No,R,kernel", [
+    (1030, 1021, 768, SMALL), (1000, 1000, 820, SMALL), (1030, 1021, 903, SMALL), (970, 1030, 960, SMALL), (1000, 1016, 1025, SMALL),
+    (2000, 1016, 512, SMALL), (1999, 1000, 579, SMALL),
+    (2040, 2001, 512, MID), (2048, 2048, 570, MID), (2001, 2040, 640, MID), (1900, 2000, 725, MID),
+    (4090, 1530, 1024, HALF), (4096, 1536, 1100, HALF), (4001, 1519, 1151, HALF)])
+@pytest.mark.parametrize("op", [axo.AXO_OP_FWD, axo.AXO_OP_DGRAD])
+def test_where_rows_lie_does_not_show(Mo, No, R, kernel, op):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(R + op)
+    normal = lambda r, c: torch.randn(r, c, device="cuda:0", generator=gen).to(torch.bfloat16)  # noqa: E731
+    M, K, N = ((Mo, R, No), (Mo, No, R))[op]
+    p, a, b = axo.Problem.make((1, 1, 1), (0, 0, 0), M, K, N), normal(Mo, R), normal(K, N)
+    lead = (No + 7) // 8 * 8
+    call = (lambda *t: axo.axo_fc_fwd(p, *t[:4], None, 0, *t[4:])) if op == axo.AXO_OP_FWD else (lambda *t: axo.axo_fc_dgrad(p, *t))
+
+    def run(A, B):
+        out = torch.full((Mo, lead), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        assert axo.axo_fc_kernel(p, op, A.stride(0), B.stride(0), lead)[1] == kernel
+        call(A.data_ptr(), A.stride(0), B.data_ptr(), B.stride(0), out.data_ptr(), lead, None, 0, gu.stream())
+        torch.cuda.synchronize()
+        return out.view(torch.int16)
+
+    want = run(placed(a, 0, 0), placed(b, 0, 0))
+    assert not want[:, :No].view(torch.bfloat16).isnan().any()
+    # (rows of A, shift of A, rows of B, shift of B): every phase of a row in its line, in one operand, the other and both
+    for place in [(i, 0, i, 0) for i in range(1, 8)] + [(0, 3, 0, 0), (0, 0, 0, 5), (0, 7, 0, 1), (3, 2, 0, 0), (0, 0, 6, 1), (1, 7, 5, 4)]:
+        assert torch.equal(run(placed(a, *place[:2]), placed(b, *place[2:])), want), place
