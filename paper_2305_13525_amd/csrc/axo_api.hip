@@ -279,21 +279,21 @@ axo::TileSched plan_product(const GemmArgs& g, int la, int lb) {
     return sc;
 }
 
-// Whether a product on these tiles fetches its operands whose reduction runs inside the rows by whole cache lines
+// Whether a product on these tiles fetches operands whose reduction runs inside the rows by whole cache lines
 // (line_phase): where such rows start elsewhere than on lines and the reduction is long enough to pay for the later start and the
-// one stage more.  Without / with it, rows 16 bytes off: 64 x 64 tiles, dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83
-// and 12.0 / 9.3 us, 1001 x 1027 (272 tiles) with 9 steps 6.25 / 6.62, 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35, dgrad
-// 2000 x 1000 x 3000 27.7 / 20.2; 128 x 128
-// tiles, dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3 and 23.1 / 20.1; half-width tiles, dgrad
-// 4096 x 2048 with 8 / 16 / 96 steps 16.1 / 16.1, 23.4 / 22.4 and 97 / 87; in forward, where only the first operand is of that
-// kind, 4096 x 1536 x 1536 24.6 / 24.9.
+// one stage more.  Without / with it, rows 16 bytes off unless sizes say it, in us:
+//   64 x 64    dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83, 12.0 / 9.3; 1001 x 1027 (272 tiles) with 9 steps
+//              6.25 / 6.62; 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35; 2000 x 1000 x 3000 27.8 / 20.6
+//   128 x 128  dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3, 23.1 / 20.5
+//   256 x 128  dgrad 4096 x 2048 with 8 / 16 / 96 steps 16.1 / 16.1, 23.4 / 22.4, 97 / 87; not in forward, where only the first
+//              operand is of that kind (4096 x 1536 x 1536 24.6 / 24.9)
+//   256 x 256  dgrad 4096 x 4096 x 8192 260 / 226, 8192 x 8192 x 2000 272 / 233, 8000 x 8000 x 520 87 / 82; forward
+//              4096 x 4096 x 8192 225 / 205 (rows on lines: dgrad 195, forward 189), 5000 x 520 x 5000 50.8 / 50.5
 bool takes_lines(const GemmArgs& g, int la, int lb, Tiles tiles) {
     auto leaves = [](const axo::bf16_t* p, int64_t ld) { return ld % 64 != 0 || reinterpret_cast<uintptr_t>(p) % 128 != 0; };
     if (!(la == axo::KC && leaves(g.A, g.lda)) && !(lb == axo::KC && leaves(g.B, g.ldb))) return false;
-    if (tiles == Tiles::big && lb != axo::KC) return false;
-    if (tiles == Tiles::mid) return steps_in(g.R) >= 8;
-    if (tiles == Tiles::big) return steps_in(g.R) >= 16;
-    return steps_in(g.R) >= (2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) <= 3 * NUM_CU ? 12 : 8);
+    const bool few = tiles == Tiles::small && 2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) <= 3 * NUM_CU;
+    return steps_in(g.R) >= (few ? 12 : 8);
 }
 
 // Launch of one product on those tiles.
@@ -302,11 +302,12 @@ int launch_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
     static std::atomic<uint64_t> raised[3]{{0}, {0}, {0}};
     if (tiles == Tiles::small) return launch_square<axo::SmallCfg<LINES>, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
     if (tiles == Tiles::mid) return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[1], g, st);
-    auto kern = axo::gemm_mixed_kernel<LA, LB, LINES && LB == axo::KC>;
-    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), axo::MIX_LDS_BYTES, &raised[2])) return AXO_ERR_HIP;
+    auto kern = axo::gemm_mixed_kernel<LA, LB, LINES>;
+    constexpr int lds = LINES ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised[2])) return AXO_ERR_HIP;
     const axo::TileSched sc = plan_product(g, LA, LB);
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), axo::MIX_LDS_BYTES, st, g, sc);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), lds, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 template <int LA, int LB>
@@ -565,8 +566,6 @@ struct Plan {
 // small tiles that ride along (Plan::small), bias gradients; at most GROUP_MAX_PRODUCTS of them, together no more
 // workgroups than a grid holds.
 int launch_group(const Plan* const* plans, int n, hipStream_t st) {
-    static std::atomic<uint64_t> raised{0};
-    if (!raise_lds_limit(reinterpret_cast<const void*>(axo::gemm_group_kernel), axo::MIX_LDS_BYTES, &raised)) return AXO_ERR_HIP;
     std::vector<GroupItem> items(n);
     for (int i = 0; i < n; ++i)
         items[i] = plans[i]->bias_grad ? GroupItem{plans[i]->bg.M, plans[i]->bg.Nl, 0, PAIR_BIAS_GRAD}
@@ -577,6 +576,7 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
     axo::GroupArgs ga{};
     ga.n_seg = (int)segs.size();
     int blocks = 0;
+    bool lines = false;
     for (int k = 0; k < ga.n_seg; ++k) {
         const SegCost& sc = segs[k];
         axo::GroupSeg& sg = ga.seg[k];
@@ -597,6 +597,11 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
             sg.group_m = std::min(sg.tiles_m, 8);
         } else {
             sg.kind = 2 * items[sc.item].pair + sc.small;
+            const Plan& pl = *plans[sc.item];
+            if (sg.kind != 1 && takes_lines(pl.g, pl.la, pl.lb, Tiles::big)) {
+                sg.kind += axo::GROUP_KIND_LINES;
+                lines = true;
+            }
             sg.tiles_m = (items[sc.item].Mo + 255) / 256;
             sg.cols = sc.count / sg.tiles_m;
             sg.col0 = sc.small ? cols[sc.item] * 256 : 0;
@@ -618,7 +623,11 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
         b.epilogue = plans[i]->bg.accumulate;
         ga.g[i] = b;
     }
-    hipLaunchKernelGGL(axo::gemm_group_kernel, dim3(blocks), dim3(axo::TILE_THREADS), axo::MIX_LDS_BYTES, st, ga);
+    static std::atomic<uint64_t> raised[2]{{0}, {0}};
+    auto kern = lines ? axo::gemm_group_kernel<true> : axo::gemm_group_kernel<false>;
+    const int lds = lines ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised[lines])) return AXO_ERR_HIP;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), lds, st, ga);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 

@@ -24,7 +24,7 @@ struct GroupSeg {
     int product;      // index into GroupArgs::g
     int kind;         // 2 * layout pair (0: KC/MC, 1: KC/KC, 2: MC/MC) + (1 if 256x128 tiles);
                       // GROUP_KIND_BIAS_GRAD: 64-column strips of a bias gradient; GROUP_KIND_SLIM + layout
-                      // pair: pairs of small tiles
+                      // pair: pairs of small tiles; GROUP_KIND_LINES + a kind of tiles: rows fetched by whole cache lines
     int tiles_m;      // tile rows
     int cols;         // tile columns of this segment
     int col0;         // first output column of this segment
@@ -33,6 +33,7 @@ struct GroupSeg {
 
 constexpr int GROUP_KIND_BIAS_GRAD = 6;
 constexpr int GROUP_KIND_SLIM = 7;  // + layout pair: 64 x 64 tiles of gemm_slim.hpp, two per workgroup
+constexpr int GROUP_KIND_LINES = 16;
 constexpr int GROUP_BIAS_COLS = 64;
 
 struct GroupArgs {
@@ -41,6 +42,8 @@ struct GroupArgs {
     GemmArgs g[GROUP_MAX_PRODUCTS];
 };
 
+// LINES: some segments are of a GROUP_KIND_LINES.  (A kernel of its own, so that the others keep their LDS size and registers.)
+template <bool LINES>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs ga) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
@@ -63,7 +66,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
         bias_grad_strip<GROUP_BIAS_COLS, TILE_THREADS>(bg, bid - sg.first_block, reinterpret_cast<float*>(smem));
         return;
     }
-    if (sg.kind >= GROUP_KIND_SLIM) {
+    if (sg.kind >= GROUP_KIND_SLIM && sg.kind < GROUP_KIND_LINES) {
         // A product on small tiles rides along: four waves per tile, two tiles per workgroup, each in its half of
         // the LDS.  (tiles_m x cols tiles; the second half of the last workgroup of an odd count runs on an empty
         // matrix, barrier included.)
@@ -87,6 +90,14 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
     int tm, tn;
     // workgroup ids with equal id % 8 share an XCD whatever the segment's first id is
     tile_of_index(xcd_run(bid - sg.first_block, sg.n_blocks), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
+    if constexpr (LINES) {
+        switch (sg.kind - GROUP_KIND_LINES) {
+            case 0: gemm_tile_body<256, 256, 2, 4, KC, MC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); return;
+            case 2: gemm_tile_body<256, 256, 2, 4, KC, KC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); return;
+            case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); return;
+            default: break;
+        }
+    }
     switch (sg.kind) {
         case 0: gemm_tile_body<256, 256, 2, 4, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
         case 1: gemm_ring_body<256, 128, 4, 2, 3, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;

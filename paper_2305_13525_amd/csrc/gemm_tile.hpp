@@ -248,18 +248,18 @@ __device__ __forceinline__ void line_load_offsets(int tid, const bf16_t* origin,
 template <int ROWS, int D>
 struct LineFragAddr {
     static constexpr int STAGE_STRIDE = ROWS * TILE_BK * 2;
-    uint32_t a[2], wrapped[2];  // per sub-step; `wrapped`: from the last stage, whose next one is stage 0
+    uint32_t a[2], last[2];  // per sub-step, from stage 0 and from the last stage, whose next one is stage 0
     __device__ __forceinline__ void init(int row0, int lane, uint32_t tile_base, const bf16_t* origin, int64_t ld) {
         const int r = row0 + (lane & 15), phase = line_phase(origin, ld, r);
 #pragma unroll
         for (int kq = 0; kq < 2; ++kq) {
             const int c = kq * 4 + (lane >> 4) + phase;
             a[kq] = tile_base + r * (TILE_BK * 2) + (((c & 7) ^ swz_kc(r)) << 4) + (c >> 3) * STAGE_STRIDE;
-            wrapped[kq] = a[kq] - (c >> 3) * (D * STAGE_STRIDE);
+            last[kq] = a[kq] + (D - 1) * STAGE_STRIDE - (c >> 3) * (D * STAGE_STRIDE);
         }
     }
     __device__ __forceinline__ bf16x8 read(const char* lds0, int s, int t, int kq) const {
-        return *reinterpret_cast<const bf16x8*>(lds0 + (s == D - 1 ? wrapped[kq] : a[kq]) + s * STAGE_STRIDE + t * (16 * TILE_BK * 2));
+        return *reinterpret_cast<const bf16x8*>(lds0 + (s == D - 1 ? last[kq] : a[kq] + s * STAGE_STRIDE) + t * (16 * TILE_BK * 2));
     }
 };
 
@@ -578,8 +578,11 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
     }
 }
 
-// One BM x BN output tile with its top-left corner at (i0, j0), whole reduction.
-template <int BM, int BN, int WGM, int WGN, int LA, int LB>
+// One BM x BN output tile with its top-left corner at (i0, j0), whole reduction.  LINES: the rows of A, which is KC, are
+// fetched by whole cache lines (line_phase), on three stages; with them and two of B the LDS is full, so rows of B that
+// do not start on lines still put every segment into two.  The loads of a step then touch 768 lines (dgrad) or 576 (forward) instead
+// of 1024 or 832.
+template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool LINES = false>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
     using C = TileCfg<BM, BN, WGM, WGN>;
     const int tid = threadIdx.x;
@@ -615,14 +618,19 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     const uint32_t a_step = (uint32_t)((LA == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.lda * 2);
     const uint32_t b_step = (uint32_t)((LB == KC) ? TILE_BK * 2 : (int64_t)TILE_BK * g.ldb * 2);
     uint32_t a_off[C::A_ROUNDS], b_off[C::B_ROUNDS];
-    load_offsets<BM, LA, C::A_ROUNDS, C::THREADS>(tid, g.lda, a_off);
+    uint32_t a_later[C::A_ROUNDS];
+    if constexpr (LINES) line_load_offsets<C::A_ROUNDS, C::THREADS>(tid, Ab, g.lda, a_off, a_later);
+    else load_offsets<BM, LA, C::A_ROUNDS, C::THREADS>(tid, g.lda, a_off);
     load_offsets<BN, LB, C::B_ROUNDS, C::THREADS>(tid, g.ldb, b_off);
 
-    // LDS side: [A stage 0][A stage 1][B stage 0][B stage 1]; fragment addresses of stage 0
-    FragAddr<BM, LA, C::TM> fra;
+    // LDS side: [A stage 0][A stage 1][B stage 0][B stage 1] (LINES: three stages of A); fragment addresses of stage 0
+    static_assert(!LINES || LA == KC, "lines of rows");
+    constexpr int A_STAGES = LINES ? 3 : 2;
+    std::conditional_t<LINES, LineFragAddr<BM, A_STAGES>, FragAddr<BM, LA, C::TM>> fra;
     FragAddr<BN, LB, C::TN> frb;
-    fra.init(wm * C::WTM, lane, 0);
-    frb.init(wn * C::WTN, lane, 2 * C::A_BYTES);
+    if constexpr (LINES) fra.init(wm * C::WTM, lane, 0, Ab, g.lda);
+    else fra.init(wm * C::WTM, lane, 0);
+    frb.init(wn * C::WTN, lane, A_STAGES * C::A_BYTES);
 
     f32x4 acc[C::TM][C::TN];
 #pragma unroll
@@ -669,17 +677,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
                      : "v"(off), "s"(rsrc), "s"(soff), "{m0}"(lds_dst)
                      : "memory");
     };
-    // Loads LO..HI-1 of the NL loads that fill stage s with the step at (a_soff, b_soff): the A
-    // rounds first, then the B rounds; round j of wave w lands at tile + (j * 512 + w * 64 + lane) * 16.
-    auto issue_range = [&](auto lo_tag, auto hi_tag, int s) __attribute__((always_inline)) {
+    // Loads LO..HI-1 of the NL loads that fill stage sa of A and stage s of B with the step at (a_soff, b_soff): the A
+    // rounds first, then the B rounds; round j of wave w lands at tile + (j * 512 + w * 64 + lane) * 16.  (LINES: what
+    // is loaded of A with a step of B is the stage behind that step's.)
+    auto issue_range = [&](auto lo_tag, auto hi_tag, int sa, int s) __attribute__((always_inline)) {
         constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
 #pragma unroll
         for (int j = LO; j < HI; ++j) {
             if (j < C::A_ROUNDS) {
-                load_lds(smem_base + s * C::A_BYTES + (j * C::THREADS + wave * 64) * 16, a_off[j], a_rsrc, a_soff);
+                load_lds(smem_base + sa * C::A_BYTES + (j * C::THREADS + wave * 64) * 16, a_off[j], a_rsrc, a_soff);
             } else {
                 const int jb = j - C::A_ROUNDS;
-                load_lds(smem_base + 2 * C::A_BYTES + s * C::B_BYTES + (jb * C::THREADS + wave * 64) * 16,
+                load_lds(smem_base + A_STAGES * C::A_BYTES + s * C::B_BYTES + (jb * C::THREADS + wave * 64) * 16,
                          b_off[jb], b_rsrc, b_soff);
             }
         }
@@ -709,14 +718,14 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     // its end is overwritten with zeros in LDS once the stage has landed, by the lane
     // that fetched them (round j of thread tid filled slot q = j * THREADS + tid of the tile: row
     // q / 8, LDS chunk q % 8, which holds global chunk (q % 8) ^ swz_kc(row), i.e. reduction
-    // elements 8 * that onwards).  `rem` = reduction elements of the stage that are real.
-    auto zero_tail = [&](auto s_tag, const int rem) __attribute__((always_inline)) {
-        constexpr int s = decltype(s_tag)::value;
-        auto clear = [&](auto part_tag, char* base, const int rounds) __attribute__((always_inline)) {
+    // elements 8 * that onwards).  `step`: 0 for step KT - 2, in stage 0, 1 for step KT - 1, in stage 1.
+    auto zero_tail = [&](const int step) __attribute__((always_inline)) {
+        auto clear = [&](auto part_tag, auto lines_tag, char* base, const int rounds, const int rem) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < rounds; ++j) {
                 const int q = j * C::THREADS + tid, r = q >> 3, cs = q & 7;
-                const int left = rem - ((cs ^ swz_kc(r)) << 3);
+                const int phase = decltype(lines_tag)::value ? line_phase(Ab, g.lda, r) : 0;
+                const int left = rem - (((cs ^ swz_kc(r)) - phase) << 3);
                 u32x4* const p = reinterpret_cast<u32x4*>(base + q * 16);
                 if (!decltype(part_tag)::value) {
                     if (left <= 0) *p = u32x4{0u, 0u, 0u, 0u};
@@ -724,8 +733,12 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
             }
         };
         auto clear_both = [&](auto part_tag) __attribute__((always_inline)) {
-            if (LA == KC) clear(part_tag, smem + s * C::A_BYTES, C::A_ROUNDS);
-            if (LB == KC) clear(part_tag, smem + 2 * C::A_BYTES + s * C::B_BYTES, C::B_ROUNDS);
+            const int rem = g.R - (KT - 2 + step) * TILE_BK;
+            if (LINES) {  // stages KT - 2 and KT - 1 of A with step KT - 2 of B, stage KT with step KT - 1
+                if (step == 0) clear(part_tag, IC<1>{}, smem, C::A_ROUNDS, rem);
+                clear(part_tag, IC<1>{}, smem + (step + 1) * C::A_BYTES, C::A_ROUNDS, rem - TILE_BK);
+            } else if (LA == KC) clear(part_tag, IC<0>{}, smem + step * C::A_BYTES, C::A_ROUNDS, rem);
+            if (LB == KC) clear(part_tag, IC<0>{}, smem + A_STAGES * C::A_BYTES + step * C::B_BYTES, C::B_ROUNDS, rem);
         };
         // Only a length that is no multiple of 8 ends inside a chunk.  The others do without the code that may read
         // one back: dgrad 8272 x 6328, reduction 712, 125 us with it, 119 without; 9864 x 2568 x 336 45.7 and 42.8; forward
@@ -735,33 +748,34 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     };
     // `fix` (first of the two tail steps only): stage s^1 holds the last step, which has just
     // landed; its chunks beyond the end of the reduction are zeroed before the barrier publishes it.
-    auto step = [&](auto s_tag, const bool head, const bool load, const bool next, const bool fix) __attribute__((always_inline)) {
+    auto step = [&](const int sa, auto s_tag, const bool head, const bool load, const bool next, const bool fix) __attribute__((always_inline)) {
         constexpr int s = decltype(s_tag)::value;
+        const int sa_next = sa + 1 < A_STAGES ? sa + 1 : 0, sa_head = sa > 0 ? sa - 1 : A_STAGES - 1;  // of the next step; being filled
         AXO_SETPRIO(2);
-        if (head) issue_range(IC<E4>{}, IC<E1>{}, s ^ 1);
-        read_a(1, s, 0, 1);
+        if (head) issue_range(IC<E4>{}, IC<E1>{}, sa_head, s ^ 1);
+        read_a(1, sa, 0, 1);
         mfma_group(0, 0, 0);  // (kq 0, ah 0)
         Interleave<N_MFMA, 0, RD_A, 0>::run();
         AXO_SETPRIO(1);
         if (head) {
-            issue_range(IC<E1>{}, IC<E2>{}, s ^ 1);
+            issue_range(IC<E1>{}, IC<E2>{}, sa_head, s ^ 1);
             advance();
         }
-        read_a(0, s, 1, 0);
+        read_a(0, sa, 1, 0);
         read_b(1, s, 1);
         mfma_group(1, 0, 1);  // (kq 0, ah 1)
         Interleave<N_MFMA, 0, RD_A + RD_B, 0>::run();
         AXO_SETPRIO(0);
-        read_a(1, s, 1, 1);
+        read_a(1, sa, 1, 1);
         mfma_group(0, 1, 0);  // (kq 1, ah 0)
         Interleave<N_MFMA, 0, RD_A, 0>::run();
         __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-        if (fix) zero_tail(IC<s ^ 1>{}, g.R - (KT - 1) * TILE_BK);
+        if (fix) zero_tail(1);
         __syncthreads();
         AXO_SETPRIO(3);
-        if (load) issue_range(IC<0>{}, IC<E4>{}, s);
+        if (load) issue_range(IC<0>{}, IC<E4>{}, sa, s);
         if (next) {
-            read_a(0, s ^ 1, 0, 0);
+            read_a(0, sa_next, 0, 0);
             read_b(0, s ^ 1, 0);
         }
         mfma_group(1, 1, 1);  // (kq 1, ah 1)
@@ -770,17 +784,42 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     using T0 = std::integral_constant<int, 0>;
     using T1 = std::integral_constant<int, 1>;
 
-    // KT is even and at least 2
-    issue_range(IC<0>{}, IC<NL>{}, 0);
+    // KT is even and at least 2.  LINES: the walk ends in stages 0 and 1 of A and starts in the one that takes.
+    const int first = LINES ? (KT - 2) % 6 / 2 : 0;
+    auto a_stage = [&](int n) __attribute__((always_inline)) { return first + n < A_STAGES ? first + n : first + n - A_STAGES; };
+    if constexpr (LINES) {
+        issue_range(IC<0>{}, IC<C::A_ROUNDS>{}, first, 0);
+#pragma unroll
+        for (int j = 0; j < C::A_ROUNDS; ++j) a_off[j] = a_later[j];
+    }
+    issue_range(IC<0>{}, IC<NL>{}, LINES ? a_stage(1) : 0, 0);
     advance();
-    issue_range(IC<0>{}, IC<E4>{}, 1);  // step 0 issues the rest of stage 1
-    AXO_WAIT_VMCNT(E4);                 // stage 0 has landed
+    issue_range(IC<0>{}, IC<E4>{}, LINES ? a_stage(2) : 1, 1);  // step 0 issues the rest of stage 1
+    AXO_WAIT_VMCNT(E4);                                         // what step 0 needs has landed
     __syncthreads();
-    read_a(0, 0, 0, 0);
+    read_a(0, first, 0, 0);
     read_b(0, 0, 0);
-    for (int j = 0; j + 2 < KT; j += 2) {  // steady state, branch free: steps j, j+1; refills j+2, j+3
-        step(T0{}, true, true, true, false);
-        step(T1{}, true, true, true, false);
+    if constexpr (LINES) {
+        int sa = first;
+#pragma nounroll
+        for (int n = first; n > 0; --n) {  // (KT - 2) % 6 steps
+            step(sa, T0{}, true, true, true, false);
+            step(sa + 1 < 3 ? sa + 1 : 0, T1{}, true, true, true, false);
+            sa = sa > 0 ? sa - 1 : 2;
+        }
+        for (int n = (KT - 2) / 6; n > 0; --n) {
+            step(0, T0{}, true, true, true, false);
+            step(1, T1{}, true, true, true, false);
+            step(2, T0{}, true, true, true, false);
+            step(0, T1{}, true, true, true, false);
+            step(1, T0{}, true, true, true, false);
+            step(2, T1{}, true, true, true, false);
+        }
+    } else {
+        for (int j = 0; j + 2 < KT; j += 2) {  // steady state, branch free: steps j, j+1; refills j+2, j+3
+            step(0, T0{}, true, true, true, false);
+            step(1, T1{}, true, true, true, false);
+        }
     }
     // The last two steps: nothing left to load.  Step KT-2 sits in stage 0, landed and published
     // (by the barrier of the step before, or the one above); where the reduction ends inside it
@@ -788,13 +827,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     // were read ahead are read again.
     const bool fix = (LA == KC || LB == KC) && tail;
     if (fix) {
-        zero_tail(T0{}, g.R - (KT - 2) * TILE_BK);
+        zero_tail(0);
         __syncthreads();
         read_a(0, 0, 0, 0);
         read_b(0, 0, 0);
     }
-    step(T0{}, true, false, true, fix);
-    step(T1{}, false, false, false, false);
+    step(0, T0{}, true, false, true, fix);
+    step(1, T1{}, false, false, false, false);
     AXO_SETPRIO(0);
 
     if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
@@ -989,6 +1028,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
 using MixBigCfg = TileCfg<256, 256, 2, 4>;
 using MixSmallCfg = RingCfg<256, 128, 4, 2, 3>;
 constexpr int MIX_LDS_BYTES = MixBigCfg::LDS_BYTES > MixSmallCfg::LDS_BYTES ? MixBigCfg::LDS_BYTES : MixSmallCfg::LDS_BYTES;
+constexpr int LINES_LDS_BYTES = 3 * MixBigCfg::A_BYTES + 2 * MixBigCfg::B_BYTES;
+static_assert(LINES_LDS_BYTES >= MIX_LDS_BYTES && LINES_LDS_BYTES <= 160 * 1024, "LDS of one CU");
 
 // Origin of a tile that would reach over the output's edge, moved back inside where that is possible, so that it
 // is a whole tile: the elements it then shares with its neighbour are computed twice, by the same instructions
@@ -1013,11 +1054,11 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     int tm, tn;
     if (bid < sc.n_big) {
         tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
-        gemm_tile_body<256, 256, 2, 4, LA, LB>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
+        gemm_tile_body<256, 256, 2, 4, LA, LB, LINES>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
         tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
+        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES && LB == KC>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
     }
 }
 

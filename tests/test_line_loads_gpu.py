@@ -1,5 +1,4 @@
-"""Operands whose rows start anywhere in a cache line.  Products on 64 x 64, 128 x 128 and half-width tiles fetch such rows by
-whole lines; where the rows lie must not show in the result, which is compared bit for bit with that of the same values in
+"""Operands whose rows start anywhere in a cache line.  Products on ring tiles and 256 x 256 tiles fetch such rows by whole lines; where the rows lie must not show in the result, which is compared bit for bit with that of the same values in
 rows that start on lines.  Everything around the operands is NaN."""
 import pytest
 import torch
@@ -10,6 +9,7 @@ import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 SMALL, MID, HALF = axo.AXO_KERNEL_TILES_64, axo.AXO_KERNEL_TILES_128, axo.AXO_KERNEL_TILES_256_HALF
+WHOLE, MIXED = axo.AXO_KERNEL_TILES_256, axo.AXO_KERNEL_TILES_256_MIXED
 
 
 def placed(values, extra, shift):
@@ -28,7 +28,9 @@ def placed(values, extra, shift):
     (1030, 1021, 768, SMALL), (1000, 1000, 820, SMALL), (1030, 1021, 903, SMALL), (970, 1030, 960, SMALL), (1000, 1016, 1025, SMALL),
     (2000, 1016, 512, SMALL), (1999, 1000, 579, SMALL),
     (2040, 2001, 512, MID), (2048, 2048, 570, MID), (2001, 2040, 640, MID), (1900, 2000, 725, MID),
-    (4090, 1530, 1024, HALF), (4096, 1536, 1100, HALF), (4001, 1519, 1151, HALF)])
+    (4090, 1530, 1024, HALF), (4096, 1536, 1100, HALF), (4001, 1519, 1151, HALF),
+    (4096, 4096, 512, WHOLE), (4096, 4096, 520, WHOLE), (4080, 4096, 701, WHOLE), (4096, 4090, 830, WHOLE), (4096, 4096, 903, WHOLE),
+    (4096, 4096, 1025, WHOLE), (4096, 4096, 1151, WHOLE), (4000, 6000, 2000, MIXED)])
 @pytest.mark.parametrize("op", [axo.AXO_OP_FWD, axo.AXO_OP_DGRAD])
 def test_where_rows_lie_does_not_show(Mo, No, R, kernel, op):
     gen = torch.Generator(device="cuda:0")
@@ -51,3 +53,25 @@ def test_where_rows_lie_does_not_show(Mo, No, R, kernel, op):
     # (rows of A, shift of A, rows of B, shift of B): every phase of a row in its line, in one operand, the other and both
     for place in [(i, 0, i, 0) for i in range(1, 8)] + [(0, 3, 0, 0), (0, 0, 0, 5), (0, 7, 0, 1), (3, 2, 0, 0), (0, 0, 6, 1), (1, 7, 5, 4)]:
         assert torch.equal(run(placed(a, *place[:2]), placed(b, *place[2:])), want), place
+
+
+@pytest.mark.parametrize("M,K,N", [(4096, 1536, 4608), (3000, 1100, 2001)])
+def test_nor_in_a_chain(M, K, N):
+    """The same for the products of a layer in one grouped launch."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(M)
+    normal = lambda r, c: torch.randn(r, c, device="cuda:0", generator=gen).to(torch.bfloat16)  # noqa: E731
+    p, x, w, dy = axo.Problem.make((1, 1, 1), (0, 0, 0), M, K, N), normal(M, K), normal(K, N), normal(M, N)
+
+    def run(extra, shift):
+        X, W, dY = (placed(t, extra, shift) for t in (x, w, dy))
+        outs = [torch.zeros((r, (c + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda:0") for r, c in ((M, N), (M, K), (K, N))]
+        layer = axo.Layer(p, 0, 0, X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), None, outs[0].data_ptr(), outs[0].stride(0),
+                          dY.data_ptr(), dY.stride(0), outs[1].data_ptr(), outs[1].stride(0), outs[2].data_ptr(), outs[2].stride(0))
+        axo.axo_layer_step([layer], None, 0, gu.stream())
+        torch.cuda.synchronize()
+        return [o.view(torch.int16) for o in outs]
+
+    want = run(0, 0)
+    for place in [(i, 0) for i in range(1, 8)] + [(0, 3), (2, 7)]:
+        assert all(torch.equal(a, b) for a, b in zip(run(*place), want)), place
