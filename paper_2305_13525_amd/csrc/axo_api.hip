@@ -430,7 +430,7 @@ struct GroupItem {
 
 struct SegCost {
     double cost;
-    int count, item, small;
+    int count, item, small;  // small: 1 half-width tiles, 2 pairs of 64 x 64 tiles
 };
 
 // A bias gradient inside a grouped launch (GroupItem::pair == PAIR_BIAS_GRAD, Mo = rows, No =
@@ -443,6 +443,10 @@ constexpr int PAIR_BIAS_GRAD = 3;
 constexpr int PAIR_SLIM = 4;
 double slim_pair_cost(int R, int pair) { return 2.0 * slim_tile_us(SLIM_MODEL[1], R, pair) / 1.33; }
 int slim_pair_blocks(int Mo, int No) { return (int)((tiles_in(Mo, 64) * tiles_in(No, 64) + 1) / 2); }
+// The same for a product that could take 256-row tiles: a pair of 64 x 64 ring tiles takes 2.2 us and 0.33 per step.  The planner
+// weighs them as one more split (PAIRS in place of a number of columns); all these tiles give the same bits.
+constexpr int PAIRS = -1, MOST_PAIRS = 8 * NUM_CU;
+double pair_cost(int R) { return (2.2 + 0.33 * steps_in(R)) / 1.33; }
 double bias_strip_cost(int rows) { return 1.0 + 15.0 * rows / 4096.0; }
 int bias_strips(int cols) { return (cols + axo::GROUP_BIAS_COLS - 1) / axo::GROUP_BIAS_COLS; }
 // The standalone launch picks its strip width by shape; only shapes for which it picks the
@@ -459,6 +463,10 @@ std::vector<SegCost> group_segments(const std::vector<GroupItem>& items, const s
         }
         if (items[i].pair >= PAIR_SLIM) {
             segs.push_back({slim_pair_cost(items[i].R, items[i].pair - PAIR_SLIM), slim_pair_blocks(items[i].Mo, items[i].No), (int)i, 0});
+            continue;
+        }
+        if (big_cols[i] == PAIRS) {
+            segs.push_back({pair_cost(items[i].R), slim_pair_blocks(items[i].Mo, items[i].No), (int)i, 2});
             continue;
         }
         const int tiles_m = (items[i].Mo + 255) / 256, cb = big_cols[i], cs = half_cols(items[i].No, cb);
@@ -519,20 +527,25 @@ std::vector<int> plan_group(const std::vector<GroupItem>& items) {
         int& c = cols[k % n];
         if (it.pair >= PAIR_BIAS_GRAD) continue;
         const double tiles_m = (double)tiles_in(it.Mo, 256), big = tile_cost(it.R, false), half = tile_cost(it.R, true);
-        auto work_of = [&](int big_cols) { return tiles_m * (big_cols * big + half_cols(it.No, big_cols) * half); };
+        const int64_t pairs = (tiles_in(it.Mo, 64) * tiles_in(it.No, 64) + 1) / 2;
+        auto work_of = [&](int big_cols) {
+            return big_cols == PAIRS ? pairs * pair_cost(it.R) : tiles_m * (big_cols * big + half_cols(it.No, big_cols) * half);
+        };
         const int max_cols = (int)tiles_in(it.No, 256), now = c;
         const int stride = max_cols > 16 ? (max_cols + 15) / 16 : 1;
         const double others = work - work_of(now);
         int best_c = now;
-        for (int to = max_cols; to >= 0; to -= stride) {
-            if (to == now || (others + work_of(to)) / NUM_CU > best * (1.0 + 1e-9)) continue;
+        auto consider = [&](int to, double margin) {
+            if (to == now || (others + work_of(to)) / NUM_CU > best * (1.0 + 1e-9)) return;
             c = to;
             const double t = group_makespan(group_segments(items, cols));
-            if (t < best - 1e-9) {
+            if (t < best * margin - 1e-9) {
                 best = t;
                 best_c = to;
             }
-        }
+        };
+        for (int to = max_cols; to >= 0; to -= stride) consider(to, 1.0);
+        if (pairs <= MOST_PAIRS) consider(PAIRS, 0.92);  // only for a clear gain: among large tiles they cost more than estimated
         c = best_c;
         if (best_c != now) {
             work = others + work_of(best_c);
@@ -591,6 +604,12 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
             sg.group_m = 1;
         } else if (items[sc.item].pair >= PAIR_SLIM) {
             sg.kind = axo::GROUP_KIND_SLIM + items[sc.item].pair - PAIR_SLIM;
+            sg.tiles_m = (items[sc.item].Mo + 63) / 64;
+            sg.cols = (items[sc.item].No + 63) / 64;
+            sg.col0 = 0;
+            sg.group_m = std::min(sg.tiles_m, 8);
+        } else if (sc.small == 2) {
+            sg.kind = axo::GROUP_KIND_PAIR + items[sc.item].pair;
             sg.tiles_m = (items[sc.item].Mo + 63) / 64;
             sg.cols = (items[sc.item].No + 63) / 64;
             sg.col0 = 0;
@@ -1140,7 +1159,7 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
     std::vector<const Plan*> riders;  // bias gradients of the level that may share their launch
     int64_t group_blocks = 0;         // at most so many workgroups in the group so far
     auto blocks_of = [](const Plan& pl) -> int64_t {
-        return pl.bias_grad ? bias_strips(pl.bg.Nl) : pl.small ? slim_pair_blocks(pl.g.Mo, pl.g.No) : most_tile_blocks(pl.g);
+        return pl.bias_grad ? bias_strips(pl.bg.Nl) : pl.small ? slim_pair_blocks(pl.g.Mo, pl.g.No) : std::max<int64_t>(most_tile_blocks(pl.g), MOST_PAIRS);
     };
     auto joins = [&](const Plan& pl) { return grid_fits(group_blocks + blocks_of(pl), axo::TILE_THREADS); };
     auto join = [&](const Plan* pl) {

@@ -33,6 +33,7 @@ struct GroupSeg {
 
 constexpr int GROUP_KIND_BIAS_GRAD = 6;
 constexpr int GROUP_KIND_SLIM = 7;  // + layout pair: 64 x 64 tiles of gemm_slim.hpp, two per workgroup
+constexpr int GROUP_KIND_PAIR = 10;  // + layout pair: 64 x 64 tiles of a ring, two per workgroup
 constexpr int GROUP_KIND_LINES = 16;
 constexpr int GROUP_BIAS_COLS = 64;
 
@@ -66,7 +67,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
         bias_grad_strip<GROUP_BIAS_COLS, TILE_THREADS>(bg, bid - sg.first_block, reinterpret_cast<float*>(smem));
         return;
     }
-    if (sg.kind >= GROUP_KIND_SLIM && sg.kind < GROUP_KIND_LINES) {
+    if (sg.kind >= GROUP_KIND_SLIM && sg.kind < GROUP_KIND_PAIR) {
         // A product on small tiles rides along: four waves per tile, two tiles per workgroup, each in its half of
         // the LDS.  (tiles_m x cols tiles; the second half of the last workgroup of an odd count runs on an empty
         // matrix, barrier included.)
@@ -87,6 +88,24 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
         }
         return;
     }
+    if (sg.kind >= GROUP_KIND_PAIR && sg.kind < GROUP_KIND_LINES) {
+        // Two 64 x 64 tiles of a product, each on four waves and in its half of the LDS; the halves take the same number of
+        // steps, so they share the barriers of both walks.
+        using C = SmallCfg<false>;
+        static_assert(2 * C::THREADS == TILE_THREADS && 2 * C::LDS_BYTES <= MIX_LDS_BYTES, "two tiles per workgroup");
+        const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / C::THREADS), tiles = sg.tiles_m * sg.cols;
+        const int t = 2 * xcd_run(bid - sg.first_block, sg.n_blocks) + half, tid = threadIdx.x % C::THREADS;
+        int tm, tn;
+        tile_of_index(min(t, tiles - 1), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
+        char* const lds = smem + half * C::LDS_BYTES;
+        const int j0 = inside_col<64>(g, tn * 64);
+        switch (sg.kind - GROUP_KIND_PAIR) {
+            case 0: gemm_ring_body<64, 64, 2, 2, 4, KC, MC>(g, inside_row<64, KC>(g, tm * 64), j0, lds, tid, t < tiles); break;
+            case 1: gemm_ring_body<64, 64, 2, 2, 4, KC, KC>(g, inside_row<64, KC>(g, tm * 64), j0, lds, tid, t < tiles); break;
+            default: gemm_ring_body<64, 64, 2, 2, 4, MC, MC>(g, inside_row<64, MC>(g, tm * 64), j0, lds, tid, t < tiles); break;
+        }
+        return;
+    }
     int tm, tn;
     // workgroup ids with equal id % 8 share an XCD whatever the segment's first id is
     tile_of_index(xcd_run(bid - sg.first_block, sg.n_blocks), sg.tiles_m, sg.cols, sg.group_m, tm, tn);
@@ -94,17 +113,17 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_group_kernel(GroupArgs g
         switch (sg.kind - GROUP_KIND_LINES) {
             case 0: gemm_tile_body<256, 256, 2, 4, KC, MC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); return;
             case 2: gemm_tile_body<256, 256, 2, 4, KC, KC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); return;
-            case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); return;
+            case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC, true>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem, threadIdx.x); return;
             default: break;
         }
     }
     switch (sg.kind) {
         case 0: gemm_tile_body<256, 256, 2, 4, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        case 1: gemm_ring_body<256, 128, 4, 2, 3, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
+        case 1: gemm_ring_body<256, 128, 4, 2, 3, KC, MC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem, threadIdx.x); break;
         case 2: gemm_tile_body<256, 256, 2, 4, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
+        case 3: gemm_ring_body<256, 128, 4, 2, 3, KC, KC>(g, inside_row<256, KC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem, threadIdx.x); break;
         case 4: gemm_tile_body<256, 256, 2, 4, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<256>(g, sg.col0 + tn * 256), smem); break;
-        default: gemm_ring_body<256, 128, 4, 2, 3, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem); break;
+        default: gemm_ring_body<256, 128, 4, 2, 3, MC, MC>(g, inside_row<256, MC>(g, tm * 256), inside_col<128>(g, sg.col0 + tn * 128), smem, threadIdx.x); break;
     }
 }
 

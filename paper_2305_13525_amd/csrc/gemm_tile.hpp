@@ -854,10 +854,12 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 // the compiler waits for all LDS reads in flight, those of the other sub-step too.  Peeled: forward 1024 x 1024 with
 // reduction 4096 on 64 x 64 tiles 18.7 -> 14.6 us, dgrad 2048^3 on 128 x 128 ones 18.6 -> 16.5, dgrad 4096 x 2048 with
 // reduction 6144 on half-width ones 80.3 -> 76.2, 10600 x 7736 with reduction 48 73.4 -> 66.4.
+// `tid`: among the threads that work on the tile; `store`: false for a tile whose results are not wanted, as the second of a
+// pair of workgroup halves that has none (both halves meet at the same barriers).
 template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB, bool LINES = false>
-__device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
+__device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, const int j0, char* smem, const int tid,
+                                               const bool store = true) {
     using C = RingCfg<BM, BN, WGM, WGN, D>;
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
@@ -1021,7 +1023,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
     const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No && (C::WTN == 64 || g.epilogue != EPI_ACC_F32);
-    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    if (!store) __syncthreads();  // the one of an epilogue
+    else if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
@@ -1058,7 +1061,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
         tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES && LB == KC>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem);
+        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES && LB == KC>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem, threadIdx.x);
     }
 }
 
@@ -1075,7 +1078,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
-    gemm_ring_body<128, 128, 4, 2, 4, LA, LB, LINES>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem);
+    gemm_ring_body<128, 128, 4, 2, 4, LA, LB, LINES>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem, threadIdx.x);
 }
 
 // The same for smaller outputs: 64 x 64, four waves of 32 x 32 on a four-stage ring, two workgroups per CU.  (Five stages are
@@ -1091,7 +1094,7 @@ __global__ void __launch_bounds__(256, 2) gemm_small_kernel(GemmArgs g, int tile
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
-    gemm_ring_body<64, 64, 2, 2, LINES ? 5 : 4, LA, LB, LINES>(g, inside_row<64, LA>(g, tm * 64), inside_col<64>(g, tn * 64), smem);
+    gemm_ring_body<64, 64, 2, 2, LINES ? 5 : 4, LA, LB, LINES>(g, inside_row<64, LA>(g, tm * 64), inside_col<64>(g, tn * 64), smem, threadIdx.x);
 }
 
 }  // namespace axo
