@@ -80,7 +80,8 @@ __device__ __forceinline__ float gelu_tanh(float v) {
 // most up to a = 14, where the tail is below the normal range of floats.  (A minimax fit made for this file: weighted least
 // squares with reweighting by the error.)  Straight-line code of one reciprocal and one exp2, because an epilogue
 // runs it on every output: with erfcf, which branches over ranges and a wave takes all of them, forward, dgrad and wgrad of
-// 4000 x 2000 x 6000 took 326 us (the forward without an epilogue 34 less), now 310; 1001 x 1027 x 515 with it in the data gradient 32.4, now 29.3.  Errors against 64 bits, over |v| < 13, are at or below those of the erfcf form in every
+// 4000 x 2000 x 6000 took 326 us (the forward without an epilogue 34 less), with this 310; 1001 x 1027 x 515 with it in the data
+// gradient 32.4 and 29.3.  Errors against 64 bits, over |v| < 13, are at or below those of the erfcf form in every
 // range: 3e-8 to 7e-8 rms for v > -1, 1.4e-7 on [-3, -1], 2.3e-6 on [-13, -9], where that form had 4.1e-6.
 __device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss) {
     const float a = fminf(__builtin_fabsf(v), 14.0f);  // an infinite v has gauss = 0 and wants a finite ratio
