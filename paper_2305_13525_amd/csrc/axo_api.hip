@@ -283,8 +283,8 @@ axo::TileSched plan_product(const GemmArgs& g, int la, int lb) {
 // (line_phase): where such rows start elsewhere than on lines and the reduction is long enough to pay for the later start and the
 // one stage more.  Without / with it, rows 16 bytes off unless sizes say it, in us:
 //   64 x 64    dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83, 12.0 / 9.3; 1001 x 1027 (272 tiles) with 9 steps
-//              6.25 / 6.62; 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35; 2000 x 1000 x 3000 27.8 / 20.6
-//   128 x 128  dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3, 23.1 / 20.5
+//              6.25 / 6.62; 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35; 2000 x 1000 x 3000 27.8 / 20.0
+//   128 x 128  dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3, 23.1 / 19.2
 //   256 x 128  dgrad 4096 x 2048 with 8 / 16 / 96 steps 16.1 / 16.1, 23.4 / 22.4, 97 / 87; not in forward, where only the first
 //              operand is of that kind (4096 x 1536 x 1536 24.6 / 24.9)
 //   256 x 256  dgrad 4096 x 4096 x 8192 260 / 226, 8192 x 8192 x 2000 272 / 233, 8000 x 8000 x 520 87 / 82; forward

@@ -230,6 +230,9 @@ struct FragAddr {
 __device__ __forceinline__ int line_phase(const bf16_t* origin, int64_t ld, int r) {
     return (int)((uint32_t)(reinterpret_cast<uint64_t>(origin) >> 4) + (uint32_t)r * (uint32_t)(ld >> 3)) & 7;
 }
+// Chunk c of a step lies in its stage where it lies without phases, c ^ swz_kc, so that fragment reads stay free of bank conflicts
+// (at its place in the line, 30-50 % of the LDS cycles were conflicts).  Stage j thus holds there chunk 8 j + line_chunk(c, phase).
+__device__ __forceinline__ int line_chunk(int c, int phase) { return c + phase < 8 ? c : c - 8; }
 // load_offsets for that: `first` for stage 0, where chunks in front of the row are replaced by its first one; `later`
 // counts from the line behind stage 0's, so that it is never negative.
 template <int ROUNDS, int THREADS>
@@ -237,7 +240,7 @@ __device__ __forceinline__ void line_load_offsets(int tid, const bf16_t* origin,
 #pragma unroll
     for (int j = 0; j < ROUNDS; ++j) {
         const int q = j * THREADS + tid, r = q >> 3, cs = q & 7;
-        const int chunk = (cs ^ swz_kc(r)) - line_phase(origin, ld, r);
+        const int chunk = line_chunk(cs ^ swz_kc(r), line_phase(origin, ld, r));
         const uint32_t row = (uint32_t)r * (uint32_t)(ld * 2);  // the caller sees to it that offsets stay below 2^32
         first[j] = row + (uint32_t)(max(chunk, 0) * 16);
         later[j] = row + (uint32_t)((chunk + 8) * 16);
@@ -254,7 +257,7 @@ struct LineFragAddr {
 #pragma unroll
         for (int kq = 0; kq < 2; ++kq) {
             const int c = kq * 4 + (lane >> 4) + phase;
-            a[kq] = tile_base + r * (TILE_BK * 2) + (((c & 7) ^ swz_kc(r)) << 4) + (c >> 3) * STAGE_STRIDE;
+            a[kq] = tile_base + r * (TILE_BK * 2) + (((c - phase) ^ swz_kc(r)) << 4) + (c >> 3) * STAGE_STRIDE;
             last[kq] = a[kq] + (D - 1) * STAGE_STRIDE - (c >> 3) * (D * STAGE_STRIDE);
         }
     }
@@ -725,7 +728,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
             for (int j = 0; j < rounds; ++j) {
                 const int q = j * C::THREADS + tid, r = q >> 3, cs = q & 7;
                 const int phase = decltype(lines_tag)::value ? line_phase(Ab, g.lda, r) : 0;
-                const int left = rem - (((cs ^ swz_kc(r)) - phase) << 3);
+                const int left = rem - (line_chunk(cs ^ swz_kc(r), phase) << 3);
                 u32x4* const p = reinterpret_cast<u32x4*>(base + q * 16);
                 if (!decltype(part_tag)::value) {
                     if (left <= 0) *p = u32x4{0u, 0u, 0u, 0u};
@@ -1070,7 +1073,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
 // LDS traffic (128 KB per 515 cycles of MFMA), so this is no tile for larger outputs.  Eight waves rather than
 // four of 64 x 64 (a quarter less LDS traffic, but one wave per SIMD: 2048^3 21 us), four stages rather than two
 // and two workgroups per CU (24 us).  Measured against the 256-row tiles, forward / dgrad / wgrad: 2048^3
-// 25.6 / 24.9 / 24.2 -> 19.5 / 19.0 / 18.4 us, 1536^3 19.6 / 19.0 / 18.4 -> 14.4 / 13.8 / 13.2, wgrad 1536 x 1536 of 4096
+// 25.6 / 24.9 / 24.2 -> 18.2 / 17.4 / 18.2 us, 1536^3 19.6 / 19.0 / 18.4 -> 12.1 / 12.4 / 12.1, wgrad 1536 x 1536 of 4096
 // tokens 44 -> 30.  Sums run in the same order as on the other tiles: same bits.
 using MidCfg = RingCfg<128, 128, 4, 2, 4>;
 template <int LA, int LB, bool LINES>
@@ -1085,7 +1088,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
 // what two workgroups leave room for; they pay where a step needs two of them: 12.0 -> 9.3 us instead of 10.8 for dgrad 1024 x 1024
 // with 32 steps and rows 16 bytes off.)  Measured
 // against the small tiles whose waves split the reduction (gemm_slim.hpp), forward / dgrad / wgrad: 2048 x 1024 x 1024
-// 11.9 / 12.1 / 11.5 -> 9.4 / 8.5 / 10.2 us, 1000^3 10.0 / 9.6 / 10.2 -> 8.8 / 8.6 / 8.2, wgrad 1024 x 1024 of 8192 tokens 30
+// 11.9 / 12.1 / 11.5 -> 8.7 / 8.2 / 9.0 us, 1000^3 10.0 / 9.6 / 10.2 -> 7.3 / 6.6 / 7.9, wgrad 1024 x 1024 of 8192 tokens 29
 // both (128 x 128 tiles: 51).  Those stay quicker below some 100 tiles (300^3 3.7 against 5.4).
 template <bool LINES>
 using SmallCfg = RingCfg<64, 64, 2, 2, LINES ? 5 : 4>;
