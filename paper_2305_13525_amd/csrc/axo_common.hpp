@@ -83,7 +83,7 @@ __device__ __forceinline__ float gelu_tanh(float v) {
 // 4000 x 2000 x 6000 took 326 us (the forward without an epilogue 34 less), with this 310; 1001 x 1027 x 515 with it in the data
 // gradient 32.4 and 29.3.  Errors against 64 bits, over |v| < 13, are at or below those of the erfcf form in every
 // range: 3e-8 to 7e-8 rms for v > -1, 1.4e-7 on [-3, -1], 2.3e-6 on [-13, -9], where that form had 4.1e-6.
-__device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss) {
+__device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss, float up = 0.0f) {
     const float a = fminf(__builtin_fabsf(v), 14.0f);  // an infinite v has gauss = 0 and wants a finite ratio
     const float w = a * __builtin_amdgcn_rcpf(__builtin_fmaf(0.35f, a, 1.0f));
     float r = 3.2823087e-07f;
@@ -97,15 +97,21 @@ __device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss)
     r = __builtin_fmaf(r, w, 1.1036798e-01f);
     r = __builtin_fmaf(r, w, -3.9894214e-01f);
     ratio = __builtin_fmaf(r, w, 0.5f);
-    gauss = __builtin_amdgcn_exp2f(v * v * -0.72134752f);  // log2(e) / 2
+    gauss = __builtin_amdgcn_exp2f(__builtin_fmaf(v * v, -0.72134752f, up));  // log2(e) / 2
 }
 
-// GELU, erf form: v Phi(v), Phi(v) = Q(|v|) below zero and 1 - Q(v) above (no cancellation).
+// GELU, erf form: v Phi(v), Phi(v) = Q(|v|) below zero and 1 - Q(v) above (no cancellation).  The hardware's exp2 has no
+// results below 2^-126.  The Gaussian falls under that at v = -13.2, v Phi(v) leaves the subnormal numbers of bf16 only at -13.6; from
+// -13 on a factor of 2^64 keeps it in range and is taken back from the product.  On every value that cost 473 -> 490 us (forward
+// 32768 x 2048 x 4096), so epilogues ask first whether a wave has such a value at hand (FAR); all other values have the same bits either way.
+constexpr float GELU_ERF_FAR = -13.0f;
+template <bool FAR = true>
 __device__ __forceinline__ float gelu_erf(float v) {
+    const bool far = FAR && v < GELU_ERF_FAR;
     float ratio, gauss;
-    normal_tail(v, ratio, gauss);
-    const float q = ratio * gauss;
-    return v * (v < 0.0f ? q : 1.0f - q);
+    normal_tail(v, ratio, gauss, far ? 64.0f : 0.0f);
+    const float q = ratio * gauss, r = v * (v < 0.0f ? q : 1.0f - q);
+    return FAR ? __builtin_ldexpf(r, far ? -64 : 0) : r;
 }
 
 // d/dv of the tanh-form GELU.  With s = sigmoid(2 z): 0.5 (1 + tanh z) = s and 1 - tanh^2 z = 4 s (1 - s),

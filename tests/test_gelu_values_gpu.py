@@ -1,6 +1,8 @@
 """The GELU epilogues value by value: every bf16 number from 2^-20 to 13 in magnitude through a reduction of one term, whose
 sum is the number itself.  The epilogues compute in fp32 with relative errors below 1e-5 (3e-4 next to the derivative's zero, where no bf16
 number comes closer than 1e-3), far inside half a bf16 step (2e-3), so every result is the oracle's rounded once, or its neighbour."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -10,6 +12,14 @@ import paper_2305_13525_amd as axo
 import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
+
+
+def bf16_numbers(bits):
+    return (bits.astype(np.uint32) << np.uint32(16)).view(np.float32).astype(np.float64)
+
+
+def erf_tail(v):
+    return np.array([0.5 * math.erfc(-x / math.sqrt(2.0)) for x in v])
 
 
 def bf16_values(cols):
@@ -57,3 +67,22 @@ def test_infinities_and_nans():
         h = gu.to_host(Y)
         assert (h[0] == 0x7F80).all()
         assert ((h[1:] & 0x7FFF) > 0x7F80).all()
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (128, 8, 1, axo.AXO_KERNEL_TILES_64), (256, 256, 1, axo.AXO_KERNEL_TILES_64), (2000, 1000, 1, axo.AXO_KERNEL_TILES_128),
+    (4096, 1530, 1, axo.AXO_KERNEL_TILES_256_HALF), (4000, 4096, 1, axo.AXO_KERNEL_TILES_256), (200, 300, 400, axo.AXO_KERNEL_SPLIT_32)])
+def test_erf_form_down_its_tail(M, N, K, kernel):
+    """Every bf16 number from -8 to -16, against erfc in doubles, which does not cancel: the value keeps to one bf16 step down to the last
+    subnormal number (-9.2e-41 at -13.5), in tiles inside the output and over its edge."""
+    v = bf16_numbers(np.tile(np.arange(0xC100, 0xC180, dtype=np.uint16), -(-M // 128))[:M])
+    p, ldx, lead = axo.Problem.make((1, 1, 1), (0, 0, 0), M, K, N), -(-K // 8) * 8, -(-N // 8) * 8
+    assert axo.axo_fc_kernel(p, axo.AXO_OP_FWD, ldx, lead, lead)[1] == kernel
+    X, W = np.zeros((M, ldx), dtype=np.uint16), np.full((K, lead), 0x3F80, dtype=np.uint16)
+    X[:, 0] = (v.astype(np.float32).view(np.uint32) >> np.uint32(16)).astype(np.uint16)
+    Y = gu.empty_dev(M, lead)
+    gu.run_fwd(p, gu.to_dev(X), gu.to_dev(W), Y, gu.to_dev(np.zeros(N, dtype=np.uint16)), axo.AXO_EPI_BIAS_GELU_ERF)
+    torch.cuda.synchronize()
+    ref = v * erf_tail(v)
+    steps = oracle.ulp_distance_bf16(gu.to_host(Y)[:, :N], np.broadcast_to(ref[:, None], (M, N)))
+    assert steps.max() <= 1, [(v[i], steps[i].max()) for i in np.argwhere(steps.max(1) > 1)[:4, 0]]
