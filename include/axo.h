@@ -152,9 +152,17 @@ typedef enum axo_kernel {
 /* Host only.  Reports in *kernel (axo_kernel_t) the kernel on which the product runs when it is called on its
  * own; arguments and errors as axo_fc_route.  A function of the shard shape and the leading dimensions only.
  * The kernels are chosen by estimated time, so the answer for a shape may change from one version to the next.  In
- * a chain's grouped launch the products of classes 5 to 9 run on 256-row tiles and those of classes 2 to 4 on
- * either size of split tile; all kernels of one of these two classes give the same bits. */
+ * a chain's grouped launch the products of classes 5 to 9 run on 256-row tiles or pairs of 64 x 64 ones and those of classes 2 to 4 on
+ * either size of split tile (axo_layer_step_tiles tells); all kernels of one of these two classes give the same bits. */
 int axo_fc_kernel(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int *kernel);
+
+/* Host only.  Reports in *tiles the kinds of tiles that a call of the product on its own runs on, with inputs at the addresses a and b:
+ * bit k for axo_kernel_t k (1 to 8; two of them for AXO_KERNEL_TILES_256_MIXED), and bit 16 + k where tiles of that kind fetch
+ * rows that do not start on cache lines by whole lines.  That choice looks at the addresses; it does not show in the results.
+ * Other arguments and errors as axo_fc_route. */
+#define AXO_TILES_BY_LINES (1 << 16)
+int axo_fc_tiles(const axo_problem_t *p, int op, const void *a, int64_t ld_a, const void *b, int64_t ld_b, int64_t ld_out,
+                 int *tiles);
 
 /* Forward local product  Y[M x Nl] = epilogue( X[M x Kl] . W[Kl x Nl] ).
  * X, W, Y: device pointers, bf16, row-major, 16-byte aligned; ldx >= Kl, ldw >= Nl, ldy >= Nl,
@@ -345,6 +353,11 @@ typedef struct axo_layer_ext {
  * > 4096).  On a validation error nothing is enqueued. */
 int axo_layer_step_ext(const axo_layer_ext_t *layers, int n_layers, void *ws, size_t ws_bytes,
                        void *hip_stream);
+
+/* Host only.  The kinds of tiles that axo_layer_step_ext runs the chain on, and axo_layer_step one without extras: tiles[j]
+ * receives the bits of axo_fc_tiles for unit j in program order, 0 for bias gradients and empty products.  `tiles` has room for four units per layer.
+ * Errors: those of axo_layer_step_ext's validation (with ws = NULL, ws_bytes = 0), NULL_PTR (tiles). */
+int axo_layer_step_tiles(const axo_layer_ext_t *layers, int n_layers, int *tiles);
 
 #ifdef __cplusplus
 }

@@ -21,6 +21,8 @@ AXO_ROUTE_NONE, AXO_ROUTE_TILED, AXO_ROUTE_COVERED, AXO_ROUTE_INTERIOR_STRIPS, A
  AXO_KERNEL_TILES_64, AXO_KERNEL_TILES_128, AXO_KERNEL_TILES_256, AXO_KERNEL_TILES_256_HALF,
  AXO_KERNEL_TILES_256_MIXED) = range(10)
 
+AXO_TILES_BY_LINES = 1 << 16
+
 
 class AxoError(RuntimeError):
     def __init__(self, status: int, where: str):
@@ -97,6 +99,8 @@ def library() -> ctypes.CDLL:
     L.axo_fc_route.restype = i32
     L.axo_fc_kernel.argtypes = [PP, i32, i64, i64, i64, ctypes.POINTER(ctypes.c_int)]
     L.axo_fc_kernel.restype = i32
+    L.axo_fc_tiles.argtypes = [PP, i32, vp, i64, vp, i64, i64, ctypes.POINTER(ctypes.c_int)]
+    L.axo_fc_tiles.restype = i32
     L.axo_fc_fwd.argtypes = [PP, vp, i64, vp, i64, vp, i32, vp, i64, vp, sz, vp]
     L.axo_fc_fwd.restype = i32
     L.axo_fc_dgrad.argtypes = [PP, vp, i64, vp, i64, vp, i64, vp, sz, vp]
@@ -127,6 +131,8 @@ def library() -> ctypes.CDLL:
     L.axo_layer_step_levels.argtypes = [ctypes.POINTER(Layer), i32, ctypes.POINTER(ctypes.c_int),
                                         ctypes.POINTER(ctypes.c_int)]
     L.axo_layer_step_levels.restype = i32
+    L.axo_layer_step_tiles.argtypes = [ctypes.POINTER(LayerExt), i32, ctypes.POINTER(ctypes.c_int)]
+    L.axo_layer_step_tiles.restype = i32
     _lib = L
     return L
 
@@ -171,6 +177,13 @@ def axo_fc_kernel(p: Problem, op: int, ld_a: int, ld_b: int, ld_out: int, check:
     rc = library().axo_fc_kernel(ctypes.byref(p) if p is not None else None, int(op), ld_a, ld_b, ld_out,
                                  ctypes.byref(k))
     return _check(rc, "axo_fc_kernel", check), int(k.value)
+
+
+def axo_fc_tiles(p: Problem, op: int, a: int, ld_a: int, b: int, ld_b: int, ld_out: int, check: bool = True) -> Tuple[int, int]:
+    """(status, bits): 1 << axo_kernel_t per kind of tiles, AXO_TILES_BY_LINES << axo_kernel_t where those fetch rows by whole lines."""
+    t = ctypes.c_int(-1)
+    rc = library().axo_fc_tiles(ctypes.byref(p) if p is not None else None, int(op), a, ld_a, b, ld_b, ld_out, ctypes.byref(t))
+    return _check(rc, "axo_fc_tiles", check), int(t.value)
 
 
 def axo_fc_fwd(p: Problem, X: int, ldx: int, W: int, ldw: int, bias: Optional[int], epilogue: int, Y: int,
@@ -233,6 +246,17 @@ def axo_layer_step_levels(layers: Sequence[Layer], check: bool = True) -> Tuple[
     lv = (ctypes.c_int * max(1, 3 * len(layers)))()
     rc = library().axo_layer_step_levels(_layer_array(layers), len(layers), ctypes.byref(n), lv)
     return _check(rc, "axo_layer_step_levels", check), int(n.value), list(lv)[:3 * len(layers)]
+
+
+def axo_layer_step_tiles(layers: Sequence[LayerExt], check: bool = True) -> Tuple[int, list]:
+    """(status, bits of axo_fc_tiles of each unit of axo_layer_step_ext in program order)."""
+    arr = (LayerExt * max(1, len(layers)))()
+    for i, l in enumerate(layers):
+        arr[i] = l
+    t = (ctypes.c_int * max(1, 4 * len(layers)))()
+    rc = library().axo_layer_step_tiles(arr, len(layers), t)
+    units = 3 * len(layers) + sum(1 for l in layers if l.db)
+    return _check(rc, "axo_layer_step_tiles", check), list(t)[:units]
 
 
 def axo_fc_dgrad_act(p: Problem, dY: int, lddy: int, W: int, ldw: int, pre: int, ldpre: int, act: int, dX: int,

@@ -279,42 +279,77 @@ axo::TileSched plan_product(const GemmArgs& g, int la, int lb) {
     return sc;
 }
 
-// Whether a product on these tiles fetches operands whose reduction runs inside the rows by whole cache lines
-// (line_phase): where such rows start elsewhere than on lines and the reduction is long enough to pay for the later start and the
-// one stage more.  Without / with it, rows 16 bytes off unless sizes say it, in us:
-//   64 x 64    dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83, 12.0 / 9.3; 1001 x 1027 (272 tiles) with 9 steps
-//              6.25 / 6.62; 2048 x 1024 (two tiles per CU) with 8 6.66 / 6.35; 2000 x 1000 x 3000 27.8 / 20.0
-//   128 x 128  dgrad 2048 x 2048 with 4 / 8 / 16 / 32 steps 6.97 / 7.26, 9.62 / 9.33, 14.6 / 13.3, 23.1 / 19.2
-//   256 x 128  dgrad 4096 x 2048 with 8 / 16 / 96 steps 16.1 / 16.1, 23.4 / 22.4, 97 / 87; not in forward, where only the first
-//              operand is of that kind (4096 x 1536 x 1536 24.6 / 24.9)
-//   256 x 256  dgrad 4096 x 4096 x 8192 260 / 226, 8192 x 8192 x 2000 272 / 233, 8000 x 8000 x 520 87 / 82; forward
-//              4096 x 4096 x 8192 225 / 205 (rows on lines: dgrad 195, forward 189), 5000 x 520 x 5000 50.8 / 50.5
-bool takes_lines(const GemmArgs& g, int la, int lb, Tiles tiles) {
-    auto leaves = [](const axo::bf16_t* p, int64_t ld) { return ld % 64 != 0 || reinterpret_cast<uintptr_t>(p) % 128 != 0; };
-    if (!(la == axo::KC && leaves(g.A, g.lda)) && !(lb == axo::KC && leaves(g.B, g.ldb))) return false;
-    const bool few = tiles == Tiles::small && 2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) <= 3 * NUM_CU;
-    return steps_in(g.R) >= (few ? 12 : 8);
+// Rows, of eight that follow each other, that start elsewhere than on a cache line: 7 where the pitch is an odd number of 16-byte
+// chunks, 6 or 4 where it is an odd number of 2 or of 4, none or (by the first one's address) all where it is whole lines.
+int straddling(const axo::bf16_t* p, int64_t ld) {
+    int n = 0;
+    for (int64_t r = 0; r < 8; ++r) n += ((int64_t)(reinterpret_cast<uintptr_t>(p) >> 4) + r * (ld >> 3)) % 8 != 0;
+    return n;
+}
+
+// Whether a product fetches operands whose reduction runs inside the rows by whole cache lines (line_phase) on tiles of this kind:
+// where enough rows straddle lines and the reduction is long enough to pay for the later start and the one stage more.
+//   64 x 64, 128 x 128  a stage was added for it, or there were four: wherever either operand has such rows.  Without / with it, rows 16
+//              bytes off, in us: dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83, 12.0 / 9.3; 2048 x 1024 (two
+//              tiles per CU) with 8 6.66 / 6.35; 2048 x 2048 with 8 / 16 / 32 9.62 / 9.33, 14.6 / 13.3, 23.3 / 18.0; one operand
+//              off and half its rows straddling 1024 x 1024 x 2048 8.98 / 8.73, 2048 x 2048 x 2048 19.1 / 18.2
+//   256 x 128  dgrad only.  Its three stages are then requested one step ahead instead of two, whatever the rows: 4096 x 1536 x 6144 takes
+//              77 us in any place.  Without it 64 on lines, 76 or 67 with 16 bytes off dY or W, 85 with both, 81 with 32 bytes
+//              off both, 81 with 16 and 64 and 72 with 64 (2304 x 2176 x 2240 32 with it and 25, 31, 26, 34, 33, 33, 29): by the
+//              share of a step's 384 rows that straddle, the line lies at two thirds, 18 of 24 is on the right side of it.
+//   256 x 256  of the first operand only, so only where that one's rows straddle: dgrad 4096 x 4096 x 8192 260 / 226 us, 8192 x 8192
+//              x 2000 272 / 233, 5120 x 5120 x 1024 58.6 / 53.4, forward 4096 x 4096 x 8192 225 / 205; with 64 bytes off, half the
+//              rows, 4096 x 4096 with 12 / 16 / 24 / 32 steps 26.5 / 27.0, 32.1 / 32.6, 43.6 / 43.6, 53.5 / 53.4.
+enum class Tile { t64, t128, half, whole };
+bool takes_lines(const GemmArgs& g, int la, int lb, Tile tile) {
+    if (la != axo::KC) return false;
+    const int a = straddling(g.A, g.lda), b = lb == axo::KC ? straddling(g.B, g.ldb) : 0;
+    const int64_t steps = steps_in(g.R);
+    if (steps < 8) return false;
+    switch (tile) {
+        case Tile::t64: return a + b > 0 && (steps >= 12 || 2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) > 3 * NUM_CU);
+        case Tile::t128: return a + b > 0;
+        case Tile::half: return lb == axo::KC && 2 * a + b >= 18;
+        default: return a > 4 || (a > 0 && steps >= 24);
+    }
+}
+// The same for a launch on 256-row tiles: on none of them, on whole ones, on all.
+enum Lines { LINES_NONE = 0, LINES_WHOLE = 1, LINES_ALL = 2 };
+Lines lines_of(const GemmArgs& g, int la, int lb, const axo::TileSched& sc) {
+    if (sc.small_cols > 0 && takes_lines(g, la, lb, Tile::half)) return LINES_ALL;  // more than half of A's rows straddle, too
+    return sc.n_big > 0 && takes_lines(g, la, lb, Tile::whole) ? LINES_WHOLE : LINES_NONE;
 }
 
 // Launch of one product on those tiles.
-template <int LA, int LB, bool LINES>
-int launch_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
-    static std::atomic<uint64_t> raised[3]{{0}, {0}, {0}};
-    if (tiles == Tiles::small) return launch_square<axo::SmallCfg<LINES>, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
-    if (tiles == Tiles::mid) return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[1], g, st);
+template <int LA, int LB, int LINES>
+int launch_mixed(const GemmArgs& g, const axo::TileSched& sc, hipStream_t st) {
     auto kern = axo::gemm_mixed_kernel<LA, LB, LINES>;
-    constexpr int lds = LINES ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
-    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised[2])) return AXO_ERR_HIP;
-    const axo::TileSched sc = plan_product(g, LA, LB);
+    constexpr int lds = LINES != LINES_NONE ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
+    static std::atomic<uint64_t> raised{0};
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised)) return AXO_ERR_HIP;
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), lds, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
+template <int LA, int LB, bool LINES>
+int launch_square_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
+    static std::atomic<uint64_t> raised[2]{{0}, {0}};
+    if (tiles == Tiles::small) return launch_square<axo::SmallCfg<LINES>, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
+    return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[1], g, st);
+}
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
     const Tiles tiles = tiles_of(g.Mo, g.No, g.R);
-    if constexpr (LA == axo::KC) if (takes_lines(g, LA, LB, tiles)) return launch_tiles<LA, LB, true>(g, tiles, st);
-    return launch_tiles<LA, LB, false>(g, tiles, st);
+    if (tiles != Tiles::big) {
+        if constexpr (LA == axo::KC)
+            if (takes_lines(g, LA, LB, tiles == Tiles::small ? Tile::t64 : Tile::t128)) return launch_square_tiles<LA, LB, true>(g, tiles, st);
+        return launch_square_tiles<LA, LB, false>(g, tiles, st);
+    }
+    const axo::TileSched sc = plan_product(g, LA, LB);
+    const Lines lines = lines_of(g, LA, LB, sc);
+    if constexpr (LA == axo::KC && LB == axo::KC) if (lines == LINES_ALL) return launch_mixed<LA, LB, LINES_ALL>(g, sc, st);
+    if constexpr (LA == axo::KC) if (lines == LINES_WHOLE) return launch_mixed<LA, LB, LINES_WHOLE>(g, sc, st);
+    return launch_mixed<LA, LB, LINES_NONE>(g, sc, st);
 }
 
 int launch_tile_layout(const GemmArgs& g, int la, int lb, hipStream_t st) {
@@ -575,10 +610,10 @@ struct Plan {
     bool nothing_to_do() const { return bias_grad ? bg.Nl == 0 : (g.Mo == 0 || g.No == 0); }
 };
 
-// One launch over the tiles of all given units of work: products on 256-row tiles (Kernel::tiles), products on
+// The segments of one launch over the tiles of all given units of work: products on 256-row tiles (Kernel::tiles), products on
 // small tiles that ride along (Plan::small), bias gradients; at most GROUP_MAX_PRODUCTS of them, together no more
-// workgroups than a grid holds.
-int launch_group(const Plan* const* plans, int n, hipStream_t st) {
+// workgroups than a grid holds.  Returns the number of workgroups.
+int group_launch(const Plan* const* plans, int n, axo::GroupArgs& ga, bool& lines) {
     std::vector<GroupItem> items(n);
     for (int i = 0; i < n; ++i)
         items[i] = plans[i]->bias_grad ? GroupItem{plans[i]->bg.M, plans[i]->bg.Nl, 0, PAIR_BIAS_GRAD}
@@ -586,10 +621,9 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
                                                    layout_pair(plans[i]->la, plans[i]->lb) + (plans[i]->small ? PAIR_SLIM : 0)};
     const std::vector<int> cols = plan_group(items);
     const std::vector<SegCost> segs = group_segments(items, cols);
-    axo::GroupArgs ga{};
     ga.n_seg = (int)segs.size();
     int blocks = 0;
-    bool lines = false;
+    lines = false;
     for (int k = 0; k < ga.n_seg; ++k) {
         const SegCost& sc = segs[k];
         axo::GroupSeg& sg = ga.seg[k];
@@ -617,7 +651,7 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
         } else {
             sg.kind = 2 * items[sc.item].pair + sc.small;
             const Plan& pl = *plans[sc.item];
-            if (sg.kind != 1 && takes_lines(pl.g, pl.la, pl.lb, Tiles::big)) {
+            if (takes_lines(pl.g, pl.la, pl.lb, sc.small ? Tile::half : Tile::whole)) {
                 sg.kind += axo::GROUP_KIND_LINES;
                 lines = true;
             }
@@ -642,6 +676,12 @@ int launch_group(const Plan* const* plans, int n, hipStream_t st) {
         b.epilogue = plans[i]->bg.accumulate;
         ga.g[i] = b;
     }
+    return blocks;
+}
+int launch_group(const Plan* const* plans, int n, hipStream_t st) {
+    axo::GroupArgs ga{};
+    bool lines;
+    const int blocks = group_launch(plans, n, ga, lines);
     static std::atomic<uint64_t> raised[2]{{0}, {0}};
     auto kern = lines ? axo::gemm_group_kernel<true> : axo::gemm_group_kernel<false>;
     const int lds = lines ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
@@ -686,6 +726,21 @@ int kernel_id(const GemmArgs& g, int la, int lb) {
     }
     const axo::TileSched sc = plan_product(g, la, lb);
     return sc.small_cols == 0 ? AXO_KERNEL_TILES_256 : sc.big_cols == 0 ? AXO_KERNEL_TILES_256_HALF : AXO_KERNEL_TILES_256_MIXED;
+}
+
+// The kinds of tiles of a call on its own, as axo_fc_tiles reports them.
+int tile_bits(int kernel, bool lines) { return (1 << kernel) | (lines ? AXO_TILES_BY_LINES << kernel : 0); }
+int tiles_id(const GemmArgs& g, int la, int lb) {
+    const int kernel = kernel_id(g, la, lb);
+    if (kernel == AXO_KERNEL_NONE) return 0;
+    if (kernel < AXO_KERNEL_TILES_256) {
+        const bool ring = kernel == AXO_KERNEL_TILES_64 || kernel == AXO_KERNEL_TILES_128;
+        return tile_bits(kernel, ring && takes_lines(g, la, lb, kernel == AXO_KERNEL_TILES_64 ? Tile::t64 : Tile::t128));
+    }
+    const axo::TileSched sc = plan_product(g, la, lb);
+    const Lines lines = lines_of(g, la, lb, sc);
+    return (sc.n_big > 0 ? tile_bits(AXO_KERNEL_TILES_256, lines != LINES_NONE) : 0) |
+           (sc.small_cols > 0 ? tile_bits(AXO_KERNEL_TILES_256_HALF, lines == LINES_ALL) : 0);
 }
 
 // How the shape fits the 256 x 128 granularity of the tiles, for axo_fc_route.
@@ -1123,15 +1178,12 @@ int launch_slim_group_rows(const std::vector<const Plan*>& plans, hipStream_t st
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::THREADS), C::LDS_BYTES, st, ga);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
-int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
+// Rows of its tiles, 0 where the products are launched one by one, each of which fits.  Puts long reductions first.
+int slim_group_rows(std::vector<const Plan*>& plans) {
     int64_t blocks[2] = {0, 0};
     for (const Plan* pl : plans)
         for (int m = 0; m < 2; ++m) blocks[m] += tiles_in(pl->g.Mo, SLIM_MODEL[m].rows) * tiles_in(pl->g.No, SLIM_MODEL[m].rows);
-    if (plans.size() == 1 || !grid_fits(blocks[1], axo::SLIM_WAVES * 64)) {  // one by one, each of which fits
-        int rc = AXO_OK;
-        for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = launch_slim(plans[i]->g, plans[i]->la, plans[i]->lb, st);
-        return rc;
-    }
+    if (plans.size() == 1 || !grid_fits(blocks[1], axo::SLIM_WAVES * 64)) return 0;
     std::stable_sort(plans.begin(), plans.end(), [](const Plan* a, const Plan* b) { return a->g.R > b->g.R; });
     double us[2];
     for (int m = 0; m < 2; ++m) {
@@ -1143,17 +1195,65 @@ int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
         }
         us[m] = std::max(busy, chain);
     }
-    return us[0] <= us[1] && grid_fits(blocks[0], axo::SLIM_WAVES * 64) ? launch_slim_group_rows<32>(plans, st) : launch_slim_group_rows<64>(plans, st);
+    return us[0] <= us[1] && grid_fits(blocks[0], axo::SLIM_WAVES * 64) ? 32 : 64;
+}
+int launch_slim_group(std::vector<const Plan*> plans, hipStream_t st) {
+    const int rows = slim_group_rows(plans);
+    if (rows == 0) {
+        int rc = AXO_OK;
+        for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = launch_slim(plans[i]->g, plans[i]->la, plans[i]->lb, st);
+        return rc;
+    }
+    return rows == 32 ? launch_slim_group_rows<32>(plans, st) : launch_slim_group_rows<64>(plans, st);
 }
 
-// Enqueues the products level by level: those of a level that the tiled kernel takes share
+// What becomes of the launches that a chain is cut into: enqueued on a stream, or reported (axo_layer_step_tiles).
+struct Enqueue {
+    hipStream_t st;
+    int group(const Plan* const* plans, int n) { return launch_group(plans, n, st); }
+    int small_group(const std::vector<const Plan*>& plans) { return launch_slim_group(plans, st); }
+    int one(const Plan& pl) { return launch_plan(pl, st); }
+};
+struct Report {
+    const Plan* first;  // of the chain
+    int* tiles;         // per unit of work
+    int group(const Plan* const* plans, int n) {
+        axo::GroupArgs ga{};
+        bool lines;
+        group_launch(plans, n, ga, lines);
+        for (int k = 0; k < ga.n_seg; ++k) {
+            const int kind = ga.seg[k].kind;
+            if (kind == axo::GROUP_KIND_BIAS_GRAD) continue;
+            const bool by_lines = kind >= axo::GROUP_KIND_LINES;
+            const int kernel = !by_lines && kind >= axo::GROUP_KIND_PAIR ? AXO_KERNEL_TILES_64
+                               : !by_lines && kind >= axo::GROUP_KIND_SLIM ? AXO_KERNEL_SPLIT_64
+                               : kind % 2 ? AXO_KERNEL_TILES_256_HALF : AXO_KERNEL_TILES_256;
+            tiles[plans[ga.seg[k].product] - first] |= tile_bits(kernel, by_lines);
+        }
+        return AXO_OK;
+    }
+    int small_group(std::vector<const Plan*> plans) {
+        const int rows = slim_group_rows(plans);
+        for (const Plan* pl : plans)
+            if (rows == 0) one(*pl);
+            else tiles[pl - first] |= tile_bits(rows == 32 ? AXO_KERNEL_SPLIT_32 : AXO_KERNEL_SPLIT_64, false);
+        return AXO_OK;
+    }
+    int one(const Plan& pl) {
+        if (!pl.bias_grad) tiles[&pl - first] |= tiles_id(pl.g, pl.la, pl.lb);
+        return AXO_OK;
+    }
+};
+
+// Cuts a chain into launches level by level: the products of a level that the tiled kernel takes share
 // grouped launches (GROUP_MAX_PRODUCTS per launch), those on small tiles likewise, the others get a launch of their own.
-int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, int levels, hipStream_t st) {
+template <typename Sink>
+int by_level(std::vector<Plan>& plans, const std::vector<int>& level, int levels, Sink sink) {
     int rc = AXO_OK;
     std::vector<const Plan*> group;   // products of the level the tiled kernel takes
     std::vector<const Plan*> small;   // products of the level that run on small tiles
     auto flush_small = [&]() {
-        if (!small.empty() && rc == AXO_OK) rc = launch_slim_group(small, st);
+        if (!small.empty() && rc == AXO_OK) rc = sink.small_group(small);
         small.clear();
     };
     std::vector<const Plan*> riders;  // bias gradients of the level that may share their launch
@@ -1169,8 +1269,7 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
     auto flush = [&]() {
         group_blocks = 0;
         if (group.empty() || rc != AXO_OK) return;
-        rc = group.size() == 1 ? launch_tile_layout(group[0]->g, group[0]->la, group[0]->lb, st)
-                               : launch_group(group.data(), (int)group.size(), st);
+        rc = group.size() == 1 ? sink.one(*group[0]) : sink.group(group.data(), (int)group.size());
         group.clear();
     };
     // the last launch of a level takes the level's small products and bias gradients along, as many as fit
@@ -1182,7 +1281,7 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
             }
         flush();
         flush_small();
-        for (size_t k = 0; k < riders.size() && rc == AXO_OK; ++k) rc = launch_bias_grad(riders[k]->bg, st);
+        for (size_t k = 0; k < riders.size() && rc == AXO_OK; ++k) rc = sink.one(*riders[k]);
         riders.clear();
     };
     for (int lv = 0; lv < levels && rc == AXO_OK; ++lv) {
@@ -1191,7 +1290,7 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
             if (level[i] != lv || pl.nothing_to_do()) continue;
             if (pl.bias_grad) {
                 if (bias_grad_groupable(pl.bg)) riders.push_back(&pl);
-                else rc = launch_bias_grad(pl.bg, st);
+                else rc = sink.one(pl);
                 continue;
             }
             const Kernel kernel = kernel_of(pl.g, pl.la, pl.lb);
@@ -1202,7 +1301,7 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
                 continue;
             }
             if (kernel != Kernel::tiles) {
-                rc = launch(pl.g, pl.la, pl.lb, st);
+                rc = sink.one(pl);
                 continue;
             }
             if (!group.empty() && !joins(pl)) flush();
@@ -1215,27 +1314,28 @@ int enqueue_by_level(std::vector<Plan>& plans, const std::vector<int>& level, in
 }
 
 // A validated chain, scheduled by dependence level.
-int enqueue_scheduled(std::vector<Plan>& plans, hipStream_t st) {
+template <typename Sink>
+int scheduled(std::vector<Plan>& plans, Sink sink) {
     if (plans.size() > MAX_ANALYSED) {  // not analysed: program order, one unit per launch
         int rc = AXO_OK;
-        for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = launch_plan(plans[i], st);
+        for (size_t i = 0; i < plans.size() && rc == AXO_OK; ++i) rc = sink.one(plans[i]);
         return rc;
     }
     std::vector<int> level;
     const int levels = dependence_levels(plans, &level);
-    return enqueue_by_level(plans, level, levels, st);
+    return by_level(plans, level, levels, sink);
 }
 
-// The product that a query (axo_fc_route, axo_fc_kernel) asks about, at made-up, well-separated and aligned
-// addresses: the planners compare pointers, never follow them.
-int plan_query(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, Plan* pl) {
+// The product that a query asks about: the planners compare pointers, never follow them.
+int plan_query(const axo_problem_t* p, int op, const void* a, int64_t ld_a, const void* b, int64_t ld_b, void* c, int64_t ld_out, Plan* pl) {
     if (op < AXO_OP_FWD || op > AXO_OP_WGRAD) return AXO_ERR_BAD_ARG;
-    const void* a = reinterpret_cast<const void*>((uintptr_t)1 << 40);
-    const void* b = reinterpret_cast<const void*>((uintptr_t)2 << 40);
-    void* c = reinterpret_cast<void*>((uintptr_t)3 << 40);
     if (op == AXO_OP_FWD) return plan_fwd(p, a, ld_a, b, ld_b, nullptr, AXO_EPI_NONE, c, ld_out, nullptr, 0, pl);
     if (op == AXO_OP_DGRAD) return plan_dgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, pl);
     return plan_wgrad(p, a, ld_a, b, ld_b, c, ld_out, nullptr, 0, pl);
+}
+void* made_up(int n) { return reinterpret_cast<void*>((uintptr_t)n << 40); }  // well-separated and aligned
+int plan_query(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, Plan* pl) {
+    return plan_query(p, op, made_up(1), ld_a, made_up(2), ld_b, made_up(3), ld_out, pl);
 }
 
 // No exception leaves the library: the planners keep their lists and caches in standard
@@ -1316,6 +1416,17 @@ int axo_fc_kernel(const axo_problem_t* p, int op, int64_t ld_a, int64_t ld_b, in
         const int rc = plan_query(p, op, ld_a, ld_b, ld_out, &pl);
         if (rc) return rc;
         *kernel = kernel_id(pl.g, pl.la, pl.lb);
+        return AXO_OK;
+    });
+}
+
+int axo_fc_tiles(const axo_problem_t* p, int op, const void* a, int64_t ld_a, const void* b, int64_t ld_b, int64_t ld_out, int* tiles) {
+    return guarded([&]() -> int {
+        if (!tiles) return AXO_ERR_NULL_PTR;
+        Plan pl;
+        const int rc = plan_query(p, op, a, ld_a, b, ld_b, made_up(1 << 20), ld_out, &pl);  // an output far from any input
+        if (rc) return rc;
+        *tiles = tiles_id(pl.g, pl.la, pl.lb);
         return AXO_OK;
     });
 }
@@ -1430,7 +1541,7 @@ int axo_layer_step(const axo_layer_t* layers, int n_layers, void* ws, size_t ws_
         std::vector<Plan> plans;
         const int rc = plan_chain(layers, n_layers, ws, ws_bytes, &plans);
         if (rc != AXO_OK) return rc;
-        return enqueue_scheduled(plans, static_cast<hipStream_t>(hip_stream));
+        return scheduled(plans, Enqueue{static_cast<hipStream_t>(hip_stream)});
     });
 }
 
@@ -1439,7 +1550,7 @@ int axo_layer_step_ext(const axo_layer_ext_t* layers, int n_layers, void* ws, si
         std::vector<Plan> plans;
         const int rc = plan_chain_ext(layers, n_layers, ws, ws_bytes, &plans);
         if (rc != AXO_OK) return rc;
-        return enqueue_scheduled(plans, static_cast<hipStream_t>(hip_stream));
+        return scheduled(plans, Enqueue{static_cast<hipStream_t>(hip_stream)});
     });
 }
 
@@ -1464,6 +1575,17 @@ int axo_layer_step_levels(const axo_layer_t* layers, int n_layers, int* n_levels
         if (levels)
             for (size_t i = 0; i < level.size(); ++i) levels[i] = level[i];
         return AXO_OK;
+    });
+}
+
+int axo_layer_step_tiles(const axo_layer_ext_t* layers, int n_layers, int* tiles) {
+    return guarded([&]() -> int {
+        if (!tiles) return AXO_ERR_NULL_PTR;
+        std::vector<Plan> plans;
+        const int rc = plan_chain_ext(layers, n_layers, nullptr, 0, &plans);
+        if (rc != AXO_OK) return rc;
+        std::fill(tiles, tiles + plans.size(), 0);
+        return scheduled(plans, Report{plans.data(), tiles});
     });
 }
 

@@ -882,7 +882,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 // The same tile on a ring of D stages, for tiles whose step is too short to cover a load's way from HBM: in
 // gemm_tile_body the last loads of a stage have little more than half a step to arrive, which a 1.3 us step of
 // a 256 x 256 tile covers and the 0.8 us step of a 256 x 128 tile does not once the operands come from HBM.  Here a
-// stage is requested D - 1 steps ahead (three stages of a 256 x 128 tile are the LDS of two of a 256 x 256 one).
+// stage is requested D - 1 steps ahead (three stages of a 256 x 128 tile are the LDS of two of a 256 x 256 one).  By whole lines
+// (LINES) a step needs the next stage too and a stage is requested D - 2 steps ahead, on a 256 x 128 tile one: as with two
+// stages, which is what takes_lines weighs against the lines saved there.
 // A step is two MFMA groups (sub-steps of 32); its barrier sits before the second, half of the refill's loads
 // right behind it and the other half at the head of the next step, and wave priorities fall through the step, as
 // in gemm_tile_body.  (All loads behind the barrier and no priorities: 238 us instead of 216 in the case below.)
@@ -1088,8 +1090,8 @@ __device__ __forceinline__ int inside_col(const GemmArgs& g, const int j0) {
     return g.No >= BN && g.epilogue != EPI_ACC_F32 && g.No % 8 == 0 ? min(j0, g.No - BN) : j0;
 }
 
-// One launch over both regions of a TileSched.
-template <int LA, int LB, bool LINES>
+// One launch over both regions of a TileSched.  LINES: rows by whole lines on no tiles (0), on the large ones (1), on both (2).
+template <int LA, int LB, int LINES>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g, TileSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
@@ -1097,11 +1099,11 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     int tm, tn;
     if (bid < sc.n_big) {
         tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
-        gemm_tile_body<256, 256, 2, 4, LA, LB, LINES>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
+        gemm_tile_body<256, 256, 2, 4, LA, LB, LINES != 0>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
         tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES && LB == KC>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem, threadIdx.x);
+        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES == 2>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem, threadIdx.x);
     }
 }
 
