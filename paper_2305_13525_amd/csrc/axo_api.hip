@@ -306,9 +306,11 @@ bool takes_lines(const GemmArgs& g, int la, int lb, Tile tile) {
     const int a = straddling(g.A, g.lda), b = lb == axo::KC ? straddling(g.B, g.ldb) : 0;
     const int64_t steps = steps_in(g.R);
     if (steps < 8) return false;
+    // the ring then walks one stage more of the other operand, too, which spans_ok does not count where there are an even number of steps
+    const bool in_span = lb == axo::KC || span_ok(axo::MC, g.ldb, (steps + 1) * axo::TILE_BK);
     switch (tile) {
-        case Tile::t64: return a + b > 0 && (steps >= 12 || 2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) > 3 * NUM_CU);
-        case Tile::t128: return a + b > 0;
+        case Tile::t64: return in_span && a + b > 0 && (steps >= 12 || 2 * tiles_in(g.Mo, 64) * tiles_in(g.No, 64) > 3 * NUM_CU);
+        case Tile::t128: return in_span && a + b > 0;
         case Tile::half: return lb == axo::KC && 2 * a + b >= 18;
         default: return a > 4 || (a > 0 && steps >= 24);
     }

@@ -59,6 +59,18 @@ def test_square_tiles_want_either_operand():
     assert tiles(DG, 2048, 2048, 64 * 7, 1, 1) == {MID: False} and tiles(DG, 2048, 2048, 64 * 8, 1, 1) == {MID: True}
 
 
+def test_the_stage_behind_the_last_keeps_its_offsets_in_32_bits():
+    """Forward by lines walks one stage of W more than there are steps.  16 steps of rows of ldw elements pass 4 GiB from ldw = 2097120 on (and the
+    product takes the general kernel), 17 from 1973760."""
+    for kernel, M, N in ((SMALL, 1000, 1000), (MID, 2048, 2048)):
+        p = axo.Problem.make((1, 1, 1), (0, 0, 0), M, 1024, N)
+        for ldw, by_lines in ((2048, True), (1973752, True), (1973760, False), (2097112, False)):
+            assert axo.axo_fc_tiles(p, FWD, A, 1032, B, ldw, 2048)[1] == (1 << kernel) * (1 + by_lines * axo.AXO_TILES_BY_LINES)
+        assert axo.axo_fc_tiles(p, FWD, A, 1032, B, 2097120, 2048)[1] == 1 << axo.AXO_KERNEL_GENERAL
+        odd = axo.Problem.make((1, 1, 1), (0, 0, 0), M, 960, N)  # 15 steps, of which 16 are walked anyhow
+        assert axo.axo_fc_tiles(odd, FWD, A, 1032, B, 2097112, 2048)[1] == (1 << kernel) * (1 + axo.AXO_TILES_BY_LINES)
+
+
 def layer(M, K, N, off_x=0, off_w=0, off_y=0, at=A):
     p, ptr = axo.Problem.make((1, 1, 1), (0, 0, 0), M, K, N), [at + (i << 34) for i in range(6)]
     x, w, y = lines(K) + 8 * off_x, lines(N) + 8 * off_w, lines(N) + 8 * off_y
