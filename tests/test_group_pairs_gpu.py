@@ -1,6 +1,7 @@
 """Products of a chain that share a grouped launch as pairs of 64 x 64 tiles, two to a workgroup: the same bits as in launches of
-their own.  The sizes are such that one product of the layer runs that way (forward, dgrad, wgrad in turn), on an odd number of
-tiles, so that the last workgroup holds one tile only, with edges inside tiles and reductions that end inside steps."""
+their own.  `pairs` are the products of the layer that run that way (0 forward, 1 dgrad, 2 wgrad), asked for in each case.  All but
+the last two sizes have an odd number of tiles there, so that the last workgroup holds one tile only, edges inside tiles and
+reductions that end inside steps."""
 import pytest
 import torch
 
@@ -16,10 +17,10 @@ def rows(r, c, gen, dtype=torch.bfloat16):
     return a
 
 
-@pytest.mark.parametrize("M,K,N", [(1187, 2671, 668), (534, 935, 903), (287, 3859, 1811), (391, 2217, 1244), (1980, 300, 1450),
-                                   (2010, 330, 830), (4096, 512, 512)])
+@pytest.mark.parametrize("M,K,N,pairs", [(1187, 2671, 668, {0}), (534, 935, 903, {0, 2}), (287, 3859, 1811, {1}), (391, 2217, 1244, {1}),
+                                         (1980, 300, 1450, {2}), (2010, 330, 830, {2}), (4096, 512, 512, {2})])
 @pytest.mark.parametrize("extras", [False, True])
-def test_pairs_give_the_bits_of_single_launches(M, K, N, extras):
+def test_pairs_give_the_bits_of_single_launches(M, K, N, pairs, extras):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(M + K)
     p = axo.Problem.make((1, 1, 1), (0, 0, 0), M, K, N)
@@ -33,8 +34,11 @@ def test_pairs_give_the_bits_of_single_launches(M, K, N, extras):
         if chain:
             layer = axo.Layer(p, epi, 0, X.data_ptr(), ld(X), W.data_ptr(), ld(W), bias.data_ptr(), Y.data_ptr(), ld(Y), dY.data_ptr(),
                               ld(dY), dX.data_ptr(), ld(dX), dW.data_ptr(), ld(dW))
+            ext = axo.LayerExt.make(layer)
             if extras:
                 ext = axo.LayerExt.make(layer, pre.data_ptr(), ld(pre), axo.AXO_EPI_BIAS_GELU_TANH, dW32.data_ptr(), ld(dW32))
+            assert {i for i, t in enumerate(axo.axo_layer_step_tiles([ext])[1]) if t == 1 << axo.AXO_KERNEL_TILES_64} == pairs
+            if extras:
                 axo.axo_layer_step_ext([ext], None, 0, gu.stream())
             else:
                 axo.axo_layer_step([layer], None, 0, gu.stream())

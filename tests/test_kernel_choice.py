@@ -68,3 +68,21 @@ def test_long_reductions_on_few_large_tiles_stay_on_them():
     assert kernel(1176, 6592, 3872, DG) in big       # 111 and 79
     assert kernel(1408, 11008, 7296, DG) in big      # 427 and 259
     assert kernel(6320, 5648, 104, WG) == axo.AXO_KERNEL_TILES_64       # 89 x 2 of those tiles: 32 and 81
+
+
+def pairs(M, K, N):
+    """The products of a one-layer chain (0 forward, 1 dgrad, 2 wgrad) that its grouped launch runs as pairs of 64 x 64 tiles."""
+    pad, at = lambda n: (n + 7) // 8 * 8, [(i + 1) << 34 for i in range(6)]
+    layer = axo.Layer(mk(M, K, N), 0, 0, at[0], pad(K), at[1], pad(N), None, at[2], pad(N), at[3], pad(N), at[4], pad(K), at[5], pad(N))
+    return {i for i, t in enumerate(axo.axo_layer_step_tiles([axo.LayerExt.make(layer)])[1]) if t == 1 << axo.AXO_KERNEL_TILES_64}
+
+
+def test_pairs_take_the_tail_of_a_group():
+    """A product of few outputs and a long reduction would be what a grouped launch ends with on 256-row tiles; as pairs only where
+    the launch then ends 8 % earlier by the estimates."""
+    assert pairs(4096, 512, 512) == {2}     # 37.5 -> 25.7 us
+    assert pairs(3200, 512, 512) == {2} and pairs(3000, 512, 512) == set()  # either side of the 8 %
+    assert pairs(2000, 333, 1500) == {2}    # 25.8 -> 20.0
+    assert pairs(1187, 2671, 668) == {0} and pairs(391, 2217, 1244) == {1}
+    assert pairs(2048, 1024, 1024) == set()  # 2 % slower with pairs at any gain
+    assert pairs(1500, 1500, 1500) == set() and pairs(4096, 1536, 4608) == set()
