@@ -76,15 +76,15 @@ __device__ __forceinline__ float gelu_tanh(float v) {
 }
 
 // The upper tail Q(a) = erfc(a / sqrt 2) / 2 of the normal distribution at a = |v|, as ratio * gauss with gauss = exp(-v^2 / 2):
-// the ratio is smooth and tends to 1 / (a sqrt(2 pi)), here a polynomial of degree 10 in w = a / (1 + 0.35 a), 6e-9 off at
+// the ratio is smooth and tends to 1 / (a sqrt(2 pi)), here a polynomial of degree 10 in w = a / (1 + 0.35 a), 1.2e-8 off at
 // most up to a = 14, where the tail is below the normal range of floats.  (A minimax fit made for this file: weighted least
 // squares with reweighting by the error.)  Straight-line code of one reciprocal and one exp2, because an epilogue
 // runs it on every output: with erfcf, which branches over ranges and a wave takes all of them, forward, dgrad and wgrad of
 // 4000 x 2000 x 6000 took 326 us (the forward without an epilogue 34 less), with this 310; 1001 x 1027 x 515 with it in the data
 // gradient 32.4 and 29.3.  Errors against 64 bits, over |v| < 13, are at or below those of the erfcf form in every
-// range: 3e-8 to 7e-8 rms for v > -1, 1.4e-7 on [-3, -1], 2.3e-6 on [-13, -9], where that form had 4.1e-6.
-__device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss, float up = 0.0f) {
-    const float a = fminf(__builtin_fabsf(v), 14.0f);  // an infinite v has gauss = 0 and wants a finite ratio
+// range: 2e-8 to 6e-8 rms for v > -1, 1.4e-7 on [-3, -1], 2.3e-6 on [-13, -9], where that form had 4.1e-6.
+__device__ __forceinline__ void normal_tail(float v, float& a, float& ratio, float& gauss, float up = 0.0f) {
+    a = __builtin_fabsf(fminf(v, 14.0f));  // plus infinity has gauss = 0 and wants a finite ratio
     const float w = a * __builtin_amdgcn_rcpf(__builtin_fmaf(0.35f, a, 1.0f));
     float r = 3.2823087e-07f;
     r = __builtin_fmaf(r, w, -1.9183292e-06f);
@@ -100,18 +100,17 @@ __device__ __forceinline__ void normal_tail(float v, float& ratio, float& gauss,
     gauss = __builtin_amdgcn_exp2f(__builtin_fmaf(v * v, -0.72134752f, up));  // log2(e) / 2
 }
 
-// GELU, erf form: v Phi(v), Phi(v) = Q(|v|) below zero and 1 - Q(v) above (no cancellation).  The hardware's exp2 has no
+// GELU, erf form: v Phi(v) = max(v, 0) - |v| Q(|v|), rounded once (the -0 keeps the sign of zero results).  The hardware's exp2 has no
 // results below 2^-126.  The Gaussian falls under that at v = -13.2, v Phi(v) leaves the subnormal numbers of bf16 only at -13.6; from
-// -13 on a factor of 2^64 keeps it in range and is taken back from the product.  On every value that cost 473 -> 490 us (forward
-// 32768 x 2048 x 4096), so epilogues ask first whether a wave has such a value at hand (FAR); all other values have the same bits either way.
+// -13 on a factor of 2^64 keeps it in range and is taken back from the result (FAR).  All other values have the same bits either way.
 constexpr float GELU_ERF_FAR = -13.0f;
 template <bool FAR = true>
 __device__ __forceinline__ float gelu_erf(float v) {
     const bool far = FAR && v < GELU_ERF_FAR;
-    float ratio, gauss;
-    normal_tail(v, ratio, gauss, far ? 64.0f : 0.0f);
-    const float q = ratio * gauss, r = v * (v < 0.0f ? q : 1.0f - q);
-    return FAR ? __builtin_ldexpf(r, far ? -64 : 0) : r;
+    float a, ratio, gauss;
+    normal_tail(v, a, ratio, gauss, far ? 64.0f : 0.0f);
+    const float r = __builtin_fmaf(-a, ratio * gauss, fmaxf(v, -0.0f));
+    return FAR ? (far ? r * 0x1p-64f : r) : r;
 }
 
 // d/dv of the tanh-form GELU.  With s = sigmoid(2 z): 0.5 (1 + tanh z) = s and 1 - tanh^2 z = 4 s (1 - s),
@@ -127,8 +126,8 @@ __device__ __forceinline__ float dgelu_tanh(float v) {
 
 // d/dv of the exact GELU: Phi(v) + v phi(v), phi(v) = gauss / sqrt(2 pi).
 __device__ __forceinline__ float dgelu_erf(float v) {
-    float ratio, gauss;
-    normal_tail(v, ratio, gauss);
+    float a, ratio, gauss;
+    normal_tail(v, a, ratio, gauss);
     const float below = __builtin_fmaf(__builtin_fabsf(v), -0.3989422804014327f, ratio) * gauss;
     return v < 0.0f ? below : 1.0f - below;
 }

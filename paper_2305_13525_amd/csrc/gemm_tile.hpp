@@ -345,7 +345,7 @@ __device__ __forceinline__ void store_bf16_quad(const GemmArgs& g, f32x4 v, cons
     }
 }
 // The same after the epilogue, whose kind is decided once for the four (once per value: forward 1001 x 1027 x 515 with a bias 8.6 us, now
-// 7.9; dgrad through the erf form 9.8 and 9.1).
+// 7.9, with the erf form 9.0 and 8.1; dgrad through the erf form 9.8 and 9.1).
 // `x` is what the epilogue adds or multiplies with: bias, pre-activations, or the fp32 values accumulated into.
 __device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, f32x4 x, const int row, const int col, const int valid) {
     if (g.epilogue == EPI_ACC_F32) {
@@ -361,11 +361,7 @@ __device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, f32x4 x, 
         for (int e = 0; e < 4; ++e) v[e] = f(v[e], x[e]);
     };
     if (g.epilogue != EPI_NONE) switch (g.epilogue) {
-        case EPI_BIAS_GELU_ERF:  // as in tile_epilogue, with the choice per wave and quad
-            v = v + x;
-            if (__any(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])) < GELU_ERF_FAR)) each([](float s, float) { return gelu_erf(s); });
-            else each([](float s, float) { return gelu_erf<false>(s); });
-            break;
+        case EPI_BIAS_GELU_ERF: each([](float s, float t) { return apply_epilogue(s, t, EPI_BIAS_GELU_ERF); }); break;
         case EPI_BIAS: v = v + x; break;
         case EPI_BIAS_GELU_TANH: each([](float s, float t) { return apply_epilogue(s, t, EPI_BIAS_GELU_TANH); }); break;
         case EPI_MUL_DGELU_TANH: each([](float s, float t) { return apply_dact(s, t, EPI_MUL_DGELU_TANH); }); break;
@@ -404,9 +400,9 @@ struct Interleave {
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
 // Epilogue of a workgroup tile: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].  The operand
-// buffers are free.  False where the wave's part has values that this form of the epilogue does not cover; then nothing has been stored.
+// buffers are free.
 template <typename C, int LA, int LB>
-__device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
                                               const int wave, const int wm, const int wn, const int lane, char* smem) {
     char* stage = smem + wave * (C::WTM * C::EPI_STRIDE);
     // The epilogue kind is decided once, outside the element loops: the plain path is then
@@ -421,22 +417,24 @@ __device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     int wrow0 = i0 + wm * C::WTM, wcol0 = j0 + wn * C::WTN;
     asm volatile("" : "+s"(wrow0), "+s"(wcol0));
     bf16_t* const Cw = g.C + (int64_t)wrow0 * g.ldc + wcol0;
-    auto convert_and_stage = [&](auto epi_tag) __attribute__((always_inline)) {
+    // Whether a wave asks first if the erf form meets values that want the longer arithmetic (FAR of gelu_erf).  With 64 or 128 values
+    // per lane that pays: forward 8192 x 512 x 8192 takes 101 us where there are none, 112 where there are, and 109 with that arithmetic
+    // throughout (32768 x 2048 x 4096: 452, 469 and 462).  With fewer it does not: 1024^3 6.4 us with the question, 6.2 without.
+    constexpr bool ASKS = C::TM * C::TN >= 16;
+    // The bias of a lane's four columns in the wave tile's block b of 16.
+    auto bias_of = [&](const int b) __attribute__((always_inline)) {
+        return g.add_bias ? load_bf16x4(g.bias + wcol0 + b * 16 + 4 * (lane >> 4), 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto convert_and_stage = [&](auto epi_tag, auto far_tag) __attribute__((always_inline)) {
         constexpr int EPI = decltype(epi_tag)::value;
+        constexpr bool FAR = decltype(far_tag)::value != 0;
         constexpr bool FWD_EPI = EPI >= EPI_BIAS && EPI <= EPI_BIAS_GELU_ERF;
         constexpr bool DACT = EPI == EPI_MUL_DGELU_TANH || EPI == EPI_MUL_DGELU_ERF;
-        float least = 0.0f;
 #pragma unroll
         for (int b = 0; b < C::TN; ++b) {
             const int ncol = b * 16 + 4 * (lane >> 4);  // within the wave tile
-            float bv[4] = {0.f, 0.f, 0.f, 0.f};
-            if (FWD_EPI && g.add_bias) {
-                const uint2 raw = *reinterpret_cast<const uint2*>(g.bias + wcol0 + ncol);
-                bv[0] = __uint_as_float(raw.x << 16);
-                bv[1] = __uint_as_float(raw.x & 0xFFFF0000u);
-                bv[2] = __uint_as_float(raw.y << 16);
-                bv[3] = __uint_as_float(raw.y & 0xFFFF0000u);
-            }
+            f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+            if (FWD_EPI) bv = bias_of(b);
 #pragma unroll
             for (int a = 0; a < C::TM; ++a) {
                 const int mrow = a * 16 + (lane & 15);
@@ -446,9 +444,9 @@ __device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
                 if (EPI == EPI_BIAS_GELU_ERF) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        v[e] += bv[e];
-                        least = fminf(least, v[e]);
-                        v[e] = gelu_erf<false>(v[e]);
+                        // FAR: or the arithmetic that both forms share moves ahead of the choice between them, and the kernel spills
+                        if (FAR && ASKS) asm volatile("" : "+v"(v[e]));
+                        v[e] = gelu_erf<FAR>(v[e] + bv[e]);
                     }
                 } else if (FWD_EPI) {
 #pragma unroll
@@ -468,7 +466,6 @@ __device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
                 *reinterpret_cast<uint2*>(stage + mrow * C::EPI_STRIDE + ncol * 2) = packed;
             }
         }
-        return EPI != EPI_BIAS_GELU_ERF || !__any(least < GELU_ERF_FAR);
     };
     // The staged sub-tile out to memory as full row segments of 16 bytes per lane.
     auto store_staged = [&]() __attribute__((always_inline)) {
@@ -496,24 +493,40 @@ __device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
             __builtin_nontemporal_store(vdat[p], reinterpret_cast<u32x4*>(Cw + (int64_t)row * g.ldc + ch * 8));
         }
     };
-    auto finish = [&](auto epi_tag) __attribute__((always_inline)) {
-        if (!convert_and_stage(epi_tag)) return false;
+    auto finish = [&](auto epi_tag, auto far_tag) __attribute__((always_inline)) {
+        convert_and_stage(epi_tag, far_tag);
         store_staged();
-        return true;
     };
     // Each product has its own epilogue kinds, so each layout pair compiles only those.
     if (LA == KC && LB == MC) {  // forward
         switch (g.epilogue) {
-            case EPI_NONE: return finish(IC<EPI_NONE>{});
-            case EPI_BIAS: return finish(IC<EPI_BIAS>{});
-            case EPI_BIAS_GELU_TANH: return finish(IC<EPI_BIAS_GELU_TANH>{});
-            default: return finish(IC<EPI_BIAS_GELU_ERF>{});
+            case EPI_NONE: finish(IC<EPI_NONE>{}, IC<0>{}); return;
+            case EPI_BIAS: finish(IC<EPI_BIAS>{}, IC<0>{}); return;
+            case EPI_BIAS_GELU_TANH: finish(IC<EPI_BIAS_GELU_TANH>{}, IC<0>{}); return;
+            default: break;
+        }
+        if constexpr (!ASKS) finish(IC<EPI_BIAS_GELU_ERF>{}, IC<1>{});
+        else {
+            float least = 0.f;  // the least sum of a column plus its bias is its least value
+#pragma unroll
+            for (int b = 0; b < C::TN; ++b) {
+                const f32x4 bv = bias_of(b);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float sum = acc[0][b][e];
+#pragma unroll
+                    for (int a = 1; a < C::TM; ++a) sum = fminf(sum, acc[a][b][e]);
+                    least = fminf(least, sum + bv[e]);
+                }
+            }
+            if (__any(least < GELU_ERF_FAR)) finish(IC<EPI_BIAS_GELU_ERF>{}, IC<1>{});
+            else finish(IC<EPI_BIAS_GELU_ERF>{}, IC<0>{});
         }
     } else if (LA == KC && LB == KC) {  // dgrad
         switch (g.epilogue) {
-            case EPI_NONE: return finish(IC<EPI_NONE>{});
-            case EPI_MUL_DGELU_TANH: return finish(IC<EPI_MUL_DGELU_TANH>{});
-            default: return finish(IC<EPI_MUL_DGELU_ERF>{});
+            case EPI_NONE: finish(IC<EPI_NONE>{}, IC<0>{}); return;
+            case EPI_MUL_DGELU_TANH: finish(IC<EPI_MUL_DGELU_TANH>{}, IC<0>{}); return;
+            default: finish(IC<EPI_MUL_DGELU_ERF>{}, IC<0>{}); return;
         }
     } else {  // wgrad
         if constexpr (C::WTN == 64) if (g.epilogue == EPI_ACC_F32) {
@@ -553,9 +566,9 @@ __device__ __forceinline__ bool tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
                     *reinterpret_cast<f32x4*>(Cf + (int64_t)(h * RP + i * 4 + frow) * g.ldc + fcol) = old[i] + sum[i];
                 __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
             }
-            return true;
+            return;
         }
-        return finish(IC<EPI_NONE>{});
+        finish(IC<EPI_NONE>{}, IC<0>{});
     }
 }
 
@@ -875,8 +888,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 
     __syncthreads();  // all waves are done reading the operand buffers
     const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
-    if (!whole || !tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem))
-        tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
 // The same tile on a ring of D stages, for tiles whose step is too short to cover a load's way from HBM: in
@@ -1066,8 +1079,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No && (C::WTN == 64 || g.epilogue != EPI_ACC_F32);
     __syncthreads();  // all waves are done reading the operand buffers
     if (!store) return;
-    if (!whole || !tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem))
-        tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
 using MixBigCfg = TileCfg<256, 256, 2, 4>;

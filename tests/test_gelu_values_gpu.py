@@ -101,3 +101,26 @@ def test_erf_form_down_its_tail(M, N, K, kernel):
     ref = v * erf_tail(v)
     steps = oracle.ulp_distance_bf16(gu.to_host(Y)[:, :N], np.broadcast_to(ref[:, None], (M, N)))
     assert steps.max() <= 1, [(v[i], steps[i].max()) for i in np.argwhere(steps.max(1) > 1)[:4, 0]]
+
+
+@pytest.mark.parametrize("M,N,kernel", [(4096, 1536, axo.AXO_KERNEL_TILES_256_HALF), (4096, 4096, axo.AXO_KERNEL_TILES_256),
+                                        (4001, 4093, axo.AXO_KERNEL_TILES_256)])
+def test_a_far_value_leaves_the_others_alone(M, N, kernel):
+    """A wave that meets a value below -13 takes longer arithmetic for all of its values: the same bits for those above."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(M)
+    p, lead = axo.Problem.make((1, 1, 1), (0, 0, 0), M, 1, N), -(-N // 8) * 8
+    assert axo.axo_fc_kernel(p, axo.AXO_OP_FWD, 8, lead, lead)[1] == kernel
+    X = torch.zeros((M, 8), dtype=torch.bfloat16, device="cuda:0")
+    X[:, 0] = (torch.randn(M, device="cuda:0", generator=gen) * 3).clamp(-12.9, 100.0)
+    X[:2, 0] = 0.0
+    W, far = torch.ones((1, lead), dtype=torch.bfloat16, device="cuda:0"), torch.arange(M, device="cuda:0") % 300 == 7
+    outs = []
+    for x in (X, torch.where(far[:, None], torch.full_like(X, -13.25), X)):
+        Y = torch.full((M, lead), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        axo.axo_fc_fwd(p, x.data_ptr(), 8, W.data_ptr(), lead, torch.zeros_like(W).data_ptr(), axo.AXO_EPI_BIAS_GELU_ERF, Y.data_ptr(), lead,
+                       None, 0, gu.stream())
+        torch.cuda.synchronize()
+        outs.append(Y[:, :N].view(torch.int16))
+    assert torch.equal(outs[0][~far], outs[1][~far]) and (outs[0][:2] == 0).all()
+    assert (outs[1][far] == outs[1][far][0, 0]).all() and not (outs[1][far] & 0x7FFF == 0).any()
