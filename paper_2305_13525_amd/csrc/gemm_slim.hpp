@@ -207,20 +207,30 @@ __device__ __forceinline__ void slim_tile_body(const GemmArgs& g, const int i0, 
     __syncthreads();
     constexpr int QPR = BN / 4, QUADS = BM * QPR;  // quads of columns per row, per tile
     static_assert(QUADS % C::THREADS == 0, "whole rounds of quads");
+    auto each_quad = [&](auto store) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q0 = 0; q0 < QUADS; q0 += C::THREADS) {
-        const int q = q0 + tid;
-        const int lr = q / QPR, lc = (q % QPR) * 4;
-        const int row = i0 + lr, col = j0 + lc;
-        if (row >= g.Mo || col >= g.No) continue;
-        const int valid = min(4, g.No - col);
-        f32x4 x = {0.f, 0.f, 0.f, 0.f}, v = x;
-        if (g.epilogue >= EPI_MUL_DGELU_TANH) x = load_quad_extra(g, row, col, valid);
-        else if (g.epilogue != EPI_NONE && g.add_bias) x = load_bf16x4(g.bias + col, valid);
-        for (int w = 0; w < n_part; ++w)
-            v += *reinterpret_cast<const f32x4*>(smem + w * C::WAVE_BYTES + (lr * C::PART_STRIDE + lc) * 4);
-        store_quad(g, v, x, row, col, valid);
+        for (int q0 = 0; q0 < QUADS; q0 += C::THREADS) {
+            const int q = q0 + tid;
+            const int lr = q / QPR, lc = (q % QPR) * 4;
+            const int row = i0 + lr, col = j0 + lc;
+            if (row < g.Mo && col < g.No) store(row, col, min(4, g.No - col), smem + (lr * C::PART_STRIDE + lc) * 4);
+        }
+    };
+    auto sum_of = [&](const char* parts) __attribute__((always_inline)) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < n_part; ++w) v += *reinterpret_cast<const f32x4*>(parts + w * C::WAVE_BYTES);
+        return v;
+    };
+    if (g.epilogue == EPI_NONE) {
+        each_quad([&](int row, int col, int valid, const char* parts) { store_bf16_quad(g, sum_of(parts), row, col, valid); });
+        return;
     }
+    each_quad([&](int row, int col, int valid, const char* parts) {
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if (g.epilogue >= EPI_MUL_DGELU_TANH) x = load_quad_extra(g, row, col, valid);
+        else if (g.add_bias) x = load_bf16x4(g.bias + col, valid);
+        store_quad(g, sum_of(parts), x, row, col, valid);
+    });
 }
 
 // How a product is cut: tiles_m x tiles_n workgroups, tiles ordered in bands of group_m tile rows.

@@ -399,11 +399,11 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// Epilogue of a workgroup tile: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].  The operand
-// buffers are free.
+// Epilogue of a workgroup tile: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
 template <typename C, int LA, int LB>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
                                               const int wave, const int wm, const int wn, const int lane, char* smem) {
+    __syncthreads();  // all waves are done reading the operand buffers
     char* stage = smem + wave * (C::WTM * C::EPI_STRIDE);
     // The epilogue kind is decided once, outside the element loops: the plain path is then
     // straight-line code (the activation code is large; branching around it per element made the
@@ -575,10 +575,11 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
 // The epilogue of a tile that reaches over the output's edge, any kind, one compact path: the wave stages its
 // sums in fp32, half its rows at a time, and stores the quads of columns that lie inside.  (wrow0, wcol0): the
 // wave tile's origin.  Same operations per element as the whole-tile epilogue, so an element's bits do not
-// depend on the tile that it falls in.  The operand buffers are free.
+// depend on the tile that it falls in.
 template <typename C>
 __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int wrow0,
                                                       const int wcol0, const int wave, const int lane, char* smem) {
+    __syncthreads();  // all waves are done reading the operand buffers
     char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
     constexpr int F_STRIDE = C::WTN * 4 + 16, RP = C::WTM / 2, QPR = C::WTN / 4;
     static_assert(RP * F_STRIDE <= C::WTM * C::EPI_STRIDE, "fits the wave's staging region");
@@ -886,9 +887,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     step(1, T1{}, false, false, false, false);
     AXO_SETPRIO(0);
 
-    __syncthreads();  // all waves are done reading the operand buffers
-    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
-    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
@@ -1077,9 +1076,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
     const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No && (C::WTN == 64 || g.epilogue != EPI_ACC_F32);
-    __syncthreads();  // all waves are done reading the operand buffers
-    if (!store) return;
-    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    if (!store) __syncthreads();  // the one of an epilogue
+    else if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
