@@ -344,18 +344,18 @@ __device__ __forceinline__ void store_bf16_quad(const GemmArgs& g, f32x4 v, cons
         if (valid > 2) out[2] = (bf16_t)packed.y;
     }
 }
-// The same after the epilogue, whose kind is decided once for the four (once per value: forward 1001 x 1027 x 515 with a bias 8.6 us, now
-// 7.9, with the erf form 9.0 and 8.1; dgrad through the erf form 9.8 and 9.1).
+// The same in fp32.
+__device__ __forceinline__ void store_f32_quad(const GemmArgs& g, f32x4 v, const int row, const int col, const int valid) {
+    float* out = reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col;
+    if (valid >= 4) *reinterpret_cast<f32x4*>(out) = v;
+    else
+        for (int e = 0; e < valid; ++e) out[e] = v[e];
+}
+// bf16 after the epilogue, or fp32 with what is there added.  The kind is decided once for the four (once per value: forward
+// 1001 x 1027 x 515 with a bias 8.6 us, now 7.9, with the erf form 9.0 and 8.1; dgrad through the erf form 9.8 and 9.1).
 // `x` is what the epilogue adds or multiplies with: bias, pre-activations, or the fp32 values accumulated into.
 __device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, f32x4 x, const int row, const int col, const int valid) {
-    if (g.epilogue == EPI_ACC_F32) {
-        float* out = reinterpret_cast<float*>(g.C) + (int64_t)row * g.ldc + col;
-        v = x + v;
-        if (valid >= 4) *reinterpret_cast<f32x4*>(out) = v;
-        else
-            for (int e = 0; e < valid; ++e) out[e] = v[e];
-        return;
-    }
+    if (g.epilogue == EPI_ACC_F32) return store_f32_quad(g, x + v, row, col, valid);
     auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = f(v[e], x[e]);
@@ -609,22 +609,28 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
             __builtin_amdgcn_wave_barrier();
             continue;
         }
+        auto rows = [&](auto extra, auto store) __attribute__((always_inline)) {
 #pragma nounroll
-        for (int i0 = 0; i0 < ITERS; i0 += BATCH) {
-            f32x4 x[BATCH];
+            for (int i0 = 0; i0 < ITERS; i0 += BATCH) {
+                f32x4 x[BATCH];
 #pragma unroll
-            for (int i = 0; i < BATCH; ++i) {
-                const int row = wrow0 + h * RP + (i0 + i) * RPI + lane / QPR;
-                x[i] = bias;
-                if (per_row && row < g.Mo && valid > 0) x[i] = load_quad_extra(g, row, col, valid);
-            }
+                for (int i = 0; i < BATCH; ++i) {
+                    const int row = wrow0 + h * RP + (i0 + i) * RPI + lane / QPR;
+                    x[i] = extra(row, row < g.Mo && valid > 0);
+                }
 #pragma unroll
-            for (int i = 0; i < BATCH; ++i) {
-                const int lr = (i0 + i) * RPI + lane / QPR, row = wrow0 + h * RP + lr;
-                if (row < g.Mo && valid > 0)
-                    store_quad(g, *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), x[i], row, col, valid);
+                for (int i = 0; i < BATCH; ++i) {
+                    const int lr = (i0 + i) * RPI + lane / QPR, row = wrow0 + h * RP + lr;
+                    if (row < g.Mo && valid > 0) store(*reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), x[i], row);
+                }
             }
-        }
+        };
+        if (g.epilogue == EPI_ACC_F32)  // likewise: wgrad 1449 x 6656 of 42 tokens 31.5 -> 29.6 us, 10496 x 1920 of 168 34.7 -> 32.9
+            rows([&](int row, bool in) { return in ? load_quad_extra(g, row, col, valid) : bias; },
+                 [&](f32x4 v, f32x4 x, int row) { store_f32_quad(g, x + v, row, col, valid); });
+        else
+            rows([&](int row, bool in) { return per_row && in ? load_quad_extra(g, row, col, valid) : bias; },
+                 [&](f32x4 v, f32x4 x, int row) { store_quad(g, v, x, row, col, valid); });
         __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
     }
 }
