@@ -214,7 +214,9 @@ double mid_time(int Mo, int No, int R) {
 }
 
 // 64 x 64 tiles of a ring: a step takes 0.235 us with a CU to itself, and 0.15 us on a busy one, where two run beside
-// each other (2048 x 1024 x 1024 forward: 9.4 us measured, 9.5 estimated; wgrad 1024 x 1024 of 8192 tokens: 30 and 33).
+// each other (wgrad 1024 x 1024 of 8192 tokens: 29 us measured, 33 estimated).  These times are from before the ring's loop was peeled:
+// forward 2048 x 1024 x 1024 takes 8.7 us now where 9.5 are estimated, 64 steps of one round 14.6 where 18.2 are, so tiles that split
+// the reduction are still taken for some products that these would be quicker for.
 double small_time(int Mo, int No, int R) {
     const int64_t n = rounds_of(tiles_in(Mo, 64) * tiles_in(No, 64));
     return n <= 1 ? 3.2 + steps_in(R) * 0.235 : 3.0 + n * (0.85 + steps_in(R) * 0.15);
@@ -296,7 +298,9 @@ int straddling(const axo::bf16_t* p, int64_t ld) {
 //   256 x 128  dgrad only.  Its three stages are then requested one step ahead instead of two, whatever the rows: 4096 x 1536 x 6144 takes
 //              77 us in any place.  Without it 64 on lines, 76 or 67 with 16 bytes off dY or W, 85 with both, 81 with 32 bytes
 //              off both, 81 with 16 and 64 and 72 with 64 (2304 x 2176 x 2240 32 with it and 25, 31, 26, 34, 33, 33, 29): by the
-//              share of a step's 384 rows that straddle, the line lies at two thirds, 18 of 24 is on the right side of it.
+//              share of a step's 384 rows that straddle, the line lies at two thirds, 18 of 24 is on the right side of it.  With
+//              operands from HBM, behind the forward, 4000 x 2000 x 6000 (18 of 24) takes 97 us without and 88 with it: the
+//              same bytes fetched, the texture path busy 0.95 of the time without and 0.55 with it.
 //   256 x 256  of the first operand only, so only where that one's rows straddle: dgrad 4096 x 4096 x 8192 260 / 226 us, 8192 x 8192
 //              x 2000 272 / 233, 5120 x 5120 x 1024 58.6 / 53.4, forward 4096 x 4096 x 8192 225 / 205; with 64 bytes off, half the
 //              rows, 4096 x 4096 with 12 / 16 / 24 / 32 steps 26.5 / 27.0, 32.1 / 32.6, 43.6 / 43.6, 53.5 / 53.4.
@@ -545,7 +549,8 @@ double group_makespan(const std::vector<SegCost>& segs) {
 // 7168 x 1152 x 4096 took 172 us, now 159; 9160 / 8 tokens of 128 x 104 with extras 50 and 26; over 500 chains 1.5 % less).  A split
 // with more work than NUM_CU CUs can do before the best plan so far ends is not simulated, nor is a product looked at again
 // when no other has changed since.  Cached per list of shapes, so every new token count is a search: a block of
-// width 2056 with 200-1000 tokens 2114 us a step when all were simulated, tile by tile, 212 now and 210 with plans at hand.
+// width 2056 with 200-1000 tokens 2114 us a step when all were simulated, tile by tile, 212 so and 210 with plans at hand.  With
+// pairs of small tiles among the choices a search takes 6 us of host time for a layer, 50 for a block of four.
 std::vector<int> plan_group(const std::vector<GroupItem>& items) {
     static std::mutex mu;
     static std::map<std::vector<GroupItem>, std::vector<int>> cache;
