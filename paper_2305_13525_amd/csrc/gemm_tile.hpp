@@ -300,6 +300,10 @@ __device__ __forceinline__ u32x4_t tile_rsrc(const bf16_t* p, uint32_t bound) {
     return r;
 }
 
+// Four bf16 values in two dwords, the first in the low half.
+__device__ __forceinline__ f32x4 bf16x4_of(uint32_t lo, uint32_t hi) {
+    return f32x4{__uint_as_float(lo << 16), __uint_as_float(lo & 0xFFFF0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xFFFF0000u)};
+}
 // Four consecutive bf16 values of memory (8-byte aligned), the first `valid` of them inside the matrix, the others zero.
 // The loads of a part are independent of each other (indices clamped, not a loop of `valid` rounds, each of which waits for
 // its load).
@@ -307,10 +311,7 @@ __device__ __forceinline__ f32x4 load_bf16x4(const bf16_t* p, int valid) {
     f32x4 x = {0.f, 0.f, 0.f, 0.f};
     if (valid >= 4) {
         const uint2 raw = *reinterpret_cast<const uint2*>(p);
-        x[0] = __uint_as_float(raw.x << 16);
-        x[1] = __uint_as_float(raw.x & 0xFFFF0000u);
-        x[2] = __uint_as_float(raw.y << 16);
-        x[3] = __uint_as_float(raw.y & 0xFFFF0000u);
+        x = bf16x4_of(raw.x, raw.y);
     } else if (valid > 0) {
         const bf16_t v0 = p[0], v1 = p[min(1, valid - 1)], v2 = p[min(2, valid - 1)];
         x[0] = bf16_bits_to_f32(v0);
