@@ -400,7 +400,7 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// Epilogue of a workgroup tile: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
+// Epilogue of a workgroup tile of 256 rows: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
 template <typename C, int LA, int LB>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
                                               const int wave, const int wm, const int wn, const int lane, char* smem) {
@@ -418,10 +418,6 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     int wrow0 = i0 + wm * C::WTM, wcol0 = j0 + wn * C::WTN;
     asm volatile("" : "+s"(wrow0), "+s"(wcol0));
     bf16_t* const Cw = g.C + (int64_t)wrow0 * g.ldc + wcol0;
-    // Whether a wave asks first if the erf form meets values that want the longer arithmetic (FAR of gelu_erf).  With 64 or 128 values
-    // per lane that pays: forward 8192 x 512 x 8192 takes 101 us where there are none, 112 where there are, and 109 with that arithmetic
-    // throughout (32768 x 2048 x 4096: 452, 469 and 462).  With fewer it does not: 1024^3 6.4 us with the question, 6.2 without.
-    constexpr bool ASKS = C::TM * C::TN >= 16;
     // The bias of a lane's four columns in the wave tile's block b of 16.
     auto bias_of = [&](const int b) __attribute__((always_inline)) {
         return g.add_bias ? load_bf16x4(g.bias + wcol0 + b * 16 + 4 * (lane >> 4), 4) : f32x4{0.f, 0.f, 0.f, 0.f};
@@ -446,7 +442,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         // FAR: or the arithmetic that both forms share moves ahead of the choice between them, and the kernel spills
-                        if (FAR && ASKS) asm volatile("" : "+v"(v[e]));
+                        if (FAR) asm volatile("" : "+v"(v[e]));
                         v[e] = gelu_erf<FAR>(v[e] + bv[e]);
                     }
                 } else if (FWD_EPI) {
@@ -506,23 +502,23 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
             case EPI_BIAS_GELU_TANH: finish(IC<EPI_BIAS_GELU_TANH>{}, IC<0>{}); return;
             default: break;
         }
-        if constexpr (!ASKS) finish(IC<EPI_BIAS_GELU_ERF>{}, IC<1>{});
-        else {
-            float least = 0.f;  // the least sum of a column plus its bias is its least value
+        // A wave asks first if the erf form meets values that want the longer arithmetic (FAR of gelu_erf).  With 64 or 128 values
+        // per lane that pays: forward 8192 x 512 x 8192 takes 101 us where there are none, 112 where there are, and 109 with that
+        // arithmetic throughout (32768 x 2048 x 4096: 452, 469 and 462).
+        float least = 0.f;  // the least sum of a column plus its bias is its least value
 #pragma unroll
-            for (int b = 0; b < C::TN; ++b) {
-                const f32x4 bv = bias_of(b);
+        for (int b = 0; b < C::TN; ++b) {
+            const f32x4 bv = bias_of(b);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float sum = acc[0][b][e];
+            for (int e = 0; e < 4; ++e) {
+                float sum = acc[0][b][e];
 #pragma unroll
-                    for (int a = 1; a < C::TM; ++a) sum = fminf(sum, acc[a][b][e]);
-                    least = fminf(least, sum + bv[e]);
-                }
+                for (int a = 1; a < C::TM; ++a) sum = fminf(sum, acc[a][b][e]);
+                least = fminf(least, sum + bv[e]);
             }
-            if (__any(least < GELU_ERF_FAR)) finish(IC<EPI_BIAS_GELU_ERF>{}, IC<1>{});
-            else finish(IC<EPI_BIAS_GELU_ERF>{}, IC<0>{});
         }
+        if (__any(least < GELU_ERF_FAR)) finish(IC<EPI_BIAS_GELU_ERF>{}, IC<1>{});
+        else finish(IC<EPI_BIAS_GELU_ERF>{}, IC<0>{});
     } else if (LA == KC && LB == KC) {  // dgrad
         switch (g.epilogue) {
             case EPI_NONE: finish(IC<EPI_NONE>{}, IC<0>{}); return;
@@ -530,7 +526,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
             default: finish(IC<EPI_MUL_DGELU_ERF>{}, IC<0>{}); return;
         }
     } else {  // wgrad
-        if constexpr (C::WTN == 64) if (g.epilogue == EPI_ACC_F32) {
+        if (g.epilogue == EPI_ACC_F32) {
             // fp32 accumulation dW32 += acc, no rounding.  The wave's 64 fp32 columns are 256 bytes
             // per row: the sums are staged through the wave's LDS region (half the wave tile's rows
             // at a time, rows padded to 272 bytes) so that 16 lanes read, add and write back one
@@ -573,7 +569,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     }
 }
 
-// The epilogue of a tile that reaches over the output's edge, any kind, one compact path: the wave stages its
+// The epilogue of a tile of 256 rows that reaches over the output's edge, any kind, one compact path: the wave stages its
 // sums in fp32, half its rows at a time, and stores the quads of columns that lie inside.  (wrow0, wcol0): the
 // wave tile's origin.  Same operations per element as the whole-tile epilogue, so an element's bits do not
 // depend on the tile that it falls in.
@@ -635,6 +631,168 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
         __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
     }
 }
+
+// Epilogue of a 64 x 64 or 128 x 128 tile, whole or reaching over the output's edge.  What it reads from memory beside the sums is
+// requested on its own and kept as it comes, so that 64 x 64 tiles can do that ahead of the reduction: a short kernel has nothing else to
+// hide a trip to memory behind.  The arithmetic is done in the accumulators' layout for both kinds of tiles, only the stores differ.
+// With the epilogues of the 256-row tiles, which load when they need it, and where clipped in two batches one behind the other, dgrad
+// 1001 x 1027 x 515 through the erf form spent 1.4 us between the last MFMA of a whole tile and its last store, and 3.3 us in the
+// tiles of the last three columns; the kernel took 10.6 us and takes 9.8 now.  Likewise, before and now: forward 1001 x 515 x 1027 with a bias
+// 8.0 and 7.25, 512 x 1024 x 1024 with tanh GELU 6.6 and 6.3, wgrad into fp32 1000^3 9.6 and 9.1, 1001 x 1003 x 1000 9.95 and 8.8; on
+// 128 x 128 tiles dgrad 2001 x 2037 x 725 through the erf form 18.7 and 16.1, forward 2048 x 2048 x 512 with tanh GELU 9.5 and 9.0.
+template <typename C, int LA, int LB>
+struct SmallEpilogue {
+    static constexpr bool FWD = LA == KC && LB == MC, DGRAD = LA == KC && LB == KC;
+    static constexpr int ROWS = C::TM, COLS = C::TN;
+    // fp32 sums are added in another layout, in which the lanes of a row follow each other: QPR quads per row, half the rows at a time
+    static constexpr int F_STRIDE = C::WTN * 4 + 16, RP = C::WTM / 2, QPR = C::WTN / 4, RPI = 64 / QPR, ITERS = RP / RPI;
+    static_assert(RP * F_STRIDE <= C::WTM * C::EPI_STRIDE, "fits the wave's staging region");
+    u32x4 in[FWD ? COLS : DGRAD ? ROWS * COLS : 2 * ITERS];
+    int wrow0, wcol0, lane;
+    bool inside;
+
+    __device__ __forceinline__ int sum_row(int i) const { return wrow0 + i / ITERS * RP + i % ITERS * RPI + lane / QPR; }
+    __device__ __forceinline__ int sum_col() const { return wcol0 + lane % QPR * 4; }
+    // (wrow0_, wcol0_): the wave tile's origin
+    __device__ __forceinline__ void request(const GemmArgs& g, int wrow0_, int wcol0_, int lane_) {
+        wrow0 = wrow0_;
+        wcol0 = wcol0_;
+        lane = lane_;
+        if (g.epilogue == EPI_NONE) return;
+        if (FWD && !g.add_bias) {
+#pragma unroll
+            for (u32x4& x : in) x = u32x4{0u, 0u, 0u, 0u};
+            inside = true;
+            return;
+        }
+        // A wave tile inside the columns takes whole quads, one that reaches over the last column single values; what lies beyond the
+        // matrix stands for the last row's or column's, and is not stored.  One choice per wave, no lane's own: registers that different
+        // loads of a lane may write make the compiler wait for one before the other.
+        inside = wcol0 + C::WTN <= g.No;
+        if (inside) load(g, std::true_type{});
+        else load(g, std::false_type{});
+    }
+    template <typename Inside>
+    __device__ __forceinline__ void load(const GemmArgs& g, Inside) {
+        if constexpr (FWD || DGRAD) {
+#pragma unroll
+            for (int b = 0; b < COLS; ++b)
+#pragma unroll
+                for (int a = 0; a < (FWD ? 1 : ROWS); ++a) {
+                    const int row = min(wrow0 + a * 16 + (lane & 15), g.Mo - 1), col = wcol0 + b * 16 + 4 * (lane >> 4);
+                    const bf16_t* const p = FWD ? g.bias : g.aux + (int64_t)row * g.ldaux;
+                    u32x4& x = in[FWD ? b : a * COLS + b];  // four values in two dwords, or in one each
+                    if constexpr (Inside::value) {
+                        const uint2 raw = *reinterpret_cast<const uint2*>(p + col);
+                        x[0] = raw.x;
+                        x[1] = raw.y;
+                    } else
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[e] = p[min(col + e, g.No - 1)];
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2 * ITERS; ++i) {
+                const uint32_t* const p = reinterpret_cast<const uint32_t*>(g.C) + (int64_t)min(sum_row(i), g.Mo - 1) * g.ldc;
+                if constexpr (Inside::value) in[i] = *reinterpret_cast<const u32x4*>(p + sum_col());
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) in[i][e] = p[min(sum_col() + e, g.No - 1)];
+            }
+        }
+    }
+    __device__ __forceinline__ f32x4 extra(int a, int b) const {
+        const u32x4 x = in[FWD ? b : a * COLS + b];
+        return bf16x4_of(x[0], x[1]);
+    }
+    __device__ __forceinline__ void finish(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], int wave, char* smem, bool whole) {
+        __syncthreads();  // all waves are done reading the operand buffers
+        char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
+        if constexpr (!FWD && !DGRAD) if (g.epilogue == EPI_ACC_F32) {
+            float* const out = reinterpret_cast<float*>(g.C);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int a = 0; a < ROWS / 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < COLS; ++b)
+                        *reinterpret_cast<f32x4*>(stage + (a * 16 + (lane & 15)) * F_STRIDE + (b * 16 + 4 * (lane >> 4)) * 4) =
+                            acc[h * (ROWS / 2) + a][b];
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the region is private to the wave
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < ITERS; ++i) {
+                    const int row = sum_row(h * ITERS + i), col = sum_col();
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(stage + (i * RPI + lane / QPR) * F_STRIDE + lane % QPR * 16);
+                    const f32x4 sum = __builtin_bit_cast(f32x4, in[h * ITERS + i]) + v;
+                    if (whole) *reinterpret_cast<f32x4*>(out + (int64_t)row * g.ldc + col) = sum;
+                    else if (row < g.Mo && col < g.No) store_f32_quad(g, sum, row, col, min(4, g.No - col));
+                }
+                __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
+            }
+            return;
+        }
+        auto convert = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int b = 0; b < COLS; ++b)
+#pragma unroll
+                for (int a = 0; a < ROWS; ++a) {
+                    const f32x4 v = f(acc[a][b], a, b);
+                    uint2 packed;
+                    packed.x = pack_bf16x2(v[0], v[1]);
+                    packed.y = pack_bf16x2(v[2], v[3]);
+                    *reinterpret_cast<uint2*>(stage + (a * 16 + (lane & 15)) * C::EPI_STRIDE + (b * 16 + 4 * (lane >> 4)) * 2) = packed;
+                }
+        };
+        auto each = [&](auto f) __attribute__((always_inline)) {  // f(sum, what is read for it)
+            if (!inside)
+#pragma unroll
+                for (u32x4& x : in) x = u32x4{x[0] | x[1] << 16, x[2] | x[3] << 16, 0u, 0u};
+            convert([&](f32x4 v, int a, int b) __attribute__((always_inline)) {
+                const f32x4 x = extra(a, b);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = f(v[e], x[e]);
+                return v;
+            });
+        };
+        auto plain = [&]() __attribute__((always_inline)) { convert([](f32x4 v, int, int) { return v; }); };
+        if constexpr (FWD) switch (g.epilogue) {
+            case EPI_NONE: plain(); break;
+            case EPI_BIAS: each([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS); }); break;
+            case EPI_BIAS_GELU_TANH: each([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS_GELU_TANH); }); break;
+            // the longer arithmetic on every value: 1024^3 6.2 us, 6.4 where a wave asks first if it needs it
+            default: each([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS_GELU_ERF); }); break;
+        } else if constexpr (DGRAD) switch (g.epilogue) {
+            case EPI_NONE: plain(); break;
+            case EPI_MUL_DGELU_TANH: each([](float s, float x) { return apply_dact(s, x, EPI_MUL_DGELU_TANH); }); break;
+            default: each([](float s, float x) { return apply_dact(s, x, EPI_MUL_DGELU_ERF); }); break;
+        } else plain();
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the region is private to the wave
+        __builtin_amdgcn_wave_barrier();
+        constexpr int LANES_PER_ROW = C::WTN * 2 / 16, ROWS_PER_PASS = 64 / LANES_PER_ROW, PASSES = C::WTM / ROWS_PER_PASS;
+        u32x4 out[PASSES];
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p)  // all reads ahead of the first store, as in tile_epilogue
+            out[p] = *reinterpret_cast<const u32x4*>(stage + (p * ROWS_PER_PASS + lane / LANES_PER_ROW) * C::EPI_STRIDE + lane % LANES_PER_ROW * 16);
+        const int row0 = wrow0 + lane / LANES_PER_ROW, col = wcol0 + lane % LANES_PER_ROW * 8, valid = g.No - col;
+        bf16_t* const to = g.C + (int64_t)row0 * g.ldc + col;
+        if (whole) {
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) __builtin_nontemporal_store(out[p], reinterpret_cast<u32x4*>(to + (int64_t)(p * ROWS_PER_PASS) * g.ldc));
+            return;
+        }
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            bf16_t* const at = to + (int64_t)(p * ROWS_PER_PASS) * g.ldc;
+            if (row0 + p * ROWS_PER_PASS >= g.Mo) continue;
+            if (valid >= 8) *reinterpret_cast<u32x4*>(at) = out[p];
+            else
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (e < valid) at[e] = (bf16_t)(out[p][e / 2] >> (e % 2 * 16));
+        }
+    }
+};
 
 // One BM x BN output tile with its top-left corner at (i0, j0), whole reduction.  LINES: the rows of A, which is KC, are
 // fetched by whole cache lines (line_phase), on three stages; with them and two of B the LDS is full, so rows of B that
@@ -1034,6 +1192,15 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     // The walk ends in stage D - 1 and starts in whichever stage that takes, so that the last steps, which differ from the
     // others, exist once, behind a loop without branches.
     static_assert(D >= 3 && D <= 5, "stages of the ring");
+    // What SmallEpilogue reads beside the sums is requested ahead of everything else (EARLY) where it is little beside a stage of the
+    // operands.  On 128 x 128 tiles pre-activations and old fp32 values are as much as a stage or two, and the reduction would start that
+    // much later (dgrad 2048 x 2048 x 1024 through the erf form 14.7 us, 15.4 with them first): those are requested behind it (LATE), and
+    // pre-activations of whole tiles a block at a time, by tile_epilogue, where requesting all at once is 2 % slower still (MIXED).
+    enum { EARLY, LATE, MIXED };
+    constexpr bool SMALL = BM <= 128;
+    constexpr int EPILOGUE = BM <= 64 || (LA == KC && LB == MC) ? EARLY : LB == KC ? MIXED : LATE;
+    [[maybe_unused]] std::conditional_t<SMALL, SmallEpilogue<C, LA, LB>, char> epilogue;
+    if constexpr (SMALL && EPILOGUE == EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
     const int lead = KT % D, first = lead > 0 ? D - lead : 0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
@@ -1082,10 +1249,17 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if (KT >= 3) step(IC<D - 3>{}, IC<3>{});
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
-    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No && (C::WTN == 64 || g.epilogue != EPI_ACC_F32);
-    if (!store) __syncthreads();  // the one of an epilogue
-    else if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
-    else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
+    if (!store) {
+        __syncthreads();  // the one of an epilogue
+        return;
+    }
+    if constexpr (!SMALL || EPILOGUE == MIXED)
+        if (whole) return tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    if constexpr (SMALL) {
+        if constexpr (EPILOGUE != EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
+        epilogue.finish(g, acc, wave, smem, whole);
+    } else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
 using MixBigCfg = TileCfg<256, 256, 2, 4>;
