@@ -1,4 +1,5 @@
-"""ctypes binding of libaxo.so: argument marshalling only.
+"""Binding of libaxo.so: argument marshalling only, by ctypes, and for the calls of a training loop by the extension
+module _calls (csrc/calls.c), whose functions stand in for the wrappers below and call them for all but plain arguments.
 
 Function names and argument order mirror include/axo.h.  Matrices are passed as raw device
 addresses (`tensor.data_ptr()`), streams as raw `hipStream_t` values
@@ -10,6 +11,11 @@ from __future__ import annotations
 import ctypes
 import os
 from typing import Optional, Sequence, Tuple
+
+try:
+    from . import _calls
+except ImportError:  # not built yet: the ctypes wrappers do the same, slower
+    _calls = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libaxo.so")
@@ -69,6 +75,9 @@ class LayerExt(ctypes.Structure):
 
 
 _lib: Optional[ctypes.CDLL] = None
+# the functions that _calls has
+_QUICK = ("axo_fc_fwd", "axo_fc_dgrad", "axo_fc_wgrad", "axo_fc_dgrad_act", "axo_fc_wgrad_acc", "axo_bias_grad", "axo_bias_grad_ws",
+          "axo_bias_grad_static")
 
 
 def library_path() -> str:
@@ -133,6 +142,8 @@ def library() -> ctypes.CDLL:
     L.axo_layer_step_levels.restype = i32
     L.axo_layer_step_tiles.argtypes = [ctypes.POINTER(LayerExt), i32, ctypes.POINTER(ctypes.c_int)]
     L.axo_layer_step_tiles.restype = i32
+    if _calls is not None:
+        _calls.bind({name: ctypes.cast(getattr(L, name), vp).value for name in _QUICK})
     _lib = L
     return L
 
@@ -296,3 +307,9 @@ def axo_bias_grad_static(p: Problem, dY: int, lddy: int, db: int, accumulate: in
 
 def axo_bias_grad_static_limit() -> int:
     return int(library().axo_bias_grad_static_limit())
+
+
+_WRAPPERS = {name: globals()[name] for name in _QUICK}
+if _calls is not None:
+    _calls.set_up(Problem, _WRAPPERS, _check)
+    globals().update({name: getattr(_calls, name) for name in _QUICK})

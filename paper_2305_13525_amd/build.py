@@ -1,12 +1,14 @@
-"""Compile the HIP library for gfx950 into paper_2305_13525_amd/libaxo.so (in-tree)."""
+"""Compile the HIP library for gfx950 into paper_2305_13525_amd/libaxo.so, and the extension module _calls beside it (in-tree)."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaxo.so")
+CALLS = os.path.join(HERE, "_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -21,16 +23,23 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip"))) + sorted(glob.glob(os.path.join(CSRC, "*.cpp")))
 
 
-def build(verbose: bool = False, extra=()) -> str:
-    cmd = [HIPCC] + FLAGS + list(extra) + sources() + ["-o", LIB]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd))
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + out)
     if verbose and out.strip():
         print(out)
+
+
+def build(verbose: bool = False, extra=()) -> str:
+    _run([HIPCC] + FLAGS + list(extra) + sources() + ["-o", LIB], verbose)
+    # to a new file, moved into place: a running process may have the old one mapped
+    _run([os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "calls.c"), "-o", CALLS + ".new"], verbose)
+    os.replace(CALLS + ".new", CALLS)
     return LIB
 
 
