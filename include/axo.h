@@ -146,18 +146,20 @@ typedef enum axo_kernel {
     AXO_KERNEL_TILES_128 = 6,           /* 128 x 128 tiles, reduction in order                             */
     AXO_KERNEL_TILES_256 = 7,           /* 256 x 256 tiles, reduction in order                             */
     AXO_KERNEL_TILES_256_HALF = 8,      /* 256 x 128 tiles, reduction in order                             */
-    AXO_KERNEL_TILES_256_MIXED = 9      /* both of these in one launch                                     */
+    AXO_KERNEL_TILES_256_MIXED = 9,     /* both of these in one launch                                     */
+    AXO_KERNEL_TILES_64_128 = 10,       /* 64 x 128 tiles, reduction in order                              */
+    AXO_KERNEL_TILES_128_64 = 11        /* 128 x 64 tiles, reduction in order                              */
 } axo_kernel_t;
 
 /* Host only.  Reports in *kernel (axo_kernel_t) the kernel on which the product runs when it is called on its
  * own; arguments and errors as axo_fc_route.  A function of the shard shape and the leading dimensions only.
  * The kernels are chosen by estimated time, so the answer for a shape may change from one version to the next.  In
- * a chain's grouped launch the products of classes 5 to 9 run on 256-row tiles or pairs of 64 x 64 ones and those of classes 2 to 4 on
+ * a chain's grouped launch the products of classes 5 to 11 run on 256-row tiles or pairs of 64 x 64 ones and those of classes 2 to 4 on
  * either size of split tile (axo_layer_step_tiles tells); all kernels of one of these two classes give the same bits. */
 int axo_fc_kernel(const axo_problem_t *p, int op, int64_t ld_a, int64_t ld_b, int64_t ld_out, int *kernel);
 
 /* Host only.  Reports in *tiles the kinds of tiles that a call of the product on its own runs on, with inputs at the addresses a and b:
- * bit k for axo_kernel_t k (1 to 8; two of them for AXO_KERNEL_TILES_256_MIXED), and bit 16 + k where tiles of that kind fetch
+ * bit k for axo_kernel_t k (1 to 8, 10, 11; two of them for AXO_KERNEL_TILES_256_MIXED), and bit 16 + k where tiles of that kind fetch
  * rows that do not start on cache lines by whole lines.  That choice looks at the addresses; it does not show in the results.
  * Other arguments and errors as axo_fc_route. */
 #define AXO_TILES_BY_LINES (1 << 16)

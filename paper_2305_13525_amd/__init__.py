@@ -6,7 +6,8 @@ include/axo.h); this package is the thin binding the tests and the benchmark cal
 from .binding import (  # noqa: F401
     AXO_EPI_BIAS, AXO_EPI_BIAS_GELU_ERF, AXO_EPI_BIAS_GELU_TANH, AXO_EPI_NONE,
     AXO_KERNEL_GENERAL, AXO_KERNEL_NONE, AXO_KERNEL_SPLIT_32, AXO_KERNEL_SPLIT_32_TWO_STAGES, AXO_KERNEL_SPLIT_64,
-    AXO_KERNEL_TILES_128, AXO_KERNEL_TILES_256, AXO_KERNEL_TILES_256_HALF, AXO_KERNEL_TILES_256_MIXED, AXO_KERNEL_TILES_64,
+    AXO_KERNEL_TILES_128, AXO_KERNEL_TILES_128_64, AXO_KERNEL_TILES_256, AXO_KERNEL_TILES_256_HALF, AXO_KERNEL_TILES_256_MIXED, AXO_KERNEL_TILES_64,
+    AXO_KERNEL_TILES_64_128,
     AXO_OP_DGRAD, AXO_OP_FWD, AXO_OP_WGRAD, AXO_ROUTE_COVERED, AXO_ROUTE_GENERAL, AXO_ROUTE_INTERIOR_STRIPS,
     AXO_ROUTE_NONE, AXO_ROUTE_TILED, AXO_TILES_BY_LINES, AxoError, Layer, LayerExt, Problem,
     axo_bias_grad, axo_bias_grad_static, axo_bias_grad_static_limit,

@@ -25,7 +25,7 @@ AXO_OP_FWD, AXO_OP_DGRAD, AXO_OP_WGRAD = 0, 1, 2
 AXO_ROUTE_NONE, AXO_ROUTE_TILED, AXO_ROUTE_COVERED, AXO_ROUTE_INTERIOR_STRIPS, AXO_ROUTE_GENERAL = 0, 1, 2, 3, 4
 (AXO_KERNEL_NONE, AXO_KERNEL_GENERAL, AXO_KERNEL_SPLIT_32, AXO_KERNEL_SPLIT_32_TWO_STAGES, AXO_KERNEL_SPLIT_64,
  AXO_KERNEL_TILES_64, AXO_KERNEL_TILES_128, AXO_KERNEL_TILES_256, AXO_KERNEL_TILES_256_HALF,
- AXO_KERNEL_TILES_256_MIXED) = range(10)
+ AXO_KERNEL_TILES_256_MIXED, AXO_KERNEL_TILES_64_128, AXO_KERNEL_TILES_128_64) = range(12)
 
 AXO_TILES_BY_LINES = 1 << 16
 

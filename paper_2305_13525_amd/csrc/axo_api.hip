@@ -229,20 +229,26 @@ double small_time_long(int Mo, int No, int R) {
     return n <= 1 || late <= 0 ? 0.0 : n * late * 0.05;
 }
 
-// Launch of one product on square tiles of `ROWS` rows.
-template <typename C, int ROWS>
-int launch_square(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* raised, const GemmArgs& g, hipStream_t st) {
+// Launch of one product on tiles of ROWS x COLS.
+template <typename C, int ROWS, int COLS>
+int launch_tiles(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* raised, const GemmArgs& g, hipStream_t st) {
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, raised)) return AXO_ERR_HIP;
-    const int tm = (g.Mo + ROWS - 1) / ROWS, tn = (g.No + ROWS - 1) / ROWS;
+    const int tm = (int)tiles_in(g.Mo, ROWS), tn = (int)tiles_in(g.No, COLS);
     hipLaunchKernelGGL(kern, dim3((unsigned)tm * (unsigned)tn), dim3(C::THREADS), C::LDS_BYTES, st, g, tm, tn, std::min(tm, 8));
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 
-// The tiles of a product on its own, 64 x 64, 128 x 128 or 256-row ones, whichever are estimated quickest (all give
-// the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by LDS
-// traffic (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
-enum class Tiles { small, mid, big };
+// The tiles of a product on its own, whichever are estimated quickest (all give
+// the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by the rate at which a CU takes in
+// operands (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
+// Halves of those, 64 x 128 or 128 x 64 (`wide`, `tall`), where every one has a CU of its own, 64 x 64 tiles would take clearly more than one
+// round and the reduction has at least 16 steps: there they are the quickest by 7 to 45 % (gemm_rect_kernel; with 8 steps 64 x 64 tiles
+// are as quick, 2000 x 1000 x 512 6.2 us either way, and with 16 tiles too many for one round: 1001 x 1027 x 1300 13.2 and 13.4).  Of the two the one with fewer tiles, else the wide one, which reads the rows of a forward's W
+// in segments of 256 bytes (1000 x 2000 x 3000 23.1 us, 27.0 on the tall ones; other products take either in the same time).
+enum class Tiles { small, wide, tall, mid, big };
 Tiles tiles_of(int Mo, int No, int R) {
+    const int64_t wide = tiles_in(Mo, 64) * tiles_in(No, 128), tall = tiles_in(Mo, 128) * tiles_in(No, 64);
+    if (std::min(wide, tall) <= NUM_CU && 8 * tiles_in(Mo, 64) * tiles_in(No, 64) > 9 * NUM_CU && steps_in(R) >= 16) return wide <= tall ? Tiles::wide : Tiles::tall;
     const double small_us = small_time(Mo, No, R) + small_time_long(Mo, No, R), mid_us = mid_time(Mo, No, R), big_us = tile_time(Mo, No, R);
     if (small_us < mid_us && small_us < big_us && grid_fits(tiles_in(Mo, 64) * tiles_in(No, 64), axo::SmallCfg<false>::THREADS)) return Tiles::small;
     return mid_us < big_us ? Tiles::mid : Tiles::big;
@@ -291,7 +297,7 @@ int straddling(const axo::bf16_t* p, int64_t ld) {
 
 // Whether a product fetches operands whose reduction runs inside the rows by whole cache lines (line_phase) on tiles of this kind:
 // where enough rows straddle lines and the reduction is long enough to pay for the later start and the one stage more.
-//   64 x 64, 128 x 128  a stage was added for it, or there were four: wherever either operand has such rows.  Without / with it, rows 16
+//   64 x 64, 128 x 128 and its halves  a stage was added for it, or there were four: wherever either operand has such rows.  Without / with it, rows 16
 //              bytes off, in us: dgrad 1024 x 1024 with 8 / 16 / 32 steps 4.70 / 5.11, 7.82 / 6.83, 12.0 / 9.3; 2048 x 1024 (two
 //              tiles per CU) with 8 6.66 / 6.35; 2048 x 2048 with 8 / 16 / 32 9.62 / 9.33, 14.6 / 13.3, 23.3 / 18.0; one operand
 //              off and half its rows straddling 1024 x 1024 x 2048 8.98 / 8.73, 2048 x 2048 x 2048 19.1 / 18.2
@@ -338,18 +344,20 @@ int launch_mixed(const GemmArgs& g, const axo::TileSched& sc, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 template <int LA, int LB, bool LINES>
-int launch_square_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
-    static std::atomic<uint64_t> raised[2]{{0}, {0}};
-    if (tiles == Tiles::small) return launch_square<axo::SmallCfg<LINES>, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
-    return launch_square<axo::MidCfg, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[1], g, st);
+int launch_ring_tiles(const GemmArgs& g, Tiles tiles, hipStream_t st) {
+    static std::atomic<uint64_t> raised[4]{{0}, {0}, {0}, {0}};
+    if (tiles == Tiles::small) return launch_tiles<axo::SmallCfg<LINES>, 64, 64>(axo::gemm_small_kernel<LA, LB, LINES>, &raised[0], g, st);
+    if (tiles == Tiles::wide) return launch_tiles<axo::RectCfg<true>, 64, 128>(axo::gemm_rect_kernel<LA, LB, true, LINES>, &raised[1], g, st);
+    if (tiles == Tiles::tall) return launch_tiles<axo::RectCfg<false>, 128, 64>(axo::gemm_rect_kernel<LA, LB, false, LINES>, &raised[2], g, st);
+    return launch_tiles<axo::MidCfg, 128, 128>(axo::gemm_mid_kernel<LA, LB, LINES>, &raised[3], g, st);
 }
 template <int LA, int LB>
 int launch_tile(const GemmArgs& g, hipStream_t st) {
     const Tiles tiles = tiles_of(g.Mo, g.No, g.R);
     if (tiles != Tiles::big) {
         if constexpr (LA == axo::KC)
-            if (takes_lines(g, LA, LB, tiles == Tiles::small ? Tile::t64 : Tile::t128)) return launch_square_tiles<LA, LB, true>(g, tiles, st);
-        return launch_square_tiles<LA, LB, false>(g, tiles, st);
+            if (takes_lines(g, LA, LB, tiles == Tiles::small ? Tile::t64 : Tile::t128)) return launch_ring_tiles<LA, LB, true>(g, tiles, st);
+        return launch_ring_tiles<LA, LB, false>(g, tiles, st);
     }
     const axo::TileSched sc = plan_product(g, LA, LB);
     const Lines lines = lines_of(g, LA, LB, sc);
@@ -728,6 +736,8 @@ int kernel_id(const GemmArgs& g, int la, int lb) {
     }
     switch (tiles_of(g.Mo, g.No, g.R)) {
         case Tiles::small: return AXO_KERNEL_TILES_64;
+        case Tiles::wide: return AXO_KERNEL_TILES_64_128;
+        case Tiles::tall: return AXO_KERNEL_TILES_128_64;
         case Tiles::mid: return AXO_KERNEL_TILES_128;
         default: break;
     }
@@ -740,8 +750,8 @@ int tile_bits(int kernel, bool lines) { return (1 << kernel) | (lines ? AXO_TILE
 int tiles_id(const GemmArgs& g, int la, int lb) {
     const int kernel = kernel_id(g, la, lb);
     if (kernel == AXO_KERNEL_NONE) return 0;
-    if (kernel < AXO_KERNEL_TILES_256) {
-        const bool ring = kernel == AXO_KERNEL_TILES_64 || kernel == AXO_KERNEL_TILES_128;
+    if (kernel < AXO_KERNEL_TILES_256 || kernel > AXO_KERNEL_TILES_256_MIXED) {
+        const bool ring = kernel >= AXO_KERNEL_TILES_64;
         return tile_bits(kernel, ring && takes_lines(g, la, lb, kernel == AXO_KERNEL_TILES_64 ? Tile::t64 : Tile::t128));
     }
     const axo::TileSched sc = plan_product(g, la, lb);

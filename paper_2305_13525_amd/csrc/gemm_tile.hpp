@@ -632,7 +632,7 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
     }
 }
 
-// Epilogue of a 64 x 64 or 128 x 128 tile, whole or reaching over the output's edge.  What it reads from memory beside the sums is
+// Epilogue of a tile of at most 128 x 128, whole or reaching over the output's edge.  What it reads from memory beside the sums is
 // requested on its own and kept as it comes, so that 64 x 64 tiles can do that ahead of the reduction: a short kernel has nothing else to
 // hide a trip to memory behind.  The arithmetic is done in the accumulators' layout for both kinds of tiles, only the stores differ.
 // With the epilogues of the 256-row tiles, which load when they need it, and where clipped in two batches one behind the other, dgrad
@@ -1198,7 +1198,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     // pre-activations of whole tiles a block at a time, by tile_epilogue, where requesting all at once is 2 % slower still (MIXED).
     enum { EARLY, LATE, MIXED };
     constexpr bool SMALL = BM <= 128;
-    constexpr int EPILOGUE = BM <= 64 || (LA == KC && LB == MC) ? EARLY : LB == KC ? MIXED : LATE;
+    constexpr int EPILOGUE = BM * BN < 128 * 128 || (LA == KC && LB == MC) ? EARLY : LB == KC ? MIXED : LATE;
     [[maybe_unused]] std::conditional_t<SMALL, SmallEpilogue<C, LA, LB>, char> epilogue;
     if constexpr (SMALL && EPILOGUE == EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
     const int lead = KT % D, first = lead > 0 ? D - lead : 0;
@@ -1313,6 +1313,23 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
     int tm, tn;
     tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
     gemm_ring_body<128, 128, 4, 2, 4, LA, LB, LINES>(g, inside_row<128, LA>(g, tm * 128), inside_col<128>(g, tn * 128), smem, threadIdx.x);
+}
+
+// Between those and 64 x 64 ones: 64 x 128 and 128 x 64 tiles, eight waves of 32 x 32 on a four-stage ring, for outputs of at most one
+// such tile per CU that are more than one round of 64 x 64 tiles.  A CU takes in operands at 100-115 KB per us, whatever the depth of
+// the ring, and that is what these launches are bound by (the loads of a 128 x 128 tile's step alone take 0.31 us, its MFMAs 0.22): half
+// as many CUs on 128 x 128 tiles take in two thirds of the bytes, two rounds of 64 x 64 tiles a third more.  64 x 64 / 128 x 128 / these in us:
+// forward 1000 x 2000 x 3000 31 / 27 / 23, dgrad 512 x 4096 x 4096 27 / 24 / 21.5, 256 x 8192 x 8192 71 / 72 / 57, wgrad 1400^3 16.3 / 13.7 / 12.3,
+// 900 x 1300 of 6000 tokens 58 / 45 / 38, forward 2000 x 1000 x 1000 12.8 / 12.1 / 10.5.  Three stages and two workgroups per CU: the same.
+template <bool WIDE>
+using RectCfg = RingCfg<WIDE ? 64 : 128, WIDE ? 128 : 64, WIDE ? 2 : 4, WIDE ? 4 : 2, 4>;
+template <int LA, int LB, bool WIDE, bool LINES>
+__global__ void __launch_bounds__(TILE_THREADS, 1) gemm_rect_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    constexpr int BM = WIDE ? 64 : 128, BN = WIDE ? 128 : 64;
+    int tm, tn;
+    tile_of_index(xcd_run(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
+    gemm_ring_body<BM, BN, WIDE ? 2 : 4, WIDE ? 4 : 2, 4, LA, LB, LINES>(g, inside_row<BM, LA>(g, tm * BM), inside_col<BN>(g, tn * BN), smem, threadIdx.x);
 }
 
 // The same for smaller outputs: 64 x 64, four waves of 32 x 32 on a four-stage ring, two workgroups per CU.  (Five stages are
