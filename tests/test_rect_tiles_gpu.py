@@ -69,3 +69,14 @@ def test_bits_of_a_grouped_launch(M, K, N, kernels):
     assert kernels <= used, used
     for a, b in zip(*results):
         assert not a.isnan().any() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("Mo,No,R", [(512, 512, 300), (330, 705, 260), (705, 330, 260), (64, 1000, 200), (1000, 64, 200), (1090, 930, 130),
+                                     (1300, 1301, 1030), (1536, 1400, 530)])
+def test_weight_gradients_in_bands_of_any_height(Mo, No, R):
+    """Tile grids whose runs per XCD make bands of one row, of all rows and of heights between, some that do not divide the rows."""
+    q = variants.Product(WG, Mo, No, R)
+    o = variants.out(Mo, No)
+    q.run(o)
+    sums, mag = q.sums()
+    variants.check(o, sums, 2.0 ** -8 * sums.abs() + 2.0 ** -24 * (R + 4) * mag, No, "wgrad")
