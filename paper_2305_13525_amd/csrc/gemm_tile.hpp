@@ -400,31 +400,10 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// The bias of a wave tile's columns on tiles of 256 rows, kept as it comes: a lane's four columns in each block of 16.  Requested ahead of a
-// reduction of at least EARLY_STEPS steps, so that the epilogue does not open with a trip to memory, else behind it: tiles of few steps
-// start later by as much (8192 x 8192 x 512 with erf GELU 101.3 us so, 102.8 ahead).  Before, a block's bias when its turn came, and now in us:
-// forward 4000 x 6000 x 2000 with erf GELU 98.4 / 97.1, 4096 x 1536 x 1536 with a bias 20.3 / 19.95, 4096 x 4096 x 2048 with tanh GELU 53.7 / 52.6,
-// 8192 x 8192 x 512 with erf GELU 100.2 / 98.2, 8192 x 8192 x 256 with a bias 47.6 / 46.1.
-constexpr int EARLY_STEPS = 16;
-template <typename C>
-struct WaveBias {
-    uint2 raw[C::TN];
-    __device__ __forceinline__ void request(const GemmArgs& g, const int wcol0, const int lane) {
-        const bool any = g.epilogue != EPI_NONE && g.add_bias;
-#pragma unroll
-        for (int b = 0; b < C::TN; ++b) {
-            raw[b] = uint2{0u, 0u};
-            if (any) raw[b] = *reinterpret_cast<const uint2*>(g.bias + wcol0 + b * 16 + 4 * (lane >> 4));
-        }
-    }
-    __device__ __forceinline__ f32x4 of(int b) const { return bf16x4_of(raw[b].x, raw[b].y); }
-};
-
 // Epilogue of a workgroup tile of 256 rows: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
 template <typename C, int LA, int LB>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
-                                              const int wave, const int wm, const int wn, const int lane, char* smem,
-                                              const WaveBias<C>& bias) {
+                                              const int wave, const int wm, const int wn, const int lane, char* smem) {
     __syncthreads();  // all waves are done reading the operand buffers
     char* stage = smem + wave * (C::WTM * C::EPI_STRIDE);
     // The epilogue kind is decided once, outside the element loops: the plain path is then
@@ -439,6 +418,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     int wrow0 = i0 + wm * C::WTM, wcol0 = j0 + wn * C::WTN;
     asm volatile("" : "+s"(wrow0), "+s"(wcol0));
     bf16_t* const Cw = g.C + (int64_t)wrow0 * g.ldc + wcol0;
+    // The bias of a lane's four columns in the wave tile's block b of 16.
+    auto bias_of = [&](const int b) __attribute__((always_inline)) {
+        return g.add_bias ? load_bf16x4(g.bias + wcol0 + b * 16 + 4 * (lane >> 4), 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
     auto convert_and_stage = [&](auto epi_tag, auto far_tag) __attribute__((always_inline)) {
         constexpr int EPI = decltype(epi_tag)::value;
         constexpr bool FAR = decltype(far_tag)::value != 0;
@@ -448,7 +431,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
         for (int b = 0; b < C::TN; ++b) {
             const int ncol = b * 16 + 4 * (lane >> 4);  // within the wave tile
             f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-            if (FWD_EPI) bv = bias.of(b);
+            if (FWD_EPI) bv = bias_of(b);
 #pragma unroll
             for (int a = 0; a < C::TM; ++a) {
                 const int mrow = a * 16 + (lane & 15);
@@ -525,7 +508,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
         float least = 0.f;  // the least sum of a column plus its bias is its least value
 #pragma unroll
         for (int b = 0; b < C::TN; ++b) {
-            const f32x4 bv = bias.of(b);
+            const f32x4 bv = bias_of(b);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float sum = acc[0][b][e];
@@ -873,11 +856,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
 
-    constexpr bool FWD = LA == KC && LB == MC;
-    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
-    WaveBias<C> bias;
-    if (FWD && whole && KT >= EARLY_STEPS) bias.request(g, j0 + wn * C::WTN, lane);
-
     // A reduction step of 64 is four MFMA groups: (sub-step kq, row half ah) for kq, ah in {0, 1};
     // a group multiplies AH A fragments with all TN B fragments of its sub-step.  A fragments are
     // double buffered per group, B fragments per sub-step.
@@ -1074,8 +1052,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     step(1, T1{}, false, false, false, false);
     AXO_SETPRIO(0);
 
-    if (FWD && whole && KT < EARLY_STEPS) bias.request(g, j0 + wn * C::WTN, lane);
-    if (whole) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem, bias);
+    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
@@ -1224,10 +1201,6 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     constexpr int EPILOGUE = BM * BN < 128 * 128 || (LA == KC && LB == MC) ? EARLY : LB == KC ? MIXED : LATE;
     [[maybe_unused]] std::conditional_t<SMALL, SmallEpilogue<C, LA, LB>, char> epilogue;
     if constexpr (SMALL && EPILOGUE == EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
-    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
-    WaveBias<C> bias;
-    constexpr bool BIAS = !SMALL && LA == KC && LB == MC;
-    if (BIAS && whole && KT >= EARLY_STEPS) bias.request(g, j0 + wn * C::WTN, lane);
     const int lead = KT % D, first = lead > 0 ? D - lead : 0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
@@ -1276,13 +1249,13 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if (KT >= 3) step(IC<D - 3>{}, IC<3>{});
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
-    if (BIAS && whole && KT < EARLY_STEPS) bias.request(g, j0 + wn * C::WTN, lane);
+    const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
     if (!store) {
         __syncthreads();  // the one of an epilogue
         return;
     }
     if constexpr (!SMALL || EPILOGUE == MIXED)
-        if (whole) return tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem, bias);
+        if (whole) return tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     if constexpr (SMALL) {
         if constexpr (EPILOGUE != EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
         epilogue.finish(g, acc, wave, smem, whole);
