@@ -352,30 +352,6 @@ __device__ __forceinline__ void store_f32_quad(const GemmArgs& g, f32x4 v, const
     else
         for (int e = 0; e < valid; ++e) out[e] = v[e];
 }
-// bf16 after the epilogue, or fp32 with what is there added.  The kind is decided once for the four (once per value: forward
-// 1001 x 1027 x 515 with a bias 8.6 us, now 7.9, with the erf form 9.0 and 8.1; dgrad through the erf form 9.8 and 9.1).
-// `x` is what the epilogue adds or multiplies with: bias, pre-activations, or the fp32 values accumulated into.
-__device__ __forceinline__ void store_quad(const GemmArgs& g, f32x4 v, f32x4 x, const int row, const int col, const int valid) {
-    if (g.epilogue == EPI_ACC_F32) return store_f32_quad(g, x + v, row, col, valid);
-    auto each = [&](auto f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = f(v[e], x[e]);
-    };
-    if (g.epilogue != EPI_NONE) switch (g.epilogue) {
-        case EPI_BIAS_GELU_ERF: each([](float s, float t) { return apply_epilogue(s, t, EPI_BIAS_GELU_ERF); }); break;
-        case EPI_BIAS: v = v + x; break;
-        case EPI_BIAS_GELU_TANH: each([](float s, float t) { return apply_epilogue(s, t, EPI_BIAS_GELU_TANH); }); break;
-        case EPI_MUL_DGELU_TANH: each([](float s, float t) { return apply_dact(s, t, EPI_MUL_DGELU_TANH); }); break;
-        default: each([](float s, float t) { return apply_dact(s, t, EPI_MUL_DGELU_ERF); }); break;
-    }
-    store_bf16_quad(g, v, row, col, valid);
-}
-// The `x` of store_quad for these outputs, apart from the bias, which depends on the column only.
-__device__ __forceinline__ f32x4 load_quad_extra(const GemmArgs& g, const int row, const int col, const int valid) {
-    if (g.epilogue == EPI_ACC_F32) return load_f32x4(reinterpret_cast<const float*>(g.C) + (int64_t)row * g.ldc + col, valid);
-    return load_bf16x4(g.aux + (int64_t)row * g.ldaux + col, valid);
-}
-
 template <int V>
 using IC = std::integral_constant<int, V>;
 
@@ -569,66 +545,160 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
     }
 }
 
+// f(0) .. f(N - 1), four to a pass of a loop.
+template <int N, typename F>
+__device__ __forceinline__ void by_four(F f) {
+    static_assert(N % 4 == 0, "whole passes");
+#pragma nounroll
+    for (int i0 = 0; i0 < N; i0 += 4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f(i0 + i);
+}
+
 // The epilogue of a tile of 256 rows that reaches over the output's edge, any kind, one compact path: the wave stages its
-// sums in fp32, half its rows at a time, and stores the quads of columns that lie inside.  (wrow0, wcol0): the
-// wave tile's origin.  Same operations per element as the whole-tile epilogue, so an element's bits do not
-// depend on the tile that it falls in.
-template <typename C>
+// sums in fp32 and stores the quads of columns that lie inside.  Same operations per element as the whole-tile epilogue, so an element's
+// bits do not depend on the tile that it falls in.  (wrow0, wcol0): the wave tile's origin.
+// Plain sums and forward kinds go half the wave tile's rows at a time.  What reads pre-activations or old fp32 values goes 32 rows at a
+// time and requests them a pass ahead: one trip to memory is left of each tile's.  (Requested four rows at a time when they were wanted there
+// were eight, every quad of columns chose its kind anew, and in launches of one round the tiles at the edge ended long after the others.)
+// Before and now in us: wgrad into fp32 3001 x 3003 of 77 tokens 32.8 / 20.4, 4001 x 4003 of 1000 71 / 56, 3000 x 3000 of 100 19.1 / 17.6; dgrad 3001 x 3003
+// x 77 through tanh GELU 35.3 / 21.2, x 1000 through the erf form 52.4 / 38.6; forward 3001 x 3003 x 1000 with a bias 31.0 / 26.1, with erf GELU
+// 39.3 / 35.5, without either 25.3 / 25.2.
+template <typename C, int LA, int LB>
 __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int wrow0,
                                                       const int wcol0, const int wave, const int lane, char* smem) {
-    __syncthreads();  // all waves are done reading the operand buffers
-    char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
-    constexpr int F_STRIDE = C::WTN * 4 + 16, RP = C::WTM / 2, QPR = C::WTN / 4;
-    static_assert(RP * F_STRIDE <= C::WTM * C::EPI_STRIDE, "fits the wave's staging region");
-    // a lane keeps its four columns; what its outputs need from memory is requested BATCH rows ahead
-    constexpr int RPI = 64 / QPR, ITERS = RP / RPI, BATCH = ITERS < 4 ? ITERS : 4;
+    constexpr bool FWD = LA == KC && LB == MC, DGRAD = LA == KC && LB == KC;
+    constexpr int F_STRIDE = C::WTN * 4 + 16, QPR = C::WTN / 4, RPI = 64 / QPR;
+    // a lane keeps its four columns
     const int lc = (lane % QPR) * 4, col = wcol0 + lc, valid = min(4, g.No - col);
-    const bool per_row = g.epilogue >= EPI_MUL_DGELU_TANH;
-    f32x4 bias = {0.f, 0.f, 0.f, 0.f};
-    if (g.epilogue != EPI_NONE && !per_row && g.add_bias && valid > 0) bias = load_bf16x4(g.bias + col, valid);
+    // sums of `tiles` rows of MFMA tiles from `first` on to the wave's region
+    auto put_sums = [&](char* stage, auto first, auto tiles) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int a = 0; a < C::TM / 2; ++a)
+        for (int a = 0; a < decltype(tiles)::value; ++a)
 #pragma unroll
             for (int b = 0; b < C::TN; ++b)
                 *reinterpret_cast<f32x4*>(stage + (a * 16 + (lane & 15)) * F_STRIDE + (b * 16 + 4 * (lane >> 4)) * 4) =
-                    acc[h * (C::TM / 2) + a][b];
+                    acc[decltype(first)::value + a][b];
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the region is private to the wave
         __builtin_amdgcn_wave_barrier();
-        if (g.epilogue == EPI_NONE) {  // a loop of its own: forward 1001 x 1027 x 515 7.3 -> 7.0 us, 3000 x 1000 x 3001 29.3 -> 25.1
-#pragma unroll BATCH
-            for (int i = 0; i < ITERS; ++i) {
-                const int lr = i * RPI + lane / QPR, row = wrow0 + h * RP + lr;
-                if (row < g.Mo && valid > 0)
-                    store_bf16_quad(g, *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), row, col, valid);
+    };
+    if (FWD || g.epilogue == EPI_NONE) {
+        constexpr int RP = C::WTM / 2, ITERS = RP / RPI;
+        static_assert(RP * F_STRIDE <= C::WTM * C::EPI_STRIDE, "fits the wave's staging region");
+        char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if (FWD && g.epilogue != EPI_NONE && g.add_bias && valid > 0) bias = load_bf16x4(g.bias + col, valid);
+        __syncthreads();  // all waves are done reading the operand buffers
+        auto half = [&](auto h) __attribute__((always_inline)) {
+            put_sums(stage, IC<decltype(h)::value * (C::TM / 2)>{}, IC<C::TM / 2>{});
+            const int row0 = wrow0 + decltype(h)::value * RP;
+            if (g.epilogue == EPI_NONE) {
+#pragma unroll 4
+                for (int i = 0; i < ITERS; ++i) {
+                    const int lr = i * RPI + lane / QPR, row = row0 + lr;
+                    if (row < g.Mo && valid > 0)
+                        store_bf16_quad(g, *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), row, col, valid);
+                }
+            } else if constexpr (FWD) {
+                auto rows = [&](auto f) __attribute__((always_inline)) {
+                    by_four<ITERS>([&](int i) __attribute__((always_inline)) {
+                        const int lr = i * RPI + lane / QPR, row = row0 + lr;
+                        f32x4 v = *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = f(v[e], bias[e]);
+                        if (row < g.Mo && valid > 0) store_bf16_quad(g, v, row, col, valid);
+                    });
+                };
+                switch (g.epilogue) {
+                    case EPI_BIAS: rows([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS); }); break;
+                    case EPI_BIAS_GELU_TANH: rows([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS_GELU_TANH); }); break;
+                    default: rows([](float s, float x) { return apply_epilogue(s, x, EPI_BIAS_GELU_ERF); }); break;
+                }
             }
-            __builtin_amdgcn_wave_barrier();
-            continue;
-        }
-        auto rows = [&](auto extra, auto store) __attribute__((always_inline)) {
-#pragma nounroll
-            for (int i0 = 0; i0 < ITERS; i0 += BATCH) {
-                f32x4 x[BATCH];
+            __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
+        };
+        half(IC<0>{});
+        half(IC<1>{});
+        return;
+    }
+    if constexpr (!FWD) {
+        constexpr int ROWS = 32, ITERS = ROWS / RPI;
+        constexpr int WAVE_BYTES = ROWS * (F_STRIDE + C::WTN * 2);  // the sums, and behind them the pre-activations
+        static_assert(C::WAVES * WAVE_BYTES <= C::LDS_BYTES, "fits the operand buffers");
+        char* const stage = smem + wave * WAVE_BYTES;
+        char* const pre = stage + ROWS * F_STRIDE;
+        const bool inside = wcol0 + C::WTN <= g.No;
+        // A pass's old fp32 values or pre-activations: in four dwords or in two, or, in a wave tile that reaches over the last column, in
+        // one each.  What lies beyond the matrix stands for the last row's or column's, and is not stored.
+        u32x4 in[ITERS];
+        auto request = [&](auto inside_tag, const int row0, const int i) __attribute__((always_inline)) {
+            const int row = min(row0 + i * RPI + lane / QPR, g.Mo - 1);
+            auto load = [&](auto* at) __attribute__((always_inline)) {
+                if constexpr (!decltype(inside_tag)::value) {
 #pragma unroll
-                for (int i = 0; i < BATCH; ++i) {
-                    const int row = wrow0 + h * RP + (i0 + i) * RPI + lane / QPR;
-                    x[i] = extra(row, row < g.Mo && valid > 0);
+                    for (int e = 0; e < 4; ++e) in[i][e] = at[min(col + e, g.No - 1)];
+                } else if constexpr (!DGRAD) in[i] = *reinterpret_cast<const u32x4*>(at + col);
+                else {
+                    const uint2 raw = *reinterpret_cast<const uint2*>(at + col);
+                    in[i][0] = raw.x;
+                    in[i][1] = raw.y;
                 }
+            };
+            if constexpr (DGRAD) load(g.aux + (int64_t)row * g.ldaux);
+            else load(reinterpret_cast<const uint32_t*>(g.C) + (int64_t)row * g.ldc);
+        };
+        auto tile = [&](auto inside_tag) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < BATCH; ++i) {
-                    const int lr = (i0 + i) * RPI + lane / QPR, row = wrow0 + h * RP + lr;
-                    if (row < g.Mo && valid > 0) store(*reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4), x[i], row);
+            for (int i = 0; i < ITERS; ++i) request(inside_tag, wrow0, i);
+            __syncthreads();  // all waves are done reading the operand buffers
+            auto pass = [&](auto p_tag) __attribute__((always_inline)) {
+                constexpr int p = decltype(p_tag)::value;
+                constexpr bool more = p + 1 < C::WTM / ROWS;
+                const int row0 = wrow0 + p * ROWS;
+                if constexpr (DGRAD) {
+#pragma unroll
+                    for (int i = 0; i < ITERS; ++i) {
+                        *reinterpret_cast<uint2*>(pre + (i * RPI + lane / QPR) * (C::WTN * 2) + lc * 2) =
+                            decltype(inside_tag)::value ? uint2{in[i][0], in[i][1]} : uint2{in[i][0] | in[i][1] << 16, in[i][2] | in[i][3] << 16};
+                        if constexpr (more) request(inside_tag, row0 + ROWS, i);
+                    }
                 }
+                put_sums(stage, IC<p * (ROWS / 16)>{}, IC<ROWS / 16>{});
+                auto sums = [&](int lr) __attribute__((always_inline)) { return *reinterpret_cast<const f32x4*>(stage + lr * F_STRIDE + lc * 4); };
+                if constexpr (!DGRAD) {
+#pragma unroll
+                    for (int i = 0; i < ITERS; ++i) {
+                        const int lr = i * RPI + lane / QPR, row = row0 + lr;
+                        const f32x4 sum = __builtin_bit_cast(f32x4, in[i]) + sums(lr);
+                        if (row < g.Mo && valid > 0) store_f32_quad(g, sum, row, col, decltype(inside_tag)::value ? 4 : valid);
+                        if constexpr (more) request(inside_tag, row0 + ROWS, i);
+                    }
+                } else {
+                    auto rows = [&](auto f) __attribute__((always_inline)) {
+                        by_four<ITERS>([&](int i) __attribute__((always_inline)) {
+                            const int lr = i * RPI + lane / QPR, row = row0 + lr;
+                            const uint2 raw = *reinterpret_cast<const uint2*>(pre + lr * (C::WTN * 2) + lc * 2);
+                            const f32x4 x = bf16x4_of(raw.x, raw.y);
+                            f32x4 v = sums(lr);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = f(v[e], x[e]);
+                            if (row < g.Mo && valid > 0) store_bf16_quad(g, v, row, col, valid);
+                        });
+                    };
+                    if (g.epilogue == EPI_MUL_DGELU_TANH) rows([](float s, float x) { return apply_dact(s, x, EPI_MUL_DGELU_TANH); });
+                    else rows([](float s, float x) { return apply_dact(s, x, EPI_MUL_DGELU_ERF); });
+                }
+                __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
+            };
+            pass(IC<0>{});
+            pass(IC<1>{});
+            if constexpr (C::WTM > 64) {
+                pass(IC<2>{});
+                pass(IC<3>{});
             }
         };
-        if (g.epilogue == EPI_ACC_F32)  // likewise: wgrad 1449 x 6656 of 42 tokens 31.5 -> 29.6 us, 10496 x 1920 of 168 34.7 -> 32.9
-            rows([&](int row, bool in) { return in ? load_quad_extra(g, row, col, valid) : bias; },
-                 [&](f32x4 v, f32x4 x, int row) { store_f32_quad(g, x + v, row, col, valid); });
-        else
-            rows([&](int row, bool in) { return per_row && in ? load_quad_extra(g, row, col, valid) : bias; },
-                 [&](f32x4 v, f32x4 x, int row) { store_quad(g, v, x, row, col, valid); });
-        __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order: the next pass may overwrite
+        if (inside) tile(std::true_type{});
+        else tile(std::false_type{});
     }
 }
 
@@ -1053,7 +1123,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     AXO_SETPRIO(0);
 
     if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
-    else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+    else tile_epilogue_clipped<C, LA, LB>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
 // The same tile on a ring of D stages, for tiles whose step is too short to cover a load's way from HBM: in
@@ -1259,7 +1329,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if constexpr (SMALL) {
         if constexpr (EPILOGUE != EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
         epilogue.finish(g, acc, wave, smem, whole);
-    } else tile_epilogue_clipped<C>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
+    } else tile_epilogue_clipped<C, LA, LB>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
 using MixBigCfg = TileCfg<256, 256, 2, 4>;
