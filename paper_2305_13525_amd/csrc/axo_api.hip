@@ -373,10 +373,12 @@ Lines lines_of(const GemmArgs& g, int la, int lb, const axo::TileSched& sc) {
 // Launch of one product on those tiles.
 template <int LA, int LB, int LINES>
 int launch_mixed(const GemmArgs& g, const axo::TileSched& sc, hipStream_t st) {
-    auto kern = axo::gemm_mixed_kernel<LA, LB, LINES>;
+    // rows that straddle cache lines behind a short reduction: stored plainly (store_row)
+    const bool plain = g.epilogue != axo::EPI_ACC_F32 && g.ldc % 64 != 0 && steps_in(g.R) <= 16;
+    auto kern = plain ? axo::gemm_mixed_kernel<LA, LB, LINES, true> : axo::gemm_mixed_kernel<LA, LB, LINES, false>;
     constexpr int lds = LINES != LINES_NONE ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;
-    static std::atomic<uint64_t> raised{0};
-    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised)) return AXO_ERR_HIP;
+    static std::atomic<uint64_t> raised[2]{{0}, {0}};
+    if (!raise_lds_limit(reinterpret_cast<const void*>(kern), lds, &raised[plain])) return AXO_ERR_HIP;
     const int blocks = sc.n_big + sc.tiles_m * sc.small_cols;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(axo::TILE_THREADS), lds, st, g, sc);
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;

@@ -376,8 +376,22 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
+// A lane's 16 bytes of a whole tile's row.  Non-temporal where rows are whole cache lines long: the
+// output is not read again by this launch, and plain stores let it evict operand panels from L2 (0.5-5 % in grouped launches).  Plain where rows
+// straddle lines: a non-temporal store of a part of a line does not wait in L2 for the rest of it, which the tile or wave beside this one
+// writes.  On tiles of 256 rows only up to 16 steps, beyond which the panels count for more (all plain: 4104 x 4104 x 4104 152 us non-temporal, 169
+// plain, wgrad 2000 x 6000 of 4000 tokens 82 and 90, 5000 x 10000 x 1000 129 and 121).  Non-temporal / plain in us: dgrad 10600 x 7736 x 48 68.4 / 50.0, wgrad 5640 x
+// 6152 of 72 tokens 35.3 / 27.6, forward 8200 x 4104 x 200 40.4 / 35.7, 3000 x 3000 x 200 14.9 / 13.2, on smaller tiles 264 x 328 x 136 4.17 / 3.43, 1000 x 1000 x 200
+// 4.47 / 4.09, dgrad 1000^3 7.0 / 6.5, wgrad 3000 x 1000 of 2000 tokens 19.1 / 18.6.  On 256-row tiles a kernel of
+// its own, of single launches only: with the choice made in the kernel, grouped launches and others with long reductions took 0.5-1 % longer.
+template <bool PLAIN>
+__device__ __forceinline__ void store_row(const u32x4 v, u32x4* to) {
+    if constexpr (PLAIN) *to = v;
+    else __builtin_nontemporal_store(v, to);
+}
+
 // Epilogue of a workgroup tile of 256 rows: acc[a][b][e] is C[i0 + wm*WTM + a*16 + lane%16][j0 + wn*WTN + b*16 + 4*(lane/16) + e].
-template <typename C, int LA, int LB>
+template <typename C, int LA, int LB, bool PLAIN>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], const int i0, const int j0,
                                               const int wave, const int wm, const int wn, const int lane, char* smem) {
     __syncthreads();  // all waves are done reading the operand buffers
@@ -461,9 +475,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x4 (&acc)[C:
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int row = p * ROWS_PER_PASS + lane / LANES_PER_ROW, ch = lane % LANES_PER_ROW;
-            // non-temporal: the output is not read again by this launch, and a workgroup cannot retire
-            // before its stores are acknowledged
-            __builtin_nontemporal_store(vdat[p], reinterpret_cast<u32x4*>(Cw + (int64_t)row * g.ldc + ch * 8));
+            store_row<PLAIN>(vdat[p], reinterpret_cast<u32x4*>(Cw + (int64_t)row * g.ldc + ch * 8));
         }
     };
     auto finish = [&](auto epi_tag, auto far_tag) __attribute__((always_inline)) {
@@ -847,8 +859,16 @@ struct SmallEpilogue {
         const int row0 = wrow0 + lane / LANES_PER_ROW, col = wcol0 + lane % LANES_PER_ROW * 8, valid = g.No - col;
         bf16_t* const to = g.C + (int64_t)row0 * g.ldc + col;
         if (whole) {
+            auto rows = [&](auto plain_tag) __attribute__((always_inline)) {
 #pragma unroll
-            for (int p = 0; p < PASSES; ++p) __builtin_nontemporal_store(out[p], reinterpret_cast<u32x4*>(to + (int64_t)(p * ROWS_PER_PASS) * g.ldc));
+                for (int p = 0; p < PASSES; ++p)
+                    store_row<decltype(plain_tag)::value>(out[p], reinterpret_cast<u32x4*>(to + (int64_t)(p * ROWS_PER_PASS) * g.ldc));
+            };
+            if ((g.ldc & 63) != 0) rows(std::true_type{});
+            else {
+                rows(std::false_type{});
+                asm volatile("; non-temporal");  // or the compiler makes one of both kinds of stores, a plain one
+            }
             return;
         }
 #pragma unroll
@@ -868,7 +888,7 @@ struct SmallEpilogue {
 // fetched by whole cache lines (line_phase), on three stages; with them and two of B the LDS is full, so rows of B that
 // do not start on lines still put every segment into two.  The loads of a step then touch 768 lines (dgrad) or 576 (forward) instead
 // of 1024 or 832.
-template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool LINES = false>
+template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool LINES = false, bool PLAIN = false>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, const int j0, char* smem) {
     using C = TileCfg<BM, BN, WGM, WGN>;
     const int tid = threadIdx.x;
@@ -1122,7 +1142,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
     step(1, T1{}, false, false, false, false);
     AXO_SETPRIO(0);
 
-    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+    if (i0 + BM <= g.Mo && j0 + BN <= g.No) tile_epilogue<C, LA, LB, PLAIN>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     else tile_epilogue_clipped<C, LA, LB>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
@@ -1144,7 +1164,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 // reduction 6144 on half-width ones 80.3 -> 76.2, 10600 x 7736 with reduction 48 73.4 -> 66.4.
 // `tid`: among the threads that work on the tile; `store`: false for a tile whose results are not wanted, as the second of a
 // pair of workgroup halves that has none (both halves meet at the same barriers).
-template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB, bool LINES = false>
+template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB, bool LINES = false, bool PLAIN = false>
 __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, const int j0, char* smem, const int tid,
                                                const bool store = true) {
     using C = RingCfg<BM, BN, WGM, WGN, D>;
@@ -1325,7 +1345,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
         return;
     }
     if constexpr (!SMALL || EPILOGUE == MIXED)
-        if (whole) return tile_epilogue<C, LA, LB>(g, acc, i0, j0, wave, wm, wn, lane, smem);
+        if (whole) return tile_epilogue<C, LA, LB, PLAIN>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     if constexpr (SMALL) {
         if constexpr (EPILOGUE != EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
         epilogue.finish(g, acc, wave, smem, whole);
@@ -1352,8 +1372,9 @@ __device__ __forceinline__ int inside_col(const GemmArgs& g, const int j0) {
     return g.No >= BN && g.epilogue != EPI_ACC_F32 && g.No % 8 == 0 ? min(j0, g.No - BN) : j0;
 }
 
-// One launch over both regions of a TileSched.  LINES: rows by whole lines on no tiles (0), on the large ones (1), on both (2).
-template <int LA, int LB, int LINES>
+// One launch over both regions of a TileSched.  LINES: rows by whole lines on no tiles (0), on the large ones (1), on both (2).  PLAIN: stores of whole
+// tiles (store_row).
+template <int LA, int LB, int LINES, bool PLAIN>
 __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g, TileSched sc) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int bid = blockIdx.x;
@@ -1361,11 +1382,11 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
     int tm, tn;
     if (bid < sc.n_big) {
         tile_of_index(xcd_run(bid, sc.n_big), sc.tiles_m, sc.big_cols, sc.group_m, tm, tn);
-        gemm_tile_body<256, 256, 2, 4, LA, LB, LINES != 0>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
+        gemm_tile_body<256, 256, 2, 4, LA, LB, LINES != 0, PLAIN>(g, inside_row<256, LA>(g, tm * 256), inside_col<256>(g, tn * 256), smem);
     } else {
         const int n_small = (int)gridDim.x - sc.n_big;
         tile_of_index(xcd_run(bid - sc.n_big, n_small), sc.tiles_m, sc.small_cols, sc.group_m, tm, tn);
-        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES == 2>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem, threadIdx.x);
+        gemm_ring_body<256, 128, 4, 2, 3, LA, LB, LINES == 2, PLAIN>(g, inside_row<256, LA>(g, tm * 256), inside_col<128>(g, sc.big_cols * 256 + tn * 128), smem, threadIdx.x);
     }
 }
 
