@@ -4,7 +4,7 @@
 // with half-width tiles (TileSched).  A tile that would reach over the output's edge is moved back inside
 // where the sizes allow (inside_row, inside_col); otherwise it is clipped: rows beyond an operand read as
 // zeros through the buffer bound, columns beyond it are not stored, and the tile takes an epilogue of its
-// own (tile_epilogue_clipped).  Clipping a tile that could have been moved costs it 3-4 us (measured on
+// own (tile_epilogue_clipped, SmallEpilogue).  Clipping tiles that could have been moved costs time (measured on
 // 4000 x 2000 x 6000 with bias and GELU: 138 us forward clipped, 132 moved).
 //
 // One 512-thread workgroup (8 waves, two per SIMD) owns a BM x BN output tile and walks the
@@ -1392,8 +1392,8 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mixed_kernel(GemmArgs g,
 
 // One product on 128 x 128 tiles, eight waves of 32 x 64 each on a four-stage ring, for outputs of at most one
 // such tile per CU (4096 x 1024, 2048 x 2048): 256-row tiles leave most CUs without work there.  A step is bound by
-// LDS traffic (128 KB per 515 cycles of MFMA), so this is no tile for larger outputs.  Eight waves rather than
-// four of 64 x 64 (a quarter less LDS traffic, but one wave per SIMD: 2048^3 21 us), four stages rather than two
+// the rate at which a CU takes in operands (32 KB per 515 cycles of MFMA; see gemm_rect_kernel), so this is no tile for
+// larger outputs.  Eight waves rather than four of 64 x 64 (a quarter less LDS traffic, but one wave per SIMD: 2048^3 21 us), four stages rather than two
 // and two workgroups per CU (24 us).  Measured against the 256-row tiles, forward / dgrad / wgrad: 2048^3
 // 25.6 / 24.9 / 24.2 -> 18.2 / 17.4 / 18.2 us, 1536^3 19.6 / 19.0 / 18.4 -> 12.1 / 12.4 / 12.1, wgrad 1536 x 1536 of 4096
 // tokens 44 -> 30.  Sums run in the same order as on the other tiles: same bits.
