@@ -659,10 +659,11 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
             if constexpr (DGRAD) load(g.aux + (int64_t)row * g.ldaux);
             else load(reinterpret_cast<const uint32_t*>(g.C) + (int64_t)row * g.ldc);
         };
-        auto tile = [&](auto inside_tag) __attribute__((always_inline)) {
+        auto first = [&](auto inside_tag) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < ITERS; ++i) request(inside_tag, wrow0, i);
-            __syncthreads();  // all waves are done reading the operand buffers
+        };
+        auto tile = [&](auto inside_tag) __attribute__((always_inline)) {
             auto pass = [&](auto p_tag) __attribute__((always_inline)) {
                 constexpr int p = decltype(p_tag)::value;
                 constexpr bool more = p + 1 < C::WTM / ROWS;
@@ -709,6 +710,9 @@ __device__ __forceinline__ void tile_epilogue_clipped(const GemmArgs& g, f32x4 (
                 pass(IC<3>{});
             }
         };
+        if (inside) first(std::true_type{});
+        else first(std::false_type{});
+        __syncthreads();  // all waves are done reading the operand buffers; outside the branches, which the waves of a tile take differently
         if (inside) tile(std::true_type{});
         else tile(std::false_type{});
     }
