@@ -1176,6 +1176,11 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     const int KT = (g.R + TILE_BK - 1) / TILE_BK;
+    // Nothing is under way here, but the compiler does not know that: in gemm_group_kernel it lets the kinds of tiles follow each other and takes
+    // what an epilogue of another kind reads for its last outputs to be pending, where those outputs are not stored.  It then waited for that
+    // in the loop, s_waitcnt vmcnt(0) in every turn, which empties the ring (half-width forward tiles and pairs; the three
+    // products of 4096 x 2048 x 6144 in one chain call 221.1 us, 219.8 without).
+    AXO_WAIT_VMCNT(0);
 
     constexpr bool A_LINES = LINES && LA == KC, B_LINES = LINES && LB == KC;
     constexpr int AHEAD = LINES ? 1 : 0;  // stages that a step needs beyond its own
