@@ -791,8 +791,8 @@ struct SmallEpilogue {
         const u32x4 x = in[FWD ? b : a * COLS + b];
         return bf16x4_of(x[0], x[1]);
     }
+    // behind the barrier after which the operand buffers may be overwritten
     __device__ __forceinline__ void finish(const GemmArgs& g, f32x4 (&acc)[C::TM][C::TN], int wave, char* smem, bool whole) {
-        __syncthreads();  // all waves are done reading the operand buffers
         char* const stage = smem + wave * (C::WTM * C::EPI_STRIDE);
         if constexpr (!FWD && !DGRAD) if (g.epilogue == EPI_ACC_F32) {
             float* const out = reinterpret_cast<float*>(g.C);
@@ -1167,7 +1167,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, const int i0, 
 // reduction 4096 on 64 x 64 tiles 18.7 -> 14.6 us, dgrad 2048^3 on 128 x 128 ones 18.6 -> 16.5, dgrad 4096 x 2048 with
 // reduction 6144 on half-width ones 80.3 -> 76.2, 10600 x 7736 with reduction 48 73.4 -> 66.4.
 // `tid`: among the threads that work on the tile; `store`: false for a tile whose results are not wanted, as the second of a
-// pair of workgroup halves that has none (both halves meet at the same barriers).
+// pair of workgroup halves that has none (both halves meet at the same barriers; for tiles below 128 x 128).
 template <int BM, int BN, int WGM, int WGN, int D, int LA, int LB, bool LINES = false, bool PLAIN = false>
 __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, const int j0, char* smem, const int tid,
                                                const bool store = true) {
@@ -1349,15 +1349,12 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const int i0, 
     if (KT >= 2) step(IC<D - 2>{}, IC<2>{});
     step(IC<D - 1>{}, IC<1>{});
     const bool whole = i0 + BM <= g.Mo && j0 + BN <= g.No;
-    if (!store) {
-        __syncthreads();  // the one of an epilogue
-        return;
-    }
     if constexpr (!SMALL || EPILOGUE == MIXED)
         if (whole) return tile_epilogue<C, LA, LB, PLAIN>(g, acc, i0, j0, wave, wm, wn, lane, smem);
     if constexpr (SMALL) {
         if constexpr (EPILOGUE != EARLY) epilogue.request(g, i0 + wm * C::WTM, j0 + wn * C::WTN, lane);
-        epilogue.finish(g, acc, wave, smem, whole);
+        __syncthreads();  // all waves are done reading the operand buffers; outside the branch, which the halves of a pair take differently
+        if (store) epilogue.finish(g, acc, wave, smem, whole);
     } else tile_epilogue_clipped<C, LA, LB>(g, acc, i0 + wm * C::WTM, j0 + wn * C::WTN, wave, lane, smem);
 }
 
