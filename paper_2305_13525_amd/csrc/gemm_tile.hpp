@@ -376,14 +376,26 @@ struct Interleave {
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 #define AXO_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// A lane's 16 bytes of a whole tile's row.  Non-temporal where rows are whole cache lines long: the
-// output is not read again by this launch, and plain stores let it evict operand panels from L2 (0.5-5 % in grouped launches).  Plain where rows
+// Whether rows of the output straddle cache lines: by their pitch, or all alike by where the first one starts.
+__host__ __device__ __forceinline__ bool rows_straddle(const GemmArgs& g) {
+    return ((reinterpret_cast<uintptr_t>(g.C) | (uintptr_t)(g.ldc * 2)) & 127) != 0;
+}
+
+// A lane's 16 bytes of a whole tile's row.  Non-temporal where rows lie in whole cache lines: the
+// output is not read again by this launch, and plain stores let it evict operand panels from L2 (0.5-5 % in grouped launches; plain / non-temporal in
+// us on 128 x 128 tiles forward 2048 x 2048 x 256 6.65 / 6.24, x 1024 11.9 / 11.2, wgrad 4096 x 1024 of 512 tokens 8.0 / 7.55, on 64 x 64 ones two to a CU
+// wgrad 2048 x 1024 of 512 6.3 / 6.15, level in one round).  Plain where rows
 // straddle lines: a non-temporal store of a part of a line does not wait in L2 for the rest of it, which the tile or wave beside this one
-// writes.  On tiles of 256 rows only up to 16 steps, beyond which the panels count for more (all plain: 4104 x 4104 x 4104 152 us non-temporal, 169
-// plain, wgrad 2000 x 6000 of 4000 tokens 82 and 90, 5000 x 10000 x 1000 129 and 121).  Non-temporal / plain in us: dgrad 10600 x 7736 x 48 68.4 / 50.0, wgrad 5640 x
-// 6152 of 72 tokens 35.3 / 27.6, forward 8200 x 4104 x 200 40.4 / 35.7, 3000 x 3000 x 200 14.9 / 13.2, on smaller tiles 264 x 328 x 136 4.17 / 3.43, 1000 x 1000 x 200
-// 4.47 / 4.09, dgrad 1000^3 7.0 / 6.5, wgrad 3000 x 1000 of 2000 tokens 19.1 / 18.6.  On 256-row tiles a kernel of
-// its own, of single launches only: with the choice made in the kernel, grouped launches and others with long reductions took 0.5-1 % longer.
+// writes.  Non-temporal / plain in us: dgrad 10600 x 7736 x 48 69.0 / 49.4, wgrad 5640 x 6152 of 72 tokens 35.9 / 27.3, forward 8200 x 4104 x 200
+// 40.0 / 34.8, 3000 x 3000 x 200 14.9 / 13.1, 5000 x 10000 x 1000 114 / 105, on smaller tiles 264 x 328 x 136 4.17 / 3.43, 1000 x 1000 x 200 4.47 / 4.09,
+// dgrad 1000^3 7.0 / 6.5, wgrad 3000 x 1000 of 2000 tokens 19.1 / 18.6, and 8 elements off lines on a pitch of whole ones forward 2048 x 2048 x 256
+// 8.3 / 7.7, 1024 x 1024 x 128 4.1 / 3.7.  With two exceptions, which are always non-temporal:
+// * tiles of 256 rows beyond 16 steps, where the panels may count for more (wgrad 2000 x 6000 of 4000 tokens 80 us, plain 90; 4104 x 4104 x 4104 152
+//   either way; but forward 5000 x 10000 x 1200 130 and 121, x 2000 181 and 173), and in grouped launches: with the choice made in the
+//   kernel, those and single launches with long reductions took 0.5-1 % longer, so it is a kernel of its own, of single launches only, and there
+//   by the pitch alone;
+// * whole 128 x 128 data gradient tiles, whose epilogue is that of the 256-row ones: plain 0.5-2.5 % quicker without an activation
+//   (2000 x 2000 x 500 8.9 and 8.8 us), 1.6 % slower through the erf form (2001 x 2037 x 725 14.8 and 15.05).
 template <bool PLAIN>
 __device__ __forceinline__ void store_row(const u32x4 v, u32x4* to) {
     if constexpr (PLAIN) *to = v;
@@ -868,10 +880,11 @@ struct SmallEpilogue {
                 for (int p = 0; p < PASSES; ++p)
                     store_row<decltype(plain_tag)::value>(out[p], reinterpret_cast<u32x4*>(to + (int64_t)(p * ROWS_PER_PASS) * g.ldc));
             };
-            if ((g.ldc & 63) != 0) rows(std::true_type{});
-            else {
+            if (rows_straddle(g)) rows(std::true_type{});
+            else {  // between two statements that it does not move: or the compiler makes one of both kinds of stores, a plain one
+                asm volatile("; non-temporal");
                 rows(std::false_type{});
-                asm volatile("; non-temporal");  // or the compiler makes one of both kinds of stores, a plain one
+                asm volatile("; non-temporal");
             }
             return;
         }

@@ -60,3 +60,17 @@ def test_loops_wait_for_loads_only_where_they_say_so(kernels):
                 assert len(waits) == barriers, (name, len(body), waits)
                 n += 1
     assert n >= 60, n
+
+
+def test_both_kinds_of_stores_are_there(kernels):
+    """Tiles of at most 128 x 128 store rows plainly where they straddle cache lines and past the caches where they do not.  Two branches that
+    differ in that alone are one to the compiler, a plain one."""
+    n = 0
+    for name, code in kernels.items():
+        m = re.search(r"gemm_(small|rect|mid)_kernelILi(\d)ELi(\d)E", name)
+        if not m:
+            continue
+        stores = [t for _, t, _ in code if t.startswith("global_store_dwordx4")]
+        assert any(t.endswith(" nt") for t in stores) and any(not t.endswith(" nt") for t in stores), (name, len(stores))
+        n += 1
+    assert n == 20, n
