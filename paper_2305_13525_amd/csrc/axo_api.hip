@@ -20,6 +20,7 @@
 #include "gemm_group.hpp"
 #include "gemm_slim.hpp"
 #include "gemm_tile.hpp"
+#include "tile_bands.hpp"
 
 // Scratch memory of the allocation-free entry point (axo_bias_grad_static): arrival counters and
 // slice sums of the split bias gradient, laid out as BiasSplit says.  One copy per GPU, held from
@@ -229,50 +230,13 @@ double small_time_long(int Mo, int No, int R) {
     return n <= 1 || late <= 0 ? 0.0 : n * late * 0.05;
 }
 
-// Band height of the tile order of a weight gradient that runs at once: each XCD gets a run of tiles (xcd_run), and what its 4 MB of L2
-// have to take in are the operand panels of the tile rows and columns that the run touches, so the run should be as square as bands
-// allow.  Panels come over the fabric, at 4.5 TB/s for all XCDs, which is what such launches with long reductions are bound by.  8 rows / the best
-// in us: 512 x 512 of 4096 tokens 19.1 / 14.9 (bands of 4), 768 x 768 of 2048 9.0 / 8.3, 1536 x 1536 of 4096 on 128 x 128 tiles 26.3 / 25.9; nothing
-// lost at 1024 x 1024 of 512.  Products whose A lies along the reduction gain less by it and lose where rows are a power of two
-// apart (forward 512 x 1024 x 1024 5.7 us with 8 rows, 6.0 with 4; 5.9 and 5.8 with 64 elements of padding): those keep 8.  A search of less than a
-// microsecond, cached per tile count.
-int band_height(int tiles_m, int tiles_n, int rows, int cols) {
-    static std::mutex mu;
-    static std::map<std::pair<int, int>, int> cache;
-    if (tiles_m == 1 || (int64_t)tiles_m * tiles_n > 2 * NUM_CU) return std::min(tiles_m, 8);
-    const std::pair<int, int> key{tiles_m * 4 + (rows > cols ? 2 : rows < cols ? 1 : 0), tiles_n};
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) return it->second;
-    const int n = tiles_m * tiles_n;
-    int best = 1, best_cost = INT32_MAX;
-    for (int h = std::min(tiles_m, 16); h >= 1; --h) {
-        int cost = 0;
-        for (int x = 0; x < axo::NUM_XCD; ++x) {
-            const int t0 = x * (n / axo::NUM_XCD) + std::min(x, n % axo::NUM_XCD), t1 = t0 + n / axo::NUM_XCD + (x < n % axo::NUM_XCD);
-            for (int t = t0; t < t1;) {  // the run's part in each band
-                const int b = t / (h * tiles_n), first = b * h * tiles_n, height = std::min(h, tiles_m - b * h);
-                const int end = std::min(t1, first + height * tiles_n), columns = (end - 1 - first) / height - (t - first) / height + 1;
-                cost += std::min(height, end - t) * rows + columns * cols;
-                t = end;
-            }
-        }
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = h;
-        }
-    }
-    if (cache.size() < 4096) cache[key] = best;
-    return best;
-}
-
-// Launch of one product on tiles of ROWS x COLS.
+// Launch of one product on tiles of ROWS x COLS.  Weight gradients take the bands of band_height, the others 8 tile rows.
 template <typename C, int ROWS, int COLS, int LA>
 int launch_tiles(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* raised, const GemmArgs& g, hipStream_t st) {
     if (!raise_lds_limit(reinterpret_cast<const void*>(kern), C::LDS_BYTES, raised)) return AXO_ERR_HIP;
     const int tm = (int)tiles_in(g.Mo, ROWS), tn = (int)tiles_in(g.No, COLS);
     hipLaunchKernelGGL(kern, dim3((unsigned)tm * (unsigned)tn), dim3(C::THREADS), C::LDS_BYTES, st, g, tm, tn,
-                       LA == axo::MC ? band_height(tm, tn, ROWS, COLS) : std::min(tm, 8));
+                       LA == axo::MC ? axo::band_height(tm, tn, ROWS, COLS, axo::NUM_XCD) : std::min(tm, 8));
     return hipGetLastError() == hipSuccess ? AXO_OK : AXO_ERR_HIP;
 }
 
