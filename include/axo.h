@@ -50,7 +50,7 @@
 extern "C" {
 #endif
 
-#define AXO_VERSION 1
+#define AXO_VERSION 1 /* raised with every change of a function's arguments or of a structure */
 
 typedef enum axo_status {
     AXO_OK = 0,

@@ -143,7 +143,7 @@ def library() -> ctypes.CDLL:
     L.axo_layer_step_tiles.argtypes = [ctypes.POINTER(LayerExt), i32, ctypes.POINTER(ctypes.c_int)]
     L.axo_layer_step_tiles.restype = i32
     if _calls is not None:
-        _calls.bind({name: ctypes.cast(getattr(L, name), vp).value for name in _QUICK})
+        _calls.bind({name: ctypes.cast(getattr(L, name), vp).value for name in _QUICK}, L.axo_version())
     _lib = L
     return L
 

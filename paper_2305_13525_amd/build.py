@@ -9,7 +9,8 @@ import warnings
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaxo.so")
-CALLS = os.path.join(HERE, "_calls.so")
+# named for the interpreter whose headers it is built with, so that no other one loads it
+CALLS = os.path.join(HERE, "_calls" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -39,6 +40,9 @@ def build_calls(verbose: bool = False) -> bool:
     """The extension module.  Without a C compiler or Python's headers the package does without it: its functions are then the ctypes
     wrappers, which do the same and take 0.7-2 us longer per call."""
     new = CALLS + ".new"  # moved into place: a running process may have the old one mapped
+    untagged = os.path.join(os.path.dirname(CALLS), "_calls.so")  # of older builds; any interpreter would load it
+    if untagged != CALLS and os.path.exists(untagged):
+        os.remove(untagged)
     try:
         _run([os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
               os.path.join(CSRC, "calls.c"), "-o", new], verbose)

@@ -96,8 +96,9 @@ static PyObject *call(entry *e, PyObject *const *args, Py_ssize_t nargs, PyObjec
     value a[MOST_ARGUMENTS];
     Py_buffer problem;
     PyObject *result, *rc;
+    void *const address = e->address;
     int status, check = 1;
-    if (!e->address || kwnames || nargs < e->required || nargs > n + 1 || (PyObject *)Py_TYPE(args[0]) != problem_type) goto wrapper;
+    if (!address || kwnames || nargs < e->required || nargs > n + 1 || (PyObject *)Py_TYPE(args[0]) != problem_type) goto wrapper;
     for (Py_ssize_t i = 1; i < n; ++i)
         if (i >= nargs) a[i] = e->defaults[i - e->required];
         else if (!convert(args[i], e->kinds[i], &a[i])) goto wrapper;
@@ -108,7 +109,7 @@ static PyObject *call(entry *e, PyObject *const *args, Py_ssize_t nargs, PyObjec
     if (PyObject_GetBuffer(args[0], &problem, PyBUF_SIMPLE) != 0) return NULL;
     a[0].ptr = problem.buf;
     Py_BEGIN_ALLOW_THREADS;  /* as ctypes does */
-    status = e->call(e->address, a);
+    status = e->call(address, a);
     Py_END_ALLOW_THREADS;
     PyBuffer_Release(&problem);
     rc = PyLong_FromLong(status);
@@ -156,14 +157,16 @@ static PyObject *set_up(PyObject *self, PyObject *args) {
     Py_RETURN_NONE;
 }
 
-/* bind({name: address of the C function}): whenever the library has been loaded. */
-static PyObject *bind(PyObject *self, PyObject *addresses) {
+/* bind({name: address of the C function}, axo_version() of the library): whenever the library has been loaded.  Functions of another version
+ * than the one that this was compiled for may take other arguments: they are left to the wrappers, and False is returned. */
+static PyObject *bind(PyObject *self, PyObject *args) {
     void *found[ENTRIES];
+    PyObject *addresses;
+    int version;
     (void)self;
-    if (!PyDict_Check(addresses)) {
-        PyErr_SetString(PyExc_TypeError, "a dict of addresses");
-        return NULL;
-    }
+    for (int i = 0; i < ENTRIES; ++i) entries[i].address = NULL;
+    if (!PyArg_ParseTuple(args, "O!i", &PyDict_Type, &addresses, &version)) return NULL;
+    if (version != AXO_VERSION) Py_RETURN_FALSE;
     for (int i = 0; i < ENTRIES; ++i) {
         PyObject *o = PyDict_GetItemString(addresses, entries[i].name);
         if (!o) return PyErr_Format(PyExc_KeyError, "%s", entries[i].name);
@@ -171,7 +174,7 @@ static PyObject *bind(PyObject *self, PyObject *addresses) {
         if (PyErr_Occurred()) return NULL;
     }
     for (int i = 0; i < ENTRIES; ++i) entries[i].address = found[i];
-    Py_RETURN_NONE;
+    Py_RETURN_TRUE;
 }
 
 #define METHOD(ID, NAME, SIGNATURE) {NAME, (PyCFunction)(void (*)(void))py_##ID, METH_FASTCALL | METH_KEYWORDS, NAME SIGNATURE "\n--\n\n"}
@@ -185,7 +188,7 @@ static PyMethodDef methods[] = {
     METHOD(BIAS_GRAD_WS, "axo_bias_grad_ws", "($module, p, dY, lddy, db, accumulate=0, ws=None, ws_bytes=0, stream=None, check=True)"),
     METHOD(BIAS_GRAD_STATIC, "axo_bias_grad_static", "($module, p, dY, lddy, db, accumulate=0, stream=None, check=True)"),
     {"set_up", set_up, METH_VARARGS, "set_up(Problem, wrappers, raise_if)"},
-    {"bind", bind, METH_O, "bind(addresses)"},
+    {"bind", bind, METH_VARARGS, "bind(addresses, version)"},
     {NULL, NULL, 0, NULL},
 };
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", "Calls into libaxo.so without ctypes.", -1, methods, NULL, NULL, NULL, NULL};

@@ -31,6 +31,15 @@ def test_builds_without(no_library, monkeypatch, missing):
     assert os.listdir(no_library) == []
 
 
+def test_module_is_named_for_its_interpreter(no_library):
+    """No file that another interpreter would load is left, nor one of an older build."""
+    (no_library / "_calls.so").write_text("of an older build")
+    if not build.build_calls():
+        pytest.skip("no C compiler or headers")
+    tag = build.sysconfig.get_config_var("EXT_SUFFIX")
+    assert os.listdir(no_library) == ["_calls" + tag] and tag != ".so"
+
+
 def test_the_library_itself_has_to_build(no_library, monkeypatch):
     monkeypatch.setattr(build, "HIPCC", "false")
     with pytest.raises(RuntimeError):

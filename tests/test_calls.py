@@ -1,6 +1,9 @@
 """The extension module's calls against the ctypes wrappers that they stand in for: the same result, status or exception for every form
 of arguments.  Nothing is launched in any of them: outputs are empty, or two arguments are wrong of which a case mends one at most."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 
@@ -79,8 +82,52 @@ def test_same_as_the_ctypes_wrapper(name):
     assert n > 60
 
 
+# One product without outputs for each function, in a process of its own, through wrappers that count their calls.
+EACH_ONCE = """
+import ctypes
+import sys
+sys.path.insert(0, "tests")
+import paper_2305_13525_amd as axo
+from paper_2305_13525_amd import _calls, binding
+assert binding._lib is None
+import test_calls
+assert binding._lib is None
+counts = []
+def counted(name):
+    def wrapper(*a, **k):
+        counts.append(name)
+        return binding._WRAPPERS[name](*a, **k)
+    return wrapper
+_calls.set_up(axo.Problem, {name: counted(name) for name in binding._QUICK}, binding._check)
+def each():
+    del counts[:]
+    for name in binding._QUICK:
+        assert getattr(axo, name)(test_calls.empty(name), *{**test_calls.PRODUCTS, **test_calls.SUMS}[name]) == 0, name
+    return list(counts)
+"""
+
+
+def in_a_process(code):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", EACH_ONCE + code], cwd=root, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
+
+
 def test_not_loaded_yet(monkeypatch):
     """Before the library is loaded the wrapper is called, which loads it."""
     monkeypatch.setattr(binding, "_lib", None)
     axo.library()
     assert axo.axo_fc_dgrad(empty("axo_fc_dgrad"), *PRODUCTS["axo_fc_dgrad"]) == 0
+
+
+def test_library_of_another_version():
+    """Its functions may take other arguments than the module passes: the wrappers are called."""
+    in_a_process("""
+L = axo.library()
+addresses = {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in binding._QUICK}
+assert each() == []
+assert _calls.bind(addresses, L.axo_version() + 1) is False
+assert each() == list(binding._QUICK)
+assert _calls.bind(addresses, L.axo_version()) is True
+assert each() == []
+""")
