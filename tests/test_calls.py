@@ -113,11 +113,14 @@ def in_a_process(code):
     assert r.returncode == 0, r.stdout
 
 
-def test_not_loaded_yet(monkeypatch):
-    """Before the library is loaded the wrapper is called, which loads it."""
-    monkeypatch.setattr(binding, "_lib", None)
-    axo.library()
-    assert axo.axo_fc_dgrad(empty("axo_fc_dgrad"), *PRODUCTS["axo_fc_dgrad"]) == 0
+@pytest.mark.parametrize("first", binding._QUICK)
+def test_not_loaded_yet(first):
+    """Before the library is loaded the wrapper is called, which loads it; from then on none is."""
+    in_a_process(f"""
+assert getattr(axo, {first!r})(test_calls.empty({first!r}), *{{**test_calls.PRODUCTS, **test_calls.SUMS}}[{first!r}]) == 0
+assert counts == [{first!r}] and binding._lib is not None
+assert each() == []
+""")
 
 
 def test_library_of_another_version():
