@@ -244,9 +244,12 @@ int launch_tiles(void (*kern)(GemmArgs, int, int, int), std::atomic<uint64_t>* r
 // the same bits).  128 x 128 tiles only where every tile has a CU of its own: beyond that they are bound by the rate at which a CU takes in
 // operands (384 tiles: 4096 x 1536 x 1536 forward 28.6 us against 23.5; 1504 tiles: 4000 x 2000 x 6000 125 against 97).
 // Halves of those, 64 x 128 or 128 x 64 (`wide`, `tall`), where every one has a CU of its own, 64 x 64 tiles would take clearly more than one
-// round and the reduction has at least 16 steps: there they are the quickest by 7 to 45 % (gemm_rect_kernel; with 8 steps 64 x 64 tiles
-// are as quick, 2000 x 1000 x 512 6.2 us either way, and with 16 tiles too many for one round: 1001 x 1027 x 1300 13.2 and 13.4).  Of the two the one with fewer tiles, else the wide one, which reads the rows of a forward's W
-// in segments of 256 bytes (1000 x 2000 x 3000 23.1 us, 27.0 on the tall ones; other products take either in the same time).
+// round and the reduction has at least 16 steps: there they are the quickest by 8 to 45 % (gemm_rect_kernel; with 16 tiles too many for one round 64 x 64
+// ones are as quick: 1001 x 1027 x 1300 13.2 us, 13.4).  The line at 16 steps was drawn when they were level at 8 (forward 2000 x 1000 x 512 6.2 us either
+// way).  By now they are the quicker from 8 on, and the line has not been moved: 64 x 64 / these in us 2048 x 1024 x 512 6.3 / 5.9, x 768 7.5 / 6.9,
+// dgrad 7.3 / 7.0, wgrad 7.4 / 6.8, wgrad 2000 x 1000 of 512 tokens 7.8 / 6.75, dgrad 6.15 / 6.0.  Of the two kinds the one with fewer tiles, else the
+// wide one, which reads the rows of a forward's W in segments of 256 bytes (1000 x 2000 x 3000 19.7 us, 20.1 on the tall ones, dgrad 17.9 and 18.2,
+// wgrad either way 21.0; wgrad 900 x 1300 of 6000 38.3 and 36.5).
 enum class Tiles { small, wide, tall, mid, big };
 Tiles tiles_of(int Mo, int No, int R) {
     const int64_t wide = tiles_in(Mo, 64) * tiles_in(No, 128), tall = tiles_in(Mo, 128) * tiles_in(No, 64);
@@ -337,7 +340,7 @@ Lines lines_of(const GemmArgs& g, int la, int lb, const axo::TileSched& sc) {
 // Launch of one product on those tiles.
 template <int LA, int LB, int LINES>
 int launch_mixed(const GemmArgs& g, const axo::TileSched& sc, hipStream_t st) {
-    // rows that straddle cache lines behind a short reduction: stored plainly (store_row)
+    // rows whose pitch makes them straddle cache lines, behind a short reduction: stored plainly (store_row)
     const bool plain = g.epilogue != axo::EPI_ACC_F32 && g.ldc % 64 != 0 && steps_in(g.R) <= 16;
     auto kern = plain ? axo::gemm_mixed_kernel<LA, LB, LINES, true> : axo::gemm_mixed_kernel<LA, LB, LINES, false>;
     constexpr int lds = LINES != LINES_NONE ? axo::LINES_LDS_BYTES : axo::MIX_LDS_BYTES;

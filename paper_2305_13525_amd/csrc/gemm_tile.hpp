@@ -384,7 +384,7 @@ __host__ __device__ __forceinline__ bool rows_straddle(const GemmArgs& g) {
 // A lane's 16 bytes of a whole tile's row.  Non-temporal where rows lie in whole cache lines: the
 // output is not read again by this launch, and plain stores let it evict operand panels from L2 (0.5-5 % in grouped launches; plain / non-temporal in
 // us on 128 x 128 tiles forward 2048 x 2048 x 256 6.65 / 6.24, x 1024 11.9 / 11.2, wgrad 4096 x 1024 of 512 tokens 8.0 / 7.55, on 64 x 64 ones two to a CU
-// wgrad 2048 x 1024 of 512 6.3 / 6.15, level in one round).  Plain where rows
+// wgrad 2048 x 1024 of 512 6.3 / 6.15, level in one round, on 64 x 128 ones dgrad 512 x 4096 x 4096 27.4 / 20.0, 2048 x 1024 x 1024 level).  Plain where rows
 // straddle lines: a non-temporal store of a part of a line does not wait in L2 for the rest of it, which the tile or wave beside this one
 // writes.  Non-temporal / plain in us: dgrad 10600 x 7736 x 48 69.0 / 49.4, wgrad 5640 x 6152 of 72 tokens 35.9 / 27.3, forward 8200 x 4104 x 200
 // 40.0 / 34.8, 3000 x 3000 x 200 14.9 / 13.1, 5000 x 10000 x 1000 114 / 105, on smaller tiles 264 x 328 x 136 4.17 / 3.43, 1000 x 1000 x 200 4.47 / 4.09,
@@ -1429,8 +1429,8 @@ __global__ void __launch_bounds__(TILE_THREADS, 1) gemm_mid_kernel(GemmArgs g, i
 // such tile per CU that are more than one round of 64 x 64 tiles.  A CU takes in operands at 100-115 KB per us, whatever the depth of
 // the ring, and that is what these launches are bound by (the loads of a 128 x 128 tile's step alone take 0.31 us, its MFMAs 0.22): half
 // as many CUs on 128 x 128 tiles take in two thirds of the bytes, two rounds of 64 x 64 tiles a third more.  64 x 64 / 128 x 128 / these in us:
-// forward 1000 x 2000 x 3000 31 / 27 / 23, dgrad 512 x 4096 x 4096 27 / 24 / 21.5, 256 x 8192 x 8192 71 / 72 / 57, wgrad 1400^3 16.3 / 13.7 / 12.3,
-// 900 x 1300 of 6000 tokens 58 / 45 / 38, forward 2000 x 1000 x 1000 12.8 / 12.1 / 10.5.  Three stages and two workgroups per CU: the same.
+// forward 1000 x 2000 x 3000 23.9 / 22.7 / 19.9, dgrad 512 x 4096 x 4096 23.8 / 24.0 / 19.9, 256 x 8192 x 8192 71 / 73 / 58, wgrad 1400^3 15.0 / 13.5 / 11.8,
+// 900 x 1300 of 6000 tokens 56 / 44 / 38, forward 2000 x 1000 x 1000 10.7 / 10.8 / 9.6.  Three stages and two workgroups per CU: the same.
 template <bool WIDE>
 using RectCfg = RingCfg<WIDE ? 64 : 128, WIDE ? 128 : 64, WIDE ? 2 : 4, WIDE ? 4 : 2, 4>;
 template <int LA, int LB, bool WIDE, bool LINES>
